@@ -31,6 +31,29 @@ __device__ __forceinline__ mfma_f32x16 mfma_32x32x16(mfma_bf16x8 a, mfma_bf16x8 
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+typedef __attribute__((ext_vector_type(4))) float mfma_f32x4;
+// One 16x16x32 MFMA with the accumulator pinned to the accumulation registers.  Under the chip's power limit this form
+// is worth about 15 % over 32x32x16: a loop of MFMAs fed from LDS with Gaussian bf16 data, four waves of 128 x 128 per
+// compute unit, runs at 1917 TFLOP/s against 1672 (1.83 against 1.67 PFLOP/s with eight waves of 128 x 64); on zeros,
+// where power does not limit, both reach 2.41.  Inline assembly because the compiler otherwise parks operand registers
+// in the accumulation half of the register file inside the loop.  It does not see the hazards of an MFMA in assembly:
+// call mfma_fence() on the accumulators between their last MFMA and the first ordinary instruction that reads them, and
+// between ordinary writes and the first MFMA.
+template <bool F16>
+__device__ __forceinline__ void mfma_16x16x32(mfma_f32x4& c, mfma_bf16x8 a, mfma_bf16x8 b) {
+  if constexpr (F16)
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+  else
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+template <int M, int N> __device__ __forceinline__ void mfma_fence(mfma_f32x4 (&acc)[M][N]) {
+  asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+  for (int m = 0; m < M; ++m)
+#pragma unroll
+    for (int n = 0; n < N; ++n) asm volatile("" : "+a"(acc[m][n]));   // ordered behind the wait states
+}
+
 // MI355X: 256 compute units in 8 XCDs; consecutive workgroup ids are dealt round-robin to
 // the XCDs, each of which has its own L2.
 constexpr int kNumXcd = 8;

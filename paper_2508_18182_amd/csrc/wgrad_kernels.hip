@@ -4,6 +4,7 @@
 // token-major (the contraction index is the slow one), so tiles are staged in LDS as they are
 // and handed to the MFMA through the LDS transpose read of gfx950.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -12,6 +13,7 @@ namespace adloco {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef mfma_f32x4 f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
@@ -193,26 +195,30 @@ __global__ __launch_bounds__(256, 2) void wgrad_bf16_kernel(WgradArgs g) {
 }
 
 // ---------------------------------------------------------------------------------------
-// bf16 fast path: 256 (d_out) x 256 (d_in) output tile per workgroup of 8 waves (2 x 4, each
-// 128 x 64), used when every row is 16-byte aligned, widths are multiples of 8 and the number
-// of token rows is a multiple of 32.
-//   Staging: global -> LDS directly, four stages of 32 token rows x (256 + 256) columns; one
-//   wave instruction moves two token rows of one operand (2 x 512 contiguous bytes); the LDS
-//   blocks are padded so that the transpose reads of four consecutive rows fall into different
-//   banks.
-//   One barrier per 32-row chunk, between its two k-steps; loads run two chunks ahead.
-//   Tiles are dealt to the XCDs layer by layer (table built on the host): the tiles of one layer
-//   run next to each other on one XCD and stream the same columns out of that XCD's L2.
-//   Columns beyond d_out / d_in re-read the last valid 16-byte piece; those accumulators are
-//   never stored.
+// bf16 fast path: 256 (d_out) x 256 (d_in) output tile per workgroup of four waves (2 x 2, each 128 x 128, one per
+// SIMD), used when every row is 16-byte aligned, widths are multiples of 8 and the number of token rows is a multiple
+// of 32.  What bounds it is power: at 78 % busy matrix cores the chip holds 1.54 of its 2.4 GHz, so the kernel is laid
+// out for little energy per product -- the 16x16x32 MFMA, and wave tiles of 128 x 128, which read a third less from LDS
+// than eight waves of 128 x 64.  Sum over the 96 linears of the 350M model, 32 x 1024 tokens: 14.0 ms, 1.41 PFLOP/s
+// (eight waves with the 32x32x16 MFMA: 15.8 ms; four waves with it: 15.3 ms); without its global loads 11.4 ms, with
+// loads that all hit the L2 12.9 ms.
+//   Staging: global -> LDS directly, four stages of 32 token rows x (256 + 256) columns; one wave instruction moves
+//   two token rows of one operand (2 x 512 contiguous bytes).
+//   The operands of a chunk are read from LDS during the MFMAs of the chunk before, one read behind each MFMA, and
+//   the direct loads go out one behind every other MFMA: with a single wave per SIMD anything issued in a burst would
+//   leave the matrix core idle.  One barrier per chunk; loads run three chunks ahead.
+//   Tiles are dealt to the XCDs layer by layer (table built on the host): the tiles of one layer run next to each
+//   other on one XCD and stream the same columns out of that XCD's L2.
+//   Columns beyond d_out / d_in re-read the last valid 16-byte piece; those accumulators are never stored.
 // ---------------------------------------------------------------------------------------
 constexpr int kXt = 256;                          // tile edge
 constexpr int kXk = 32;                           // token rows per stage
 constexpr int kXrowB = kXt * 2;                   // bytes per staged row of one operand
-constexpr int kXblk = 2 * kXrowB + 64;            // one load instruction: rows j and j+16, + 64 B pad
+constexpr int kXblk = 2 * kXrowB + 32;            // one load instruction: two rows, + 32 B pad
 constexpr int kXop = 16 * kXblk;                  // 17 KiB
 constexpr int kXstage = 2 * kXop;                 // 34 KiB
 constexpr int kXstages = 4;
+constexpr int kXthreads = 256;
 constexpr int kXlds = kXstages * kXstage;         // 136 KiB
 
 struct WgradXArgs {
@@ -231,14 +237,13 @@ template <int N> __device__ __forceinline__ void wgx_wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 0xf) | ((N >> 4) << 14));
 }
 
-// LDS offset of staged token row `row` (0..31) of one operand: load instruction j brings rows j
-// and j+16 into one 1 KiB block; blocks are 1088 bytes apart, so four consecutive rows start
-// 64 bytes apart modulo 256 and a transpose read (per 32 lanes: 4 rows x 2 x 32 bytes) touches
-// 256 distinct bytes.  Global addresses stay linear: 512 contiguous bytes per half wave.
-__device__ __forceinline__ int wgx_row_off(int row) { return (row & 15) * kXblk + (row >> 4) * kXrowB; }
+// Token row of a chunk that half h of LDS block b holds.  Blocks are 1056 bytes apart, i.e. block b starts
+// 32 * (b % 8) bytes into the 256 bytes of the banks; a transpose read touches, per 32 lanes, 32 bytes of the rows
+// 0..3 and 8..11 (or another such octet), which this order puts into blocks of all eight residues: no conflicts.
+__device__ __forceinline__ int wgx_row(int b, int h) { return (b & 3) | (b & 8) >> 1 | (b & 4) << 1 | h << 4; }
 
 template <bool F16>
-__global__ __launch_bounds__(512, 1) void wgrad_bf16_x_kernel(WgradXArgs g) {
+__global__ __launch_bounds__(kXthreads, 1) void wgrad_bf16_x_kernel(WgradXArgs g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int xcd = blockIdx.x % kNumXcd, slot = blockIdx.x / kNumXcd;
   const int4 tile = g.tiles[xcd * g.slots + slot];
@@ -248,138 +253,139 @@ __global__ __launch_bounds__(512, 1) void wgrad_bf16_x_kernel(WgradXArgs g) {
   const int split_s = (tile.w >> 24) & 0xff, split_p = (tile.w >> 16) & 0xff, split_id = tile.w & 0xffff;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wave >> 2, wn = wave & 3;        // 2 x 4 waves; wave tile 128 (e) x 64 (c)
+  const int wm = wave >> 1, wn = wave & 1;        // 2 x 2 waves; wave tile 128 (e) x 128 (c)
   // chunk range of this workgroup: everything, or piece split_p of split_s equal parts
   // (32-bit counters keep the loop's compares on the scalar unit; the host keeps rows / 32 < 2^31)
   const long long nk_all = g.rows / kXk;
   const long long ck0 = split_s ? nk_all * split_p / split_s : 0;
   const int nk = int((split_s ? nk_all * (split_p + 1) / split_s : nk_all) - ck0);
 
-  // ---- direct loads: instruction j = wave + 8*i (i = 0..3): operand j/16, rows j%16 (lanes 0-31)
-  // and j%16 + 16 (lanes 32-63), 16-byte piece lane%32
-  // Address = (first row of the chunk: wave-uniform, scalar registers) + (row within the chunk and
+  // ---- direct loads: block b = wave + 4 * q (q = 0..3) of each operand, 16-byte piece lane % 32 of row
+  // wgx_row(b, lane / 32).  Address = (first row of the chunk: scalar registers) + (row within the chunk and
   // column: a 32-bit byte offset per lane, computed once; the host keeps row strides below 2^25).
-  // j = wave + 8*i < 16 for i = 0, 1 (delta) and >= 16 for i = 2, 3 (a).
-  unsigned lane_off[4];
-  int lds_off[4];
+  unsigned lane_off[8];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int j = wave + 8 * i;
-    const int op = i >> 1;                        // 0: delta (d_out side), 1: a (d_in side)
-    const int row = (j & 15) + 16 * (lane >> 5);
-    const int piece = lane & 31;
+  for (int i = 0; i < 8; ++i) {
+    const int op = i >> 2;                        // 0: delta (d_out side), 1: a (d_in side)
+    const int row = wgx_row(wave + 4 * (i & 3), lane >> 5);
     const int d = op ? L.d_in : L.d_out;
-    int col = (op ? c0 : e0) + piece * 8;
+    int col = (op ? c0 : e0) + (lane & 31) * 8;
     col = col < d ? col : d - 8;
     lane_off[i] = unsigned(row * (op ? L.a_stride : L.delta_stride) + col) * 2u;
-    lds_off[i] = op * kXop + (j & 15) * kXblk;
   }
-  const unsigned short* const run_e = reinterpret_cast<const unsigned short*>(L.delta) + ck0 * kXk * L.delta_stride;
-  const unsigned short* const run_c = reinterpret_cast<const unsigned short*>(L.a) + ck0 * kXk * L.a_stride;
+  const unsigned short* pe = uniform_ptr(reinterpret_cast<const unsigned short*>(L.delta) + ck0 * kXk * L.delta_stride);
+  const unsigned short* pc = uniform_ptr(reinterpret_cast<const unsigned short*>(L.a) + ck0 * kXk * L.a_stride);
   const unsigned lds_base = lds_address(lds);       // LDS byte addresses are handled as integers
-  auto issue_loads = [&](int c, int st) {
-    const unsigned stage = lds_base + unsigned(st) * kXstage;
-    const unsigned short* const pe = run_e + (long long)c * kXk * L.delta_stride;
-    const unsigned short* const pc = run_c + (long long)c * kXk * L.a_stride;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      direct_load_lds16_s(lane_off[i], i >= 2 ? pc : pe, stage + lds_off[i]);
+  const unsigned ld_base = lds_base + wave * kXblk;
+  // load i of this wave for the chunk at pe / pc, into stage st
+  auto issue_load = [&](int i, unsigned st) {
+    direct_load_lds16_s(lane_off[i], i >= 4 ? pc : pe,
+                        ld_base + st + (i >> 2) * kXop + (i & 3) * 4 * kXblk);
+  };
+  auto next_chunk = [&]() {
+    pe += kXk * L.delta_stride;
+    pc += kXk * L.a_stride;
   };
 
-  // ---- fragments by LDS transpose reads.  Within a group of 16 lanes, lane s points at the 4
-  // columns 4*(s%4).. of token row kbase + s/4; the read hands lane i column i of the group's
-  // 16 at the four token rows.  Lane l ends up with column m0 + l%32, token rows
-  // ks*16 + (l/32)*8 + 0..7.
-  const int i16 = lane & 15;
-  const int krow = (lane >> 5) * 8 + (i16 >> 2);              // + ks*16 (+4 for the upper half)
-  const int ccol = ((lane >> 4) & 1) * 16 + (i16 & 3) * 4;    // column within a 32-wide block
-  // Every read address of a k-step is stage + (a part that depends on the lane) + (a constant of
-  // the fragment): one lane part per operand is kept in a register, the constants ride in the
-  // offset field of the read.  Token rows ks*16 + krow and + 4 stay inside one 16-row block.
+  // ---- fragments by LDS transpose reads.  Within a group of 16 lanes, lane s points at the 4 columns 4*(s%4).. of
+  // token row 8*(lane/16) + s/4 (+ 4 for the second read); the read hands lane i column i of the group's 16 at the
+  // four token rows.  Lane l ends up with column m0 + l%16, token rows (l/16)*8 + 0..7: the operand of a 16x16x32
+  // MFMA.  Every read address is stage + (a part that depends on the lane) + (a constant of the fragment).
+  const int i16 = lane & 15, grp = lane >> 4;
   typedef __attribute__((address_space(3))) s16x4* lds_ptr;
-  const unsigned lane_e = unsigned(wgx_row_off(krow) + (wm * 128 + ccol) * 2);
-  const unsigned lane_c = unsigned(kXop + wgx_row_off(krow) + (wn * 64 + ccol) * 2);
-  auto frag = [&](lds_ptr base, int byte_off) -> bf16x8 {
-    s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(base + byte_off / 8);
-    s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(base + (byte_off + 4 * kXblk) / 8);
-    s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  const unsigned lane_rd = unsigned(((i16 >> 2) | (grp & 1) << 2) * kXblk + (grp >> 1) * kXrowB + (i16 & 3) * 8);
+  const unsigned lane_e = lds_base + lane_rd + wm * 256, lane_c = lds_base + lane_rd + kXop + wn * 256;
+  struct Frags { s16x4 v[16][2]; };                // [0..7] a side, [8..15] delta side; first and last four token rows
+  auto read1 = [&](int r, unsigned be, unsigned bc, Frags& f) {
+    const int i = r >> 1, h = r & 1;
+    const lds_ptr p = (lds_ptr)(size_t)(i < 8 ? bc : be);
+    f.v[i][h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p + ((i & 7) * 32 + h * 8 * kXblk) / 8);
+  };
+  auto frag = [&](const Frags& f, int i) -> bf16x8 {
+    s16x8 v = {f.v[i][0][0], f.v[i][0][1], f.v[i][0][2], f.v[i][0][3], f.v[i][1][0], f.v[i][1][1], f.v[i][1][2], f.v[i][1][3]};
     return __builtin_bit_cast(bf16x8, v);
   };
-  auto read_frags = [&](int st, int ks, bf16x8 (&fa)[4], bf16x8 (&fb)[2]) {
-    const unsigned stage = lds_base + unsigned(st) * kXstage;
-    const lds_ptr be = (lds_ptr)(size_t)(stage + lane_e), bc = (lds_ptr)(size_t)(stage + lane_c);
-    // in the order the MFMAs need them; 32 columns are 64 bytes
-    fa[0] = frag(be, ks * kXrowB);
-    fb[0] = frag(bc, ks * kXrowB);
-    fb[1] = frag(bc, ks * kXrowB + 64);
-#pragma unroll
-    for (int m = 1; m < 4; ++m) fa[m] = frag(be, ks * kXrowB + m * 64);
-  };
 
-  f32x16 acc[4][2];
+  f32x4 acc[8][8];
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int m = 0; m < 8; ++m)
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
+    for (int n = 0; n < 8; ++n)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) acc[m][n][j] = 0.f;
+      for (int j = 0; j < 4; ++j) acc[m][n][j] = 0.f;
+  mfma_fence(acc);
 
-  auto mfma8 = [&](const bf16x8 (&a)[4], const bf16x8 (&b)[2]) {
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-#pragma unroll
-      for (int n = 0; n < 2; ++n)
-        acc[m][n] = mfma_32x32x16<F16>(a[m], b[n], acc[m][n]);
-    // issue order: the 12 LDS reads of the next k-step go out two at a time behind the first
-    // six MFMAs, so that the last of them has two MFMAs to land before the next k-step starts
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+  // Chunk c's fragments are read during the MFMAs of chunk c-1, so that stage c mod 4 is free when chunk c's MFMAs
+  // begin and takes chunk c+4 there.
+  const unsigned st_end = kXstages * kXstage;
+  unsigned st = 0;                                 // byte offset of the stage of chunk c
+  auto period = [&](auto tail_tag, int c, const Frags& cur, Frags& nxt) {
+    constexpr bool tail = decltype(tail_tag)::value;
+    const unsigned stn = st + kXstage == st_end ? 0u : st + kXstage;
+    const unsigned be = lane_e + stn, bc = lane_c + stn;
+    #pragma unroll
+    for (int i = 0; i < 64; ++i) {
+      const int m = i >> 3, n = m & 1 ? 7 - (i & 7) : i & 7;
+      mfma_16x16x32<F16>(acc[m][n], frag(cur, 8 + m), frag(cur, n));
+      if (i == 1 && (!tail || c + 1 < nk)) {
+        // chunk c+1 has landed for me (the two behind it may be in flight), then for everybody; everybody has
+        // read all of chunk c
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (!tail || c + 3 < nk) wgx_wait_vmcnt<16>(); else if (c + 2 < nk) wgx_wait_vmcnt<8>(); else wgx_wait_vmcnt<0>();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
+      if (i >= 2 && i < 34) read1(i - 2, be, bc, nxt);   // (after the last chunk: of no use, but in bounds)
+      if (!tail && i >= 36 && i < 52 && (i & 1)) issue_load((i - 36) >> 1, st);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+    if (tail && c + kXstages < nk) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) issue_load(i, st);
+      next_chunk();
+    }
+    if (!tail) next_chunk();
+    st = stn;
   };
 
-  if (nk > 0) issue_loads(0, 0);
-  if (nk > 1) issue_loads(1, 1);
-  if (nk > 2) issue_loads(2, 2);
-  if (nk > 2) wgx_wait_vmcnt<8>(); else if (nk > 1) wgx_wait_vmcnt<4>(); else wgx_wait_vmcnt<0>();
+  // prologue: chunks 0 .. 3 in flight, chunk 0 landed
+#pragma unroll
+  for (int s = 0; s < kXstages; ++s)
+    if (s < nk) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) issue_load(i, s * kXstage);
+      next_chunk();
+    }
+  if (nk >= kXstages) wgx_wait_vmcnt<24>(); else wgx_wait_vmcnt<0>();
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  bf16x8 fa[2][4], fb[2][2];
-  read_frags(0, 0, fa[0], fb[0]);
-  static_assert(kXstages == 4, "the stage of chunk c+3 is the stage of chunk c-1");
-  int st_cur = 0, st_load = kXstages - 1;         // stage of chunk c; stage that chunk c-1 frees
-  for (int c = 0; c < nk; ++c) {
-    const int st_next = st_cur + 1 == kXstages ? 0 : st_cur + 1;
-    read_frags(st_cur, 1, fa[1], fb[1]);
-    mfma8(fa[0], fb[0]);
-    if (c + 1 < nk) {
-      // chunk c+1 has landed for me (chunk c+2 may still be in flight), then for everybody;
-      // every wave is done with chunk c-1, whose stage takes chunk c+3
-      if (c + 2 < nk) wgx_wait_vmcnt<4>(); else wgx_wait_vmcnt<0>();
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      if (c + 3 < nk) issue_loads(c + 3, st_load);
-    }
-    read_frags(c + 1 < nk ? st_next : st_cur, 0, fa[0], fb[0]);
-    mfma8(fa[1], fb[1]);
-    st_load = st_cur;
-    st_cur = st_next;
+  Frags f0, f1;
+#pragma unroll
+  for (int r = 0; r < 32; ++r) read1(r, lane_e, lane_c, f0);
+  int c = 0;
+  for (; c + 1 + kXstages < nk; c += 2) {
+    period(std::false_type{}, c, f0, f1);
+    period(std::false_type{}, c + 1, f1, f0);
   }
+  for (; c < nk; c += 2) {
+    period(std::true_type{}, c, f0, f1);
+    if (c + 1 < nk) period(std::true_type{}, c + 1, f1, f0);
+  }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  mfma_fence(acc);
 
-  // accumulator element j of a 32x32 block: row (j/4)*8 + (lane/32)*4 + j%4, column lane%32
+  // accumulator element j of a 16x16 block: row (lane/16)*4 + j, column lane%16
   float* part = split_s ? g.partials + (size_t)split_id * (kXt * kXt) : nullptr;
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int m = 0; m < 8; ++m)
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
-      const int tc = wn * 64 + n * 32 + (lane & 31);
+    for (int n = 0; n < 8; ++n) {
+      const int tc = wn * 128 + n * 16 + i16;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int tr = wm * 128 + m * 32 + (j >> 2) * 8 + (lane >> 5) * 4 + (j & 3);
+      for (int j = 0; j < 4; ++j) {
+        const int tr = wm * 128 + m * 16 + grp * 4 + j;
         if (split_s) {
           part[tr * kXt + tc] = acc[m][n][j];
         } else if (e0 + tr < L.d_out && c0 + tc < L.d_in) {
@@ -535,7 +541,7 @@ hipError_t launch_wgrad_x(const LayerDev* layers, const void* tiles, int slots,
     if (e != hipSuccess) return e;
   }
   WgradXArgs a{layers, static_cast<const int4*>(tiles), partials, slots, rows, accumulate};
-  hipLaunchKernelGGL(kern, dim3(unsigned(slots * kNumXcd)), dim3(512), kXlds, st, a);
+  hipLaunchKernelGGL(kern, dim3(unsigned(slots * kNumXcd)), dim3(kXthreads), kXlds, st, a);
   if (n_split > 0)
     hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(unsigned(n_split) * (kXt / kXredRows)), dim3(256), 0, st, layers,
                        static_cast<const WgradSplitTile*>(split_tiles), partials, accumulate);
