@@ -145,6 +145,17 @@ struct Scratch {
   size_t bytes = 0;
 };
 
+// Work list of the plain tile kernel (tile_plain_kernels.hip) for one layer table and batch shape.
+struct PlainTiles {
+  Scratch tab;              // int4 [8][slots] entries
+  Scratch part_idx, split, ptiles;   // statistics form: partial tile per entry, split tiles, their storage
+  Scratch out;              // double [8 * slots][group][4 waves][2]
+  Scratch csr;              // int: listed layers | offsets | entries of each
+  int W = 2;                // tiles of 64 * W
+  int slots = 0, group = 1, n_split = 0, n_listed = 0;
+  int B = -1;               // batch the list was built for (-1: none)
+};
+
 }  // namespace adloco
 
 struct adloco_ctx {
@@ -188,15 +199,16 @@ struct adloco_ctx {
   adloco::Scratch ip_tab;      // int4 tile table of the inner-product form of the tile GEMM
   adloco::Scratch ip_tile_out; // float [tiles][ip_group][8 waves][2]
   adloco::Scratch ip_dot, ip_sq;   // float [n_layers][B] of the blocks outside the tile table
-  adloco::Scratch ip_part;     // double scratch of the plain path
   adloco::Scratch ip_flags;    // unsigned char [n_layers]: 1 = block is in the tile table
-  std::vector<char> ip_use;    // host copy of ip_flags
   int ip_slots = 0, ip_group = 1, ip_B = -1, ip_T = -1;
+  adloco::PlainTiles ip_plain; // linear blocks outside that table
   int ip_group_tuning = 0;     // 0: cost model; else samples per tile entry
   // statistics by per-sample gradient tiles (explicit form fused with the gradient sum)
   adloco::Scratch ts_tab, ts_part_idx, ts_split, ts_ptiles, ts_out, ts_csr;
-  int ts_slots = 0, ts_n_split = 0, ts_n_listed = 0, ts_idx_len = 0, ts_B = -1;
+  int ts_slots = 0, ts_n_split = 0, ts_n_listed = 0, ts_B = -1;
   bool ts_ok = false;          // every linear block is aligned bf16 with its gradient sum formed here
+  adloco::PlainTiles st_plain; // the same for fp32 blocks
+  int n_formed = 0;            // linear blocks whose gradient sum is formed here
   int stats_variant = 1;       // 1: tile form when eligible; 0: Gram + gradient-sum kernels
   // the vector / table kernels (HBM-bound) can run next to the kernels of the linear blocks (MFMA /
   // L2-bound) on a second stream, forked from and joined to the caller's stream by events; measured,
@@ -304,22 +316,29 @@ hipError_t launch_vector_stats(const LayerDev* layers, const AuxDesc* tab, int n
                                int blocks_rowsum, int blocks_colsum, int B, int T, int dtype,
                                float* vec, float* partials, int n_pairs, int accumulate,
                                bool write_grad_sum, hipStream_t st);
-int make_ip_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, int T,
+// Tiles of a tile kernel: e rows (d_out side) x c columns, chunks of k token rows, `room` workgroups resident per XCD.
+struct TileGeom { int e, c, k, room; };
+int make_ip_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, int T, TileGeom geom,
                   int forced_group, std::vector<int4>& out, int& group);
+TileGeom ip_tile_geom();
+// For every layer of `use`: the indices into `tiles` of its entries, idx[ptr[q] .. ptr[q+1]) for lay[q]; appended to
+// one another in this order.
+std::vector<int> tiles_by_layer(const std::vector<int4>& tiles, const std::vector<char>& use, int& n_listed);
 hipError_t launch_ip_tiles(const LayerDev* layers, const void* tiles, int slots, int T, int group,
                            int dtype, bool want_sq, float* ip_out, hipStream_t st);
-int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B,
-                     std::vector<int4>& out, std::vector<int>& part, std::vector<int4>& split,
-                     std::vector<int>& lay, std::vector<int>& ptr, std::vector<int>& idx,
-                     int& n_pieces);
+int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, TileGeom geom,
+                     std::vector<int4>& out, std::vector<int>& part, std::vector<int4>& split, int& n_pieces);
 hipError_t launch_stats_tiles(const LayerDev* layers, const void* tiles, const int* part, int slots,
                               const void* split, int n_split, float* partial_tiles, int B, int T,
                               int dtype, int accumulate, float* tile_out, const int* lay, const int* ptr,
                               const int* idx, int n_listed, float* partials, int n_pairs,
                               hipStream_t st);
-hipError_t launch_ip_generic(const LayerDev& L, int layer, int B, int T, int dtype, double* part,
-                             float* dot, float* sq, hipStream_t st);
-size_t ip_generic_part_doubles(const LayerDev& L, int B);
+// Resident workgroups per XCD of the plain tile kernel: two (128-wide tiles) or four per compute unit.
+constexpr int plain_tile_room(int W) { return kNumCu / kNumXcd * (W == 2 ? 2 : 4); }
+int plain_tile_width(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B);
+// mode 0: <g_i, G> -> dot and ||g_i||^2 -> sq; mode 1: G and ||g_i||^2 -> sq (NULL: only G).
+hipError_t launch_plain_tiles(const LayerDev* layers, const PlainTiles& p, int mode, int B, int T, int dtype,
+                              int accumulate, float* dot, float* sq, int sq_stride, hipStream_t st);
 hipError_t launch_ip_vector_table(const LayerDev* layers, const AuxDesc* vec_tab, int n_vec,
                                   const AuxDesc* emb_tab, int n_emb, int B, int T, int dtype,
                                   const float* vec, float* dot, hipStream_t st);

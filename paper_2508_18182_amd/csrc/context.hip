@@ -144,10 +144,13 @@ extern "C" int adloco_destroy(adloco_ctx* ctx) {
                     &ctx->order_tab, &ctx->group_tab, &ctx->job_tab, &ctx->wgx_tab,
                     &ctx->wgx_split, &ctx->wgx_part, &ctx->vec_tab, &ctx->emb_tab,
                     &ctx->aux_vec, &ctx->aux_perm, &ctx->aux_part, &ctx->ip_tab, &ctx->ip_tile_out,
-                    &ctx->ip_dot, &ctx->ip_sq, &ctx->ip_part, &ctx->ip_flags, &ctx->ts_tab,
+                    &ctx->ip_dot, &ctx->ip_sq, &ctx->ip_flags, &ctx->ts_tab,
                     &ctx->ts_part_idx, &ctx->ts_split, &ctx->ts_ptiles, &ctx->ts_out, &ctx->ts_csr};
   for (Scratch* s : all)
     if (s->ptr) (void)hipFree(s->ptr);
+  for (PlainTiles* p : {&ctx->st_plain, &ctx->ip_plain})
+    for (Scratch* s : {&p->tab, &p->part_idx, &p->split, &p->ptiles, &p->out, &p->csr})
+      if (s->ptr) (void)hipFree(s->ptr);
   for (auto& r : ctx->prof) {
     (void)hipEventDestroy(r.start);
     (void)hipEventDestroy(r.stop);

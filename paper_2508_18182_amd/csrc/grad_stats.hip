@@ -253,7 +253,10 @@ int prepare_tables(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_laye
   }
   ctx->aux_B = ctx->aux_T = -1;         // the vector / table descriptor lists follow the table
   ctx->ip_B = ctx->ip_T = -1;           // and so does the inner-product tile table
-  ctx->ts_B = -1;                       // and the statistics tile table
+  ctx->ts_B = -1;                       // and the statistics tile tables
+  ctx->st_plain.B = -1;
+  ctx->n_formed = 0;
+  for (const LayerDev& L : tab) ctx->n_formed += L.kind == ADLOCO_KIND_LINEAR && !L.provided;
   {
     // (the tile kernels address the rows of a chunk with 32-bit byte offsets)
     bool ok = need_inputs && is_16bit(dtype) && !order.empty() && widest < (1 << 25);
@@ -381,6 +384,46 @@ int prepare_vector_table(adloco_ctx* ctx, int B, int T, hipStream_t st) {
   return ADLOCO_OK;
 }
 
+// Work list of the plain tile kernel for the layers of `use`: statistics form (T = 0; entries split along the samples)
+// or inner-product form.
+int build_plain_tiles(adloco_ctx* ctx, PlainTiles& p, const std::vector<char>& use, int B, int T, int forced_group,
+                      hipStream_t st) {
+  ++ctx->table_builds;
+  p.B = -1;
+  const std::vector<LayerDev>& tab = ctx->layer_tab_host;
+  p.W = plain_tile_width(tab, use, B);
+  const TileGeom geom{64 * p.W, 64 * p.W, 32 / p.W, plain_tile_room(p.W)};
+  std::vector<int4> tiles, split;
+  std::vector<int> part;
+  int n_pieces = 0;
+  if (T == 0) {
+    p.slots = make_stats_tiles(tab, use, B, geom, tiles, part, split, n_pieces);
+    p.group = B;
+  } else {
+    p.slots = make_ip_tiles(tab, use, B, T, geom, forced_group, tiles, p.group);
+    part.assign(1, -1);
+  }
+  if ((long long)p.slots * kNumXcd > 0x7fffffffLL)
+    return fail(ctx, ADLOCO_EUNSUPPORTED, "too many tiles for one launch");
+  const std::vector<int> csr = tiles_by_layer(tiles, use, p.n_listed);
+  p.n_split = int(split.size());
+  const size_t edge = size_t(64 * p.W);
+  const struct { Scratch* s; const void* src; size_t bytes; } up[] = {
+      {&p.tab, tiles.data(), tiles.size() * sizeof(int4)}, {&p.part_idx, part.data(), part.size() * sizeof(int)},
+      {&p.split, split.data(), split.size() * sizeof(int4)}, {&p.csr, csr.data(), csr.size() * sizeof(int)},
+      {&p.ptiles, nullptr, n_pieces * edge * edge * sizeof(float)},
+      {&p.out, nullptr, tiles.size() * p.group * 8 * sizeof(double)}};
+  for (const auto& u : up) {
+    int rc = ensure_scratch(ctx, *u.s, std::max<size_t>(u.bytes, 16));
+    if (rc) return rc;
+    if (u.src && u.bytes)
+      ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(u.s->ptr, u.src, u.bytes, hipMemcpyHostToDevice, st));
+  }
+  ADLOCO_HIP_CHECK(ctx, hipStreamSynchronize(st));
+  p.B = B;
+  return ADLOCO_OK;
+}
+
 }  // namespace
 
 extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers,
@@ -429,33 +472,43 @@ extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* laye
     }
     n_pairs = gram_dual_parts(ctx->job_tab_n);
   }
-  const long long n_part = (long long)n_layers * B * n_pairs;
-  if (n_pairs > 0x7fffffffLL || n_part > (1LL << 40))
+  if (n_pairs > 0x7fffffffLL || (long long)n_layers * B * n_pairs > (1LL << 40))
     return fail(ctx, ADLOCO_EUNSUPPORTED, "grad_stats: T = %d gives too many tile pairs", T);
+
+  // Per-sample gradient tiles (explicit form) when the gradient sums of all linear blocks are formed here: the tiles
+  // that add up to them are squared on the way, no Gram contraction is needed.  16-bit blocks if they are aligned;
+  // fp32 ones always, also for the plain gradient sum: 4 x {768 -> 2304, 768 -> 768, 768 -> 3072, 3072 -> 768}, B 8,
+  // T 256 takes 1.28 ms against 5.02 ms with the vector-unit kernels of the two steps, a gradient sum of 0.1 TFLOP on
+  // widths of 300 to 1600 0.6 - 1.2 ms against 1.7 - 3.4 ms.
+  const bool tile_form = !sum_only && ctx->stats_variant != 0 && ctx->ts_ok && T % 32 == 0 &&
+                         T <= (1 << 20) && B <= 0x7fff;
+  const bool plain_form = dtype == ADLOCO_F32 && ctx->n_formed > 0 && B <= 0x7fff && ctx->stats_variant != 0 &&
+                          (sum_only || ctx->n_formed == ctx->n_linear);
+  if (tile_form || plain_form) n_pairs = 1;      // one finished sum per (layer, sample)
+  const long long n_part = (long long)n_layers * B * n_pairs;
   rc = ensure_scratch(ctx, ctx->partials, size_t(n_part) * sizeof(float));
   if (rc) return rc;
   rc = ensure_scratch(ctx, ctx->sample_f64, size_t(B) * sizeof(double));
   if (rc) return rc;
-
-  // Per-sample gradient tiles (explicit form) when every linear block qualifies: the tiles that
-  // add up to the gradient sum are squared on the way, no Gram contraction is needed.
-  const bool tile_form = !sum_only && ctx->stats_variant != 0 && ctx->ts_ok && T % 32 == 0 &&
-                         T <= (1 << 20) && B <= 0x7fff;
+  if (plain_form && ctx->st_plain.B != B) {
+    std::vector<char> use(n_layers, 0);
+    for (int l = 0; l < n_layers; ++l)
+      use[l] = ctx->layer_tab_host[l].kind == ADLOCO_KIND_LINEAR && !ctx->layer_tab_host[l].provided;
+    rc = build_plain_tiles(ctx, ctx->st_plain, use, B, 0, 0, st);
+    if (rc) return rc;
+  }
   if (tile_form && ctx->ts_B != B) {
     ++ctx->table_builds;
     const std::vector<LayerDev>& tab = ctx->layer_tab_host;
     std::vector<char> use(n_layers, 0);
     for (int l = 0; l < n_layers; ++l) use[l] = tab[l].kind == ADLOCO_KIND_LINEAR;
     std::vector<int4> tiles, split;
-    std::vector<int> part, lay, ptr, idx;
-    int n_pieces = 0;
-    const int slots = make_stats_tiles(tab, use, B, tiles, part, split, lay, ptr, idx, n_pieces);
+    std::vector<int> part;
+    int n_pieces = 0, n_listed = 0;
+    const int slots = make_stats_tiles(tab, use, B, ip_tile_geom(), tiles, part, split, n_pieces);
     if ((long long)slots * kNumXcd > 0x7fffffffLL)
       return fail(ctx, ADLOCO_EUNSUPPORTED, "grad_stats: too many tiles for one launch");
-    std::vector<int> csr;
-    csr.insert(csr.end(), lay.begin(), lay.end());
-    csr.insert(csr.end(), ptr.begin(), ptr.end());
-    csr.insert(csr.end(), idx.begin(), idx.end());
+    const std::vector<int> csr = tiles_by_layer(tiles, use, n_listed);
     rc = ensure_scratch(ctx, ctx->ts_tab, tiles.size() * sizeof(int4));
     if (rc) return rc;
     rc = ensure_scratch(ctx, ctx->ts_part_idx, part.size() * sizeof(int));
@@ -481,8 +534,7 @@ extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* laye
     ADLOCO_HIP_CHECK(ctx, hipStreamSynchronize(st));
     ctx->ts_slots = slots;
     ctx->ts_n_split = int(split.size());
-    ctx->ts_n_listed = int(lay.size());
-    ctx->ts_idx_len = int(idx.size());
+    ctx->ts_n_listed = n_listed;
     ctx->ts_B = B;
   }
 
@@ -546,8 +598,17 @@ extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* laye
     if (e != hipSuccess)
       return fail(ctx, ADLOCO_EHIP, "grad_stats: tile statistics launch failed: %s", hipGetErrorString(e));
   }
-  ev = (!tile_form && !sum_only && ctx->n_linear > 0) ? prof_begin(ctx, st) : nullptr;
-  if (tile_form || sum_only || ctx->n_linear == 0)
+  if (plain_form) {
+    ev = prof_begin(ctx, st);
+    e = launch_plain_tiles(g.layers, ctx->st_plain, 1, B, T, dtype, accumulate, nullptr,
+                           sum_only ? nullptr : g.partials, int(n_pairs), st);
+    prof_end(ctx, kProfTileStats, ev, st);
+    if (e != hipSuccess)
+      return fail(ctx, ADLOCO_EHIP, "grad_stats: plain tile launch failed: %s", hipGetErrorString(e));
+  }
+  const bool formed = tile_form || plain_form;     // norms (unless sum_only) and gradient sums are done
+  ev = (!formed && !sum_only && ctx->n_linear > 0) ? prof_begin(ctx, st) : nullptr;
+  if (formed || sum_only || ctx->n_linear == 0)
     ;
   else if (dual) {
     // the dual-tile kernel walks groups of layers that share their activations (A A^T once per group)
@@ -568,9 +629,9 @@ extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* laye
   prof_end(ctx, kProfGram, ev, st);
   if (e != hipSuccess)
     return fail(ctx, ADLOCO_EHIP, "grad_stats: Gram launch failed: %s", hipGetErrorString(e));
-  ev = (!tile_form && ctx->wgrad_blocks > 0) ? prof_begin(ctx, st) : nullptr;
+  ev = (!formed && ctx->wgrad_blocks > 0) ? prof_begin(ctx, st) : nullptr;
   const long long rows = (long long)B * T;
-  if (tile_form)
+  if (formed)
     ;
   else if (is_16bit(dtype) && ctx->wgrad_variant >= 2 && ctx->wgx_slots > 0 && rows % 32 == 0 &&
            rows / 32 <= 0x7fffffffLL)
@@ -701,7 +762,7 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
     }
     std::vector<int4> tiles;
     int group = 1;
-    const int slots = any ? make_ip_tiles(tab, use, B, T, ctx->ip_group_tuning, tiles, group) : 0;
+    const int slots = any ? make_ip_tiles(tab, use, B, T, ip_tile_geom(), ctx->ip_group_tuning, tiles, group) : 0;
     if ((long long)slots * kNumXcd > 0x7fffffffLL)
       return fail(ctx, ADLOCO_EUNSUPPORTED, "inner_products: too many tiles for one launch");
     rc = ensure_scratch(ctx, ctx->ip_tab, std::max<size_t>(tiles.size(), 1) * sizeof(int4));
@@ -718,7 +779,17 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
     ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(ctx->ip_flags.ptr, use.data(), size_t(n_layers),
                                          hipMemcpyHostToDevice, st));
     ADLOCO_HIP_CHECK(ctx, hipStreamSynchronize(st));
-    ctx->ip_use = std::move(use);
+    std::vector<char> rest(n_layers, 0);
+    bool any_rest = false;
+    for (int l = 0; l < n_layers; ++l) {
+      rest[l] = tab[l].kind == ADLOCO_KIND_LINEAR && !use[l];
+      any_rest = any_rest || rest[l];
+    }
+    ctx->ip_plain.slots = 0;
+    if (any_rest) {
+      rc = build_plain_tiles(ctx, ctx->ip_plain, rest, B, T, ctx->ip_group_tuning, st);
+      if (rc) return rc;
+    }
     ctx->ip_slots = slots;
     ctx->ip_group = group;
     ctx->ip_B = B;
@@ -730,13 +801,6 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
   if (rc) return rc;
   rc = ensure_scratch(ctx, ctx->sample_f64, size_t(B) * sizeof(double));
   if (rc) return rc;
-  size_t part_doubles = 1;
-  for (int l = 0; l < n_layers; ++l)
-    if (tab[l].kind == ADLOCO_KIND_LINEAR && !ctx->ip_use[l])
-      part_doubles = std::max(part_doubles, ip_generic_part_doubles(tab[l], B));
-  rc = ensure_scratch(ctx, ctx->ip_part, part_doubles * sizeof(double));
-  if (rc) return rc;
-
   const LayerDev* dl = static_cast<const LayerDev*>(ctx->layer_tab.ptr);
   float* dot = static_cast<float*>(ctx->ip_dot.ptr);
   float* sq = static_cast<float*>(ctx->ip_sq.ptr);
@@ -744,9 +808,8 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
   hipError_t e = launch_ip_tiles(dl, ctx->ip_tab.ptr, ctx->ip_slots, T, ctx->ip_group, dtype,
                                  per_sample_sqnorm != nullptr,
                                  static_cast<float*>(ctx->ip_tile_out.ptr), st);
-  for (int l = 0; l < n_layers && e == hipSuccess; ++l)
-    if (tab[l].kind == ADLOCO_KIND_LINEAR && !ctx->ip_use[l])
-      e = launch_ip_generic(tab[l], l, B, T, dtype, static_cast<double*>(ctx->ip_part.ptr), dot, sq, st);
+  if (e == hipSuccess)
+    e = launch_plain_tiles(dl, ctx->ip_plain, 0, B, T, dtype, 0, dot, sq, 1, st);
   if (e == hipSuccess && !ctx->vec_host.empty())
     e = launch_vector_stats(dl, static_cast<const AuxDesc*>(ctx->vec_tab.ptr), int(ctx->vec_host.size()),
                             ctx->vec_blocks, ctx->vec_blocks2, B, T, dtype,

@@ -5,9 +5,9 @@
 //   * the statistics of the norm test (eq. 4, Section 3.3.1): ||g_i||^2 from the squares of the
 //     tiles while they are being added up to G -- the route of adloco_grad_stats where G is
 //     formed by the library.
-// Aligned bf16 layers take the MFMA tile kernel (ip_tile_kernel); a plain path covers every other
-// layer for the inner products, and the dot kernels of the vector / table blocks and the
-// reductions follow.  The inner-product paths also return the explicit ||g_i||^2, a second
+// Aligned 16-bit layers take the MFMA tile kernel (ip_tile_kernel); every other layer the plain tile
+// kernel (tile_plain_kernels.hip).  The dot kernels of the vector / table blocks and the reductions
+// follow.  The inner-product paths also return the explicit ||g_i||^2, a second
 // route to the Gram kernel's result.
 #include "common.h"
 
@@ -415,22 +415,23 @@ __global__ __launch_bounds__(64) void stats_tile_finalize_kernel(const int4* til
 // goes to one XCD (one L2); sets are dealt to the least loaded XCD, largest first.  The run
 // length trades the once-per-entry costs (G tile, pipeline fill) against the balance of the last
 // round of workgroups.
-int make_ip_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, int T,
+TileGeom ip_tile_geom() { return TileGeom{kIpE, kIpC, kIpK, kNumCu / kNumXcd}; }
+
+int make_ip_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, int T, TileGeom geom,
                   int forced_group, std::vector<int4>& out, int& group) {
   auto tiles_of = [&](const LayerDev& L) {
-    return (long long)((L.d_out + kIpE - 1) / kIpE) * ((L.d_in + kIpC - 1) / kIpC);
+    return (long long)((L.d_out + geom.e - 1) / geom.e) * ((L.d_in + geom.c - 1) / geom.c);
   };
   long long tiles_all = 0;
   for (size_t l = 0; l < layers.size(); ++l)
     if (use[l]) tiles_all += tiles_of(layers[l]);
-  // cost in chunks of 32 token rows: an entry of s samples costs s * T/32 + 8; 32 workgroups run
-  // at a time on each of the 8 XCDs
-  const double per_sample = double(T) / kIpK, fixed = 8.0;
+  // cost in chunks: an entry of s samples costs s * T/k + 8; `room` workgroups run at a time on each of the 8 XCDs
+  const double per_sample = double((T + geom.k - 1) / geom.k), fixed = 8.0;
   double best = 0.0;
   group = 1;
   for (int gsz = 1; gsz <= std::min(B, 0x7fff); ++gsz) {
     const long long runs = (B + gsz - 1) / gsz;
-    const double rounds = std::ceil(double(tiles_all * runs) / (32.0 * kNumXcd));
+    const double rounds = std::ceil(double(tiles_all * runs) / (double(geom.room) * kNumXcd));
     const double cost = rounds * (gsz * per_sample + fixed);
     if (gsz == 1 || cost < best * 0.999) {
       best = cost;
@@ -456,8 +457,8 @@ int make_ip_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& 
       if (load[x] < load[bx]) bx = x;
     load[bx] += S.n * S.cnt;
     const LayerDev& L = layers[S.layer];
-    for_tiles_blocked((L.d_out + kIpE - 1) / kIpE, (L.d_in + kIpC - 1) / kIpC, kIpE / kIpC, [&](int e, int c) {
-      per[bx].push_back(int4{S.layer, e * kIpE, c * kIpC, S.s0 | (S.cnt << 16)});
+    for_tiles_blocked((L.d_out + geom.e - 1) / geom.e, (L.d_in + geom.c - 1) / geom.c, geom.e / geom.c, [&](int e, int c) {
+      per[bx].push_back(int4{S.layer, e * geom.e, c * geom.c, S.s0 | (S.cnt << 16)});
     });
   }
   size_t slots = 0;
@@ -484,23 +485,19 @@ hipError_t launch_ip_tiles(const LayerDev* layers, const void* tiles, int slots,
   return hipGetLastError();
 }
 
-// Tile table of the statistics form: one entry per 256 x 128 tile covering all B samples; the
-// tiles of a layer go to one XCD where possible (they stream the same rows).  The entries of an XCD's incomplete last round of 32 are split along the samples
-// into pieces whose partial sums a small kernel adds up in piece order.
-// lay / ptr / idx: for every listed layer the indices (into `out`) of its entries.
-int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B,
-                     std::vector<int4>& out, std::vector<int>& part, std::vector<int4>& split,
-                     std::vector<int>& lay, std::vector<int>& ptr, std::vector<int>& idx,
-                     int& n_pieces) {
-  constexpr int kCuPerXcd = kNumCu / kNumXcd;
+// Tile table of the statistics form: one entry per tile covering all B samples; the tiles of a layer go to one XCD
+// where possible (they stream the same rows).  The entries of an XCD's incomplete last round of workgroups are split
+// along the samples into pieces whose partial sums a small kernel adds up in piece order.
+int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, TileGeom geom,
+                     std::vector<int4>& out, std::vector<int>& part, std::vector<int4>& split, int& n_pieces) {
   // all tiles in layer order (within a layer: blocks of tiles that share rows), cut into eight
   // equal runs: a layer stays on one XCD unless it straddles a cut, and the XCDs get the same
   // number of tiles
   std::vector<int4> all;
   for (size_t l = 0; l < layers.size(); ++l) {
     if (!use[l]) continue;
-    for_tiles_blocked((layers[l].d_out + kIpE - 1) / kIpE, (layers[l].d_in + kIpC - 1) / kIpC, kIpE / kIpC,
-                      [&](int e, int c) { all.push_back(int4{int(l), e * kIpE, c * kIpC, B << 16}); });
+    for_tiles_blocked((layers[l].d_out + geom.e - 1) / geom.e, (layers[l].d_in + geom.c - 1) / geom.c, geom.e / geom.c,
+                      [&](int e, int c) { all.push_back(int4{int(l), e * geom.e, c * geom.c, B << 16}); });
   }
   std::vector<std::vector<int4>> per(kNumXcd);
   for (int x = 0; x < kNumXcd; ++x)
@@ -512,8 +509,8 @@ int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char
   std::vector<std::vector<int>> finp(kNumXcd);
   for (int x = 0; x < kNumXcd; ++x) {
     const int n = int(per[x].size());
-    const int full = n / kCuPerXcd * kCuPerXcd, left = n - full;
-    const int S = left > 0 ? std::min(kCuPerXcd / left, B) : 1;
+    const int full = n / geom.room * geom.room, left = n - full;
+    const int S = left > 0 ? std::min(geom.room / left, B) : 1;
     for (int i = 0; i < n; ++i) {
       if (i < full || S < 2 || n_pieces + S > 0xffff) {
         fin[x].push_back(per[x][i]);
@@ -540,19 +537,24 @@ int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char
       out[x * slots + i] = fin[x][i];
       part[x * slots + i] = finp[x][i];
     }
-  std::vector<std::vector<int>> by_layer(layers.size());
-  for (size_t k = 0; k < out.size(); ++k)
-    if (out[k].x >= 0) by_layer[out[k].x].push_back(int(k));
-  lay.clear();
-  ptr.assign(1, 0);
-  idx.clear();
-  for (size_t l = 0; l < layers.size(); ++l) {
+  return int(slots);
+}
+
+std::vector<int> tiles_by_layer(const std::vector<int4>& tiles, const std::vector<char>& use, int& n_listed) {
+  std::vector<std::vector<int>> by_layer(use.size());
+  for (size_t k = 0; k < tiles.size(); ++k)
+    if (tiles[k].x >= 0) by_layer[tiles[k].x].push_back(int(k));
+  std::vector<int> lay, ptr(1, 0), idx;
+  for (size_t l = 0; l < use.size(); ++l) {
     if (!use[l]) continue;
     lay.push_back(int(l));
     idx.insert(idx.end(), by_layer[l].begin(), by_layer[l].end());
     ptr.push_back(int(idx.size()));
   }
-  return int(slots);
+  n_listed = int(lay.size());
+  lay.insert(lay.end(), ptr.begin(), ptr.end());
+  lay.insert(lay.end(), idx.begin(), idx.end());
+  return lay;
 }
 
 hipError_t launch_stats_tiles(const LayerDev* layers, const void* tiles, const int* part, int slots,
@@ -575,49 +577,6 @@ hipError_t launch_stats_tiles(const LayerDev* layers, const void* tiles, const i
   hipLaunchKernelGGL(stats_tile_finalize_kernel, dim3(unsigned(n_listed) * B), dim3(64), 0, st,
                      static_cast<const int4*>(tiles), tile_out, B, lay, ptr, idx, B, partials, n_pairs);
   return hipGetLastError();
-}
-
-// Plain path for one linear layer: workgroup = (sample, 256 rows e of the gradient); a thread owns
-// one row e and walks the columns c: g_ec = sum_t delta[t,e] a[t,c] (fp32), then adds
-// g_ec * G[e,c] and g_ec^2 in fp64.  Slab totals go to part[(sample * slabs + slab) * 2 + {0,1}].
-template <typename E>
-__global__ __launch_bounds__(kIpThreads) void ip_generic_kernel(LayerDev L, int T, int slabs,
-                                                               double* part) {
-  __shared__ double lds4[4];
-  const int sample = blockIdx.x / slabs, slab = blockIdx.x % slabs;
-  const int e = slab * kIpThreads + threadIdx.x;
-  const E* D = reinterpret_cast<const E*>(L.delta) + (long long)sample * T * L.delta_stride;
-  const E* A = reinterpret_cast<const E*>(L.a) + (long long)sample * T * L.a_stride;
-  double dot = 0.0, sq = 0.0;
-  if (e < L.d_out) {
-    for (int c = 0; c < L.d_in; ++c) {
-      float gec = 0.f;
-      for (int t = 0; t < T; ++t)
-        gec = fmaf(ip_elem(D[(long long)t * L.delta_stride + e]), ip_elem(A[(long long)t * L.a_stride + c]), gec);
-      dot += double(gec) * double(L.grad_sum[(size_t)e * L.d_in + c]);
-      sq += double(gec) * double(gec);
-    }
-  }
-  const double s0 = ip_block_sum(dot, lds4);
-  const double s1 = ip_block_sum(sq, lds4);
-  if (threadIdx.x == 0) {
-    part[((size_t)sample * slabs + slab) * 2] = s0;
-    part[((size_t)sample * slabs + slab) * 2 + 1] = s1;
-  }
-}
-
-// Slab totals of the plain path -> dot[layer, sample], sq[layer, sample].
-__global__ __launch_bounds__(64) void ip_generic_finish_kernel(const double* part, int slabs, int B,
-                                                               float* dot, float* sq) {
-  const int i = blockIdx.x * 64 + threadIdx.x;
-  if (i >= B) return;
-  double s0 = 0.0, s1 = 0.0;
-  for (int k = 0; k < slabs; ++k) {
-    s0 += part[((size_t)i * slabs + k) * 2];
-    s1 += part[((size_t)i * slabs + k) * 2 + 1];
-  }
-  dot[i] = float(s0);
-  sq[i] = float(s1);
 }
 
 // Vector blocks: v_i [d] is in `vec` (vector_rowsum_kernel); <v_i, G> -> dot[layer, sample].
@@ -727,26 +686,6 @@ __global__ __launch_bounds__(1024) void ip_finalize_batch_kernel(const double* s
     }
     acc->reserved = 0;
   }
-}
-
-hipError_t launch_ip_generic(const LayerDev& L, int layer, int B, int T, int dtype, double* part,
-                             float* dot, float* sq, hipStream_t st) {
-  const int slabs = (L.d_out + kIpThreads - 1) / kIpThreads;
-  if (dtype == ADLOCO_BF16)
-    hipLaunchKernelGGL(ip_generic_kernel<unsigned short>, dim3(unsigned(B) * slabs), dim3(kIpThreads), 0,
-                       st, L, T, slabs, part);
-  else if (dtype == ADLOCO_F16)
-    hipLaunchKernelGGL(ip_generic_kernel<_Float16>, dim3(unsigned(B) * slabs), dim3(kIpThreads), 0,
-                       st, L, T, slabs, part);
-  else
-    hipLaunchKernelGGL(ip_generic_kernel<float>, dim3(unsigned(B) * slabs), dim3(kIpThreads), 0, st, L, T,
-                       slabs, part);
-  hipLaunchKernelGGL(ip_generic_finish_kernel, dim3((B + 63) / 64), dim3(64), 0, st, part, slabs, B,
-                     dot + size_t(layer) * B, sq + size_t(layer) * B);
-  return hipGetLastError();
-}
-size_t ip_generic_part_doubles(const LayerDev& L, int B) {
-  return size_t(B) * ((L.d_out + kIpThreads - 1) / kIpThreads) * 2;
 }
 
 hipError_t launch_ip_vector_table(const LayerDev* layers, const AuxDesc* vec_tab, int n_vec,
