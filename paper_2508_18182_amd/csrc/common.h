@@ -46,6 +46,21 @@ __device__ __forceinline__ void mfma_16x16x32(mfma_f32x4& c, mfma_bf16x8 a, mfma
   else
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
+// The same from zero: the old accumulators are only overwritten.  A reader of the old values in between needs no fence
+// if many MFMAs lie between the one that wrote them and itself.
+template <bool F16>
+__device__ __forceinline__ void mfma_16x16x32_fresh(mfma_f32x4& c, mfma_bf16x8 a, mfma_bf16x8 b) {
+  if constexpr (F16)
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "+a"(c) : "v"(a), "v"(b));
+  else
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "+a"(c) : "v"(a), "v"(b));
+}
+// Element j of an accumulator block, read in place.
+__device__ __forceinline__ float mfma_acc(const mfma_f32x4& c, int j) {
+  float v;
+  asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(c[j]));
+  return v;
+}
 template <int M, int N> __device__ __forceinline__ void mfma_fence(mfma_f32x4 (&acc)[M][N]) {
   asm volatile("s_nop 15\n\ts_nop 15");
 #pragma unroll
@@ -126,6 +141,17 @@ __device__ __forceinline__ void direct_load_lds16_s(unsigned lane_off, const voi
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :: "v"(lane_off), "s"(base), "s"(lds_addr) : "m0");
 }
+// Both with only the lanes of `mask` taking part: the 16 bytes of the others stay as they are in LDS.  All 64 lanes
+// have to be active at the call.
+__device__ __forceinline__ void direct_load_lds16_masked(unsigned lane_off, const void* base, unsigned lds_addr,
+                                                         unsigned long long mask) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
+               :: "v"(lane_off), "s"(base), "s"(lds_addr), "s"(mask) : "m0");
+}
+__device__ __forceinline__ void direct_load_lds16_vmasked(const void* src, unsigned lds_addr, unsigned long long mask) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %0, off\n\ts_mov_b64 exec, -1"
+               :: "v"(src), "s"(lds_addr), "s"(mask) : "m0");
+}
 // A wave-uniform pointer that the compiler may hold in vector registers, moved to scalar registers
 // (the direct loads above take their base address there).
 template <typename P> __device__ __forceinline__ const P* uniform_ptr(const P* p) {
@@ -138,6 +164,45 @@ template <typename P> __device__ __forceinline__ const P* uniform_ptr(const P* p
 __device__ __forceinline__ unsigned lds_address(const void* p) {
   return __builtin_amdgcn_readfirstlane(
       (unsigned)(size_t)(const __attribute__((address_space(3))) unsigned char*)p);
+}
+
+// A wave's M x N accumulator blocks of 16 x 16 -> G [d_out, d_in]: this lane's element j of block (m, n) is entry
+// (r + 16 * m + j, c + 16 * n).  The old entries of `MB` block rows are requested together (addresses past the edge are
+// clamped): one by one, each load would be waited for on its own, about 1 us apiece at the end of every tile.
+template <int M, int N, int MB, typename F>
+__device__ __forceinline__ void put_grad_tile(float* G, int d_out, int d_in, int r, int c, bool accumulate, F value) {
+  static_assert(M % MB == 0, "whole batches");
+#pragma unroll
+  for (int m0 = 0; m0 < M; m0 += MB) {
+    float old[MB][N][4];
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int n = 0; n < N; ++n)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) old[m][n][j] = 0.f;
+    if (accumulate) {
+#pragma unroll
+      for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int n = 0; n < N; ++n)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int rr = r + (m0 + m) * 16 + j, cc = c + n * 16;
+            old[m][n][j] = G[(size_t)(rr < d_out ? rr : d_out - 1) * d_in + (cc < d_in ? cc : d_in - 1)];
+          }
+    }
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int n = 0; n < N; ++n)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int rr = r + (m0 + m) * 16 + j, cc = c + n * 16;
+          const float v = value(m0 + m, n, j);
+          if (rr < d_out && cc < d_in) G[(size_t)rr * d_in + cc] = accumulate ? old[m][n][j] + v : v;
+        }
+  }
 }
 
 struct Scratch {
@@ -197,7 +262,7 @@ struct adloco_ctx {
   int vec_blocks = 0, vec_blocks2 = 0, emb_blocks = 0;
   // inner products (Section 3.3.2)
   adloco::Scratch ip_tab;      // int4 tile table of the inner-product form of the tile GEMM
-  adloco::Scratch ip_tile_out; // float [tiles][ip_group][8 waves][2]
+  adloco::Scratch ip_tile_out; // float [tiles][ip_group][4 waves][2]
   adloco::Scratch ip_dot, ip_sq;   // float [n_layers][B] of the blocks outside the tile table
   adloco::Scratch ip_flags;    // unsigned char [n_layers]: 1 = block is in the tile table
   int ip_slots = 0, ip_group = 1, ip_B = -1, ip_T = -1;

@@ -480,8 +480,7 @@ extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* laye
   // fp32 ones always, also for the plain gradient sum: 4 x {768 -> 2304, 768 -> 768, 768 -> 3072, 3072 -> 768}, B 8,
   // T 256 takes 1.28 ms against 5.02 ms with the vector-unit kernels of the two steps, a gradient sum of 0.1 TFLOP on
   // widths of 300 to 1600 0.6 - 1.2 ms against 1.7 - 3.4 ms.
-  const bool tile_form = !sum_only && ctx->stats_variant != 0 && ctx->ts_ok && T % 32 == 0 &&
-                         T <= (1 << 20) && B <= 0x7fff;
+  const bool tile_form = !sum_only && ctx->stats_variant != 0 && ctx->ts_ok && T <= (1 << 20) && B <= 0x7fff;
   const bool plain_form = dtype == ADLOCO_F32 && ctx->n_formed > 0 && B <= 0x7fff && ctx->stats_variant != 0 &&
                           (sum_only || ctx->n_formed == ctx->n_linear);
   if (tile_form || plain_form) n_pairs = 1;      // one finished sum per (layer, sample)
@@ -517,7 +516,7 @@ extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* laye
     if (rc) return rc;
     rc = ensure_scratch(ctx, ctx->ts_ptiles, std::max<size_t>(n_pieces, 1) * 256 * 128 * sizeof(float));
     if (rc) return rc;
-    rc = ensure_scratch(ctx, ctx->ts_out, tiles.size() * size_t(B) * 16 * sizeof(float));
+    rc = ensure_scratch(ctx, ctx->ts_out, tiles.size() * size_t(B) * 8 * sizeof(float));
     if (rc) return rc;
     rc = ensure_scratch(ctx, ctx->ts_csr, csr.size() * sizeof(int));
     if (rc) return rc;
@@ -756,8 +755,7 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
     for (int l = 0; l < n_layers; ++l) {
       // the tile kernel counts an entry's chunks of 32 rows in 32 bits and addresses the rows of a
       // chunk with 32-bit byte offsets
-      use[l] = tab[l].kind == ADLOCO_KIND_LINEAR && is_16bit(dtype) && tab[l].fast && T % 32 == 0 &&
-               T <= (1 << 20) && tab[l].a_stride < (1 << 25) && tab[l].delta_stride < (1 << 25);
+      use[l] = tab[l].kind == ADLOCO_KIND_LINEAR && is_16bit(dtype) && tab[l].fast && T <= (1 << 20) && tab[l].a_stride < (1 << 25) && tab[l].delta_stride < (1 << 25);
       any = any || use[l];
     }
     std::vector<int4> tiles;
@@ -768,7 +766,7 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
     rc = ensure_scratch(ctx, ctx->ip_tab, std::max<size_t>(tiles.size(), 1) * sizeof(int4));
     if (rc) return rc;
     rc = ensure_scratch(ctx, ctx->ip_tile_out,
-                        std::max<size_t>(tiles.size(), 1) * group * 16 * sizeof(float));
+                        std::max<size_t>(tiles.size(), 1) * group * 8 * sizeof(float));
     if (rc) return rc;
     rc = ensure_scratch(ctx, ctx->ip_flags, size_t(n_layers));
     if (rc) return rc;

@@ -9,6 +9,8 @@
 // kernel (tile_plain_kernels.hip).  The dot kernels of the vector / table blocks and the reductions
 // follow.  The inner-product paths also return the explicit ||g_i||^2, a second
 // route to the Gram kernel's result.
+#include <type_traits>
+
 #include "common.h"
 
 namespace adloco {
@@ -33,46 +35,46 @@ __device__ __forceinline__ double ip_block_sum(double v, double* lds4) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Tile path (aligned bf16 linear layers, T a multiple of 32).
+// Tile path (aligned 16-bit linear layers).
 // Work item = one 256 (d_out) x 128 (d_in) tile of one layer for a run of consecutive samples.
-// The workgroup (8 waves as 4 x 2, wave tile 64 x 64) streams the token rows of its samples
-// through one uninterrupted load pipeline: the rows of consecutive samples are consecutive in
-// memory.  Every T rows the accumulators hold that sample's gradient tile.  A second set of 64
-// registers per lane, in the MFMA accumulator layout, holds
+// The workgroup (four waves as 2 x 2, one per SIMD, wave tile 128 x 64, 16x16x32 MFMA) streams the token rows of its
+// samples in chunks of 32 through one uninterrupted load pipeline.  After the last chunk of a sample the accumulators
+// hold that sample's gradient tile.  A second set of 128 registers per lane, in the MFMA accumulator layout, holds
 //   MODE 0 (inner products): the tile of G; the finished sample tile is multiplied element-wise
-//     with it, summed over the wave and cleared; two floats per (tile, sample, wave) leave the chip;
+//     with it and summed over the wave; two floats per (tile, sample, wave) leave the chip;
 //   MODE 1 (statistics): the running sum of the sample tiles; each finished tile is squared and
-//     summed (its share of ||g_i||^2), added to the running sum and cleared; the sum is stored as
-//     the tile of G at the end.
-// A 256 x 256 tile would need 128 accumulators + 128 registers of the second set per lane, the
-// whole register file at two waves per SIMD.
-//   Staging: global -> LDS directly, four stages of 32 token rows x (256 + 128) columns.  A load
-//   instruction moves 1 KiB: token rows j, j+16 of delta (2 x 512 B) or rows j, j+8, j+16, j+24 of
-//   a (4 x 256 B); the 1 KiB blocks are 1088 bytes apart so that the four consecutive rows of an
-//   LDS transpose read fall into different banks.  One barrier per chunk, loads two chunks ahead.
+//     summed (its share of ||g_i||^2) and added to the running sum, which is stored as the tile of G at the end.
+// That work on a finished tile is spread between the MFMAs of the next sample's first chunk, which start from zero
+// instead of the old accumulators: each block is read just before its first MFMA of the new sample.
+// A 256 x 256 tile would need 256 accumulators + 256 registers of the second set per lane: the whole register file.
+//   Staging: global -> LDS directly, six stages of 32 token rows x (256 + 128) columns, loads five chunks ahead.  A
+//   load instruction moves 1 KiB: two token rows of delta (2 x 512 B) or four of a (4 x 256 B); the 1 KiB blocks are
+//   1056 bytes apart and the rows are dealt to them so that the eight rows that 32 lanes of a transpose read touch
+//   start in eight different groups of banks.  LDS reads and loads go out one by one behind the MFMAs, one barrier
+//   per chunk.  Columns past the edge of the layer are never loaded: their lanes are switched off and the LDS is
+//   cleared beforehand.  RAGGED (T not a multiple of 32): token rows past T come from a line of zeros.
+// What bounds it: the LDS (96 transpose reads of 512 B and 24 KiB of direct loads per chunk of 512 MFMA cycles) and the
+// chip's power.  48 GPT-2-small linears, B 32, T 512 (2.78 TFLOP): 2.82 ms for statistics, 2.95 ms for the inner
+// products with norms (eight waves of 64 x 64 with 32x32x16 MFMAs: 2.85 and 3.00 ms); without loads 2.4 ms, with loads
+// that all hit the L2 2.35 ms, without the work on finished tiles 2.6 ms.  The same linears in fp16 with B 5, T 1001,
+// added to a gradient sum: 1.10 ms (Gram kernel and 128 x 128 gradient-sum kernel: 2.37 ms).
 // ---------------------------------------------------------------------------------------
-typedef __attribute__((ext_vector_type(8))) __bf16 ip_bf16x8;
-typedef __attribute__((ext_vector_type(16))) float ip_f32x16;
 typedef __attribute__((ext_vector_type(4))) short ip_s16x4;
 typedef __attribute__((ext_vector_type(8))) short ip_s16x8;
+typedef __attribute__((ext_vector_type(4))) unsigned ip_u32x4;
 
 constexpr int kIpE = 256;                         // tile rows (d_out side)
 constexpr int kIpC = 128;                         // tile columns (d_in side)
 constexpr int kIpK = 32;                          // token rows per stage
-constexpr int kIpBlk = 1024 + 64;                 // one load instruction + 64 B skew
+constexpr int kIpBlk = 1024 + 32;                 // one load instruction + 32 B skew
 constexpr int kIpOpE = 16 * kIpBlk;               // delta side of a stage
 constexpr int kIpOpC = 8 * kIpBlk;                // a side of a stage
-constexpr int kIpStage = kIpOpE + kIpOpC;         // 25.5 KiB
-#ifndef IP_WM
-#define IP_WM 4
-#endif
-constexpr int kIpWM = IP_WM, kIpWN = 2;           // waves along d_out and d_in
-constexpr int kIpWaves = kIpWM * kIpWN;
-constexpr int kIpFM = kIpE / (32 * kIpWM);        // 32x32 MFMA blocks per wave along d_out
-constexpr int kIpFN = kIpC / (32 * kIpWN);        // ... along d_in
-constexpr int kIpLdE = 16 / kIpWaves, kIpLdC = 8 / kIpWaves, kIpLd = kIpLdE + kIpLdC;   // loads per wave
-constexpr int kIpStages = 4;
-constexpr int kIpLds = kIpStages * kIpStage;      // 102 KiB
+constexpr int kIpStage = kIpOpE + kIpOpC;         // 24.75 KiB
+constexpr int kIpWaves = 4;
+constexpr int kIpFM = 8, kIpFN = 4;               // 16x16 MFMA blocks per wave along d_out and d_in
+constexpr int kIpLd = 6;                          // loads per wave and chunk: four of delta, two of a
+constexpr int kIpStages = 6;
+constexpr int kIpLds = kIpStages * kIpStage;      // 148.5 KiB
 
 struct IpTileArgs {
   const LayerDev* layers;
@@ -86,6 +88,8 @@ struct IpTileArgs {
   float* partials;        // [pieces][256][128] fp32
   int accumulate;         // G += sum instead of G = sum
 };
+
+__device__ __attribute__((aligned(16))) const unsigned ip_zero_line[4] = {0, 0, 0, 0};
 
 // Sum over the 64 lanes without the LDS round trips of a shuffle chain: four DPP steps leave the
 // total of each row of 16 lanes in all of its lanes, the four row totals are then read as scalars.
@@ -107,13 +111,12 @@ __device__ __forceinline__ float ip_wave_sum_f32(float v) {
 template <int N> __device__ __forceinline__ void ip_wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 0xf) | ((N >> 4) << 14));
 }
-__device__ __forceinline__ int ip_row_off_e(int row) { return (row & 15) * kIpBlk + (row >> 4) * 512; }
-__device__ __forceinline__ int ip_row_off_c(int row) { return (row & 7) * kIpBlk + (row >> 3) * 256; }
 
 // MODE 1 is the explicit form of the per-sample norms: when G has to be formed here anyway, its
 // per-sample terms pass through the registers and the Gram contraction is not needed.
-// SQ: also return the tile's sum of squares (always in MODE 1).
-template <int MODE, bool SQ, bool F16>
+// SQ: also return the tile's sum of squares (always in MODE 1).  ODD: a sample has an odd number of chunks (the two
+// fragment sets take turns, so that the loop over the samples is written for one parity).
+template <int MODE, bool SQ, bool F16, bool RAGGED, bool ODD>
 __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int xcd = blockIdx.x % kNumXcd, slot = blockIdx.x / kNumXcd;
@@ -123,237 +126,260 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
   const int e0 = tile.y, c0 = tile.z;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wave / kIpWN, wn = wave % kIpWN;  // kIpWM x kIpWN waves
-  const int nk_sample = g.T / kIpK;               // chunks per sample
-  const long long ck0 = (long long)(tile.w & 0xffff) * nk_sample;
-  const int nk = (tile.w >> 16) * nk_sample;       // chunks of this entry: the host keeps it below 2^31
+  const int wm = wave >> 1, wn = wave & 1;        // 2 x 2 waves
+  const int i16 = lane & 15, grp = lane >> 4;
+  const int nk_sample = (g.T + kIpK - 1) / kIpK;  // chunks per sample
+  const int nk = (tile.w >> 16) * nk_sample;      // chunks of this entry: the host keeps it below 2^31
+  const unsigned lds_base = lds_address(lds);     // LDS byte addresses are handled as integers
 
-  // ---- second register set.  Accumulator element j of a 32x32 block: row
-  // (j/4)*8 + (lane/32)*4 + j%4, column lane%32.  MODE 0: this lane's entries of the G tile
-  // (zero past the edge); MODE 1: running sum of the sample tiles.
-  float gt[kIpFM][kIpFN][16];
+  // ---- second register set.  Accumulator element j of a 16x16 block: row grp * 4 + j, column i16.  MODE 0: this
+  // lane's entries of the G tile (zero past the edge); MODE 1: running sum of the sample tiles.
+  float gt[kIpFM][kIpFN][4];
 #pragma unroll
   for (int m = 0; m < kIpFM; ++m)
 #pragma unroll
     for (int n = 0; n < kIpFN; ++n) {
-      const int tc = c0 + wn * (32 * kIpFN) + n * 32 + (lane & 31);
+      const int tc = c0 + wn * 64 + n * 16 + i16;
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int tr = e0 + wm * (32 * kIpFM) + m * 32 + (j >> 2) * 8 + (lane >> 5) * 4 + (j & 3);
+      for (int j = 0; j < 4; ++j) {
+        const int tr = e0 + wm * 128 + m * 16 + grp * 4 + j;
         if (MODE == 0) {
           const bool ok = tr < L.d_out && tc < L.d_in;
           const float v = L.grad_sum[ok ? (size_t)tr * L.d_in + tc : 0];
           gt[m][n][j] = ok ? v : 0.f;
         } else {
-          gt[m][n][j] = 0.f;                       // running sum of the per-sample tiles
+          gt[m][n][j] = 0.f;
         }
       }
     }
-  const bool ragged = e0 + kIpE > L.d_out || c0 + kIpC > L.d_in;
-
-  // ---- direct loads, kIpLd per wave and chunk: delta instructions j = wave, wave + kIpWaves, ..
-  // (rows j and j + 16, 16-byte piece lane % 32), then a instructions j = wave, .. (rows
-  // j + 8 * (lane / 16), piece lane % 16).  Columns past the edge re-read the last valid piece.
-  // Address = (first row of the chunk: wave-uniform, scalar registers) + (row within the chunk and
-  // column: a 32-bit byte offset per lane, computed once; the host keeps row strides below 2^25).
-  unsigned lane_off[kIpLd];
-  int lds_off[kIpLd];
-#pragma unroll
-  for (int i = 0; i < kIpLd; ++i) {
-    const bool is_a = i >= kIpLdE;
-    const int j = wave + kIpWaves * (is_a ? i - kIpLdE : i);
-    const int row = is_a ? j + 8 * (lane >> 4) : j + 16 * (lane >> 5);
-    const int piece = is_a ? (lane & 15) : (lane & 31);
-    const int d = is_a ? L.d_in : L.d_out;
-    int col = (is_a ? c0 : e0) + piece * 8;
-    col = col < d ? col : d - 8;
-    lane_off[i] = unsigned(row * (is_a ? L.a_stride : L.delta_stride) + col) * 2u;
-    lds_off[i] = (is_a ? kIpOpE : 0) + j * kIpBlk;
+  if (e0 + kIpE > L.d_out || c0 + kIpC > L.d_in) {   // tile on the edge: the columns past it stay zero throughout
+    for (int o = threadIdx.x * 16; o < kIpLds; o += 64 * kIpWaves * 16)
+      *reinterpret_cast<ip_u32x4*>(lds + o) = ip_u32x4{0, 0, 0, 0};
+    __syncthreads();
   }
-  const unsigned short* const run_e = reinterpret_cast<const unsigned short*>(L.delta) + ck0 * kIpK * L.delta_stride;
-  const unsigned short* const run_c = reinterpret_cast<const unsigned short*>(L.a) + ck0 * kIpK * L.a_stride;
-  const unsigned lds_base = lds_address(lds);       // LDS byte addresses are handled as integers
-  // stage indices are carried along (no modulo in the loop: kIpStages need not be a power of two)
-  auto issue_loads = [&](int c, int st) {
-    const unsigned stage = lds_base + unsigned(st) * kIpStage;
-    const unsigned short* const pe = run_e + (long long)c * kIpK * L.delta_stride;
-    const unsigned short* const pc = run_c + (long long)c * kIpK * L.a_stride;
+
+  // ---- direct loads.  Delta: block b = wave + 4 * i (i = 0..3) holds rows r and r + 16 (lanes 0-31, 32-63) with
+  // r = (b & 3) | (b & 4) << 1 | (b & 8) >> 1, i.e. wave + {0, 8, 4, 12}[i].  a: block b = wave + 4 * i (i = 0, 1)
+  // holds rows r, r + 4, r + 16, r + 20 (16 lanes each) with r = wave + 8 * i.  Address = scalar base (first row of
+  // the chunk + the rows of i) + a byte offset per lane (the host keeps row strides below 2^25).
+  const int row_e = wave + 16 * (lane >> 5), row_c = wave + 4 * (grp & 1) + 16 * (grp >> 1);
+  const int col_e = e0 + (lane & 31) * 8, col_c = c0 + i16 * 8;
+  const unsigned off_e = unsigned(row_e * L.delta_stride + col_e) * 2u;
+  const unsigned off_c = unsigned(row_c * L.a_stride + col_c) * 2u;
+  const unsigned long long ok_e = __builtin_amdgcn_ballot_w64(col_e < L.d_out);
+  const unsigned long long ok_c = __builtin_amdgcn_ballot_w64(col_c < L.d_in);
+  const long long first = (long long)(tile.w & 0xffff) * g.T;
+  const unsigned short* pe = uniform_ptr(reinterpret_cast<const unsigned short*>(L.delta) + first * L.delta_stride);
+  const unsigned short* pc = uniform_ptr(reinterpret_cast<const unsigned short*>(L.a) + first * L.a_stride);
+  const unsigned ld_base = lds_base + wave * kIpBlk;
+  int ld_left = g.T;                              // RAGGED: rows of the sample from the next chunk to load on
+  constexpr int kRowsE[4] = {0, 8, 4, 12};
+  auto issue_load = [&](int i, unsigned st, unsigned long long on) {
+    if (i < 4)
+      direct_load_lds16_masked(off_e, pe + kRowsE[i] * L.delta_stride, ld_base + st + i * 4 * kIpBlk, ok_e & on);
+    else
+      direct_load_lds16_masked(off_c, pc + (i - 4) * 8 * L.a_stride, ld_base + st + kIpOpE + (i - 4) * 4 * kIpBlk, ok_c & on);
+  };
+  auto next_chunk = [&]() {
+    int step = kIpK;
+    if (RAGGED) {
+      step = ld_left < kIpK ? ld_left : kIpK;
+      ld_left -= step;
+      if (ld_left == 0) ld_left = g.T;
+    }
+    pe += step * L.delta_stride;
+    pc += step * L.a_stride;
+  };
+  // all loads of a chunk with fewer than 32 rows
+  auto issue_short_chunk = [&](unsigned st) {
+    const unsigned char* z = reinterpret_cast<const unsigned char*>(ip_zero_line);
 #pragma unroll
-    for (int i = 0; i < kIpLd; ++i)
-      direct_load_lds16_s(lane_off[i], i >= kIpLdE ? pc : pe, stage + lds_off[i]);
+    for (int i = 0; i < kIpLd; ++i) {
+      const bool e = i < 4;
+      const int extra = e ? kRowsE[i & 3] : (i - 4) * 8;
+      const unsigned char* p = e ? reinterpret_cast<const unsigned char*>(pe + extra * L.delta_stride) + off_e
+                                 : reinterpret_cast<const unsigned char*>(pc + extra * L.a_stride) + off_c;
+      const bool row_ok = (e ? row_e : row_c) + extra < ld_left;
+      direct_load_lds16_vmasked(row_ok ? p : z, ld_base + st + (e ? i * 4 * kIpBlk : kIpOpE + (i - 4) * 4 * kIpBlk),
+                                e ? ok_e : ok_c);
+    }
   };
 
-  // ---- fragments by LDS transpose reads.  Within a group of 16 lanes, lane s points at the 4
-  // columns 4*(s%4).. of token row kbase + s/4; the read hands lane i column i of the group's
-  // 16 at the four token rows.  Lane l ends up with column m0 + l%32, token rows
-  // ks*16 + (l/32)*8 + 0..7.
-  const int i16 = lane & 15;
-  const int krow = (lane >> 5) * 8 + (i16 >> 2);              // + ks*16 (+4 for the upper half)
-  const int ccol = ((lane >> 4) & 1) * 16 + (i16 & 3) * 4;    // column within a 32-wide block
-  // Every read address of a k-step is stage + (a part that depends on the lane) + (a constant of the
-  // fragment): three lane parts -- delta side; a side, rows r and r + 4, which wrap differently in
-  // its 8-row blocks -- are kept in registers, the constants ride in the offset field of the read.
+  // ---- fragments by LDS transpose reads.  Within a group of 16 lanes, lane s points at the 4 columns 4*(s%4).. of
+  // token row 8*grp + s/4 (+ 4 for the second read); the read hands lane i column i of the group's 16 at the four
+  // token rows: lane l ends up with column m0 + l%16, token rows (l/16)*8 + 0..7, the operand of a 16x16x32 MFMA.
   typedef __attribute__((address_space(3))) ip_s16x4* lds_ptr;
-  const unsigned lane_e = unsigned(ip_row_off_e(krow) + (wm * (32 * kIpFM) + ccol) * 2);
-  const unsigned lane_c0 = unsigned(kIpOpE + ip_row_off_c(krow) + (wn * (32 * kIpFN) + ccol) * 2);
-  const unsigned lane_c1 = unsigned(kIpOpE + ip_row_off_c(krow + 4) + (wn * (32 * kIpFN) + ccol) * 2);
-  auto frag = [&](lds_ptr p0, lds_ptr p1) -> ip_bf16x8 {
-    ip_s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p0);
-    ip_s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p1);
-    ip_s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return __builtin_bit_cast(ip_bf16x8, v);
+  const unsigned lane_rd = unsigned(((i16 >> 2) | (grp & 1) << 2) * kIpBlk + (grp >> 1) * 512 + (i16 & 3) * 8);
+  const unsigned lane_e = lds_base + lane_rd + wm * 256, lane_c = lds_base + lane_rd + kIpOpE + wn * 128;
+  struct Frags { ip_s16x4 v[kIpFN + kIpFM][2]; };  // a side, then delta side; first and last four token rows
+  auto read1 = [&](int r, unsigned be, unsigned bc, Frags& f) {
+    const int i = r >> 1, h = r & 1;
+    if (i < kIpFN)
+      f.v[i][h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(size_t)bc + (i * 32 + h * 256) / 8);
+    else
+      f.v[i][h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(size_t)be + ((i - kIpFN) * 32 + h * 8 * kIpBlk) / 8);
   };
-  // token rows ks*16 + krow (+4) of the stage: row blocks of 16 (delta) and 8 (a) rows make ks * 512
-  // bytes on both sides; 32 columns are 64 bytes; offsets in units of the 8-byte read
-  auto read_frags = [&](int st, int ks, ip_bf16x8 (&fa)[kIpFM], ip_bf16x8 (&fb)[kIpFN]) {
-    const unsigned stage = lds_base + unsigned(st) * kIpStage;
-    const lds_ptr be = (lds_ptr)(size_t)(stage + lane_e);
-    const lds_ptr bc0 = (lds_ptr)(size_t)(stage + lane_c0), bc1 = (lds_ptr)(size_t)(stage + lane_c1);
-#pragma unroll
-    for (int m = 0; m < kIpFM; ++m)
-      fa[m] = frag(be + (ks * 512 + m * 64) / 8, be + (ks * 512 + m * 64 + 4 * kIpBlk) / 8);
-#pragma unroll
-    for (int n = 0; n < kIpFN; ++n)
-      fb[n] = frag(bc0 + (ks * 512 + n * 64) / 8, bc1 + (ks * 512 + n * 64) / 8);
+  auto frag = [&](const Frags& f, int i) -> mfma_bf16x8 {
+    ip_s16x8 v = {f.v[i][0][0], f.v[i][0][1], f.v[i][0][2], f.v[i][0][3], f.v[i][1][0], f.v[i][1][1], f.v[i][1][2], f.v[i][1][3]};
+    return __builtin_bit_cast(mfma_bf16x8, v);
   };
 
-  ip_f32x16 acc[kIpFM][kIpFN];
+  mfma_f32x4 acc[kIpFM][kIpFN];
 #pragma unroll
   for (int m = 0; m < kIpFM; ++m)
 #pragma unroll
     for (int n = 0; n < kIpFN; ++n)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) acc[m][n][j] = 0.f;
+      for (int j = 0; j < 4; ++j) acc[m][n][j] = 0.f;
+  mfma_fence(acc);
 
-  auto mfma4 = [&](const ip_bf16x8 (&a)[kIpFM], const ip_bf16x8 (&b)[kIpFN]) {
+  float dot[4] = {0.f, 0.f, 0.f, 0.f}, sq[4] = {0.f, 0.f, 0.f, 0.f};
+  auto take_block = [&](int m, int n) {           // one block of a finished sample tile
 #pragma unroll
-    for (int m = 0; m < kIpFM; ++m)
-#pragma unroll
-      for (int n = 0; n < kIpFN; ++n)
-        acc[m][n] = mfma_32x32x16<F16>(a[m], b[n], acc[m][n]);
-    // the LDS reads of the next k-step go out two at a time behind the first MFMAs
-#pragma unroll
-    for (int i = 0; i < kIpFM + kIpFN; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    for (int j = 0; j < 4; ++j) {
+      const float v = mfma_acc(acc[m][n], j);
+      if (MODE == 0) dot[j] = fmaf(v, gt[m][n][j], dot[j]);
+      else asm volatile("v_add_f32 %0, %0, %1" : "+v"(gt[m][n][j]) : "v"(v));   // (in place: no register to spare)
+      if (SQ) sq[j] = fmaf(v, v, sq[j]);
     }
-    if (kIpFM * kIpFN > kIpFM + kIpFN)
-      __builtin_amdgcn_sched_group_barrier(0x008, kIpFM * kIpFN - kIpFM - kIpFN, 0);
+  };
+  float* dst = g.out + ((size_t(xcd) * g.slots + slot) * g.group * kIpWaves + wave) * 2;
+  auto put_sample = [&]() {
+    const float d = MODE == 0 ? ip_wave_sum_f32((dot[0] + dot[1]) + (dot[2] + dot[3])) : 0.f;
+    const float s = SQ ? ip_wave_sum_f32((sq[0] + sq[1]) + (sq[2] + sq[3])) : 0.f;
+    if (lane == 0) {
+      if (MODE == 0) {
+        dst[0] = d;
+        dst[1] = s;
+      } else {
+        dst[0] = s;
+      }
+    }
+    dst += 2 * kIpWaves;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) dot[j] = sq[j] = 0.f;
   };
 
-  // prologue: chunks 0 .. kIpStages-2 in flight
+  // Chunk c's fragments are read during the MFMAs of chunk c-1, so that the stage of chunk c is free when its MFMAs
+  // begin and takes chunk c + kIpStages there.
+  const unsigned st_end = kIpStages * kIpStage;
+  unsigned st = 0;                                // byte offset of the stage of chunk c
+  // fresh: first chunk of a sample; on: all ones, or 0 where no whole chunk is left to load: the loads are then issued
+  // with no lane taking part, so that the number of loads behind a chunk is always the same
+  auto period = [&](auto fresh_tag, unsigned long long on, const Frags& cur, Frags& nxt) {
+    constexpr bool fresh = decltype(fresh_tag)::value;
+    const unsigned stn = st + kIpStage == st_end ? 0u : st + kIpStage;
+    const unsigned be = lane_e + stn, bc = lane_c + stn;
 #pragma unroll
-  for (int s = 0; s < kIpStages - 1; ++s)
-    if (s < nk) issue_loads(s, s);
+    for (int i = 0; i < kIpFM * kIpFN; ++i) {
+      const int m = i / kIpFN, n = m & 1 ? kIpFN - 1 - i % kIpFN : i % kIpFN;
+      if (fresh) {
+        take_block(m, n);
+        mfma_16x16x32_fresh<F16>(acc[m][n], frag(cur, kIpFN + m), frag(cur, n));
+      } else {
+        mfma_16x16x32<F16>(acc[m][n], frag(cur, kIpFN + m), frag(cur, n));
+      }
+      if (i == 1) {
+        // chunk c+1 has landed for me (the ones behind it may be in flight), then for everybody; everybody has
+        // read all of chunk c
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        ip_wait_vmcnt<kIpLd * (kIpStages - 2)>();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
+      if (i >= 2 && i < 2 + 2 * (kIpFM + kIpFN)) read1(i - 2, be, bc, nxt);   // (after the last chunk: in bounds)
+      if (i % 4 == 3 && i / 4 < kIpLd) issue_load(i / 4, st, on);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    st = stn;
+  };
+
+  // prologue: kIpStages chunks in flight, chunk 0 landed
+#pragma unroll
+  for (int s = 0; s < kIpStages; ++s)
+    if (s < nk) {
+      if (RAGGED && ld_left < kIpK) {
+        issue_short_chunk(s * kIpStage);
+      } else {
+#pragma unroll
+        for (int i = 0; i < kIpLd; ++i) issue_load(i, s * kIpStage, ~0ull);
+      }
+      next_chunk();
+    }
   // The G registers are needed only at the end of the first sample, but a wait placed there by the
   // compiler would drain the load pipeline at every sample; pin them down here, once.
-  if (MODE == 0) {
 #pragma unroll
-    for (int m = 0; m < kIpFM; ++m)
+  for (int m = 0; m < kIpFM; ++m)
 #pragma unroll
-      for (int n = 0; n < kIpFN; ++n)
+    for (int n = 0; n < kIpFN; ++n)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) asm volatile("" : "+v"(gt[m][n][j]));
-  }
-  if (nk >= kIpStages - 1) ip_wait_vmcnt<kIpLd * (kIpStages - 2)>(); else ip_wait_vmcnt<0>();
+      for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(gt[m][n][j]));
+  if (nk >= kIpStages) ip_wait_vmcnt<kIpLd * (kIpStages - 1)>(); else ip_wait_vmcnt<0>();
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+  Frags f0, f1;
+#pragma unroll
+  for (int r = 0; r < 2 * (kIpFM + kIpFN); ++r) read1(r, lane_e, lane_c, f0);
 
-  int left = nk_sample, sample_out = 0;
-  float* dst = g.out + ((size_t(xcd) * g.slots + slot) * g.group * kIpWaves + wave) * 2;
-  ip_bf16x8 fa[2][kIpFM], fb[2][kIpFN];
-  read_frags(0, 0, fa[0], fb[0]);
-  int st_cur = 0, st_load = kIpStages - 1;        // stage of chunk c; stage that chunk c-1 frees
-  for (int c = 0; c < nk; ++c) {
-    const int st_next = st_cur + 1 == kIpStages ? 0 : st_cur + 1;
-    read_frags(st_cur, 1, fa[1], fb[1]);
-    mfma4(fa[0], fb[0]);
-    if (c + 1 < nk) {
-      // chunk c+1 has landed for me (the chunks behind it may still be in flight), then for
-      // everybody; every wave is done with chunk c-1, whose stage takes chunk c-1+kIpStages
-      if (c + kIpStages - 2 < nk) ip_wait_vmcnt<kIpLd * (kIpStages - 3)>(); else ip_wait_vmcnt<0>();
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      if (c + kIpStages - 1 < nk) issue_loads(c + kIpStages - 1, st_load);
+  int c = 0;                                      // chunk of the entry
+  auto chunk = [&](auto fresh_tag, const Frags& cur, Frags& nxt) {
+    const unsigned st_now = st;
+    const bool more = c + kIpStages < nk;
+    const bool whole = more && !(RAGGED && ld_left < kIpK);
+    period(fresh_tag, whole ? ~0ull : 0ull, cur, nxt);
+    if (RAGGED && more && !whole) issue_short_chunk(st_now);   // (the barrier inside the period has freed the stage)
+    if (more) next_chunk();
+    ++c;
+  };
+  const std::true_type fresh{};
+  const std::false_type rest{};
+  const int pairs = (nk_sample - 1) / 2;
+  // One straight chain of definitions for the accumulators (no two code paths that join): the register allocator would
+  // otherwise copy them from one set of registers to another in every chunk.
+  for (;;) {
+    chunk(fresh, f0, f1);
+    if (c > 1) put_sample();
+    for (int p = 0; p < pairs; ++p) {
+      chunk(rest, f1, f0);
+      chunk(rest, f0, f1);
     }
-    read_frags(c + 1 < nk ? st_next : st_cur, 0, fa[0], fb[0]);
-    mfma4(fa[1], fb[1]);
-    st_load = st_cur;
-    st_cur = st_next;
-    if (--left == 0) {
-      // the sample's tile is complete: reduce it against the G tile, clear it
-      float dot = 0.f, sq = 0.f;
-      if (!ragged) {
-#pragma unroll
-        for (int m = 0; m < kIpFM; ++m)
-#pragma unroll
-          for (int n = 0; n < kIpFN; ++n)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-              const float v = acc[m][n][j];
-              if (MODE == 0) dot = fmaf(v, gt[m][n][j], dot);
-              else gt[m][n][j] += v;
-              if (SQ) sq = fmaf(v, v, sq);
-              acc[m][n][j] = 0.f;
-            }
-      } else {
-        // tile on the edge of the layer: entries past the edge hold products of re-read columns;
-        // they meet zeros in the G registers (MODE 0) or are never stored (MODE 1), but must not
-        // enter the sum of squares
-#pragma unroll
-        for (int m = 0; m < kIpFM; ++m)
-#pragma unroll
-          for (int n = 0; n < kIpFN; ++n) {
-            const bool col_ok = c0 + wn * (32 * kIpFN) + n * 32 + (lane & 31) < L.d_in;
-            const int tr0 = e0 + wm * (32 * kIpFM) + m * 32 + (lane >> 5) * 4;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-              const float v = acc[m][n][j];
-              if (MODE == 0) dot = fmaf(v, gt[m][n][j], dot);
-              else gt[m][n][j] += v;
-              if (SQ) {
-                const float vm = (col_ok && tr0 + (j >> 2) * 8 + (j & 3) < L.d_out) ? v : 0.f;
-                sq = fmaf(vm, vm, sq);
-              }
-              acc[m][n][j] = 0.f;
-            }
-          }
+    if (!ODD) chunk(rest, f1, f0);
+    if (c >= nk) break;
+    if (ODD) {
+      chunk(fresh, f1, f0);
+      put_sample();
+      for (int p = 0; p < pairs; ++p) {
+        chunk(rest, f0, f1);
+        chunk(rest, f1, f0);
       }
-      if (MODE == 0) dot = ip_wave_sum_f32(dot);
-      if (SQ) sq = ip_wave_sum_f32(sq);
-      if (lane == 0) {
-        if (MODE == 0) {
-          dst[size_t(sample_out) * (2 * kIpWaves)] = dot;
-          dst[size_t(sample_out) * (2 * kIpWaves) + 1] = sq;
-        } else {
-          dst[size_t(sample_out) * (2 * kIpWaves)] = sq;
-        }
-      }
-      ++sample_out;
-      left = nk_sample;
+      if (c >= nk) break;
     }
   }
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  mfma_fence(acc);
+#pragma unroll
+  for (int m = 0; m < kIpFM; ++m)
+#pragma unroll
+    for (int n = 0; n < kIpFN; ++n) take_block(m, n);
+  put_sample();
+
   if (MODE == 1) {
     const int part = g.part[xcd * g.slots + slot];
-    float* pt = part >= 0 ? g.partials + (size_t)part * (kIpE * kIpC) : nullptr;
+    if (part >= 0) {
+      float* pt = g.partials + (size_t)part * (kIpE * kIpC);
 #pragma unroll
-    for (int m = 0; m < kIpFM; ++m)
+      for (int m = 0; m < kIpFM; ++m)
 #pragma unroll
-      for (int n = 0; n < kIpFN; ++n) {
-        const int tc = wn * (32 * kIpFN) + n * 32 + (lane & 31);
+        for (int n = 0; n < kIpFN; ++n)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int tr = wm * (32 * kIpFM) + m * 32 + (j >> 2) * 8 + (lane >> 5) * 4 + (j & 3);
-          if (pt) {
-            pt[tr * kIpC + tc] = gt[m][n][j];
-          } else if (e0 + tr < L.d_out && c0 + tc < L.d_in) {
-            float* d = L.grad_sum + (size_t)(e0 + tr) * L.d_in + c0 + tc;
-            *d = g.accumulate ? *d + gt[m][n][j] : gt[m][n][j];
-          }
-        }
-      }
+          for (int j = 0; j < 4; ++j)
+            pt[(wm * 128 + m * 16 + grp * 4 + j) * kIpC + wn * 64 + n * 16 + i16] = gt[m][n][j];
+    } else {
+      put_grad_tile<kIpFM, kIpFN, 4>(L.grad_sum, L.d_out, L.d_in, e0 + wm * 128 + grp * 4, c0 + wn * 64 + i16,
+                                     g.accumulate != 0, [&](int m, int n, int j) { return gt[m][n][j]; });
+    }
   }
 }
 
@@ -469,12 +495,20 @@ int make_ip_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& 
   return int(slots);
 }
 
+template <int MODE, bool SQ, bool F16> static auto ip_tile_variant_t(int T) {
+  const bool odd = (T + kIpK - 1) / kIpK % 2 != 0;
+  if (T % kIpK != 0)
+    return odd ? ip_tile_kernel<MODE, SQ, F16, true, true> : ip_tile_kernel<MODE, SQ, F16, true, false>;
+  return odd ? ip_tile_kernel<MODE, SQ, F16, false, true> : ip_tile_kernel<MODE, SQ, F16, false, false>;
+}
+template <int MODE, bool SQ> static auto ip_tile_variant(int dtype, int T) {
+  return dtype == ADLOCO_F16 ? ip_tile_variant_t<MODE, SQ, true>(T) : ip_tile_variant_t<MODE, SQ, false>(T);
+}
+
 hipError_t launch_ip_tiles(const LayerDev* layers, const void* tiles, int slots, int T, int group,
                            int dtype, bool want_sq, float* ip_out, hipStream_t st) {
   if (slots <= 0) return hipSuccess;
-  const bool h = dtype == ADLOCO_F16;
-  auto kern = want_sq ? (h ? ip_tile_kernel<0, true, true> : ip_tile_kernel<0, true, false>)
-                      : (h ? ip_tile_kernel<0, false, true> : ip_tile_kernel<0, false, false>);
+  auto kern = want_sq ? ip_tile_variant<0, true>(dtype, T) : ip_tile_variant<0, false>(dtype, T);
   {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kIpLds);
@@ -563,7 +597,7 @@ hipError_t launch_stats_tiles(const LayerDev* layers, const void* tiles, const i
                               const int* idx, int n_listed, float* partials, int n_pairs,
                               hipStream_t st) {
   if (slots <= 0) return hipSuccess;
-  auto kern = dtype == ADLOCO_F16 ? ip_tile_kernel<1, true, true> : ip_tile_kernel<1, true, false>;
+  auto kern = ip_tile_variant<1, true>(dtype, T);
   {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kIpLds);
@@ -620,7 +654,7 @@ __global__ __launch_bounds__(kIpThreads) void embed_ip_kernel(const LayerDev* la
 
 // One workgroup per sample i: c_i = sum of its tile results + sum over the other blocks;
 // likewise the explicit ||g_i||^2.  A tile entry covers samples [w & 0xffff, + (w >> 16)) and
-// leaves, per sample and wave, a pair at tile_out[((k * group + sample - first) * 8 + wave) * 2].
+// leaves, per sample and wave, a pair at tile_out[((k * group + sample - first) * kIpWaves + wave) * 2].
 __global__ __launch_bounds__(kIpThreads) void ip_finalize_samples_kernel(
     const int4* tiles, const float* tile_out, long long n_tiles, int group, const float* dot, const float* sq,
     const unsigned char* in_tiles, int n_layers, int B, float* per_sample_ip, float* per_sample_sq,

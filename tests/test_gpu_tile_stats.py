@@ -117,3 +117,37 @@ def test_tile_route_accumulates_over_micro_batches(ctx):
     for l, w in enumerate(want["G"]):
         g = gs[l].cpu().numpy().astype(np.float64)
         assert float(np.max(np.abs(g - w))) / (float(np.sqrt(np.mean(w * w))) + 1e-300) < 1e-4
+
+
+@pytest.mark.parametrize("B,T,shapes", [
+    (3, 1, [(8, 8)]),                      # one row per sample, the rest of its chunk zeros
+    (9, 33, [(136, 264)]),                 # two chunks (even), the second of one row; more chunks than stages
+    (2, 95, [(72, 520), (256, 256)]),      # three chunks (odd), the last one row short
+    (1, 250, [(264, 8)]),                  # one sample of eight chunks: the load pipeline never wraps
+    (300, 7, [(128, 256)]),                # long runs of one-chunk samples
+])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_tile_route_ragged_sequences(ctx, dtype, B, T, shapes):
+    import torch
+    import paper_2508_18182_amd as A
+    from gpu_util import DEV, code_of
+    layers = synth.custom_grad_stats_inputs(6400 + B + T, shapes, B, T, dtype, std_delta=0.2, rho=0.4)
+    entries = [(l["a"], l["delta"]) for l in layers]
+    want = orc.grad_stats(entries, two_pass=False)
+    ctx.set_tuning("stats_variant", 1)
+    got = _check(ctx, layers)
+    _compare(got, want)
+    again = _check(ctx, layers)
+    assert np.array_equal(again["per_layer"], got["per_layer"])
+    # the inner products go through the same tiles, against the gradient sums just formed
+    c, sq = torch.full((B,), float("nan"), device=DEV), torch.full((B,), float("nan"), device=DEV)
+    A.adloco_inner_products(ctx, got["layers"], B, T, code_of(dtype), c, sq,
+                            torch.zeros(4, dtype=torch.float64, device=DEV))
+    c_want = orc.inner_products(entries, G=want["G"])
+    assert np.max(np.abs(c.cpu().numpy() - c_want) / np.sqrt(want["n_sample"] * want["S2"])) < TOL_BF16
+    assert np.max(np.abs(sq.cpu().numpy() - want["n_sample"]) / want["n_sample"]) < TOL_BF16
+    # and without the explicit norms
+    c2 = torch.full((B,), float("nan"), device=DEV)
+    A.adloco_inner_products(ctx, got["layers"], B, T, code_of(dtype), c2, None,
+                            torch.zeros(4, dtype=torch.float64, device=DEV))
+    assert torch.equal(c, c2)
