@@ -199,7 +199,8 @@ __global__ __launch_bounds__(256, 2) void wgrad_bf16_kernel(WgradArgs g) {
 // SIMD), used when every row is 16-byte aligned, widths are multiples of 8 and the number of token rows is a multiple
 // of 32.  What bounds it is power: at 78 % busy matrix cores the chip holds 1.54 of its 2.4 GHz, so the kernel is laid
 // out for little energy per product -- the 16x16x32 MFMA, and wave tiles of 128 x 128, which read a third less from LDS
-// than eight waves of 128 x 64.  Sum over the 96 linears of the 350M model, 32 x 1024 tokens: 14.0 ms, 1.41 PFLOP/s
+// than eight waves of 128 x 64.  Sum over the 96 linears of the 350M model, 32 x 1024 tokens: 13.9 ms, 1.42 PFLOP/s,
+// also where it is added to a sum (15.4 ms with every old entry of G loaded and waited for by itself)
 // (eight waves with the 32x32x16 MFMA: 15.8 ms; four waves with it: 15.3 ms); without its global loads 11.4 ms, with
 // loads that all hit the L2 12.9 ms.
 //   Staging: global -> LDS directly, four stages of 32 token rows x (256 + 256) columns; one wave instruction moves
@@ -377,23 +378,19 @@ __global__ __launch_bounds__(kXthreads, 1) void wgrad_bf16_x_kernel(WgradXArgs g
   mfma_fence(acc);
 
   // accumulator element j of a 16x16 block: row (lane/16)*4 + j, column lane%16
-  float* part = split_s ? g.partials + (size_t)split_id * (kXt * kXt) : nullptr;
+  if (split_s) {
+    float* part = g.partials + (size_t)split_id * (kXt * kXt);
 #pragma unroll
-  for (int m = 0; m < 8; ++m)
+    for (int m = 0; m < 8; ++m)
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
-      const int tc = wn * 128 + n * 16 + i16;
+      for (int n = 0; n < 8; ++n)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int tr = wm * 128 + m * 16 + grp * 4 + j;
-        if (split_s) {
-          part[tr * kXt + tc] = acc[m][n][j];
-        } else if (e0 + tr < L.d_out && c0 + tc < L.d_in) {
-          float* dst = L.grad_sum + (size_t)(e0 + tr) * L.d_in + c0 + tc;
-          *dst = g.accumulate ? *dst + acc[m][n][j] : acc[m][n][j];
-        }
-      }
-    }
+        for (int j = 0; j < 4; ++j)
+          part[(wm * 128 + m * 16 + grp * 4 + j) * kXt + wn * 128 + n * 16 + i16] = acc[m][n][j];
+  } else {
+    put_grad_tile<8, 8, 4>(L.grad_sum, L.d_out, L.d_in, e0 + wm * 128 + grp * 4, c0 + wn * 128 + i16,
+                           g.accumulate != 0, [&](int m, int n, int j) { return acc[m][n][j]; });
+  }
 }
 
 // Sums the partial tiles of a split contraction in piece order (fixed order: repeatable) and
