@@ -34,14 +34,18 @@ __device__ __forceinline__ double vt_block_sum(double v, double* lds4) {
   return (lds4[0] + lds4[1]) + (lds4[2] + lds4[3]);
 }
 
-// last descriptor whose blk_start <= b
+// last descriptor whose start (blk_start, or blk_start2: SECOND) is <= b: all lanes of the wave look at one descriptor
+// each, so that the search costs one memory latency per 64 of them (the starts do not decrease)
+template <bool SECOND = false>
 __device__ __forceinline__ int find_aux(const AuxDesc* tab, int n, int b) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (tab[mid].blk_start <= b) lo = mid; else hi = mid - 1;
+  const int lane = threadIdx.x & 63;
+  int found = 0;
+  for (int base = 0; base < n; base += 64) {
+    const int i = base + lane;
+    const bool le = i < n && (SECOND ? tab[i].blk_start2 : tab[i].blk_start) <= b;
+    found += __popcll(__builtin_amdgcn_ballot_w64(le));
   }
-  return lo;
+  return __builtin_amdgcn_readfirstlane(found - 1);
 }
 
 // Eight consecutive elements of a row starting at column c (columns >= d read as zero).
@@ -95,7 +99,7 @@ __global__ __launch_bounds__(kVtThreads) void vector_rowsum_kernel(const LayerDe
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   float acc1[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (c < d) {
-#pragma unroll 4
+#pragma unroll 8
     for (int t = rg; t < T; t += 8) {
       float dv[8];
       load8<E>(D + (long long)t * L.delta_stride, c, d, L.fast, dv);
@@ -143,13 +147,7 @@ __global__ __launch_bounds__(kVtThreads) void vector_colsum_kernel(const LayerDe
                                                                    const AuxDesc* tab, int n_tab,
                                                                    int B, const float* vec,
                                                                    int accumulate) {
-  // this launch uses blk_start2 (one workgroup per slab and layer)
-  int lo = 0, hi = n_tab - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (tab[mid].blk_start2 <= int(blockIdx.x)) lo = mid; else hi = mid - 1;
-  }
-  const AuxDesc A = tab[lo];
+  const AuxDesc A = tab[find_aux<true>(tab, n_tab, blockIdx.x)];   // one workgroup per slab and layer
   const LayerDev L = layers[A.layer];
   if (L.provided) return;
   const int col = (blockIdx.x - A.blk_start2) * kSlab + threadIdx.x;
@@ -303,6 +301,7 @@ __global__ __launch_bounds__(64) void embed_finalize_kernel(const AuxDesc* tab, 
 int vector_table_slab() { return kSlab; }
 int embed_table_slab() { return kEmbSlab; }
 
+// partials NULL: only the sums
 hipError_t launch_vector_stats(const LayerDev* layers, const AuxDesc* tab, int n_tab,
                                int blocks_rowsum, int blocks_colsum, int B, int T, int dtype,
                                float* vec, float* partials, int n_pairs, int accumulate,
@@ -320,6 +319,7 @@ hipError_t launch_vector_stats(const LayerDev* layers, const AuxDesc* tab, int n
   if (write_grad_sum)
     hipLaunchKernelGGL(vector_colsum_kernel, dim3(blocks_colsum), dim3(kVtThreads), 0, st, layers, tab,
                        n_tab, B, vec, accumulate);
+  if (!partials) return hipGetLastError();
   hipLaunchKernelGGL(vector_sqnorm_kernel, dim3(n_tab * B), dim3(kVtThreads), 0, st, layers, tab, B,
                      vec, partials, n_pairs);
   return hipGetLastError();
