@@ -599,12 +599,13 @@ def adloco_round(ctx: Context, cfg: dict, trainers: Sequence[dict], blocks: Sequ
             for l in range(n):
                 e = got[l]
                 d = e["delta"]
-                layers[l].delta = d.data_ptr()
-                layers[l].delta_row_stride = d.stride(1)
+                desc = layers[l]        # (every index makes a ctypes object of its own)
+                desc.delta = d.data_ptr()
+                desc.delta_row_stride = d.stride(1)
                 x = e.get("a") if "a" in e else e.get("x")
                 if x is not None:
-                    layers[l].a = x.data_ptr()
-                    layers[l].a_row_stride = x.stride(1)
+                    desc.a = x.data_ptr()
+                    desc.a_row_stride = x.stride(1)
             return 0
         except Exception as exc:      # an exception must not cross the C frame
             errors.append(exc)

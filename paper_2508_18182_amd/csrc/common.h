@@ -273,6 +273,7 @@ struct adloco_ctx {
   int ts_slots = 0, ts_n_split = 0, ts_n_listed = 0, ts_B = -1;
   bool ts_ok = false;          // every linear block is aligned bf16 with its gradient sum formed here
   adloco::PlainTiles st_plain; // the same for fp32 blocks
+  adloco::PlainTiles sum_plain; // gradient sums alone of fp32 blocks (B = 1: all token rows as one sample)
   int n_formed = 0;            // linear blocks whose gradient sum is formed here
   int stats_variant = 1;       // 1: tile form when eligible; 0: Gram + gradient-sum kernels
   // the vector / table kernels (HBM-bound) can run next to the kernels of the linear blocks (MFMA /
@@ -287,7 +288,6 @@ struct adloco_ctx {
   int table_builds = 0;        // how often a shape-dependent table has been (re)built
   long long max_lin_stride = 0;  // widest row stride (elements) among the linear blocks of the table
   double* pinned = nullptr;    // 8 doubles of pinned host memory (read-back of the tests' sums)
-  double* dev_scalars = nullptr;  // 4 doubles on the device (S2, ...)
   // optional per-kernel event timing ("profile" knob)
   struct ProfRec { int kernel; hipEvent_t start, stop; };
   std::vector<ProfRec> prof;
@@ -401,7 +401,8 @@ hipError_t launch_stats_tiles(const LayerDev* layers, const void* tiles, const i
 // Resident workgroups per XCD of the plain tile kernel: two (128-wide tiles) or four per compute unit.
 constexpr int plain_tile_room(int W) { return kNumCu / kNumXcd * (W == 2 ? 2 : 4); }
 int plain_tile_width(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B);
-// mode 0: <g_i, G> -> dot and ||g_i||^2 -> sq; mode 1: G and ||g_i||^2 -> sq (NULL: only G).
+// mode 0: <g_i, G> -> dot and ||g_i||^2 -> sq; fp32 only: mode 1: G and ||g_i||^2 -> sq; mode 2: G (B = 1, T = all
+// token rows, sq = NULL).
 hipError_t launch_plain_tiles(const LayerDev* layers, const PlainTiles& p, int mode, int B, int T, int dtype,
                               int accumulate, float* dot, float* sq, int sq_stride, hipStream_t st);
 hipError_t launch_ip_vector_table(const LayerDev* layers, const AuxDesc* vec_tab, int n_vec,
@@ -414,14 +415,22 @@ hipError_t launch_ip_finalize(const void* tiles, const float* tile_out, long lon
 hipError_t launch_embed_stats(const LayerDev* layers, const AuxDesc* tab, int n_tab, int blocks_rows,
                               int B, int T, int dtype, int* perm, double* part, float* partials,
                               int n_pairs, hipStream_t st);
-// sum_l ||grad_sum_l||^2 -> *out (device double); partial buffer sized by sqnorm_partials().
+// sum_l ||grad_sum_l||^2 of the n_layers blocks of a device table, whose sq_blk_start fields add up to nblk workgroups
+// (sqnorm_partials()); partial holds nblk doubles.  The sum, *acc and *ip (each unless NULL) go to host[0], host[2..3]
+// and host[4..7] of pinned host memory, valid once the stream has been waited for.
 int sqnorm_chunk();
 size_t sqnorm_partials(const std::vector<LayerDev>& host_layers);
-hipError_t launch_sqnorm(const LayerDev* layers, const std::vector<LayerDev>& host_layers,
-                         double* partial, double* out, hipStream_t st);
-// The same on a device table of n_layers blocks whose sq_blk_start fields add up to nblk workgroups.
-hipError_t launch_sqnorm_table(const LayerDev* layers, int n_layers, size_t nblk, double* partial,
-                               double* out, hipStream_t st);
+hipError_t launch_sqnorm(const LayerDev* layers, int n_layers, size_t nblk, double* partial,
+                         const adloco_stats_acc* acc, const adloco_ip_acc* ip, double* host, hipStream_t st);
+// Whether a kernel may read `p` (device memory, 8-byte aligned); the read-back copies from any other address.
+bool kernel_can_read(const void* p);
+// adloco_grad_stats.  pinned_order (adloco_round): gradient sums of fp32 blocks and of token rows that are no multiple
+// of 32 are added up in the order of the kernels for whole contractions, not sample by sample or piece by piece.  A
+// round returns parameters after several AdamW steps, which divide by sqrt(v): where gradient and second moment are
+// both near zero, the last bit of a gradient sum becomes up to 4e-4 of the outer momentum's norm.
+int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, int B, int T, int dtype,
+               float* per_sample_sqnorm, float* per_layer_sample_sqnorm, adloco_stats_acc* acc, uint32_t flags,
+               bool pinned_order, void* stream);
 // Looks up, for the context's device, the address of the file-scope device array that serves
 // adloco_norm_test_noalloc (called once per context by adloco_create, with the device current).
 int no_alloc_init(adloco_ctx* ctx);

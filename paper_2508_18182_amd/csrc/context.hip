@@ -118,16 +118,13 @@ extern "C" int adloco_create(adloco_ctx** out, int device) {
   adloco_ctx* c = new adloco_ctx();
   c->device = device;
   e = hipHostMalloc(reinterpret_cast<void**>(&c->pinned), 8 * sizeof(double), hipHostMallocDefault);
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&c->dev_scalars), 8 * sizeof(double));
   if (e != hipSuccess) {
     g_create_err = std::string("adloco_create: allocation failed: ") + hipGetErrorString(e);
-    if (c->pinned) (void)hipHostFree(c->pinned);
     delete c;
     return ADLOCO_ENOMEM;
   }
   if (int rc = no_alloc_init(c)) {
     g_create_err = "adloco_create: " + c->err;
-    (void)hipFree(c->dev_scalars);
     (void)hipHostFree(c->pinned);
     delete c;
     return rc;
@@ -148,7 +145,7 @@ extern "C" int adloco_destroy(adloco_ctx* ctx) {
                     &ctx->ts_part_idx, &ctx->ts_split, &ctx->ts_ptiles, &ctx->ts_out, &ctx->ts_csr};
   for (Scratch* s : all)
     if (s->ptr) (void)hipFree(s->ptr);
-  for (PlainTiles* p : {&ctx->st_plain, &ctx->ip_plain})
+  for (PlainTiles* p : {&ctx->st_plain, &ctx->sum_plain, &ctx->ip_plain})
     for (Scratch* s : {&p->tab, &p->part_idx, &p->split, &p->ptiles, &p->out, &p->csr})
       if (s->ptr) (void)hipFree(s->ptr);
   for (auto& r : ctx->prof) {
@@ -159,7 +156,6 @@ extern "C" int adloco_destroy(adloco_ctx* ctx) {
   if (ctx->ev_fork) (void)hipEventDestroy(ctx->ev_fork);
   if (ctx->ev_join) (void)hipEventDestroy(ctx->ev_join);
   if (ctx->side_stream) (void)hipStreamDestroy(ctx->side_stream);
-  if (ctx->dev_scalars) (void)hipFree(ctx->dev_scalars);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   delete ctx;
   return ADLOCO_OK;

@@ -254,7 +254,7 @@ int prepare_tables(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_laye
   ctx->aux_B = ctx->aux_T = -1;         // the vector / table descriptor lists follow the table
   ctx->ip_B = ctx->ip_T = -1;           // and so does the inner-product tile table
   ctx->ts_B = -1;                       // and the statistics tile tables
-  ctx->st_plain.B = -1;
+  ctx->st_plain.B = ctx->sum_plain.B = -1;
   ctx->n_formed = 0;
   for (const LayerDev& L : tab) ctx->n_formed += L.kind == ADLOCO_KIND_LINEAR && !L.provided;
   {
@@ -426,10 +426,11 @@ int build_plain_tiles(adloco_ctx* ctx, PlainTiles& p, const std::vector<char>& u
 
 }  // namespace
 
-extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers,
-                                 int B, int T, int dtype, float* per_sample_sqnorm,
-                                 float* per_layer_sample_sqnorm, adloco_stats_acc* acc,
-                                 uint32_t flags, void* stream) {
+namespace adloco {
+
+int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, int B, int T, int dtype,
+               float* per_sample_sqnorm, float* per_layer_sample_sqnorm, adloco_stats_acc* acc, uint32_t flags,
+               bool pinned_order, void* stream) {
   if (!ctx) return ADLOCO_EINVAL;
   if (!layers || n_layers < 1) return fail(ctx, ADLOCO_EINVAL, "grad_stats: no layers");
   if (n_layers > kMaxLayers)
@@ -477,23 +478,28 @@ extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* laye
 
   // Per-sample gradient tiles (explicit form) when the gradient sums of all linear blocks are formed here: the tiles
   // that add up to them are squared on the way, no Gram contraction is needed.  16-bit blocks if they are aligned;
-  // fp32 ones always, also for the plain gradient sum: 4 x {768 -> 2304, 768 -> 768, 768 -> 3072, 3072 -> 768}, B 8,
-  // T 256 takes 1.28 ms against 5.02 ms with the vector-unit kernels of the two steps, a gradient sum of 0.1 TFLOP on
-  // widths of 300 to 1600 0.6 - 1.2 ms against 1.7 - 3.4 ms.
-  const bool tile_form = !sum_only && ctx->stats_variant != 0 && ctx->ts_ok && T <= (1 << 20) && B <= 0x7fff;
-  const bool plain_form = dtype == ADLOCO_F32 && ctx->n_formed > 0 && B <= 0x7fff && ctx->stats_variant != 0 &&
-                          (sum_only || ctx->n_formed == ctx->n_linear);
+  // fp32 ones always: 4 x {768 -> 2304, 768 -> 768, 768 -> 3072, 3072 -> 768}, B 8, T 256 takes 1.28 ms
+  // against 5.02 ms with the vector-unit kernels of the two steps.
+  const bool tile_form = !sum_only && ctx->stats_variant != 0 && ctx->ts_ok && (T % 32 == 0 || !pinned_order) &&
+                         T <= (1 << 20) && B <= 0x7fff;
+  const bool plain_form = dtype == ADLOCO_F32 && !pinned_order && ctx->n_formed > 0 && B <= 0x7fff && ctx->stats_variant != 0 &&
+                          !sum_only && ctx->n_formed == ctx->n_linear;
+  const long long rows = (long long)B * T;
+  const bool plain_sum = dtype == ADLOCO_F32 && !plain_form && ctx->n_formed > 0 && rows < (1 << 30) &&
+                         ctx->stats_variant != 0;
   if (tile_form || plain_form) n_pairs = 1;      // one finished sum per (layer, sample)
   const long long n_part = (long long)n_layers * B * n_pairs;
   rc = ensure_scratch(ctx, ctx->partials, size_t(n_part) * sizeof(float));
   if (rc) return rc;
   rc = ensure_scratch(ctx, ctx->sample_f64, size_t(B) * sizeof(double));
   if (rc) return rc;
-  if (plain_form && ctx->st_plain.B != B) {
+  PlainTiles* const plain = plain_form ? &ctx->st_plain : plain_sum ? &ctx->sum_plain : nullptr;
+  const int plain_B = plain_form ? B : 1;
+  if (plain && plain->B != plain_B) {
     std::vector<char> use(n_layers, 0);
     for (int l = 0; l < n_layers; ++l)
       use[l] = ctx->layer_tab_host[l].kind == ADLOCO_KIND_LINEAR && !ctx->layer_tab_host[l].provided;
-    rc = build_plain_tiles(ctx, ctx->st_plain, use, B, 0, 0, st);
+    rc = build_plain_tiles(ctx, *plain, use, plain_B, 0, 0, st);
     if (rc) return rc;
   }
   if (tile_form && ctx->ts_B != B) {
@@ -564,7 +570,7 @@ extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* laye
     hipEvent_t ev_aux = prof_begin(ctx, aux_st);
     hipError_t ea = launch_vector_stats(g.layers, static_cast<const AuxDesc*>(ctx->vec_tab.ptr),
                                         int(ctx->vec_host.size()), ctx->vec_blocks, ctx->vec_blocks2, B, T,
-                                        dtype, static_cast<float*>(ctx->aux_vec.ptr), g.partials,
+                                        dtype, static_cast<float*>(ctx->aux_vec.ptr), sum_only ? nullptr : g.partials,
                                         int(n_pairs), accumulate, true, aux_st);
     if (ea == hipSuccess && !sum_only)
       ea = launch_embed_stats(g.layers, static_cast<const AuxDesc*>(ctx->emb_tab.ptr),
@@ -599,13 +605,12 @@ extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* laye
   }
   if (plain_form) {
     ev = prof_begin(ctx, st);
-    e = launch_plain_tiles(g.layers, ctx->st_plain, 1, B, T, dtype, accumulate, nullptr,
-                           sum_only ? nullptr : g.partials, int(n_pairs), st);
+    e = launch_plain_tiles(g.layers, ctx->st_plain, 1, B, T, dtype, accumulate, nullptr, g.partials, int(n_pairs), st);
     prof_end(ctx, kProfTileStats, ev, st);
     if (e != hipSuccess)
       return fail(ctx, ADLOCO_EHIP, "grad_stats: plain tile launch failed: %s", hipGetErrorString(e));
   }
-  const bool formed = tile_form || plain_form;     // norms (unless sum_only) and gradient sums are done
+  const bool formed = tile_form || plain_form;     // norms and gradient sums are done
   ev = (!formed && !sum_only && ctx->n_linear > 0) ? prof_begin(ctx, st) : nullptr;
   if (formed || sum_only || ctx->n_linear == 0)
     ;
@@ -629,11 +634,12 @@ extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* laye
   if (e != hipSuccess)
     return fail(ctx, ADLOCO_EHIP, "grad_stats: Gram launch failed: %s", hipGetErrorString(e));
   ev = (!formed && ctx->wgrad_blocks > 0) ? prof_begin(ctx, st) : nullptr;
-  const long long rows = (long long)B * T;
   if (formed)
     ;
-  else if (is_16bit(dtype) && ctx->wgrad_variant >= 2 && ctx->wgx_slots > 0 && rows % 32 == 0 &&
-           rows / 32 <= 0x7fffffffLL)
+  else if (plain_sum)
+    e = launch_plain_tiles(g.layers, ctx->sum_plain, 2, 1, int(rows), dtype, accumulate, nullptr, nullptr, 0, st);
+  else if (is_16bit(dtype) && ctx->wgrad_variant >= 2 && ctx->wgx_slots > 0 && (rows % 32 == 0 || !pinned_order) &&
+           rows / 32 < 0x7fffffffLL)
     e = launch_wgrad_x(g.layers, ctx->wgx_tab.ptr, ctx->wgx_slots, ctx->wgx_split.ptr,
                        ctx->wgx_n_split, static_cast<float*>(ctx->wgx_part.ptr), rows, accumulate,
                        dtype, st);
@@ -660,10 +666,20 @@ extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* laye
   return ADLOCO_OK;
 }
 
-extern "C" int adloco_norm_test(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers,
-                                const adloco_stats_acc* acc, double eta, int64_t b_cur,
-                                int64_t b_max, int32_t n_switch, int64_t b_cap, uint32_t flags,
-                                adloco_norm_test_result* out, void* stream) {
+}  // namespace adloco
+
+extern "C" int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers,
+                                 int B, int T, int dtype, float* per_sample_sqnorm,
+                                 float* per_layer_sample_sqnorm, adloco_stats_acc* acc,
+                                 uint32_t flags, void* stream) {
+  return grad_stats(ctx, layers, n_layers, B, T, dtype, per_sample_sqnorm, per_layer_sample_sqnorm, acc, flags, false,
+                    stream);
+}
+
+// ip: also read back the accumulator of the inner products, into ctx->pinned[4..7] (NULL: none).
+static int norm_test(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, const adloco_stats_acc* acc,
+                     const adloco_ip_acc* ip, double eta, int64_t b_cur, int64_t b_max, int32_t n_switch,
+                     int64_t b_cap, uint32_t flags, adloco_norm_test_result* out, void* stream) {
   if (!ctx) return ADLOCO_EINVAL;
   if (!layers || n_layers < 1) return fail(ctx, ADLOCO_EINVAL, "norm_test: no layers");
   if (n_layers > kMaxLayers)
@@ -696,15 +712,17 @@ extern "C" int adloco_norm_test(adloco_ctx* ctx, const adloco_linear_desc* layer
   int rc = ensure_scratch(ctx, ctx->red_f64, nblk * sizeof(double));
   if (rc) return rc;
   hipEvent_t ev = prof_begin(ctx, st);
-  hipError_t e = launch_sqnorm(static_cast<const LayerDev*>(ctx->layer_tab.ptr), ctx->layer_tab_host,
-                               static_cast<double*>(ctx->red_f64.ptr), ctx->dev_scalars, st);
+  const bool direct = kernel_can_read(acc) && (!ip || kernel_can_read(ip));
+  hipError_t e = launch_sqnorm(static_cast<const LayerDev*>(ctx->layer_tab.ptr), n_layers, nblk,
+                               static_cast<double*>(ctx->red_f64.ptr), direct ? acc : nullptr,
+                               direct ? ip : nullptr, ctx->pinned, st);
   prof_end(ctx, kProfSqnorm, ev, st);
   if (e != hipSuccess)
     return fail(ctx, ADLOCO_EHIP, "norm_test: reduction launch failed: %s", hipGetErrorString(e));
-  ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(ctx->pinned, ctx->dev_scalars, sizeof(double),
-                                       hipMemcpyDeviceToHost, st));
-  ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(ctx->pinned + 2, acc, sizeof(adloco_stats_acc),
-                                       hipMemcpyDeviceToHost, st));
+  if (!direct) {
+    ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(ctx->pinned + 2, acc, sizeof(adloco_stats_acc), hipMemcpyDeviceToHost, st));
+    if (ip) ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(ctx->pinned + 4, ip, sizeof *ip, hipMemcpyDeviceToHost, st));
+  }
   ADLOCO_HIP_CHECK(ctx, hipStreamSynchronize(st));
   const double S2 = ctx->pinned[0];
   adloco_stats_acc h;
@@ -716,6 +734,13 @@ extern "C" int adloco_norm_test(adloco_ctx* ctx, const adloco_linear_desc* layer
                                b_cap, flags, out);
   if (rc) return fail(ctx, rc, "norm_test: decision rejected S1 = %g, S2 = %g", h.sum_sample_sqnorm, S2);
   return ADLOCO_OK;
+}
+
+extern "C" int adloco_norm_test(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers,
+                                const adloco_stats_acc* acc, double eta, int64_t b_cur,
+                                int64_t b_max, int32_t n_switch, int64_t b_cap, uint32_t flags,
+                                adloco_norm_test_result* out, void* stream) {
+  return norm_test(ctx, layers, n_layers, acc, nullptr, eta, b_cur, b_max, n_switch, b_cap, flags, out, stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -841,12 +866,9 @@ extern "C" int adloco_inner_product_test(adloco_ctx* ctx, const adloco_linear_de
   if (!acc || !ip || !out) return fail(ctx, ADLOCO_EINVAL, "inner_product_test: NULL acc, ip or out");
   // S2 exactly as the norm test forms it (also validates the layer list)
   adloco_norm_test_result nt;
-  int rc = adloco_norm_test(ctx, layers, n_layers, acc, 1.0, b_cur, b_max, n_switch, b_cap, 0, &nt, stream);
+  int rc = norm_test(ctx, layers, n_layers, acc, ip, 1.0, b_cur, b_max, n_switch, b_cap, 0, &nt, stream);
   if (rc) return rc;
-  hipStream_t st = static_cast<hipStream_t>(stream);
   adloco_ip_acc h;
-  ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(ctx->pinned + 4, ip, sizeof h, hipMemcpyDeviceToHost, st));
-  ADLOCO_HIP_CHECK(ctx, hipStreamSynchronize(st));
   std::memcpy(&h, ctx->pinned + 4, sizeof h);
   if (h.n_samples != nt.n_samples)
     return fail(ctx, ADLOCO_ESTATE, "inner_product_test: the inner products cover %lld samples, the "

@@ -16,7 +16,6 @@ namespace {
 constexpr int kNaMaxLayers = 512;                    // blocks in one call
 constexpr size_t kNaMaxPartials = 131072;            // workgroups of the squared-norm kernel: 2^31 gradient entries
 struct NaScratch {
-  double out[32];                                    // [0]: S2
   LayerDev tab[kNaMaxLayers];
   double partial[kNaMaxPartials];
 };
@@ -101,13 +100,13 @@ extern "C" int adloco_norm_test_noalloc(adloco_ctx* ctx, const adloco_linear_des
     if (e != hipSuccess)
       return fail(ctx, ADLOCO_EHIP, "norm_test_noalloc: table launch failed: %s", hipGetErrorString(e));
   }
-  // every partial sum in [0, nblk) and out[0] are overwritten: nothing of an earlier call is read
-  hipError_t e = launch_sqnorm_table(S->tab, n_layers, size_t(nblk), S->partial, S->out, st);
+  // every partial sum in [0, nblk) is overwritten: nothing of an earlier call is read
+  const bool direct = kernel_can_read(acc);
+  hipError_t e = launch_sqnorm(S->tab, n_layers, size_t(nblk), S->partial, direct ? acc : nullptr, nullptr, ctx->pinned, st);
   if (e != hipSuccess)
     return fail(ctx, ADLOCO_EHIP, "norm_test_noalloc: reduction launch failed: %s", hipGetErrorString(e));
-  ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(ctx->pinned, S->out, sizeof(double), hipMemcpyDeviceToHost, st));
-  ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(ctx->pinned + 2, acc, sizeof(adloco_stats_acc),
-                                       hipMemcpyDeviceToHost, st));
+  if (!direct)
+    ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(ctx->pinned + 2, acc, sizeof(adloco_stats_acc), hipMemcpyDeviceToHost, st));
   ADLOCO_HIP_CHECK(ctx, hipStreamSynchronize(st));
   const double S2 = ctx->pinned[0];
   adloco_stats_acc h;

@@ -34,14 +34,15 @@ __global__ __launch_bounds__(kRedThreads) void sqnorm_partial_kernel(const Layer
                                                                      int n_layers,
                                                                      double* partial) {
   __shared__ double lds[kRedThreads / 64];
-  // binary search: last layer whose sq_blk_start <= blockIdx.x
-  int lo = 0, hi = n_layers - 1;
+  // last layer whose sq_blk_start <= blockIdx.x: every lane looks at one layer (the starts do not decrease), one memory
+  // latency per 64 layers
   const int b = blockIdx.x;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (layers[mid].sq_blk_start <= b) lo = mid; else hi = mid - 1;
+  int found = 0;
+  for (int base = 0; base < n_layers; base += 64) {
+    const int i = base + int(threadIdx.x & 63);
+    found += __popcll(__builtin_amdgcn_ballot_w64(i < n_layers && layers[i].sq_blk_start <= b));
   }
-  const LayerDev L = layers[lo];
+  const LayerDev L = layers[__builtin_amdgcn_readfirstlane(found - 1)];
   const long long numel = (long long)L.d_in * L.d_out;
   const long long begin = (long long)(b - L.sq_blk_start) * kSqChunk;
   long long end = begin + kSqChunk;
@@ -65,14 +66,21 @@ __global__ __launch_bounds__(kRedThreads) void sqnorm_partial_kernel(const Layer
   if (threadIdx.x == 0) partial[b] = s;
 }
 
-// One workgroup: out[0] = sum of partial[0..n) in a fixed order.
+// One workgroup: the sum of partial[0..n) in a fixed order, and what the caller's read-back needs next to it, straight
+// into pinned host memory: host[0] = sum, host[2..3] = *acc, host[4..7] = *ip (if given).  Copies of their own
+// would cost the stream two or three more operations.
 __global__ __launch_bounds__(1024) void sum_f64_kernel(const double* partial, long long n,
-                                                       double* out) {
+                                                       const adloco_stats_acc* acc, const adloco_ip_acc* ip,
+                                                       double* host) {
   __shared__ double lds[16];
-  double acc = 0.0;
-  for (long long i = threadIdx.x; i < n; i += blockDim.x) acc += partial[i];
-  double s = block_sum_f64(acc, lds);
-  if (threadIdx.x == 0) out[0] = s;
+  double v = 0.0;
+  for (long long i = threadIdx.x; i < n; i += blockDim.x) v += partial[i];
+  double s = block_sum_f64(v, lds);
+  if (threadIdx.x == 0) {
+    host[0] = s;
+    if (acc) *reinterpret_cast<adloco_stats_acc*>(host + 2) = *acc;
+    if (ip) *reinterpret_cast<adloco_ip_acc*>(host + 4) = *ip;
+  }
 }
 
 // One workgroup per sample i: n_i^l = sum over tile pairs of the Gram partials, n_i = sum_l n_i^l.
@@ -124,18 +132,21 @@ size_t sqnorm_partials(const std::vector<LayerDev>& host_layers) {
 
 int sqnorm_chunk() { return kSqChunk; }
 
-hipError_t launch_sqnorm_table(const LayerDev* layers, int n_layers, size_t nblk, double* partial,
-                               double* out, hipStream_t st) {
-  hipLaunchKernelGGL(sqnorm_partial_kernel, dim3(unsigned(nblk)), dim3(kRedThreads), 0, st, layers,
-                     n_layers, partial);
-  hipLaunchKernelGGL(sum_f64_kernel, dim3(1), dim3(1024), 0, st, partial, (long long)nblk, out);
-  return hipGetLastError();
+bool kernel_can_read(const void* p) {
+  hipPointerAttribute_t a;
+  if (reinterpret_cast<uintptr_t>(p) % 8 == 0 && hipPointerGetAttributes(&a, p) == hipSuccess)
+    return a.type == hipMemoryTypeDevice;
+  (void)hipGetLastError();
+  return false;
 }
 
-hipError_t launch_sqnorm(const LayerDev* layers, const std::vector<LayerDev>& host_layers,
-                         double* partial, double* out, hipStream_t st) {
-  return launch_sqnorm_table(layers, int(host_layers.size()), sqnorm_partials(host_layers), partial,
-                             out, st);
+hipError_t launch_sqnorm(const LayerDev* layers, int n_layers, size_t nblk, double* partial,
+                         const adloco_stats_acc* acc, const adloco_ip_acc* ip, double* host, hipStream_t st) {
+  static_assert(sizeof(adloco_stats_acc) == 16 && sizeof(adloco_ip_acc) == 32, "layout of the read-back");
+  hipLaunchKernelGGL(sqnorm_partial_kernel, dim3(unsigned(nblk)), dim3(kRedThreads), 0, st, layers,
+                     n_layers, partial);
+  hipLaunchKernelGGL(sum_f64_kernel, dim3(1), dim3(1024), 0, st, partial, (long long)nblk, acc, ip, host);
+  return hipGetLastError();
 }
 
 hipError_t launch_finalize_stats(const float* partials, int n_layers, int B, int n_pairs,

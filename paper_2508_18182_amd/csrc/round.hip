@@ -121,9 +121,8 @@ extern "C" int adloco_round(adloco_ctx* ctx, const adloco_round_config* cfg, adl
           // only the first inner step of worker 0 feeds the norm test: every other batch is a plain
           // gradient accumulation
           const uint32_t want = (m == 0 && h == 0) ? 0u : ADLOCO_SUM_ONLY;
-          rc = adloco_grad_stats(ctx, desc.data(), n_layers, int(R.b_micro), cfg->T, cfg->dtype,
-                                 t.per_sample_sqnorm, nullptr, t.acc,
-                                 (s > 0 ? ADLOCO_ACCUMULATE : 0u) | want, stream);
+          rc = grad_stats(ctx, desc.data(), n_layers, int(R.b_micro), cfg->T, cfg->dtype, t.per_sample_sqnorm, nullptr,
+                          t.acc, (s > 0 ? ADLOCO_ACCUMULATE : 0u) | want, true, stream);
           if (rc) return rc;
         }
         if (m == 0 && h == 0) {

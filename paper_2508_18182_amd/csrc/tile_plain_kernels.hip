@@ -2,6 +2,9 @@
 // kernel does not take: fp32 activations, and 16-bit ones whose rows are not 16-byte aligned.  Two uses, as there:
 //   MODE 0 (inner products): every finished sample tile is multiplied with the tile of G;
 //   MODE 1 (statistics): it is squared (its share of ||g_i||^2) and added to the running sum that becomes G.
+// MODE 2 is the gradient sum alone, all token rows as one sample: the same chain of fused multiply-adds, in row order,
+// as wgrad_f32_kernel's, so the result is the same bit for bit (AdamW, next in a training step, divides by sqrt(v) and
+// would blow up a last bit where gradient and second moment are both near zero).
 #include <algorithm>
 
 #include "common.h"
@@ -116,7 +119,7 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
   // wn * 32W + W * (lane%32) + n.  gt: the tile of G (MODE 0) or the running sum of the sample tiles (MODE 1).
   const int out_c = wn * 32 * W + W * (lane & 31);
   auto out_r = [&](int m, int j) { return wm * 32 * W + W * ((j >> 2) * 8 + (lane >> 5) * 4 + (j & 3)) + m; };
-  pt_f32x16 acc[W][W], gt[W][W];
+  pt_f32x16 acc[W][W], gt[W][W];                  // (MODE 2 has no second set)
 #pragma unroll
   for (int m = 0; m < W; ++m)
 #pragma unroll
@@ -153,7 +156,9 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
         for (int n = 0; n < W; ++n)
           acc[m][n] = __builtin_amdgcn_mfma_f32_32x32x2f32(fe[m], fc[n], acc[m][n], 0, 0, 0);
     }
-    if (last) {
+    if (MODE == 2) {
+      ++k;                                        // (one sample)
+    } else if (last) {
       double dot = 0.0, sq = 0.0;
 #pragma unroll
       for (int m = 0; m < W; ++m)
@@ -182,8 +187,8 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
     if (more) store(st ^ 1);                      // (read last in the chunk before: everybody is past its barrier)
     __syncthreads();
   }
-  if (MODE == 1) {
-    const int part = g.part[entry];
+  if (MODE != 0) {
+    const int part = MODE == 1 ? g.part[entry] : -1;
     float* pt = part >= 0 ? g.partials + (size_t)part * (kEdge * kEdge) : nullptr;
 #pragma unroll
     for (int m = 0; m < W; ++m)
@@ -192,11 +197,12 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
           const int r = out_r(m, j), c = out_c + n;
+          const float v = MODE == 1 ? gt[m][n][j] : acc[m][n][j];
           if (pt) {
-            pt[r * kEdge + c] = gt[m][n][j];
+            pt[r * kEdge + c] = v;
           } else if (e0 + r < L.d_out && c0 + c < L.d_in) {
             float* d = L.grad_sum + (size_t)(e0 + r) * L.d_in + c0 + c;
-            *d = g.accumulate ? *d + gt[m][n][j] : gt[m][n][j];
+            *d = g.accumulate ? *d + v : v;
           }
         }
   }
@@ -293,16 +299,16 @@ hipError_t launch_plain_tiles(const LayerDev* layers, const PlainTiles& p, int m
   PtArgs a{layers, static_cast<const int4*>(p.tab.ptr), static_cast<double*>(p.out.ptr), p.slots, T, p.group,
            static_cast<const int*>(p.part_idx.ptr), static_cast<float*>(p.ptiles.ptr), accumulate};
   const dim3 grid(unsigned(p.slots) * kNumXcd), block(kPtThreads);
-#define PT_LAUNCH(E)                                                                                    \
+#define PT_LAUNCH(E, MODE)                                                                              \
   do {                                                                                                  \
-    if (mode == 0 && p.W == 2) hipLaunchKernelGGL((plain_tile_kernel<E, 0, 2>), grid, block, 0, st, a); \
-    else if (mode == 0) hipLaunchKernelGGL((plain_tile_kernel<E, 0, 1>), grid, block, 0, st, a);        \
-    else if (p.W == 2) hipLaunchKernelGGL((plain_tile_kernel<E, 1, 2>), grid, block, 0, st, a);         \
-    else hipLaunchKernelGGL((plain_tile_kernel<E, 1, 1>), grid, block, 0, st, a);                       \
+    if (p.W == 2) hipLaunchKernelGGL((plain_tile_kernel<E, MODE, 2>), grid, block, 0, st, a);           \
+    else hipLaunchKernelGGL((plain_tile_kernel<E, MODE, 1>), grid, block, 0, st, a);                    \
   } while (0)
-  if (dtype == ADLOCO_BF16) PT_LAUNCH(unsigned short);
-  else if (dtype == ADLOCO_F16) PT_LAUNCH(_Float16);
-  else PT_LAUNCH(float);
+  if (mode == 2) PT_LAUNCH(float, 2);
+  else if (mode == 1) PT_LAUNCH(float, 1);             // (16-bit statistics have kernels of their own)
+  else if (dtype == ADLOCO_BF16) PT_LAUNCH(unsigned short, 0);
+  else if (dtype == ADLOCO_F16) PT_LAUNCH(_Float16, 0);
+  else PT_LAUNCH(float, 0);
 #undef PT_LAUNCH
   if (mode == 1 && p.n_split > 0) {
     if (p.W == 2)

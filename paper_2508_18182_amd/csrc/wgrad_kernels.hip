@@ -196,8 +196,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_bf16_kernel(WgradArgs g) {
 
 // ---------------------------------------------------------------------------------------
 // bf16 fast path: 256 (d_out) x 256 (d_in) output tile per workgroup of four waves (2 x 2, each 128 x 128, one per
-// SIMD), used when every row is 16-byte aligned, widths are multiples of 8 and the number of token rows is a multiple
-// of 32.  What bounds it is power: at 78 % busy matrix cores the chip holds 1.54 of its 2.4 GHz, so the kernel is laid
+// SIMD), used when every row is 16-byte aligned and widths are multiples of 8.  What bounds it is power: at 78 % busy matrix cores the chip holds 1.54 of its 2.4 GHz, so the kernel is laid
 // out for little energy per product -- the 16x16x32 MFMA, and wave tiles of 128 x 128, which read a third less from LDS
 // than eight waves of 128 x 64.  Sum over the 96 linears of the 350M model, 32 x 1024 tokens: 13.9 ms, 1.42 PFLOP/s,
 // also where it is added to a sum (15.4 ms with every old entry of G loaded and waited for by itself)
@@ -210,7 +209,9 @@ __global__ __launch_bounds__(256, 2) void wgrad_bf16_kernel(WgradArgs g) {
 //   leave the matrix core idle.  One barrier per chunk; loads run three chunks ahead.
 //   Tiles are dealt to the XCDs layer by layer (table built on the host): the tiles of one layer run next to each
 //   other on one XCD and stream the same columns out of that XCD's L2.
-//   Columns beyond d_out / d_in re-read the last valid 16-byte piece; those accumulators are never stored.
+//   Columns beyond d_out / d_in re-read the last valid 16-byte piece; those accumulators are never stored.  Token rows
+//   past the last one (in the last chunk) come from a line of zeros: 2 blocks of 1024 -> {3 x 1024, 1024, 4 x 1024},
+//   16 x 77 tokens take 0.24 ms (128 x 128 kernel with register staging: 0.49 ms).
 // ---------------------------------------------------------------------------------------
 constexpr int kXt = 256;                          // tile edge
 constexpr int kXk = 32;                           // token rows per stage
@@ -221,6 +222,8 @@ constexpr int kXstage = 2 * kXop;                 // 34 KiB
 constexpr int kXstages = 4;
 constexpr int kXthreads = 256;
 constexpr int kXlds = kXstages * kXstage;         // 136 KiB
+
+__device__ __attribute__((aligned(16))) const unsigned wgx_zero_line[4] = {0, 0, 0, 0};
 
 struct WgradXArgs {
   const LayerDev* layers;
@@ -257,9 +260,12 @@ __global__ __launch_bounds__(kXthreads, 1) void wgrad_bf16_x_kernel(WgradXArgs g
   const int wm = wave >> 1, wn = wave & 1;        // 2 x 2 waves; wave tile 128 (e) x 128 (c)
   // chunk range of this workgroup: everything, or piece split_p of split_s equal parts
   // (32-bit counters keep the loop's compares on the scalar unit; the host keeps rows / 32 < 2^31)
-  const long long nk_all = g.rows / kXk;
+  const long long nk_all = (g.rows + kXk - 1) / kXk;
   const long long ck0 = split_s ? nk_all * split_p / split_s : 0;
   const int nk = int((split_s ? nk_all * (split_p + 1) / split_s : nk_all) - ck0);
+  // rows of the last chunk of this workgroup
+  const long long rest = g.rows - (ck0 + nk - 1) * kXk;
+  const int last_rows = rest < kXk ? int(rest) : kXk;
 
   // ---- direct loads: block b = wave + 4 * q (q = 0..3) of each operand, 16-byte piece lane % 32 of row
   // wgx_row(b, lane / 32).  Address = (first row of the chunk: scalar registers) + (row within the chunk and
@@ -282,6 +288,21 @@ __global__ __launch_bounds__(kXthreads, 1) void wgrad_bf16_x_kernel(WgradXArgs g
   auto issue_load = [&](int i, unsigned st) {
     direct_load_lds16_s(lane_off[i], i >= 4 ? pc : pe,
                         ld_base + st + (i >> 2) * kXop + (i & 3) * 4 * kXblk);
+  };
+  // all loads of chunk c at once; the last chunk may be short
+  auto issue_chunk = [&](int c, unsigned st) {
+    if (c == nk - 1 && last_rows < kXk) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const unsigned char* p = reinterpret_cast<const unsigned char*>(i >= 4 ? pc : pe) + lane_off[i];
+        const bool ok = wgx_row(wave + 4 * (i & 3), lane >> 5) < last_rows;
+        direct_load_lds16(ok ? p : reinterpret_cast<const unsigned char*>(wgx_zero_line),
+                          ld_base + st + (i >> 2) * kXop + (i & 3) * 4 * kXblk);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) issue_load(i, st);
+    }
   };
   auto next_chunk = [&]() {
     pe += kXk * L.delta_stride;
@@ -342,8 +363,7 @@ __global__ __launch_bounds__(kXthreads, 1) void wgrad_bf16_x_kernel(WgradXArgs g
       __builtin_amdgcn_sched_barrier(0);
     }
     if (tail && c + kXstages < nk) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) issue_load(i, st);
+      issue_chunk(c + kXstages, st);
       next_chunk();
     }
     if (!tail) next_chunk();
@@ -354,8 +374,7 @@ __global__ __launch_bounds__(kXthreads, 1) void wgrad_bf16_x_kernel(WgradXArgs g
 #pragma unroll
   for (int s = 0; s < kXstages; ++s)
     if (s < nk) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) issue_load(i, s * kXstage);
+      issue_chunk(s, s * kXstage);
       next_chunk();
     }
   if (nk >= kXstages) wgx_wait_vmcnt<24>(); else wgx_wait_vmcnt<0>();
@@ -366,7 +385,7 @@ __global__ __launch_bounds__(kXthreads, 1) void wgrad_bf16_x_kernel(WgradXArgs g
 #pragma unroll
   for (int r = 0; r < 32; ++r) read1(r, lane_e, lane_c, f0);
   int c = 0;
-  for (; c + 1 + kXstages < nk; c += 2) {
+  for (; c + 2 + kXstages < nk; c += 2) {          // (the last chunk is loaded in the loop below)
     period(std::false_type{}, c, f0, f1);
     period(std::false_type{}, c + 1, f1, f0);
   }
@@ -393,32 +412,46 @@ __global__ __launch_bounds__(kXthreads, 1) void wgrad_bf16_x_kernel(WgradXArgs g
   }
 }
 
-// Sums the partial tiles of a split contraction in piece order (fixed order: repeatable) and
-// adds them to / stores them in grad_sum.  One workgroup per 4 rows of one split tile, one thread
-// per column, rows unrolled so that their loads are in flight together.
+// Sums the partial tiles of a split contraction in piece order (fixed order: repeatable) and adds them to / stores
+// them in grad_sum.  One workgroup per 4 rows of one split tile, one thread per column; bound by the latency of its
+// loads, so the old entries of G and those of four pieces are requested together (48 tiles of 256 x 256 in five
+// pieces: piece by piece, G last, 14 us).
 struct WgradSplitTile { int layer, e0, c0, w; };   // w = (pieces << 16) | first partial tile
 constexpr int kXredRows = 4;
-__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const LayerDev* layers,
-                                                           const WgradSplitTile* tiles,
+__global__ __launch_bounds__(kXt) void wgrad_reduce_kernel(const LayerDev* layers, const WgradSplitTile* tiles,
                                                            const float* partials, int accumulate) {
   const int t = blockIdx.x / (kXt / kXredRows), r0 = (blockIdx.x % (kXt / kXredRows)) * kXredRows;
   const WgradSplitTile S = tiles[t];
   const LayerDev L = layers[S.layer];
   const int pieces = S.w >> 16;
-  const float* base = partials + (size_t)(S.w & 0xffff) * (kXt * kXt) + threadIdx.x;
+  const float* base = partials + (size_t)(S.w & 0xffff) * (kXt * kXt) + r0 * kXt + threadIdx.x;
   const int col = S.c0 + threadIdx.x;
-  float v[kXredRows];
-#pragma unroll
-  for (int r = 0; r < kXredRows; ++r) v[r] = 0.f;
-  for (int p = 0; p < pieces; ++p)
-#pragma unroll
-    for (int r = 0; r < kXredRows; ++r) v[r] += base[(size_t)p * (kXt * kXt) + (r0 + r) * kXt];
+  float old[kXredRows], v[kXredRows];
 #pragma unroll
   for (int r = 0; r < kXredRows; ++r) {
     const int row = S.e0 + r0 + r;
-    if (row >= L.d_out || col >= L.d_in) continue;
-    float* dst = L.grad_sum + (size_t)row * L.d_in + col;
-    *dst = accumulate ? *dst + v[r] : v[r];
+    old[r] = accumulate && row < L.d_out && col < L.d_in ? L.grad_sum[(size_t)row * L.d_in + col] : 0.f;
+    v[r] = 0.f;
+  }
+  constexpr int kAhead = 4;
+  for (int p = 0; p < pieces; p += kAhead) {
+    float x[kAhead][kXredRows];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) {
+      const int pp = p + q < pieces ? p + q : pieces - 1;
+#pragma unroll
+      for (int r = 0; r < kXredRows; ++r) x[q][r] = base[(size_t)pp * (kXt * kXt) + r * kXt];
+    }
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q)
+#pragma unroll
+      for (int r = 0; r < kXredRows; ++r) v[r] += p + q < pieces ? x[q][r] : 0.f;
+  }
+#pragma unroll
+  for (int r = 0; r < kXredRows; ++r) {
+    const int row = S.e0 + r0 + r;
+    if (row < L.d_out && col < L.d_in)
+      L.grad_sum[(size_t)row * L.d_in + col] = accumulate ? old[r] + v[r] : v[r];
   }
 }
 

@@ -151,3 +151,26 @@ def test_tile_route_ragged_sequences(ctx, dtype, B, T, shapes):
     A.adloco_inner_products(ctx, got["layers"], B, T, code_of(dtype), c2, None,
                             torch.zeros(4, dtype=torch.float64, device=DEV))
     assert torch.equal(c, c2)
+
+
+@pytest.mark.parametrize("B,T,shapes", [
+    (1, 1, [(8, 8)]),                      # one token row
+    (5, 77, [(136, 264)]),                 # 385 rows: one over twelve chunks
+    (3, 21, [(128, 256), (520, 72)]),      # 63 rows: a short second chunk, fewer chunks than pieces
+    (2, 512, [(256, 768), (1032, 264)]),   # whole chunks, tiles on the edge
+])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_gradient_sum_alone(ctx, dtype, B, T, shapes):
+    # the gradient-only call: short last chunk, pieces of split tiles (more than chunks), added to a sum
+    import torch
+    import paper_2508_18182_amd as A
+    from gpu_util import DEV, code_of, to_dev
+    host = synth.custom_grad_stats_inputs(6500 + B + T, shapes, B, T, dtype, std_delta=0.2, rho=0.4)
+    want = orc.grad_stats([(l["a"], l["delta"]) for l in host], two_pass=False)["G"]
+    layers = [dict(a=to_dev(l["a"]), delta=to_dev(l["delta"]),
+                   grad_sum=torch.full((l["d_out"], l["d_in"]), float("nan"), device=DEV)) for l in host]
+    for k, flags in enumerate((0, A.ADLOCO_ACCUMULATE)):
+        A.adloco_grad_stats(ctx, layers, B, T, code_of(dtype), None, None, None, A.ADLOCO_SUM_ONLY | flags)
+        for l, w in zip(layers, want):
+            err = np.max(np.abs(l["grad_sum"].cpu().numpy().astype(np.float64) - (k + 1) * w))
+            assert err < (k + 1) * 1e-4 * float(np.sqrt(np.mean(w * w)))
