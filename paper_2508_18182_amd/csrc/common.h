@@ -46,6 +46,15 @@ __device__ __forceinline__ void mfma_16x16x32(mfma_f32x4& c, mfma_bf16x8 a, mfma
   else
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
+// The same instruction with its scheduling and registers left to the compiler.
+template <bool F16>
+__device__ __forceinline__ mfma_f32x4 mfma_16x16x32_v(mfma_bf16x8 a, mfma_bf16x8 b, mfma_f32x4 c) {
+  if constexpr (F16)
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(mfma_f16x8, a), __builtin_bit_cast(mfma_f16x8, b), c,
+                                                  0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
 // The same from zero: the old accumulators are only overwritten.  A reader of the old values in between needs no fence
 // if many MFMAs lie between the one that wrote them and itself.
 template <bool F16>
