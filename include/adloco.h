@@ -153,12 +153,13 @@ typedef struct {
  * Linear blocks that are handed the SAME activation tensor (same address, stride and d_in) with the same
  * d_out -- q / k / v or gate / up of a transformer block -- share their a_i a_i^T: the Gram kernel forms
  * it once for the group (same results up to fp32 summation order).
- * Two routes give the norms of the linear blocks.  With ADLOCO_GRAD_PROVIDED (the framework's
- * backward already holds the weight gradient) only the Gram contractions run.  When grad_sum
- * is formed here for every linear block and all of them are 16-byte aligned bf16 / fp16 with
- * T % 32 == 0, the 256 x 128 tiles of the per-sample gradients delta_i^T a_i that add up to
- * grad_sum pass through the registers one sample after the other and are squared there, so the
- * Gram contractions are not needed at all; adloco_set_tuning(ctx, "stats_variant", 0) keeps the
+ * Two routes give the norms of the linear blocks.  With ADLOCO_GRAD_PROVIDED for every block (the
+ * framework's backward already holds the weight gradient) the Gram contractions run, or, on sequences
+ * that are long for the widths, the per-sample gradients delta_i^T a_i are formed tile by tile in
+ * registers and squared there, whichever takes less time.  When grad_sum is formed here for every
+ * linear block and all of them are fp32, or 16-byte aligned bf16 / fp16, the tiles of the per-sample
+ * gradients that add up to grad_sum pass through the registers one sample after the other and are
+ * squared there, so the Gram contractions are not needed at all; adloco_set_tuning(ctx, "stats_variant", 0) keeps the
  * Gram kernel plus a separate gradient-sum GEMM instead.  Same results up to fp32 rounding. */
 int adloco_grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers,
                       int B, int T, int dtype,
@@ -283,9 +284,9 @@ typedef struct {
 
 /* adloco_inner_products: c_i for the B samples of one micro-batch against the grad_sum buffers
  * of the descriptors (every kind; all grad_sum non-NULL, only read; table ids outside [0, V)
- * contribute nothing).  For 16-byte aligned bf16 linear layers with T % 32 == 0 the 256 x 128
- * tiles of each per-sample gradient delta_i^T a_i are formed by MFMA in registers and reduced
- * against the fp32 tile of G on the spot; other blocks take a plain (slow) path.  B <= 32767.
+ * contribute nothing).  Tiles of each per-sample gradient delta_i^T a_i are formed by MFMA in
+ * registers and reduced against the fp32 tile of G on the spot (fp32 MFMA for fp32 and for unaligned
+ * 16-bit blocks).  B <= 32767.
  *   per_sample_ip      device [B] fp32, overwritten: c_i
  *   per_sample_sqnorm  device [B] fp32 or NULL, overwritten: ||g_i||^2 from the explicit per-sample
  *                      gradients (a second route to adloco_grad_stats' Gram result)

@@ -223,11 +223,11 @@ struct Scratch {
 struct PlainTiles {
   Scratch tab;              // int4 [8][slots] entries
   Scratch part_idx, split, ptiles;   // statistics form: partial tile per entry, split tiles, their storage
-  Scratch out;              // double [8 * slots][group][4 waves][2]
+  Scratch out;              // double (16-bit kernel: float) [8 * slots][group][4 waves][2]
   Scratch csr;              // int: listed layers | offsets | entries of each
   int W = 2;                // tiles of 64 * W
   int slots = 0, group = 1, n_split = 0, n_listed = 0;
-  int B = -1;               // batch the list was built for (-1: none)
+  int B = -1, T = -1;       // batch and (inner-product form) sequence length the list was built for (-1: none)
 };
 
 }  // namespace adloco
@@ -283,6 +283,8 @@ struct adloco_ctx {
   bool ts_ok = false;          // every linear block is aligned bf16 with its gradient sum formed here
   adloco::PlainTiles st_plain; // the same for fp32 blocks
   adloco::PlainTiles sum_plain; // gradient sums alone of fp32 blocks (B = 1: all token rows as one sample)
+  adloco::PlainTiles sq_tiles; // norms alone of blocks whose gradient sum is supplied (16-bit or plain kernel)
+  bool lin_fast = false;       // every linear block: 16-byte aligned rows, widths % 8 == 0, strides below 2^25
   int n_formed = 0;            // linear blocks whose gradient sum is formed here
   int stats_variant = 1;       // 1: tile form when eligible; 0: Gram + gradient-sum kernels
   // the vector / table kernels (HBM-bound) can run next to the kernels of the linear blocks (MFMA /
@@ -400,6 +402,9 @@ TileGeom ip_tile_geom();
 std::vector<int> tiles_by_layer(const std::vector<int4>& tiles, const std::vector<char>& use, int& n_listed);
 hipError_t launch_ip_tiles(const LayerDev* layers, const void* tiles, int slots, int T, int group,
                            int dtype, bool want_sq, float* ip_out, hipStream_t st);
+// ||g_i||^2 of aligned 16-bit blocks -> one partial sum per (layer, sample).
+hipError_t launch_square_tiles(const LayerDev* layers, const PlainTiles& p, int B, int T, int dtype, float* partials,
+                               hipStream_t st);
 int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, TileGeom geom,
                      std::vector<int4>& out, std::vector<int>& part, std::vector<int4>& split, int& n_pieces);
 hipError_t launch_stats_tiles(const LayerDev* layers, const void* tiles, const int* part, int slots,
@@ -411,7 +416,7 @@ hipError_t launch_stats_tiles(const LayerDev* layers, const void* tiles, const i
 constexpr int plain_tile_room(int W) { return kNumCu / kNumXcd * (W == 2 ? 2 : 4); }
 int plain_tile_width(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B);
 // mode 0: <g_i, G> -> dot and ||g_i||^2 -> sq; fp32 only: mode 1: G and ||g_i||^2 -> sq; mode 2: G (B = 1, T = all
-// token rows, sq = NULL).
+// token rows, sq = NULL); mode 3: ||g_i||^2 -> sq.
 hipError_t launch_plain_tiles(const LayerDev* layers, const PlainTiles& p, int mode, int B, int T, int dtype,
                               int accumulate, float* dot, float* sq, int sq_stride, hipStream_t st);
 hipError_t launch_ip_vector_table(const LayerDev* layers, const AuxDesc* vec_tab, int n_vec,

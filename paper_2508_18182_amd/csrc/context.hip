@@ -145,7 +145,7 @@ extern "C" int adloco_destroy(adloco_ctx* ctx) {
                     &ctx->ts_part_idx, &ctx->ts_split, &ctx->ts_ptiles, &ctx->ts_out, &ctx->ts_csr};
   for (Scratch* s : all)
     if (s->ptr) (void)hipFree(s->ptr);
-  for (PlainTiles* p : {&ctx->st_plain, &ctx->sum_plain, &ctx->ip_plain})
+  for (PlainTiles* p : {&ctx->st_plain, &ctx->sum_plain, &ctx->sq_tiles, &ctx->ip_plain})
     for (Scratch* s : {&p->tab, &p->part_idx, &p->split, &p->ptiles, &p->out, &p->csr})
       if (s->ptr) (void)hipFree(s->ptr);
   for (auto& r : ctx->prof) {

@@ -254,7 +254,10 @@ int prepare_tables(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_laye
   ctx->aux_B = ctx->aux_T = -1;         // the vector / table descriptor lists follow the table
   ctx->ip_B = ctx->ip_T = -1;           // and so does the inner-product tile table
   ctx->ts_B = -1;                       // and the statistics tile tables
-  ctx->st_plain.B = ctx->sum_plain.B = -1;
+  ctx->st_plain.B = ctx->sum_plain.B = ctx->sq_tiles.B = -1;
+  ctx->lin_fast = need_inputs && widest < (1 << 25);
+  for (const LayerDev& L : tab)
+    if (L.kind == ADLOCO_KIND_LINEAR) ctx->lin_fast = ctx->lin_fast && L.fast;
   ctx->n_formed = 0;
   for (const LayerDev& L : tab) ctx->n_formed += L.kind == ADLOCO_KIND_LINEAR && !L.provided;
   {
@@ -384,15 +387,15 @@ int prepare_vector_table(adloco_ctx* ctx, int B, int T, hipStream_t st) {
   return ADLOCO_OK;
 }
 
-// Work list of the plain tile kernel for the layers of `use`: statistics form (T = 0; entries split along the samples)
-// or inner-product form.
+// Work list of the plain tile kernel (mfma16: of the 16-bit one) for the layers of `use`: statistics form (T = 0;
+// entries split along the samples) or inner-product form.
 int build_plain_tiles(adloco_ctx* ctx, PlainTiles& p, const std::vector<char>& use, int B, int T, int forced_group,
-                      hipStream_t st) {
+                      bool mfma16, hipStream_t st) {
   ++ctx->table_builds;
   p.B = -1;
   const std::vector<LayerDev>& tab = ctx->layer_tab_host;
   p.W = plain_tile_width(tab, use, B);
-  const TileGeom geom{64 * p.W, 64 * p.W, 32 / p.W, plain_tile_room(p.W)};
+  const TileGeom geom = mfma16 ? ip_tile_geom() : TileGeom{64 * p.W, 64 * p.W, 32 / p.W, plain_tile_room(p.W)};
   std::vector<int4> tiles, split;
   std::vector<int> part;
   int n_pieces = 0;
@@ -412,7 +415,7 @@ int build_plain_tiles(adloco_ctx* ctx, PlainTiles& p, const std::vector<char>& u
       {&p.tab, tiles.data(), tiles.size() * sizeof(int4)}, {&p.part_idx, part.data(), part.size() * sizeof(int)},
       {&p.split, split.data(), split.size() * sizeof(int4)}, {&p.csr, csr.data(), csr.size() * sizeof(int)},
       {&p.ptiles, nullptr, n_pieces * edge * edge * sizeof(float)},
-      {&p.out, nullptr, tiles.size() * p.group * 8 * sizeof(double)}};
+      {&p.out, nullptr, tiles.size() * p.group * 8 * (mfma16 ? sizeof(float) : sizeof(double))}};
   for (const auto& u : up) {
     int rc = ensure_scratch(ctx, *u.s, std::max<size_t>(u.bytes, 16));
     if (rc) return rc;
@@ -421,7 +424,33 @@ int build_plain_tiles(adloco_ctx* ctx, PlainTiles& p, const std::vector<char>& u
   }
   ADLOCO_HIP_CHECK(ctx, hipStreamSynchronize(st));
   p.B = B;
+  p.T = T;
   return ADLOCO_OK;
+}
+
+// Norms of linear blocks whose gradient sums are supplied: true where the tiles of the per-sample gradients
+// (2 d_in d_out T products) take less time than the Gram contraction ((d_in + d_out) T (T + 1)), as on sequences that
+// are long for the widths.  Microseconds from measured rates: 16-bit tiles 0.95 PFLOP/s on 256 workgroups of 256 x 128
+// (0.55 where widths are no multiple of 64: the pieces of a row straddle cache lines), the Gram kernel 0.92 (its general
+// form, for such widths, 0.35); fp32 tiles 80 TFLOP/s on 512 workgroups of 128 x 128, the fp32 Gram kernel 23; 20 us for
+// starts and ends.  Measured, Gram -> tiles: bf16 7 x {600 -> 1800, ..}, B 3, T 2688 2.77 -> 0.77 ms; 6 x {320 -> 960,
+// ..}, B 6, T 1792 0.90 -> 0.37; fp32 {512 -> 1408, ..}, B 11, T 1395 8.3 -> 1.1; {1336 -> 4008, ..}, B 3, T 1024 stays
+// with the Gram kernel: 0.28 against 0.40.
+bool tiles_beat_gram(const std::vector<LayerDev>& tab, int B, int T, int dtype, bool dual) {
+  const bool b16 = is_16bit(dtype);
+  const long long te = b16 ? 256 : 128, tc = 128, gt = b16 ? 128 : 32, wgs = b16 ? 256 : 512;
+  const double tile_rate = b16 ? (dual ? 9.5e8 : 5.5e8) : 8e7, gram_rate = b16 ? (dual ? 9.2e8 : 3.5e8) : 2.3e7;   // flop per us
+  const double nt = double((T + gt - 1) / gt);
+  double tiles = 0.0, gram = 0.0;
+  for (const LayerDev& L : tab) {
+    if (L.kind != ADLOCO_KIND_LINEAR) continue;
+    tiles += double((L.d_out + te - 1) / te) * double((L.d_in + tc - 1) / tc);
+    // (layers that share their activations share that half of the contraction)
+    gram += nt * (nt + 1) * gt * gt * ((dual && T % 128 == 0 && L.a_twin >= 0 ? 0 : L.d_in) + L.d_out);
+  }
+  const double per_round = 2.0 * te * tc * double((T + 31) / 32 * 32) * wgs / tile_rate;
+  const double t_tiles = std::max(1.0, tiles * B / wgs) * per_round + 20.0;
+  return t_tiles < 0.95 * gram * B / gram_rate;
 }
 
 }  // namespace
@@ -487,7 +516,10 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   const long long rows = (long long)B * T;
   const bool plain_sum = dtype == ADLOCO_F32 && !plain_form && ctx->n_formed > 0 && rows < (1 << 30) &&
                          ctx->stats_variant != 0;
-  if (tile_form || plain_form) n_pairs = 1;      // one finished sum per (layer, sample)
+  const bool square_form = !sum_only && ctx->stats_variant != 0 && ctx->n_linear > 0 && ctx->n_formed == 0 &&
+                           B <= 0x7fff && T <= (1 << 20) && (dtype == ADLOCO_F32 || ctx->lin_fast) &&
+                           tiles_beat_gram(ctx->layer_tab_host, B, T, dtype, dual);
+  if (tile_form || plain_form || square_form) n_pairs = 1;      // one finished sum per (layer, sample)
   const long long n_part = (long long)n_layers * B * n_pairs;
   rc = ensure_scratch(ctx, ctx->partials, size_t(n_part) * sizeof(float));
   if (rc) return rc;
@@ -499,7 +531,13 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
     std::vector<char> use(n_layers, 0);
     for (int l = 0; l < n_layers; ++l)
       use[l] = ctx->layer_tab_host[l].kind == ADLOCO_KIND_LINEAR && !ctx->layer_tab_host[l].provided;
-    rc = build_plain_tiles(ctx, *plain, use, plain_B, 0, 0, st);
+    rc = build_plain_tiles(ctx, *plain, use, plain_B, 0, 0, false, st);
+    if (rc) return rc;
+  }
+  if (square_form && (ctx->sq_tiles.B != B || ctx->sq_tiles.T != T)) {
+    std::vector<char> use(n_layers, 0);
+    for (int l = 0; l < n_layers; ++l) use[l] = ctx->layer_tab_host[l].kind == ADLOCO_KIND_LINEAR;
+    rc = build_plain_tiles(ctx, ctx->sq_tiles, use, B, T, 0, is_16bit(dtype), st);
     if (rc) return rc;
   }
   if (tile_form && ctx->ts_B != B) {
@@ -610,7 +648,15 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
     if (e != hipSuccess)
       return fail(ctx, ADLOCO_EHIP, "grad_stats: plain tile launch failed: %s", hipGetErrorString(e));
   }
-  const bool formed = tile_form || plain_form;     // norms and gradient sums are done
+  if (square_form) {
+    ev = prof_begin(ctx, st);
+    e = is_16bit(dtype) ? launch_square_tiles(g.layers, ctx->sq_tiles, B, T, dtype, g.partials, st)
+                        : launch_plain_tiles(g.layers, ctx->sq_tiles, 3, B, T, dtype, 0, nullptr, g.partials, 1, st);
+    prof_end(ctx, kProfTileStats, ev, st);
+    if (e != hipSuccess)
+      return fail(ctx, ADLOCO_EHIP, "grad_stats: square tile launch failed: %s", hipGetErrorString(e));
+  }
+  const bool formed = tile_form || plain_form || square_form;     // norms (and gradient sums) are done
   ev = (!formed && !sum_only && ctx->n_linear > 0) ? prof_begin(ctx, st) : nullptr;
   if (formed || sum_only || ctx->n_linear == 0)
     ;
@@ -810,7 +856,7 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
     }
     ctx->ip_plain.slots = 0;
     if (any_rest) {
-      rc = build_plain_tiles(ctx, ctx->ip_plain, rest, B, T, ctx->ip_group_tuning, st);
+      rc = build_plain_tiles(ctx, ctx->ip_plain, rest, B, T, ctx->ip_group_tuning, false, st);
       if (rc) return rc;
     }
     ctx->ip_slots = slots;

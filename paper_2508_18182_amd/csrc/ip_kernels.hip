@@ -43,7 +43,8 @@ __device__ __forceinline__ double ip_block_sum(double v, double* lds4) {
 //   MODE 0 (inner products): the tile of G; the finished sample tile is multiplied element-wise
 //     with it and summed over the wave; two floats per (tile, sample, wave) leave the chip;
 //   MODE 1 (statistics): the running sum of the sample tiles; each finished tile is squared and
-//     summed (its share of ||g_i||^2) and added to the running sum, which is stored as the tile of G at the end.
+//     summed (its share of ||g_i||^2) and added to the running sum, which is stored as the tile of G at the end;
+//   MODE 2 (norms of blocks whose gradient sum is supplied): nothing, each finished tile is squared and summed.
 // That work on a finished tile is spread between the MFMAs of the next sample's first chunk, which start from zero
 // instead of the old accumulators: each block is read just before its first MFMA of the new sample.
 // A 256 x 256 tile would need 256 accumulators + 256 registers of the second set per lane: the whole register file.
@@ -135,6 +136,7 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
   // ---- second register set.  Accumulator element j of a 16x16 block: row grp * 4 + j, column i16.  MODE 0: this
   // lane's entries of the G tile (zero past the edge); MODE 1: running sum of the sample tiles.
   float gt[kIpFM][kIpFN][4];
+  if constexpr (MODE != 2)
 #pragma unroll
   for (int m = 0; m < kIpFM; ++m)
 #pragma unroll
@@ -238,8 +240,8 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const float v = mfma_acc(acc[m][n], j);
-      if (MODE == 0) dot[j] = fmaf(v, gt[m][n][j], dot[j]);
-      else asm volatile("v_add_f32 %0, %0, %1" : "+v"(gt[m][n][j]) : "v"(v));   // (in place: no register to spare)
+      if constexpr (MODE == 0) dot[j] = fmaf(v, gt[m][n][j], dot[j]);
+      else if constexpr (MODE == 1) asm volatile("v_add_f32 %0, %0, %1" : "+v"(gt[m][n][j]) : "v"(v));   // (in place: no register to spare)
       if (SQ) sq[j] = fmaf(v, v, sq[j]);
     }
   };
@@ -309,6 +311,7 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
     }
   // The G registers are needed only at the end of the first sample, but a wait placed there by the
   // compiler would drain the load pipeline at every sample; pin them down here, once.
+  if constexpr (MODE != 2)
 #pragma unroll
   for (int m = 0; m < kIpFM; ++m)
 #pragma unroll
@@ -365,7 +368,7 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
     for (int n = 0; n < kIpFN; ++n) take_block(m, n);
   put_sample();
 
-  if (MODE == 1) {
+  if constexpr (MODE == 1) {
     const int part = g.part[xcd * g.slots + slot];
     if (part >= 0) {
       float* pt = g.partials + (size_t)part * (kIpE * kIpC);
@@ -516,6 +519,26 @@ hipError_t launch_ip_tiles(const LayerDev* layers, const void* tiles, int slots,
   }
   IpTileArgs a{layers, static_cast<const int4*>(tiles), ip_out, slots, T, group, nullptr, nullptr, 0};
   hipLaunchKernelGGL(kern, dim3(unsigned(slots) * kNumXcd), dim3(64 * kIpWaves), kIpLds, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_square_tiles(const LayerDev* layers, const PlainTiles& p, int B, int T, int dtype, float* partials,
+                               hipStream_t st) {
+  if (p.slots <= 0) return hipSuccess;
+  auto kern = ip_tile_variant<2, true>(dtype, T);
+  {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kIpLds);
+    if (e != hipSuccess) return e;
+  }
+  const int4* tiles = static_cast<const int4*>(p.tab.ptr);
+  float* out = static_cast<float*>(p.out.ptr);
+  IpTileArgs a{layers, tiles, out, p.slots, T, p.group, nullptr, nullptr, 0};
+  hipLaunchKernelGGL(kern, dim3(unsigned(p.slots) * kNumXcd), dim3(64 * kIpWaves), kIpLds, st, a);
+  const int* csr = static_cast<const int*>(p.csr.ptr);
+  const int nl = p.n_listed;
+  hipLaunchKernelGGL(stats_tile_finalize_kernel, dim3(unsigned(nl) * B), dim3(64), 0, st, tiles, out, p.group, csr,
+                     csr + nl, csr + nl + nl + 1, B, partials, 1);
   return hipGetLastError();
 }
 

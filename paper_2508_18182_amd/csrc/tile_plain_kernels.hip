@@ -2,6 +2,7 @@
 // kernel does not take: fp32 activations, and 16-bit ones whose rows are not 16-byte aligned.  Two uses, as there:
 //   MODE 0 (inner products): every finished sample tile is multiplied with the tile of G;
 //   MODE 1 (statistics): it is squared (its share of ||g_i||^2) and added to the running sum that becomes G.
+//   MODE 3 (norms of blocks whose gradient sum is supplied): it is squared.
 // MODE 2 is the gradient sum alone, all token rows as one sample: the same chain of fused multiply-adds, in row order,
 // as wgrad_f32_kernel's, so the result is the same bit for bit (AdamW, next in a training step, divides by sqrt(v) and
 // would blow up a last bit where gradient and second moment are both near zero).
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
   // wn * 32W + W * (lane%32) + n.  gt: the tile of G (MODE 0) or the running sum of the sample tiles (MODE 1).
   const int out_c = wn * 32 * W + W * (lane & 31);
   auto out_r = [&](int m, int j) { return wm * 32 * W + W * ((j >> 2) * 8 + (lane >> 5) * 4 + (j & 3)) + m; };
-  pt_f32x16 acc[W][W], gt[W][W];                  // (MODE 2 has no second set)
+  pt_f32x16 acc[W][W], gt[W][W];                  // (MODE 2 and 3 have no second set)
 #pragma unroll
   for (int m = 0; m < W; ++m)
 #pragma unroll
@@ -168,7 +169,7 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
           for (int j = 0; j < 16; ++j) {
             const float v = acc[m][n][j];
             if (MODE == 0) dot = fma(double(v), double(gt[m][n][j]), dot);
-            else gt[m][n][j] += v;
+            else if (MODE == 1) gt[m][n][j] += v;
             sq = fma(double(v), double(v), sq);
             acc[m][n][j] = 0.f;
           }
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
     if (more) store(st ^ 1);                      // (read last in the chunk before: everybody is past its barrier)
     __syncthreads();
   }
-  if (MODE != 0) {
+  if (MODE == 1 || MODE == 2) {
     const int part = MODE == 1 ? g.part[entry] : -1;
     float* pt = part >= 0 ? g.partials + (size_t)part * (kEdge * kEdge) : nullptr;
 #pragma unroll
@@ -306,6 +307,7 @@ hipError_t launch_plain_tiles(const LayerDev* layers, const PlainTiles& p, int m
   } while (0)
   if (mode == 2) PT_LAUNCH(float, 2);
   else if (mode == 1) PT_LAUNCH(float, 1);             // (16-bit statistics have kernels of their own)
+  else if (mode == 3) PT_LAUNCH(float, 3);
   else if (dtype == ADLOCO_BF16) PT_LAUNCH(unsigned short, 0);
   else if (dtype == ADLOCO_F16) PT_LAUNCH(_Float16, 0);
   else PT_LAUNCH(float, 0);

@@ -174,3 +174,26 @@ def test_gradient_sum_alone(ctx, dtype, B, T, shapes):
         for l, w in zip(layers, want):
             err = np.max(np.abs(l["grad_sum"].cpu().numpy().astype(np.float64) - (k + 1) * w))
             assert err < (k + 1) * 1e-4 * float(np.sqrt(np.mean(w * w)))
+
+
+@pytest.mark.parametrize("B,T,shapes", [
+    (3, 513, [(64, 128), (128, 64)]),      # long for the widths: tiles of the per-sample gradients, ragged
+    (2, 1024, [(136, 72), (8, 264)]),      # whole chunks, widths that are no multiple of 64
+    (40, 160, [(64, 64)]),                 # several samples per entry
+    (2, 96, [(512, 1024)]),                # short: the Gram contraction
+])
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+def test_norms_of_supplied_gradients(ctx, dtype, B, T, shapes):
+    # both routes against the oracle; the supplied gradient sums are read by nobody and stay as they are
+    import torch
+    from gpu_util import DEV, rel_err, run_grad_stats
+    layers = synth.custom_grad_stats_inputs(6600 + B + T, shapes, B, T, dtype, std_delta=0.2, rho=0.4)
+    want = orc.grad_stats([(l["a"], l["delta"]) for l in layers], two_pass=False)
+    gs = [torch.full((l["d_out"], l["d_in"]), 7.0, device=DEV) for l in layers]
+    for variant in (1, 0):
+        ctx.set_tuning("stats_variant", variant)
+        got = run_grad_stats(ctx, layers, grad_sums=gs, provided=True)
+        assert rel_err(got["per_layer"], want["n_layer_sample"]) < (1e-4 if dtype == "f32" else TOL_BF16)
+        assert rel_err(got["S1"], want["S1"]) < (1e-4 if dtype == "f32" else TOL_BF16)
+        assert all(bool((g == 7.0).all()) for g in gs)
+    ctx.set_tuning("stats_variant", 1)
