@@ -453,6 +453,26 @@ bool tiles_beat_gram(const std::vector<LayerDev>& tab, int B, int T, int dtype, 
   return t_tiles < 0.95 * gram * B / gram_rate;
 }
 
+// Gradient sums formed here: true where the tiles of the per-sample gradients, whose samples are padded to whole chunks
+// (32 token rows; fp32: 16), take less time than the Gram contraction followed by the sum over all rows, which pays for
+// no padding: short sequences on wide layers go the second way.  Rates as above, gradient sums at 1.2 PFLOP/s / 80
+// TFLOP/s; the work on a finished 16-bit tile is worth 48 token rows.  Measured, fp16: {1024 -> 3072, ..} x 4, B 8, T 17
+// 0.30 ms by tiles, 0.23 the second way; {512 -> 1536, ..}, B 8, T 333 0.11 against 0.14.
+bool formed_tiles_pay(const std::vector<LayerDev>& tab, int T, int dtype, bool dual) {
+  const bool b16 = is_16bit(dtype);
+  const long long gt = b16 ? 128 : 32, chunk = b16 ? 32 : 16;
+  const double tile_rate = b16 ? 9.5e8 : 8e7, gram_rate = b16 ? (dual ? 9.2e8 : 3.5e8) : 2.3e7, sum_rate = b16 ? 1.2e9 : 8e7;
+  const double nt = double((T + gt - 1) / gt), rows = double((T + chunk - 1) / chunk * chunk + (b16 ? 48 : 0));
+  double tiles = 0.0, gram = 0.0;
+  for (const LayerDev& L : tab) {
+    if (L.kind != ADLOCO_KIND_LINEAR) continue;
+    const double io = 2.0 * L.d_in * L.d_out;
+    tiles += io * rows / tile_rate;
+    gram += nt * (nt + 1) * gt * gt * (double(L.d_in) + L.d_out) / gram_rate + io * T / sum_rate;
+  }
+  return tiles <= gram;
+}
+
 }  // namespace
 
 namespace adloco {
@@ -507,12 +527,14 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
 
   // Per-sample gradient tiles (explicit form) when the gradient sums of all linear blocks are formed here: the tiles
   // that add up to them are squared on the way, no Gram contraction is needed.  16-bit blocks if they are aligned;
-  // fp32 ones always: 4 x {768 -> 2304, 768 -> 768, 768 -> 3072, 3072 -> 768}, B 8, T 256 takes 1.28 ms
+  // fp32 ones too: 4 x {768 -> 2304, 768 -> 768, 768 -> 3072, 3072 -> 768}, B 8, T 256 takes 1.28 ms
   // against 5.02 ms with the vector-unit kernels of the two steps.
-  const bool tile_form = !sum_only && ctx->stats_variant != 0 && ctx->ts_ok && (T % 32 == 0 || !pinned_order) &&
+  const bool tile_form = !sum_only && ctx->stats_variant != 0 && ctx->ts_ok &&
+                         (T % 32 == 0 || (!pinned_order && formed_tiles_pay(ctx->layer_tab_host, T, dtype, dual))) &&
                          T <= (1 << 20) && B <= 0x7fff;
   const bool plain_form = dtype == ADLOCO_F32 && !pinned_order && ctx->n_formed > 0 && B <= 0x7fff && ctx->stats_variant != 0 &&
-                          !sum_only && ctx->n_formed == ctx->n_linear;
+                          !sum_only && ctx->n_formed == ctx->n_linear &&
+                          formed_tiles_pay(ctx->layer_tab_host, T, dtype, dual);
   const long long rows = (long long)B * T;
   const bool plain_sum = dtype == ADLOCO_F32 && !plain_form && ctx->n_formed > 0 && rows < (1 << 30) &&
                          ctx->stats_variant != 0;

@@ -125,6 +125,7 @@ def test_tile_route_accumulates_over_micro_batches(ctx):
     (2, 95, [(72, 520), (256, 256)]),      # three chunks (odd), the last one row short
     (1, 250, [(264, 8)]),                  # one sample of eight chunks: the load pipeline never wraps
     (300, 7, [(128, 256)]),                # long runs of one-chunk samples
+    (2, 45, [(1024, 2048)]),               # short for the widths: Gram contraction and gradient sum of ragged rows
 ])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_tile_route_ragged_sequences(ctx, dtype, B, T, shapes):
