@@ -405,7 +405,8 @@ hipError_t launch_ip_tiles(const LayerDev* layers, const void* tiles, int slots,
 // ||g_i||^2 of aligned 16-bit blocks -> one partial sum per (layer, sample).
 hipError_t launch_square_tiles(const LayerDev* layers, const PlainTiles& p, int B, int T, int dtype, float* partials,
                                hipStream_t st);
-int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, TileGeom geom,
+// max_split: pieces of a tile at most
+int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, TileGeom geom, int max_split,
                      std::vector<int4>& out, std::vector<int>& part, std::vector<int4>& split, int& n_pieces);
 hipError_t launch_stats_tiles(const LayerDev* layers, const void* tiles, const int* part, int slots,
                               const void* split, int n_split, float* partial_tiles, int B, int T,

@@ -387,8 +387,8 @@ int prepare_vector_table(adloco_ctx* ctx, int B, int T, hipStream_t st) {
   return ADLOCO_OK;
 }
 
-// Work list of the plain tile kernel (mfma16: of the 16-bit one) for the layers of `use`: statistics form (T = 0;
-// entries split along the samples) or inner-product form.
+// Work list of the plain tile kernel (mfma16: of the 16-bit one) for the layers of `use`: statistics form (T = 0:
+// entries split along the samples, T = -1: whole entries only) or inner-product form.
 int build_plain_tiles(adloco_ctx* ctx, PlainTiles& p, const std::vector<char>& use, int B, int T, int forced_group,
                       bool mfma16, hipStream_t st) {
   ++ctx->table_builds;
@@ -399,8 +399,8 @@ int build_plain_tiles(adloco_ctx* ctx, PlainTiles& p, const std::vector<char>& u
   std::vector<int4> tiles, split;
   std::vector<int> part;
   int n_pieces = 0;
-  if (T == 0) {
-    p.slots = make_stats_tiles(tab, use, B, geom, tiles, part, split, n_pieces);
+  if (T <= 0) {
+    p.slots = make_stats_tiles(tab, use, B, geom, T == 0 ? 0x7fff : 1, tiles, part, split, n_pieces);
     p.group = B;
   } else {
     p.slots = make_ip_tiles(tab, use, B, T, geom, forced_group, tiles, p.group);
@@ -549,11 +549,13 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   if (rc) return rc;
   PlainTiles* const plain = plain_form ? &ctx->st_plain : plain_sum ? &ctx->sum_plain : nullptr;
   const int plain_B = plain_form ? B : 1;
-  if (plain && plain->B != plain_B) {
+  // (adding up partial tiles is one more launch of about 5 us, as long as 512 token rows of a tile take)
+  const int plain_T = plain_form && rows <= 512 ? -1 : 0;
+  if (plain && (plain->B != plain_B || plain->T != plain_T)) {
     std::vector<char> use(n_layers, 0);
     for (int l = 0; l < n_layers; ++l)
       use[l] = ctx->layer_tab_host[l].kind == ADLOCO_KIND_LINEAR && !ctx->layer_tab_host[l].provided;
-    rc = build_plain_tiles(ctx, *plain, use, plain_B, 0, 0, false, st);
+    rc = build_plain_tiles(ctx, *plain, use, plain_B, plain_T, 0, false, st);
     if (rc) return rc;
   }
   if (square_form && (ctx->sq_tiles.B != B || ctx->sq_tiles.T != T)) {
@@ -570,7 +572,7 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
     std::vector<int4> tiles, split;
     std::vector<int> part;
     int n_pieces = 0, n_listed = 0;
-    const int slots = make_stats_tiles(tab, use, B, ip_tile_geom(), tiles, part, split, n_pieces);
+    const int slots = make_stats_tiles(tab, use, B, ip_tile_geom(), 0x7fff, tiles, part, split, n_pieces);
     if ((long long)slots * kNumXcd > 0x7fffffffLL)
       return fail(ctx, ADLOCO_EUNSUPPORTED, "grad_stats: too many tiles for one launch");
     const std::vector<int> csr = tiles_by_layer(tiles, use, n_listed);

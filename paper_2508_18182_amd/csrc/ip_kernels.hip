@@ -545,7 +545,7 @@ hipError_t launch_square_tiles(const LayerDev* layers, const PlainTiles& p, int 
 // Tile table of the statistics form: one entry per tile covering all B samples; the tiles of a layer go to one XCD
 // where possible (they stream the same rows).  The entries of an XCD's incomplete last round of workgroups are split
 // along the samples into pieces whose partial sums a small kernel adds up in piece order.
-int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, TileGeom geom,
+int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, TileGeom geom, int max_split,
                      std::vector<int4>& out, std::vector<int>& part, std::vector<int4>& split, int& n_pieces) {
   // all tiles in layer order (within a layer: blocks of tiles that share rows), cut into eight
   // equal runs: a layer stays on one XCD unless it straddles a cut, and the XCDs get the same
@@ -567,7 +567,7 @@ int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char
   for (int x = 0; x < kNumXcd; ++x) {
     const int n = int(per[x].size());
     const int full = n / geom.room * geom.room, left = n - full;
-    const int S = left > 0 ? std::min(geom.room / left, B) : 1;
+    const int S = left > 0 ? std::min(std::min(geom.room / left, B), max_split) : 1;
     for (int i = 0; i < n; ++i) {
       if (i < full || S < 2 || n_pieces + S > 0xffff) {
         fin[x].push_back(per[x][i]);
