@@ -177,9 +177,10 @@ __device__ __forceinline__ unsigned lds_address(const void* p) {
 
 // A wave's M x N accumulator blocks of 16 x 16 -> G [d_out, d_in]: this lane's element j of block (m, n) is entry
 // (r + 16 * m + j, c + 16 * n).  The old entries of `MB` block rows are requested together (addresses past the edge are
-// clamped): one by one, each load would be waited for on its own, about 1 us apiece at the end of every tile.
+// clamped): one by one, each load would be waited for on its own, about 1 us apiece at the end of every tile.  whole
+// (the same for all lanes): no entry lies past the edge, and none is checked.
 template <int M, int N, int MB, typename F>
-__device__ __forceinline__ void put_grad_tile(float* G, int d_out, int d_in, int r, int c, bool accumulate, F value) {
+__device__ __forceinline__ void put_grad_tile(float* G, int d_out, int d_in, int r, int c, bool accumulate, bool whole, F value) {
   static_assert(M % MB == 0, "whole batches");
 #pragma unroll
   for (int m0 = 0; m0 < M; m0 += MB) {
@@ -200,6 +201,20 @@ __device__ __forceinline__ void put_grad_tile(float* G, int d_out, int d_in, int
             const int rr = r + (m0 + m) * 16 + j, cc = c + n * 16;
             old[m][n][j] = G[(size_t)(rr < d_out ? rr : d_out - 1) * d_in + (cc < d_in ? cc : d_in - 1)];
           }
+    }
+    if (whole) {
+#pragma unroll
+      for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float* row = G + (size_t)(r + (m0 + m) * 16 + j) * d_in + c;
+#pragma unroll
+          for (int n = 0; n < N; ++n) {
+            const float v = value(m0 + m, n, j);
+            row[n * 16] = accumulate ? old[m][n][j] + v : v;
+          }
+        }
+      continue;
     }
 #pragma unroll
     for (int m = 0; m < MB; ++m)

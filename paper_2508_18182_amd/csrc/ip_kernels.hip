@@ -381,7 +381,8 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
             pt[(wm * 128 + m * 16 + grp * 4 + j) * kIpC + wn * 64 + n * 16 + i16] = gt[m][n][j];
     } else {
       put_grad_tile<kIpFM, kIpFN, 4>(L.grad_sum, L.d_out, L.d_in, e0 + wm * 128 + grp * 4, c0 + wn * 64 + i16,
-                                     g.accumulate != 0, [&](int m, int n, int j) { return gt[m][n][j]; });
+                                     g.accumulate != 0, e0 + kIpE <= L.d_out && c0 + kIpC <= L.d_in,
+                                     [&](int m, int n, int j) { return gt[m][n][j]; });
     }
   }
 }

@@ -408,7 +408,8 @@ __global__ __launch_bounds__(kXthreads, 1) void wgrad_bf16_x_kernel(WgradXArgs g
           part[(wm * 128 + m * 16 + grp * 4 + j) * kXt + wn * 128 + n * 16 + i16] = acc[m][n][j];
   } else {
     put_grad_tile<8, 8, 4>(L.grad_sum, L.d_out, L.d_in, e0 + wm * 128 + grp * 4, c0 + wn * 128 + i16,
-                           g.accumulate != 0, [&](int m, int n, int j) { return acc[m][n][j]; });
+                           g.accumulate != 0, e0 + kXt <= L.d_out && c0 + kXt <= L.d_in,
+                           [&](int m, int n, int j) { return acc[m][n][j]; });
   }
 }
 
