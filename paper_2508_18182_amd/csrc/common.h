@@ -146,16 +146,22 @@ __device__ __forceinline__ void direct_load_lds16(const void* src, unsigned lds_
 // The same with the address split into a wave-uniform 64-bit base (scalar registers) and a 32-bit
 // byte offset per lane: a kernel that walks along its rows bumps the base on the scalar unit and
 // keeps the lane offsets constant, so that no vector instruction is spent on addresses.
+// The base goes through a scalar copy: a load needs five wait states behind a vector instruction that wrote its scalar
+// base (v_readfirstlane, or v_readlane where the compiler reloads a spilled register), and the compiler does not count
+// them for inline assembly; the copy is interlocked by the hardware, and stands where M0 needs a wait state anyway.
 __device__ __forceinline__ void direct_load_lds16_s(unsigned lane_off, const void* base, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :: "v"(lane_off), "s"(base), "s"(lds_addr) : "m0");
+  unsigned long long b;
+  asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
+               : "=&s"(b) : "v"(lane_off), "s"(base), "s"(lds_addr) : "m0");
 }
 // Both with only the lanes of `mask` taking part: the 16 bytes of the others stay as they are in LDS.  All 64 lanes
 // have to be active at the call.
 __device__ __forceinline__ void direct_load_lds16_masked(unsigned lane_off, const void* base, unsigned lds_addr,
                                                          unsigned long long mask) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
-               :: "v"(lane_off), "s"(base), "s"(lds_addr), "s"(mask) : "m0");
+  unsigned long long b;
+  asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\ts_mov_b64 exec, %4\n\tglobal_load_lds_dwordx4 %1, %0\n\t"
+               "s_mov_b64 exec, -1"
+               : "=&s"(b) : "v"(lane_off), "s"(base), "s"(lds_addr), "s"(mask) : "m0");
 }
 __device__ __forceinline__ void direct_load_lds16_vmasked(const void* src, unsigned lds_addr, unsigned long long mask) {
   asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %0, off\n\ts_mov_b64 exec, -1"
