@@ -154,7 +154,7 @@ __device__ __forceinline__ void direct_load_lds16_s(unsigned lane_off, const voi
   asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
                : "=&s"(b) : "v"(lane_off), "s"(base), "s"(lds_addr) : "m0");
 }
-// Both with only the lanes of `mask` taking part: the 16 bytes of the others stay as they are in LDS.  All 64 lanes
+// The same with only the lanes of `mask` taking part: the 16 bytes of the others stay as they are in LDS.  All 64 lanes
 // have to be active at the call.
 __device__ __forceinline__ void direct_load_lds16_masked(unsigned lane_off, const void* base, unsigned lds_addr,
                                                          unsigned long long mask) {
@@ -162,10 +162,6 @@ __device__ __forceinline__ void direct_load_lds16_masked(unsigned lane_off, cons
   asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\ts_mov_b64 exec, %4\n\tglobal_load_lds_dwordx4 %1, %0\n\t"
                "s_mov_b64 exec, -1"
                : "=&s"(b) : "v"(lane_off), "s"(base), "s"(lds_addr), "s"(mask) : "m0");
-}
-__device__ __forceinline__ void direct_load_lds16_vmasked(const void* src, unsigned lds_addr, unsigned long long mask) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %0, off\n\ts_mov_b64 exec, -1"
-               :: "v"(src), "s"(lds_addr), "s"(mask) : "m0");
 }
 // A wave-uniform pointer that the compiler may hold in vector registers, moved to scalar registers
 // (the direct loads above take their base address there).

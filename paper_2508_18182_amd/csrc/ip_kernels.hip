@@ -52,8 +52,10 @@ __device__ __forceinline__ double ip_block_sum(double v, double* lds4) {
 //   load instruction moves 1 KiB: two token rows of delta (2 x 512 B) or four of a (4 x 256 B); the 1 KiB blocks are
 //   1056 bytes apart and the rows are dealt to them so that the eight rows that 32 lanes of a transpose read touch
 //   start in eight different groups of banks.  LDS reads and loads go out one by one behind the MFMAs, one barrier
-//   per chunk.  Columns past the edge of the layer are never loaded: their lanes are switched off and the LDS is
-//   cleared beforehand.  RAGGED (T not a multiple of 32): token rows past T come from a line of zeros.
+//   per chunk.  Columns of a past the edge of the layer re-read the last valid 16-byte piece and are left out of every
+//   sum.  Columns of delta past the edge are never loaded: their lanes are switched off and the LDS is cleared
+//   beforehand; check_rows() takes care of what an infinite a makes of those zeros.  RAGGED (T not a multiple of 32):
+//   token rows past T come from a line of zeros.
 // What bounds it: the LDS (96 transpose reads of 512 B and 24 KiB of direct loads per chunk of 512 MFMA cycles) and the
 // chip's power.  48 GPT-2-small linears, B 32, T 512 (2.78 TFLOP): 2.82 ms for statistics, 2.95 ms for the inner
 // products with norms (eight waves of 64 x 64 with 32x32x16 MFMAs: 2.85 and 3.00 ms); without loads 2.4 ms, with loads
@@ -134,27 +136,25 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
   const unsigned lds_base = lds_address(lds);     // LDS byte addresses are handled as integers
 
   // ---- second register set.  Accumulator element j of a 16x16 block: row grp * 4 + j, column i16.  MODE 0: this
-  // lane's entries of the G tile (zero past the edge); MODE 1: running sum of the sample tiles.
+  // lane's entries of the G tile (past the edge: the last ones, which meet nothing); MODE 1: running sum of the sample tiles.
+  const int rows_in = L.d_out - e0 - wm * 128;    // rows of this wave's part that the layer has
   float gt[kIpFM][kIpFN][4];
   if constexpr (MODE != 2)
 #pragma unroll
-  for (int m = 0; m < kIpFM; ++m)
+  for (int m = 0; m < kIpFM; ++m) {
+    const bool in = m * 16 + grp * 4 < rows_in;   // (widths are multiples of 8: the four rows are in or out together)
 #pragma unroll
-    for (int n = 0; n < kIpFN; ++n) {
-      const int tc = c0 + wn * 64 + n * 16 + i16;
+    for (int j = 0; j < 4; ++j) {
+      const int tr = e0 + wm * 128 + m * 16 + grp * 4 + j;
+      const float* const row = MODE == 0 ? L.grad_sum + (size_t)(in ? tr : 0) * L.d_in : nullptr;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int tr = e0 + wm * 128 + m * 16 + grp * 4 + j;
-        if (MODE == 0) {
-          const bool ok = tr < L.d_out && tc < L.d_in;
-          const float v = L.grad_sum[ok ? (size_t)tr * L.d_in + tc : 0];
-          gt[m][n][j] = ok ? v : 0.f;
-        } else {
-          gt[m][n][j] = 0.f;
-        }
+      for (int n = 0; n < kIpFN; ++n) {
+        const float v = MODE == 0 ? row[std::min(c0 + wn * 64 + n * 16 + i16, L.d_in - 1)] : 0.f;
+        gt[m][n][j] = in ? v : 0.f;
       }
     }
-  if (e0 + kIpE > L.d_out || c0 + kIpC > L.d_in) {   // tile on the edge: the columns past it stay zero throughout
+  }
+  if (e0 + kIpE > L.d_out) {                      // the columns of delta past the edge stay zero throughout
     for (int o = threadIdx.x * 16; o < kIpLds; o += 64 * kIpWaves * 16)
       *reinterpret_cast<ip_u32x4*>(lds + o) = ip_u32x4{0, 0, 0, 0};
     __syncthreads();
@@ -165,11 +165,11 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
   // holds rows r, r + 4, r + 16, r + 20 (16 lanes each) with r = wave + 8 * i.  Address = scalar base (first row of
   // the chunk + the rows of i) + a byte offset per lane (the host keeps row strides below 2^25).
   const int row_e = wave + 16 * (lane >> 5), row_c = wave + 4 * (grp & 1) + 16 * (grp >> 1);
-  const int col_e = e0 + (lane & 31) * 8, col_c = c0 + i16 * 8;
+  const int col_e = e0 + (lane & 31) * 8, col_c = std::min(c0 + i16 * 8, L.d_in - 8);
   const unsigned off_e = unsigned(row_e * L.delta_stride + col_e) * 2u;
   const unsigned off_c = unsigned(row_c * L.a_stride + col_c) * 2u;
+  const unsigned long long all = __builtin_amdgcn_ballot_w64(lane < 64);   // (kept in scalar registers)
   const unsigned long long ok_e = __builtin_amdgcn_ballot_w64(col_e < L.d_out);
-  const unsigned long long ok_c = __builtin_amdgcn_ballot_w64(col_c < L.d_in);
   const long long first = (long long)(tile.w & 0xffff) * g.T;
   const unsigned short* pe = uniform_ptr(reinterpret_cast<const unsigned short*>(L.delta) + first * L.delta_stride);
   const unsigned short* pc = uniform_ptr(reinterpret_cast<const unsigned short*>(L.a) + first * L.a_stride);
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
     if (i < 4)
       direct_load_lds16_masked(off_e, pe + kRowsE[i] * L.delta_stride, ld_base + st + i * 4 * kIpBlk, ok_e & on);
     else
-      direct_load_lds16_masked(off_c, pc + (i - 4) * 8 * L.a_stride, ld_base + st + kIpOpE + (i - 4) * 4 * kIpBlk, ok_c & on);
+      direct_load_lds16_masked(off_c, pc + (i - 4) * 8 * L.a_stride, ld_base + st + kIpOpE + (i - 4) * 4 * kIpBlk, all & on);
   };
   auto next_chunk = [&]() {
     int step = kIpK;
@@ -202,8 +202,8 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
       const unsigned char* p = e ? reinterpret_cast<const unsigned char*>(pe + extra * L.delta_stride) + off_e
                                  : reinterpret_cast<const unsigned char*>(pc + extra * L.a_stride) + off_c;
       const bool row_ok = (e ? row_e : row_c) + extra < ld_left;
-      direct_load_lds16_vmasked(row_ok ? p : z, ld_base + st + (e ? i * 4 * kIpBlk : kIpOpE + (i - 4) * 4 * kIpBlk),
-                                e ? ok_e : ok_c);
+      const bool in = row_ok && (!e || col_e < L.d_out);
+      direct_load_lds16(in ? p : z, ld_base + st + (e ? i * 4 * kIpBlk : kIpOpE + (i - 4) * 4 * kIpBlk));
     }
   };
 
@@ -235,21 +235,66 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
       for (int j = 0; j < 4; ++j) acc[m][n][j] = 0.f;
   mfma_fence(acc);
 
-  float dot[4] = {0.f, 0.f, 0.f, 0.f}, sq[4] = {0.f, 0.f, 0.f, 0.f};
-  auto take_block = [&](int m, int n) {           // one block of a finished sample tile
+  // Sums of a finished sample tile, by block column n: what a lane holds there lies in one column of the layer, so that
+  // columns past the edge are left out once per sample (put_sample).
+  float dot[kIpFN] = {0.f, 0.f, 0.f, 0.f}, sq[kIpFN] = {0.f, 0.f, 0.f, 0.f};
+  const int cols_in = L.d_in - c0 - wn * 64 - i16;
+  auto take_block = [&](int m, int n) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const float v = mfma_acc(acc[m][n], j);
-      if constexpr (MODE == 0) dot[j] = fmaf(v, gt[m][n][j], dot[j]);
+      if constexpr (MODE == 0) dot[n] = fmaf(v, gt[m][n][j], dot[n]);
       else if constexpr (MODE == 1) asm volatile("v_add_f32 %0, %0, %1" : "+v"(gt[m][n][j]) : "v"(v));   // (in place: no register to spare)
-      if (SQ) sq[j] = fmaf(v, v, sq[j]);
+      if (SQ) sq[n] = fmaf(v, v, sq[n]);
     }
   };
-  float* dst = g.out + ((size_t(xcd) * g.slots + slot) * g.group * kIpWaves + wave) * 2;
+  // (Before the first sample ends there is no finished tile: the cleared accumulators, which give NaN on an infinite
+  // entry of G, are taken and not stored.)
+  float* const dst0 = g.out + ((size_t(xcd) * g.slots + slot) * g.group * kIpWaves + wave) * 2;
+  float* dst = dst0 - 2 * kIpWaves;
+  // Rows past the edge are sums of zeros times a: zero, or NaN where a column of a has an infinite entry or a NaN.  The
+  // last eight rows of the wave's part, past the edge if any are, tell which.  In the second case the finished tile is
+  // summed here row by row, before the fresh MFMAs overwrite it, and put_sample takes these sums.
+  bool again = false;
+  float dot_again = 0.f, sq_again = 0.f;
+  auto check_rows = [&]() {
+    again = false;
+    if (rows_in >= kIpFM * 16) return;
+    asm volatile("s_nop 15\n\ts_nop 15");         // (behind the last MFMA)
+    bool bad = false;
+#pragma unroll
+    for (int n = 0; n < kIpFN; ++n) bad = bad || !(mfma_acc(acc[kIpFM - 1][n], 3) == 0.f);
+    again = __builtin_amdgcn_ballot_w64(bad) >> 32 != 0;
+    if (!again) return;
+    float d[kIpFN] = {0.f, 0.f, 0.f, 0.f}, q[kIpFN] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int m = 0; m < kIpFM; ++m)
+      if (m * 16 + grp * 4 < rows_in)
+#pragma unroll
+        for (int n = 0; n < kIpFN; ++n)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float v = mfma_acc(acc[m][n], j);
+            if (MODE == 0) d[n] = fmaf(v, gt[m][n][j], d[n]);
+            if (SQ) q[n] = fmaf(v, v, q[n]);
+          }
+    dot_again = sq_again = 0.f;
+#pragma unroll
+    for (int n = 0; n < kIpFN; ++n)
+      if (n * 16 < cols_in) {
+        dot_again += d[n];
+        sq_again += q[n];
+      }
+  };
   auto put_sample = [&]() {
-    const float d = MODE == 0 ? ip_wave_sum_f32((dot[0] + dot[1]) + (dot[2] + dot[3])) : 0.f;
-    const float s = SQ ? ip_wave_sum_f32((sq[0] + sq[1]) + (sq[2] + sq[3])) : 0.f;
-    if (lane == 0) {
+#pragma unroll
+    for (int n = 0; n < kIpFN; ++n) {
+      if (MODE == 0) dot[n] = n * 16 < cols_in ? dot[n] : 0.f;
+      if (SQ) sq[n] = n * 16 < cols_in ? sq[n] : 0.f;
+    }
+    const float d = MODE == 0 ? ip_wave_sum_f32(again ? dot_again : (dot[0] + dot[1]) + (dot[2] + dot[3])) : 0.f;
+    const float s = SQ ? ip_wave_sum_f32(again ? sq_again : (sq[0] + sq[1]) + (sq[2] + sq[3])) : 0.f;
+    if (lane == 0 && dst >= dst0) {
       if (MODE == 0) {
         dst[0] = d;
         dst[1] = s;
@@ -259,7 +304,7 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
     }
     dst += 2 * kIpWaves;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) dot[j] = sq[j] = 0.f;
+    for (int n = 0; n < kIpFN; ++n) dot[n] = sq[n] = 0.f;
   };
 
   // Chunk c's fragments are read during the MFMAs of chunk c-1, so that the stage of chunk c is free when its MFMAs
@@ -294,6 +339,9 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
       if (i % 4 == 3 && i / 4 < kIpLd) issue_load(i / 4, st, on);
       __builtin_amdgcn_sched_barrier(0);
     }
+    if (fresh)                                    // (or the compiler moves sums to where they are stored, 128 values with them)
+#pragma unroll
+      for (int n = 0; n < kIpFN; ++n) asm volatile("" : "+v"(dot[n]), "+v"(sq[n]));
     st = stn;
   };
 
@@ -343,13 +391,14 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
   // otherwise copy them from one set of registers to another in every chunk.
   for (;;) {
     chunk(fresh, f0, f1);
-    if (c > 1) put_sample();
+    put_sample();
     for (int p = 0; p < pairs; ++p) {
       chunk(rest, f1, f0);
       chunk(rest, f0, f1);
     }
     if (!ODD) chunk(rest, f1, f0);
     if (c >= nk) break;
+    check_rows();
     if (ODD) {
       chunk(fresh, f1, f0);
       put_sample();
@@ -358,10 +407,12 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
         chunk(rest, f1, f0);
       }
       if (c >= nk) break;
+      check_rows();
     }
   }
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
   mfma_fence(acc);
+  check_rows();
 #pragma unroll
   for (int m = 0; m < kIpFM; ++m)
 #pragma unroll

@@ -74,6 +74,7 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
+  const bool edge = e0 + kEdge > L.d_out || c0 + kEdge > L.d_in;
   const bool fast = L.fast != 0;                  // 16-byte aligned rows, widths that are multiples of 8
 
   // ---- staging: thread's piece q of operand op is row row[q] of the chunk, columns col .. col + 3
@@ -160,6 +161,18 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
     if (MODE == 2) {
       ++k;                                        // (one sample)
     } else if (last) {
+      // on a tile that reaches past the layer, an infinite input times a column of zeros is NaN: those entries are left out
+      if (edge) {
+        int rows = L.d_out - e0 - out_r(0, 0), cols = L.d_in - c0 - out_c;
+        asm volatile("" : "+v"(rows), "+v"(cols));  // (or the comparisons would be kept in registers across the loop)
+#pragma unroll
+        for (int m = 0; m < W; ++m)
+#pragma unroll
+          for (int n = 0; n < W; ++n)
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+              if (W * ((j >> 2) * 8 + (j & 3)) + m >= rows || n >= cols) acc[m][n][j] = 0.f;
+      }
       double dot = 0.0, sq = 0.0;
 #pragma unroll
       for (int m = 0; m < W; ++m)
