@@ -218,16 +218,18 @@ __device__ __forceinline__ void put_grad_tile(float* G, int d_out, int d_in, int
         }
       continue;
     }
+    // (widths are multiples of 8: the four rows of a lane's part of a block are in or out together)
 #pragma unroll
-    for (int m = 0; m < MB; ++m)
+    for (int n = 0; n < N; ++n)
+      if (c + n * 16 < d_in)
 #pragma unroll
-      for (int n = 0; n < N; ++n)
+        for (int m = 0; m < MB; ++m)
+          if (r + (m0 + m) * 16 < d_out)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int rr = r + (m0 + m) * 16 + j, cc = c + n * 16;
-          const float v = value(m0 + m, n, j);
-          if (rr < d_out && cc < d_in) G[(size_t)rr * d_in + cc] = accumulate ? old[m][n][j] + v : v;
-        }
+            for (int j = 0; j < 4; ++j) {
+              const float v = value(m0 + m, n, j);
+              G[(size_t)(r + (m0 + m) * 16 + j) * d_in + c + n * 16] = accumulate ? old[m][n][j] + v : v;
+            }
   }
 }
 
