@@ -290,7 +290,8 @@ struct adloco_ctx {
   int vec_blocks = 0, vec_blocks2 = 0, emb_blocks = 0;
   // inner products (Section 3.3.2)
   adloco::Scratch ip_tab;      // int4 tile table of the inner-product form of the tile GEMM
-  adloco::Scratch ip_tile_out; // float [tiles][ip_group][4 waves][2]
+  adloco::Scratch ip_tile_out; // float [tiles][ip_group][waves][2]
+  bool ip_short = false;       // the tile kernel for short sequences
   adloco::Scratch ip_dot, ip_sq;   // float [n_layers][B] of the blocks outside the tile table
   adloco::Scratch ip_flags;    // unsigned char [n_layers]: 1 = block is in the tile table
   int ip_slots = 0, ip_group = 1, ip_B = -1, ip_T = -1;
@@ -420,7 +421,10 @@ TileGeom ip_tile_geom();
 // one another in this order.
 std::vector<int> tiles_by_layer(const std::vector<int4>& tiles, const std::vector<char>& use, int& n_listed);
 hipError_t launch_ip_tiles(const LayerDev* layers, const void* tiles, int slots, int T, int group,
-                           int dtype, bool want_sq, float* ip_out, hipStream_t st);
+                           int dtype, bool want_sq, bool short_form, float* ip_out, hipStream_t st);
+// Which of the two 16-bit tile kernels: the one for short sequences (short_form), and the wave sums per tile and sample.
+bool short_sequences(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, int T, bool inner_products);
+int tile_waves(bool short_form);
 // ||g_i||^2 of aligned 16-bit blocks -> one partial sum per (layer, sample).
 hipError_t launch_square_tiles(const LayerDev* layers, const PlainTiles& p, int B, int T, int dtype, float* partials,
                                hipStream_t st);
@@ -429,8 +433,8 @@ int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char
                      std::vector<int4>& out, std::vector<int>& part, std::vector<int4>& split, int& n_pieces);
 hipError_t launch_stats_tiles(const LayerDev* layers, const void* tiles, const int* part, int slots,
                               const void* split, int n_split, float* partial_tiles, int B, int T,
-                              int dtype, int accumulate, float* tile_out, const int* lay, const int* ptr,
-                              const int* idx, int n_listed, float* partials, int n_pairs,
+                              int dtype, int accumulate, bool short_form, float* tile_out, const int* lay,
+                              const int* ptr, const int* idx, int n_listed, float* partials, int n_pairs,
                               hipStream_t st);
 // Resident workgroups per XCD of the plain tile kernel: two (128-wide tiles) or four per compute unit.
 constexpr int plain_tile_room(int W) { return kNumCu / kNumXcd * (W == 2 ? 2 : 4); }
@@ -442,7 +446,7 @@ hipError_t launch_plain_tiles(const LayerDev* layers, const PlainTiles& p, int m
 hipError_t launch_ip_vector_table(const LayerDev* layers, const AuxDesc* vec_tab, int n_vec,
                                   const AuxDesc* emb_tab, int n_emb, int B, int T, int dtype,
                                   const float* vec, float* dot, hipStream_t st);
-hipError_t launch_ip_finalize(const void* tiles, const float* tile_out, long long n_tiles, int group,
+hipError_t launch_ip_finalize(const void* tiles, const float* tile_out, long long n_tiles, int group, int waves,
                               const float* dot, const float* sq, const unsigned char* in_tiles,
                               int n_layers, int B, float* per_sample_ip, float* per_sample_sq,
                               double* sample_f64, adloco_ip_acc* acc, int accumulate, hipStream_t st);

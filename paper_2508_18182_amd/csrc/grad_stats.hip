@@ -564,6 +564,13 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
     rc = build_plain_tiles(ctx, ctx->sq_tiles, use, B, T, 0, is_16bit(dtype), st);
     if (rc) return rc;
   }
+  bool short_form = false;
+  if (tile_form) {
+    const std::vector<LayerDev>& tab = ctx->layer_tab_host;
+    std::vector<char> use(n_layers, 0);
+    for (int l = 0; l < n_layers; ++l) use[l] = tab[l].kind == ADLOCO_KIND_LINEAR;
+    short_form = short_sequences(tab, use, B, T, false);
+  }
   if (tile_form && ctx->ts_B != B) {
     ++ctx->table_builds;
     const std::vector<LayerDev>& tab = ctx->layer_tab_host;
@@ -584,7 +591,7 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
     if (rc) return rc;
     rc = ensure_scratch(ctx, ctx->ts_ptiles, std::max<size_t>(n_pieces, 1) * 256 * 128 * sizeof(float));
     if (rc) return rc;
-    rc = ensure_scratch(ctx, ctx->ts_out, tiles.size() * size_t(B) * 8 * sizeof(float));
+    rc = ensure_scratch(ctx, ctx->ts_out, tiles.size() * size_t(B) * 2 * tile_waves(true) * sizeof(float));
     if (rc) return rc;
     rc = ensure_scratch(ctx, ctx->ts_csr, csr.size() * sizeof(int));
     if (rc) return rc;
@@ -658,7 +665,7 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
     const int nl = ctx->ts_n_listed;
     e = launch_stats_tiles(g.layers, ctx->ts_tab.ptr, static_cast<const int*>(ctx->ts_part_idx.ptr),
                            ctx->ts_slots, ctx->ts_split.ptr, ctx->ts_n_split,
-                           static_cast<float*>(ctx->ts_ptiles.ptr), B, T, dtype, accumulate,
+                           static_cast<float*>(ctx->ts_ptiles.ptr), B, T, dtype, accumulate, short_form,
                            static_cast<float*>(ctx->ts_out.ptr), csr, csr + nl, csr + nl + nl + 1, nl,
                            g.partials, int(n_pairs), st);
     prof_end(ctx, kProfTileStats, ev, st);
@@ -856,12 +863,13 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
     std::vector<int4> tiles;
     int group = 1;
     const int slots = any ? make_ip_tiles(tab, use, B, T, ip_tile_geom(), ctx->ip_group_tuning, tiles, group) : 0;
+    const bool short_form = short_sequences(tab, use, B, T, true);
     if ((long long)slots * kNumXcd > 0x7fffffffLL)
       return fail(ctx, ADLOCO_EUNSUPPORTED, "inner_products: too many tiles for one launch");
     rc = ensure_scratch(ctx, ctx->ip_tab, std::max<size_t>(tiles.size(), 1) * sizeof(int4));
     if (rc) return rc;
     rc = ensure_scratch(ctx, ctx->ip_tile_out,
-                        std::max<size_t>(tiles.size(), 1) * group * 8 * sizeof(float));
+                        std::max<size_t>(tiles.size(), 1) * group * 2 * tile_waves(short_form) * sizeof(float));
     if (rc) return rc;
     rc = ensure_scratch(ctx, ctx->ip_flags, size_t(n_layers));
     if (rc) return rc;
@@ -885,6 +893,7 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
     }
     ctx->ip_slots = slots;
     ctx->ip_group = group;
+    ctx->ip_short = short_form;
     ctx->ip_B = B;
     ctx->ip_T = T;
   }
@@ -899,7 +908,7 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
   float* sq = static_cast<float*>(ctx->ip_sq.ptr);
   hipEvent_t ev = prof_begin(ctx, st);
   hipError_t e = launch_ip_tiles(dl, ctx->ip_tab.ptr, ctx->ip_slots, T, ctx->ip_group, dtype,
-                                 per_sample_sqnorm != nullptr,
+                                 per_sample_sqnorm != nullptr, ctx->ip_short,
                                  static_cast<float*>(ctx->ip_tile_out.ptr), st);
   if (e == hipSuccess)
     e = launch_plain_tiles(dl, ctx->ip_plain, 0, B, T, dtype, 0, dot, sq, 1, st);
@@ -917,7 +926,7 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
                                B, T, dtype, static_cast<const float*>(ctx->aux_vec.ptr), dot, st);
   if (e == hipSuccess)
     e = launch_ip_finalize(ctx->ip_tab.ptr, static_cast<const float*>(ctx->ip_tile_out.ptr),
-                           (long long)ctx->ip_slots * kNumXcd, ctx->ip_group, dot, sq,
+                           (long long)ctx->ip_slots * kNumXcd, ctx->ip_group, tile_waves(ctx->ip_short), dot, sq,
                            static_cast<const unsigned char*>(ctx->ip_flags.ptr), n_layers, B,
                            per_sample_ip, per_sample_sqnorm, static_cast<double*>(ctx->sample_f64.ptr),
                            acc, (flags & ADLOCO_ACCUMULATE) ? 1 : 0, st);

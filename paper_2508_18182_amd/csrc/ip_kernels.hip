@@ -82,7 +82,7 @@ constexpr int kIpLds = kIpStages * kIpStage;      // 148.5 KiB
 struct IpTileArgs {
   const LayerDev* layers;
   const int4* tiles;      // [8][slots]: (layer, e0, c0, first sample | samples << 16); layer < 0: none
-  float* out;             // [8 * slots][group][kIpWaves][2]: <tile_i, G tile>, sum of squares of tile_i
+  float* out;             // [8 * slots][group][waves][2]: <tile_i, G tile>, sum of squares of tile_i
                           // (statistics form: sum of squares, unused)
   int slots, T, group;
   // statistics form only
@@ -438,6 +438,276 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// The same tiles for short sequences (whole chunks): eight waves as 4 x 2, two per SIMD, wave tile 64 x 64, 32x32x16
+// MFMA.  What a sample costs beyond its MFMAs -- the work on its finished tile, and the start and end of an entry -- runs
+// next to the MFMAs of the SIMD's other wave here, while the four waves above have nothing to hide it behind; their
+// cheaper chunks outweigh that on longer sequences (short_sequences()).
+//   Staging: four stages of 32 token rows, loads two chunks ahead.  A load instruction moves token rows j, j + 16 of delta
+//   (2 x 512 B) or rows j, j + 8, j + 16, j + 24 of a (4 x 256 B); the 1 KiB blocks are 1088 bytes apart so that the four
+//   consecutive rows of a transpose read fall into different banks.  Columns past the edge re-read the last valid piece.
+// ---------------------------------------------------------------------------------------
+constexpr int kStBlk = 1024 + 64;                 // one load instruction + 64 B skew
+constexpr int kStOpE = 16 * kStBlk;               // delta side of a stage
+constexpr int kStOpC = 8 * kStBlk;                // a side of a stage
+constexpr int kStStage = kStOpE + kStOpC;         // 25.5 KiB
+constexpr int kStWM = 4, kStWN = 2;               // waves along d_out and d_in
+constexpr int kStWaves = kStWM * kStWN;
+constexpr int kStFM = kIpE / (32 * kStWM);        // 32x32 MFMA blocks per wave along d_out
+constexpr int kStFN = kIpC / (32 * kStWN);        // ... along d_in
+constexpr int kStLdE = 16 / kStWaves, kStLdC = 8 / kStWaves, kStLd = kStLdE + kStLdC;   // loads per wave
+constexpr int kStStages = 4;
+constexpr int kStLds = kStStages * kStStage;      // 102 KiB
+
+__device__ __forceinline__ int st_row_off_e(int row) { return (row & 15) * kStBlk + (row >> 4) * 512; }
+__device__ __forceinline__ int st_row_off_c(int row) { return (row & 7) * kStBlk + (row >> 3) * 256; }
+
+template <int MODE, bool SQ, bool F16>
+__global__ __launch_bounds__(64 * kStWaves, 1) void short_tile_kernel(IpTileArgs g) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const int xcd = blockIdx.x % kNumXcd, slot = blockIdx.x / kNumXcd;
+  const int4 tile = g.tiles[xcd * g.slots + slot];
+  if (tile.x < 0) return;
+  const LayerDev L = g.layers[tile.x];
+  const int e0 = tile.y, c0 = tile.z;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / kStWN, wn = wave % kStWN;  // kStWM x kStWN waves
+  const int nk_sample = g.T / kIpK;               // chunks per sample
+  const long long ck0 = (long long)(tile.w & 0xffff) * nk_sample;
+  const int nk = (tile.w >> 16) * nk_sample;       // chunks of this entry: the host keeps it below 2^31
+
+  // ---- second register set.  Accumulator element j of a 32x32 block: row
+  // (j/4)*8 + (lane/32)*4 + j%4, column lane%32.  MODE 0: this lane's entries of the G tile
+  // (zero past the edge); MODE 1: running sum of the sample tiles.
+  float gt[kStFM][kStFN][16];
+#pragma unroll
+  for (int m = 0; m < kStFM; ++m)
+#pragma unroll
+    for (int n = 0; n < kStFN; ++n) {
+      const int tc = c0 + wn * (32 * kStFN) + n * 32 + (lane & 31);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int tr = e0 + wm * (32 * kStFM) + m * 32 + (j >> 2) * 8 + (lane >> 5) * 4 + (j & 3);
+        gt[m][n][j] = MODE == 0 ? L.grad_sum[(size_t)std::min(tr, L.d_out - 1) * L.d_in + std::min(tc, L.d_in - 1)] : 0.f;
+      }
+    }
+  const bool edge = e0 + kIpE > L.d_out || c0 + kIpC > L.d_in;
+  auto for_past_edge = [&](auto&& f) {
+    int rows = L.d_out - e0 - wm * (32 * kStFM) - (lane >> 5) * 4, cols = L.d_in - c0 - wn * (32 * kStFN) - (lane & 31);
+    asm volatile("" : "+v"(rows), "+v"(cols));     // (or the comparisons would be kept in registers across the loop)
+#pragma unroll
+    for (int m = 0; m < kStFM; ++m)
+#pragma unroll
+      for (int n = 0; n < kStFN; ++n)
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+          if (n * 32 >= cols || m * 32 + (j >> 2) * 8 + (j & 3) >= rows) f(m, n, j);
+  };
+  if (MODE == 0 && edge) for_past_edge([&](int m, int n, int j) { gt[m][n][j] = 0.f; });
+
+  // ---- direct loads, kStLd per wave and chunk: delta instructions j = wave, wave + kStWaves, ..
+  // (rows j and j + 16, 16-byte piece lane % 32), then a instructions j = wave, .. (rows
+  // j + 8 * (lane / 16), piece lane % 16).  Columns past the edge re-read the last valid piece.
+  // Address = (first row of the chunk: wave-uniform, scalar registers) + (row within the chunk and
+  // column: a 32-bit byte offset per lane, computed once; the host keeps row strides below 2^25).
+  unsigned lane_off[kStLd];
+  int lds_off[kStLd];
+#pragma unroll
+  for (int i = 0; i < kStLd; ++i) {
+    const bool is_a = i >= kStLdE;
+    const int j = wave + kStWaves * (is_a ? i - kStLdE : i);
+    const int row = is_a ? j + 8 * (lane >> 4) : j + 16 * (lane >> 5);
+    const int piece = is_a ? (lane & 15) : (lane & 31);
+    const int d = is_a ? L.d_in : L.d_out;
+    int col = (is_a ? c0 : e0) + piece * 8;
+    col = col < d ? col : d - 8;
+    lane_off[i] = unsigned(row * (is_a ? L.a_stride : L.delta_stride) + col) * 2u;
+    lds_off[i] = (is_a ? kStOpE : 0) + j * kStBlk;
+  }
+  const unsigned short* const run_e = reinterpret_cast<const unsigned short*>(L.delta) + ck0 * kIpK * L.delta_stride;
+  const unsigned short* const run_c = reinterpret_cast<const unsigned short*>(L.a) + ck0 * kIpK * L.a_stride;
+  const unsigned lds_base = lds_address(lds);       // LDS byte addresses are handled as integers
+  // stage indices are carried along (no modulo in the loop: kStStages need not be a power of two)
+  auto issue_loads = [&](int c, int st) {
+    const unsigned stage = lds_base + unsigned(st) * kStStage;
+    const unsigned short* const pe = run_e + (long long)c * kIpK * L.delta_stride;
+    const unsigned short* const pc = run_c + (long long)c * kIpK * L.a_stride;
+#pragma unroll
+    for (int i = 0; i < kStLd; ++i)
+      direct_load_lds16_s(lane_off[i], i >= kStLdE ? pc : pe, stage + lds_off[i]);
+  };
+
+  // ---- fragments by LDS transpose reads.  Within a group of 16 lanes, lane s points at the 4
+  // columns 4*(s%4).. of token row kbase + s/4; the read hands lane i column i of the group's
+  // 16 at the four token rows.  Lane l ends up with column m0 + l%32, token rows
+  // ks*16 + (l/32)*8 + 0..7.
+  const int i16 = lane & 15;
+  const int krow = (lane >> 5) * 8 + (i16 >> 2);              // + ks*16 (+4 for the upper half)
+  const int ccol = ((lane >> 4) & 1) * 16 + (i16 & 3) * 4;    // column within a 32-wide block
+  // Every read address of a k-step is stage + (a part that depends on the lane) + (a constant of the
+  // fragment): three lane parts -- delta side; a side, rows r and r + 4, which wrap differently in
+  // its 8-row blocks -- are kept in registers, the constants ride in the offset field of the read.
+  typedef __attribute__((address_space(3))) ip_s16x4* lds_ptr;
+  const unsigned lane_e = unsigned(st_row_off_e(krow) + (wm * (32 * kStFM) + ccol) * 2);
+  const unsigned lane_c0 = unsigned(kStOpE + st_row_off_c(krow) + (wn * (32 * kStFN) + ccol) * 2);
+  const unsigned lane_c1 = unsigned(kStOpE + st_row_off_c(krow + 4) + (wn * (32 * kStFN) + ccol) * 2);
+  auto frag = [&](lds_ptr p0, lds_ptr p1) -> mfma_bf16x8 {
+    ip_s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p0);
+    ip_s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(p1);
+    ip_s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(mfma_bf16x8, v);
+  };
+  // token rows ks*16 + krow (+4) of the stage: row blocks of 16 (delta) and 8 (a) rows make ks * 512
+  // bytes on both sides; 32 columns are 64 bytes; offsets in units of the 8-byte read
+  auto read_frags = [&](int st, int ks, mfma_bf16x8 (&fa)[kStFM], mfma_bf16x8 (&fb)[kStFN]) {
+    const unsigned stage = lds_base + unsigned(st) * kStStage;
+    const lds_ptr be = (lds_ptr)(size_t)(stage + lane_e);
+    const lds_ptr bc0 = (lds_ptr)(size_t)(stage + lane_c0), bc1 = (lds_ptr)(size_t)(stage + lane_c1);
+#pragma unroll
+    for (int m = 0; m < kStFM; ++m)
+      fa[m] = frag(be + (ks * 512 + m * 64) / 8, be + (ks * 512 + m * 64 + 4 * kStBlk) / 8);
+#pragma unroll
+    for (int n = 0; n < kStFN; ++n)
+      fb[n] = frag(bc0 + (ks * 512 + n * 64) / 8, bc1 + (ks * 512 + n * 64) / 8);
+  };
+
+  mfma_f32x16 acc[kStFM][kStFN];
+#pragma unroll
+  for (int m = 0; m < kStFM; ++m)
+#pragma unroll
+    for (int n = 0; n < kStFN; ++n)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[m][n][j] = 0.f;
+
+  auto mfma4 = [&](const mfma_bf16x8 (&a)[kStFM], const mfma_bf16x8 (&b)[kStFN]) {
+#pragma unroll
+    for (int m = 0; m < kStFM; ++m)
+#pragma unroll
+      for (int n = 0; n < kStFN; ++n)
+        acc[m][n] = mfma_32x32x16<F16>(a[m], b[n], acc[m][n]);
+    // the LDS reads of the next k-step go out two at a time behind the first MFMAs
+#pragma unroll
+    for (int i = 0; i < kStFM + kStFN; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    }
+    if (kStFM * kStFN > kStFM + kStFN)
+      __builtin_amdgcn_sched_group_barrier(0x008, kStFM * kStFN - kStFM - kStFN, 0);
+  };
+
+  // prologue: chunks 0 .. kStStages-2 in flight
+#pragma unroll
+  for (int s = 0; s < kStStages - 1; ++s)
+    if (s < nk) issue_loads(s, s);
+  // The G registers are needed only at the end of the first sample, but a wait placed there by the
+  // compiler would drain the load pipeline at every sample; pin them down here, once.
+  if (MODE == 0) {
+#pragma unroll
+    for (int m = 0; m < kStFM; ++m)
+#pragma unroll
+      for (int n = 0; n < kStFN; ++n)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) asm volatile("" : "+v"(gt[m][n][j]));
+  }
+  if (nk >= kStStages - 1) ip_wait_vmcnt<kStLd * (kStStages - 2)>(); else ip_wait_vmcnt<0>();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+
+  int left = nk_sample, sample_out = 0;
+  float* dst = g.out + ((size_t(xcd) * g.slots + slot) * g.group * kStWaves + wave) * 2;
+  mfma_bf16x8 fa[2][kStFM], fb[2][kStFN];
+  read_frags(0, 0, fa[0], fb[0]);
+  int st_cur = 0, st_load = kStStages - 1;        // stage of chunk c; stage that chunk c-1 frees
+  for (int c = 0; c < nk; ++c) {
+    const int st_next = st_cur + 1 == kStStages ? 0 : st_cur + 1;
+    read_frags(st_cur, 1, fa[1], fb[1]);
+    mfma4(fa[0], fb[0]);
+    if (c + 1 < nk) {
+      // chunk c+1 has landed for me (the chunks behind it may still be in flight), then for
+      // everybody; every wave is done with chunk c-1, whose stage takes chunk c-1+kStStages
+      if (c + kStStages - 2 < nk) ip_wait_vmcnt<kStLd * (kStStages - 3)>(); else ip_wait_vmcnt<0>();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (c + kStStages - 1 < nk) issue_loads(c + kStStages - 1, st_load);
+    }
+    read_frags(c + 1 < nk ? st_next : st_cur, 0, fa[0], fb[0]);
+    mfma4(fa[1], fb[1]);
+    st_load = st_cur;
+    st_cur = st_next;
+    if (--left == 0) {
+      // the sample's tile is complete: reduce it against the G tile, clear it
+      float dot = 0.f, sq = 0.f;
+      if (edge) {
+        // entries past the edge of the layer hold products of re-read columns, which must not enter a sum
+        for_past_edge([&](int m, int n, int j) { acc[m][n][j] = 0.f; });
+      }
+#pragma unroll
+      for (int m = 0; m < kStFM; ++m)
+#pragma unroll
+        for (int n = 0; n < kStFN; ++n)
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const float v = acc[m][n][j];
+            if (MODE == 0) dot = fmaf(v, gt[m][n][j], dot);
+            else gt[m][n][j] += v;
+            if (SQ) sq = fmaf(v, v, sq);
+            acc[m][n][j] = 0.f;
+          }
+      if (MODE == 0) dot = ip_wave_sum_f32(dot);
+      if (SQ) sq = ip_wave_sum_f32(sq);
+      if (lane == 0) {
+        if (MODE == 0) {
+          dst[size_t(sample_out) * (2 * kStWaves)] = dot;
+          dst[size_t(sample_out) * (2 * kStWaves) + 1] = sq;
+        } else {
+          dst[size_t(sample_out) * (2 * kStWaves)] = sq;
+        }
+      }
+      ++sample_out;
+      left = nk_sample;
+    }
+  }
+  if constexpr (MODE == 1) {
+    const int part = g.part[xcd * g.slots + slot];
+    float* const pt = part >= 0 ? g.partials + (size_t)part * (kIpE * kIpC) : nullptr;
+#pragma unroll
+    for (int m = 0; m < kStFM; ++m)
+#pragma unroll
+      for (int n = 0; n < kStFN; ++n) {
+        const int tc = wn * (32 * kStFN) + n * 32 + (lane & 31), tr0 = wm * (32 * kStFM) + m * 32 + (lane >> 5) * 4;
+        if (pt) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) pt[(tr0 + (j >> 2) * 8 + (j & 3)) * kIpC + tc] = gt[m][n][j];
+          continue;
+        }
+        // (the old entries are requested together, at addresses clamped to the layer; widths are multiples of 8: four
+        // rows are in or out together)
+        float was[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) was[j] = 0.f;
+        if (g.accumulate) {
+#pragma unroll
+          for (int j = 0; j < 16; ++j) {
+            const int r = std::min(e0 + tr0 + (j >> 2) * 8 + (j & 3), L.d_out - 1), c = std::min(c0 + tc, L.d_in - 1);
+            was[j] = L.grad_sum[(size_t)r * L.d_in + c];
+          }
+        }
+        if (c0 + tc < L.d_in)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (e0 + tr0 + q * 8 < L.d_out)
+#pragma unroll
+              for (int j = q * 4; j < q * 4 + 4; ++j) {
+                float* const d = L.grad_sum + (size_t)(e0 + tr0 + q * 8 + (j & 3)) * L.d_in + c0 + tc;
+                *d = g.accumulate ? was[j] + gt[m][n][j] : gt[m][n][j];
+              }
+      }
+  }
+}
+
 // Statistics form: sums the partial tiles of the entries that were split along the samples, in
 // piece order (fixed order: repeatable), into grad_sum.  One workgroup per 4 rows of a split tile,
 // one thread per column, rows unrolled so that their loads are in flight together;
@@ -470,7 +740,7 @@ __global__ __launch_bounds__(kIpC) void stats_tile_reduce_kernel(const LayerDev*
 // squares -> slot 0 of the layer's partial sums (the other slots are cleared), from where the
 // common reduction picks it up.  One workgroup per (listed layer, sample); the entries of layer
 // `lay[q]` are idx[ptr[q] .. ptr[q+1]).
-__global__ __launch_bounds__(64) void stats_tile_finalize_kernel(const int4* tiles, const float* out, int group,
+__global__ __launch_bounds__(64) void stats_tile_finalize_kernel(const int4* tiles, const float* out, int group, int waves,
                                                                 const int* lay, const int* ptr, const int* idx,
                                                                 int B, float* partials, int n_pairs) {
   const int q = blockIdx.x / B, i = blockIdx.x % B;
@@ -481,9 +751,10 @@ __global__ __launch_bounds__(64) void stats_tile_finalize_kernel(const int4* til
     const int4 t = tiles[e];
     const int s0 = t.w & 0xffff, cnt = t.w >> 16;
     if (i >= s0 && i < s0 + cnt) {
-      const float* o = out + ((size_t)e * group + (i - s0)) * (2 * kIpWaves);
+      const float* o = out + ((size_t)e * group + (i - s0)) * (2 * waves);
+      for (int w = 0; w < waves; w += 4)
 #pragma unroll
-      for (int w = 0; w < kIpWaves; ++w) s += double(o[2 * w]);
+        for (int v = 0; v < 4; ++v) s += double(o[2 * (w + v)]);
     }
   }
   s = ip_wave_sum(s);
@@ -560,37 +831,57 @@ template <int MODE, bool SQ> static auto ip_tile_variant(int dtype, int T) {
   return dtype == ADLOCO_F16 ? ip_tile_variant_t<MODE, SQ, true>(T) : ip_tile_variant_t<MODE, SQ, false>(T);
 }
 
-hipError_t launch_ip_tiles(const LayerDev* layers, const void* tiles, int slots, int T, int group,
-                           int dtype, bool want_sq, float* ip_out, hipStream_t st) {
-  if (slots <= 0) return hipSuccess;
-  auto kern = want_sq ? ip_tile_variant<0, true>(dtype, T) : ip_tile_variant<0, false>(dtype, T);
-  {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kIpLds);
-    if (e != hipSuccess) return e;
-  }
-  IpTileArgs a{layers, static_cast<const int4*>(tiles), ip_out, slots, T, group, nullptr, nullptr, 0};
-  hipLaunchKernelGGL(kern, dim3(unsigned(slots) * kNumXcd), dim3(64 * kIpWaves), kIpLds, st, a);
+template <typename K> static hipError_t launch_tiles(K kern, int waves, int lds, const IpTileArgs& a, hipStream_t st) {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(unsigned(a.slots) * kNumXcd), dim3(64 * waves), lds, st, a);
   return hipGetLastError();
+}
+
+// True where the eight-wave kernel takes less time: T, and chunks of 32 token rows per compute unit (a small call does
+// not reach the power limit, under which the four waves gain).  Measured, eight against four waves, gpt blocks of width
+// d, us: statistics {d 1024, 6 blocks, B 5}: T 64 165 / 182, T 128 218 / 217, T 256 307 / 294; {768, 1 block, B 16}: T 128
+// 57.8 / 62.4, T 256 83 / 87, T 512 140 / 138; {1024, 6, 16}: T 96 391 / 402, T 128 472 / 455; {1024, 1, 32}: T 160 182 /
+// 189, T 256 259 / 258.  Inner products {1024, 6, 5}: T 64 171 / 202, T 128 214 / 242, T 256 307 / 313, T 512 514 / 480;
+// {1024, 6, 16}: T 256 772 / 760; {1024, 1, 2}: T 512 72 / 78; {1024, 1, 5}: T 512 127 / 128, T 1024 216 / 203.
+bool short_sequences(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, int T, bool inner_products) {
+  if (T % kIpK != 0) return false;                // (whole chunks only)
+  double tiles = 0.0;
+  for (size_t l = 0; l < layers.size(); ++l)
+    if (use[l]) tiles += double((layers[l].d_out + kIpE - 1) / kIpE) * double((layers[l].d_in + kIpC - 1) / kIpC);
+  const double chunks = tiles * B * (T / kIpK) / kNumCu;
+  if (inner_products) return T <= 128 || (T <= 256 && chunks < 600.0) || (T <= 512 && chunks < 100.0);
+  return T <= 96 || (T <= 192 && chunks < 200.0) || (T <= 256 && tiles <= kNumCu);
+}
+
+int tile_waves(bool short_form) { return short_form ? kStWaves : kIpWaves; }
+
+hipError_t launch_ip_tiles(const LayerDev* layers, const void* tiles, int slots, int T, int group,
+                           int dtype, bool want_sq, bool short_form, float* ip_out, hipStream_t st) {
+  if (slots <= 0) return hipSuccess;
+  const IpTileArgs a{layers, static_cast<const int4*>(tiles), ip_out, slots, T, group, nullptr, nullptr, 0};
+  if (short_form) {
+    const bool h = dtype == ADLOCO_F16;
+    auto kern = want_sq ? (h ? short_tile_kernel<0, true, true> : short_tile_kernel<0, true, false>)
+                        : (h ? short_tile_kernel<0, false, true> : short_tile_kernel<0, false, false>);
+    return launch_tiles(kern, kStWaves, kStLds, a, st);
+  }
+  return launch_tiles(want_sq ? ip_tile_variant<0, true>(dtype, T) : ip_tile_variant<0, false>(dtype, T), kIpWaves, kIpLds, a,
+                      st);
 }
 
 hipError_t launch_square_tiles(const LayerDev* layers, const PlainTiles& p, int B, int T, int dtype, float* partials,
                                hipStream_t st) {
   if (p.slots <= 0) return hipSuccess;
-  auto kern = ip_tile_variant<2, true>(dtype, T);
-  {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kIpLds);
-    if (e != hipSuccess) return e;
-  }
   const int4* tiles = static_cast<const int4*>(p.tab.ptr);
   float* out = static_cast<float*>(p.out.ptr);
-  IpTileArgs a{layers, tiles, out, p.slots, T, p.group, nullptr, nullptr, 0};
-  hipLaunchKernelGGL(kern, dim3(unsigned(p.slots) * kNumXcd), dim3(64 * kIpWaves), kIpLds, st, a);
+  const IpTileArgs a{layers, tiles, out, p.slots, T, p.group, nullptr, nullptr, 0};
+  hipError_t e = launch_tiles(ip_tile_variant<2, true>(dtype, T), kIpWaves, kIpLds, a, st);
+  if (e != hipSuccess) return e;
   const int* csr = static_cast<const int*>(p.csr.ptr);
   const int nl = p.n_listed;
-  hipLaunchKernelGGL(stats_tile_finalize_kernel, dim3(unsigned(nl) * B), dim3(64), 0, st, tiles, out, p.group, csr,
-                     csr + nl, csr + nl + nl + 1, B, partials, 1);
+  hipLaunchKernelGGL(stats_tile_finalize_kernel, dim3(unsigned(nl) * B), dim3(64), 0, st, tiles, out, p.group,
+                     kIpWaves, csr, csr + nl, csr + nl + nl + 1, B, partials, 1);
   return hipGetLastError();
 }
 
@@ -668,23 +959,24 @@ std::vector<int> tiles_by_layer(const std::vector<int4>& tiles, const std::vecto
 
 hipError_t launch_stats_tiles(const LayerDev* layers, const void* tiles, const int* part, int slots,
                               const void* split, int n_split, float* partial_tiles, int B, int T,
-                              int dtype, int accumulate, float* tile_out, const int* lay, const int* ptr,
-                              const int* idx, int n_listed, float* partials, int n_pairs,
+                              int dtype, int accumulate, bool short_form, float* tile_out, const int* lay,
+                              const int* ptr, const int* idx, int n_listed, float* partials, int n_pairs,
                               hipStream_t st) {
   if (slots <= 0) return hipSuccess;
-  auto kern = ip_tile_variant<1, true>(dtype, T);
-  {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kIpLds);
-    if (e != hipSuccess) return e;
-  }
-  IpTileArgs a{layers, static_cast<const int4*>(tiles), tile_out, slots, T, B, part, partial_tiles, accumulate};
-  hipLaunchKernelGGL(kern, dim3(unsigned(slots) * kNumXcd), dim3(64 * kIpWaves), kIpLds, st, a);
+  const IpTileArgs a{layers, static_cast<const int4*>(tiles), tile_out, slots, T, B, part, partial_tiles, accumulate};
+  hipError_t e;
+  if (short_form)
+    e = launch_tiles(dtype == ADLOCO_F16 ? short_tile_kernel<1, true, true> : short_tile_kernel<1, true, false>, kStWaves,
+                     kStLds, a, st);
+  else
+    e = launch_tiles(ip_tile_variant<1, true>(dtype, T), kIpWaves, kIpLds, a, st);
+  if (e != hipSuccess) return e;
   if (n_split > 0)
     hipLaunchKernelGGL(stats_tile_reduce_kernel, dim3(unsigned(n_split) * (kIpE / kIpRedRows)), dim3(kIpC), 0, st,
                        layers, static_cast<const int4*>(split), partial_tiles, accumulate);
   hipLaunchKernelGGL(stats_tile_finalize_kernel, dim3(unsigned(n_listed) * B), dim3(64), 0, st,
-                     static_cast<const int4*>(tiles), tile_out, B, lay, ptr, idx, B, partials, n_pairs);
+                     static_cast<const int4*>(tiles), tile_out, B, tile_waves(short_form), lay, ptr, idx, B, partials,
+                     n_pairs);
   return hipGetLastError();
 }
 
@@ -729,9 +1021,9 @@ __global__ __launch_bounds__(kIpThreads) void embed_ip_kernel(const LayerDev* la
 
 // One workgroup per sample i: c_i = sum of its tile results + sum over the other blocks;
 // likewise the explicit ||g_i||^2.  A tile entry covers samples [w & 0xffff, + (w >> 16)) and
-// leaves, per sample and wave, a pair at tile_out[((k * group + sample - first) * kIpWaves + wave) * 2].
+// leaves, per sample and wave, a pair at tile_out[((k * group + sample - first) * waves + wave) * 2].
 __global__ __launch_bounds__(kIpThreads) void ip_finalize_samples_kernel(
-    const int4* tiles, const float* tile_out, long long n_tiles, int group, const float* dot, const float* sq,
+    const int4* tiles, const float* tile_out, long long n_tiles, int group, int waves, const float* dot, const float* sq,
     const unsigned char* in_tiles, int n_layers, int B, float* per_sample_ip, float* per_sample_sq,
     double* sample_f64) {
   __shared__ double lds4[4];
@@ -741,12 +1033,13 @@ __global__ __launch_bounds__(kIpThreads) void ip_finalize_samples_kernel(
     const int4 t = tiles[k];
     const int s0 = t.w & 0xffff, cnt = t.w >> 16;
     if (t.x >= 0 && i >= s0 && i < s0 + cnt) {
-      const float* o = tile_out + ((size_t)k * group + (i - s0)) * (2 * kIpWaves);
+      const float* o = tile_out + ((size_t)k * group + (i - s0)) * (2 * waves);
+      for (int w = 0; w < waves; w += 4)
 #pragma unroll
-      for (int w = 0; w < kIpWaves; ++w) {
-        c += double(o[2 * w]);
-        q += double(o[2 * w + 1]);
-      }
+        for (int v = 0; v < 4; ++v) {
+          c += double(o[2 * (w + v)]);
+          q += double(o[2 * (w + v) + 1]);
+        }
     }
   }
   for (int l = threadIdx.x; l < n_layers; l += kIpThreads)
@@ -817,12 +1110,12 @@ hipError_t launch_ip_vector_table(const LayerDev* layers, const AuxDesc* vec_tab
   return hipGetLastError();
 }
 
-hipError_t launch_ip_finalize(const void* tiles, const float* tile_out, long long n_tiles, int group,
+hipError_t launch_ip_finalize(const void* tiles, const float* tile_out, long long n_tiles, int group, int waves,
                               const float* dot, const float* sq, const unsigned char* in_tiles,
                               int n_layers, int B, float* per_sample_ip, float* per_sample_sq,
                               double* sample_f64, adloco_ip_acc* acc, int accumulate, hipStream_t st) {
   hipLaunchKernelGGL(ip_finalize_samples_kernel, dim3(B), dim3(kIpThreads), 0, st,
-                     static_cast<const int4*>(tiles), tile_out, n_tiles, group, dot, sq, in_tiles, n_layers, B,
+                     static_cast<const int4*>(tiles), tile_out, n_tiles, group, waves, dot, sq, in_tiles, n_layers, B,
                      per_sample_ip, per_sample_sq, sample_f64);
   hipLaunchKernelGGL(ip_finalize_batch_kernel, dim3(1), dim3(1024), 0, st, sample_f64, B, acc,
                      accumulate);

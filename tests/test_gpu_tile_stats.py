@@ -154,6 +154,34 @@ def test_tile_route_ragged_sequences(ctx, dtype, B, T, shapes):
     assert torch.equal(c, c2)
 
 
+@pytest.mark.parametrize("B,T", [(3, 32), (2, 96), (5, 256),        # the tile kernel for short sequences: one chunk, odd, even
+                                 (2, 288), (3, 320),                # statistics by the other one, odd and even
+                                 (2, 544), (2, 576)])               # inner products too
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_short_and_long_sequences(ctx, dtype, B, T):
+    import torch
+    import paper_2508_18182_amd as A
+    from gpu_util import DEV, code_of
+    layers = synth.custom_grad_stats_inputs(6450 + B + T, [(136, 264), (256, 128), (8, 520)], B, T, dtype, std_delta=0.2, rho=0.4)
+    entries = [(l["a"], l["delta"]) for l in layers]
+    want = orc.grad_stats(entries, two_pass=False)
+    ctx.set_tuning("stats_variant", 1)
+    got = _check(ctx, layers)
+    _compare(got, want)
+    for sq in (torch.full((B,), float("nan"), device=DEV), None):
+        c = torch.full((B,), float("nan"), device=DEV)
+        A.adloco_inner_products(ctx, got["layers"], B, T, code_of(dtype), c, sq, torch.zeros(4, dtype=torch.float64, device=DEV))
+        c_want = orc.inner_products(entries, G=want["G"])
+        assert np.max(np.abs(c.cpu().numpy() - c_want) / np.sqrt(want["n_sample"] * want["S2"])) < TOL_BF16
+        if sq is not None:
+            assert np.max(np.abs(sq.cpu().numpy() - want["n_sample"]) / want["n_sample"]) < TOL_BF16
+    # added to what is there: twice the sums
+    gs = [l["grad_sum"] for l in got["layers"]]
+    _check(ctx, layers, flags=A.ADLOCO_ACCUMULATE, acc=got["acc"], grad_sums=gs)
+    for g, w in zip(gs, want["G"]):
+        assert np.max(np.abs(g.cpu().numpy() - 2 * w)) < 2e-4 * float(np.sqrt(np.mean(w * w)))
+
+
 @pytest.mark.parametrize("B,T,shapes", [
     (1, 1, [(8, 8)]),                      # one token row
     (5, 77, [(136, 264)]),                 # 385 rows: one over twelve chunks
