@@ -154,14 +154,14 @@ __device__ __forceinline__ void direct_load_lds16_s(unsigned lane_off, const voi
   asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
                : "=&s"(b) : "v"(lane_off), "s"(base), "s"(lds_addr) : "m0");
 }
-// The same with only the lanes of `mask` taking part: the 16 bytes of the others stay as they are in LDS.  All 64 lanes
-// have to be active at the call.
-__device__ __forceinline__ void direct_load_lds16_masked(unsigned lane_off, const void* base, unsigned lds_addr,
-                                                         unsigned long long mask) {
+// Two such loads from one base with only the lanes of `mask` taking part: the 16 bytes of the others stay as they are in
+// LDS.  All 64 lanes have to be active at the call.
+__device__ __forceinline__ void direct_load_lds16_masked2(const void* base, unsigned off0, unsigned lds_addr0, unsigned off1,
+                                                          unsigned lds_addr1, unsigned long long mask) {
   unsigned long long b;
-  asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\ts_mov_b64 exec, %4\n\tglobal_load_lds_dwordx4 %1, %0\n\t"
-               "s_mov_b64 exec, -1"
-               : "=&s"(b) : "v"(lane_off), "s"(base), "s"(lds_addr), "s"(mask) : "m0");
+  asm volatile("s_mov_b32 m0, %4\n\ts_mov_b64 %0, %3\n\ts_mov_b64 exec, %6\n\tglobal_load_lds_dwordx4 %1, %0\n\t"
+               "s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %0\n\ts_mov_b64 exec, -1"
+               : "=&s"(b) : "v"(off0), "v"(off1), "s"(base), "s"(lds_addr0), "s"(lds_addr1), "s"(mask) : "m0");
 }
 // A wave-uniform pointer that the compiler may hold in vector registers, moved to scalar registers
 // (the direct loads above take their base address there).

@@ -162,12 +162,16 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
 
   // ---- direct loads.  Delta: block b = wave + 4 * i (i = 0..3) holds rows r and r + 16 (lanes 0-31, 32-63) with
   // r = (b & 3) | (b & 4) << 1 | (b & 8) >> 1, i.e. wave + {0, 8, 4, 12}[i].  a: block b = wave + 4 * i (i = 0, 1)
-  // holds rows r, r + 4, r + 16, r + 20 (16 lanes each) with r = wave + 8 * i.  Address = scalar base (first row of
-  // the chunk + the rows of i) + a byte offset per lane (the host keeps row strides below 2^25).
+  // holds rows r, r + 4, r + 16, r + 20 (16 lanes each) with r = wave + 8 * i.  Address = first row of the chunk (scalar
+  // registers) + a byte offset per lane, computed once (the host keeps row strides below 2^25).
+  constexpr int kRowsE[4] = {0, 8, 4, 12};
   const int row_e = wave + 16 * (lane >> 5), row_c = wave + 4 * (grp & 1) + 16 * (grp >> 1);
   const int col_e = e0 + (lane & 31) * 8, col_c = std::min(c0 + i16 * 8, L.d_in - 8);
-  const unsigned off_e = unsigned(row_e * L.delta_stride + col_e) * 2u;
-  const unsigned off_c = unsigned(row_c * L.a_stride + col_c) * 2u;
+  unsigned off_e[4], off_c[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) off_e[i] = unsigned((row_e + kRowsE[i]) * L.delta_stride + col_e) * 2u;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) off_c[i] = unsigned((row_c + 8 * i) * L.a_stride + col_c) * 2u;
   const unsigned long long all = __builtin_amdgcn_ballot_w64(lane < 64);   // (kept in scalar registers)
   const unsigned long long ok_e = __builtin_amdgcn_ballot_w64(col_e < L.d_out);
   const long long first = (long long)(tile.w & 0xffff) * g.T;
@@ -175,12 +179,12 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
   const unsigned short* pc = uniform_ptr(reinterpret_cast<const unsigned short*>(L.a) + first * L.a_stride);
   const unsigned ld_base = lds_base + wave * kIpBlk;
   int ld_left = g.T;                              // RAGGED: rows of the sample from the next chunk to load on
-  constexpr int kRowsE[4] = {0, 8, 4, 12};
-  auto issue_load = [&](int i, unsigned st, unsigned long long on) {
-    if (i < 4)
-      direct_load_lds16_masked(off_e, pe + kRowsE[i] * L.delta_stride, ld_base + st + i * 4 * kIpBlk, ok_e & on);
+  auto issue_loads = [&](int i, unsigned st, unsigned long long on) {   // loads 2 * i and 2 * i + 1
+    const unsigned to = ld_base + st + (i < 2 ? 2 * i * 4 * kIpBlk : kIpOpE);
+    if (i < 2)
+      direct_load_lds16_masked2(pe, off_e[2 * i], to, off_e[2 * i + 1], to + 4 * kIpBlk, ok_e & on);
     else
-      direct_load_lds16_masked(off_c, pc + (i - 4) * 8 * L.a_stride, ld_base + st + kIpOpE + (i - 4) * 4 * kIpBlk, all & on);
+      direct_load_lds16_masked2(pc, off_c[0], to, off_c[1], to + 4 * kIpBlk, all & on);
   };
   auto next_chunk = [&]() {
     int step = kIpK;
@@ -198,11 +202,8 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
 #pragma unroll
     for (int i = 0; i < kIpLd; ++i) {
       const bool e = i < 4;
-      const int extra = e ? kRowsE[i & 3] : (i - 4) * 8;
-      const unsigned char* p = e ? reinterpret_cast<const unsigned char*>(pe + extra * L.delta_stride) + off_e
-                                 : reinterpret_cast<const unsigned char*>(pc + extra * L.a_stride) + off_c;
-      const bool row_ok = (e ? row_e : row_c) + extra < ld_left;
-      const bool in = row_ok && (!e || col_e < L.d_out);
+      const unsigned char* p = reinterpret_cast<const unsigned char*>(e ? pe : pc) + (e ? off_e[i & 3] : off_c[i & 1]);
+      const bool in = e ? row_e + kRowsE[i & 3] < ld_left && col_e < L.d_out : row_c + 8 * (i & 1) < ld_left;
       direct_load_lds16(in ? p : z, ld_base + st + (e ? i * 4 * kIpBlk : kIpOpE + (i - 4) * 4 * kIpBlk));
     }
   };
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
         asm volatile("" ::: "memory");
       }
       if (i >= 2 && i < 2 + 2 * (kIpFM + kIpFN)) read1(i - 2, be, bc, nxt);   // (after the last chunk: in bounds)
-      if (i % 4 == 3 && i / 4 < kIpLd) issue_load(i / 4, st, on);
+      if (i % 8 == 7 && i / 8 < kIpLd / 2) issue_loads(i / 8, st, on);
       __builtin_amdgcn_sched_barrier(0);
     }
     if (fresh)                                    // (or the compiler moves sums to where they are stored, 128 values with them)
@@ -353,7 +354,7 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
         issue_short_chunk(s * kIpStage);
       } else {
 #pragma unroll
-        for (int i = 0; i < kIpLd; ++i) issue_load(i, s * kIpStage, ~0ull);
+        for (int i = 0; i < kIpLd / 2; ++i) issue_loads(i, s * kIpStage, ~0ull);
       }
       next_chunk();
     }

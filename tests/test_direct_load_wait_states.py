@@ -21,8 +21,8 @@ extern "C" __global__ void fresh_base(const char* const* tab, unsigned long long
   CALL
 }
 """
-CALLS = ["direct_load_lds16_s(threadIdx.x * 16u, uniform_ptr(p), at);",
-         "direct_load_lds16_masked(threadIdx.x * 16u, uniform_ptr(p), at, mask);"]
+CALLS = [("direct_load_lds16_s(threadIdx.x * 16u, uniform_ptr(p), at);", 1),
+         ("direct_load_lds16_masked2(uniform_ptr(p), threadIdx.x * 16u, at, threadIdx.x * 16u + 1024, at + 1024, mask);", 2)]
 
 
 def scalars(text):
@@ -32,8 +32,8 @@ def scalars(text):
     return out
 
 
-@pytest.mark.parametrize("call", CALLS, ids=["plain", "masked"])
-def test_base_fresh_from_the_vector_unit(call, tmp_path):
+@pytest.mark.parametrize("call,count", CALLS, ids=["plain", "masked"])
+def test_base_fresh_from_the_vector_unit(call, count, tmp_path):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if not shutil.which(hipcc):
         pytest.skip("no hipcc")
@@ -61,4 +61,4 @@ def test_base_fresh_from_the_vector_unit(call, tmp_path):
         elif op.startswith("s_"):
             for r in dst:
                 since.pop(r, None)
-    assert loads == 1 and fresh >= 2
+    assert loads == count and fresh >= 2
