@@ -460,8 +460,12 @@ int sqnorm_chunk();
 size_t sqnorm_partials(const std::vector<LayerDev>& host_layers);
 hipError_t launch_sqnorm(const LayerDev* layers, int n_layers, size_t nblk, double* partial,
                          const adloco_stats_acc* acc, const adloco_ip_acc* ip, double* host, hipStream_t st);
-// Whether a kernel may read `p` (device memory, 8-byte aligned); the read-back copies from any other address.
-bool kernel_can_read(const void* p);
+// Whether a kernel on `device` may read `p`: memory of that device (another one's need not be mapped here), 8-byte
+// aligned.  The read-back copies from any other address.
+inline bool is_memory_of(const hipPointerAttribute_t& a, int device) {
+  return a.type == hipMemoryTypeDevice && a.device == device;
+}
+bool kernel_can_read(const adloco_ctx* ctx, const void* p);
 // adloco_grad_stats.  pinned_order (adloco_round): gradient sums of fp32 blocks and of token rows that are no multiple
 // of 32 are added up in the order of the kernels for whole contractions, not sample by sample or piece by piece.  A
 // round returns parameters after several AdamW steps, which divide by sqrt(v): where gradient and second moment are

@@ -789,7 +789,7 @@ static int norm_test(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_la
   int rc = ensure_scratch(ctx, ctx->red_f64, nblk * sizeof(double));
   if (rc) return rc;
   hipEvent_t ev = prof_begin(ctx, st);
-  const bool direct = kernel_can_read(acc) && (!ip || kernel_can_read(ip));
+  const bool direct = kernel_can_read(ctx, acc) && (!ip || kernel_can_read(ctx, ip));
   hipError_t e = launch_sqnorm(static_cast<const LayerDev*>(ctx->layer_tab.ptr), n_layers, nblk,
                                static_cast<double*>(ctx->red_f64.ptr), direct ? acc : nullptr,
                                direct ? ip : nullptr, ctx->pinned, st);

@@ -101,7 +101,7 @@ extern "C" int adloco_norm_test_noalloc(adloco_ctx* ctx, const adloco_linear_des
       return fail(ctx, ADLOCO_EHIP, "norm_test_noalloc: table launch failed: %s", hipGetErrorString(e));
   }
   // every partial sum in [0, nblk) is overwritten: nothing of an earlier call is read
-  const bool direct = kernel_can_read(acc);
+  const bool direct = kernel_can_read(ctx, acc);
   hipError_t e = launch_sqnorm(S->tab, n_layers, size_t(nblk), S->partial, direct ? acc : nullptr, nullptr, ctx->pinned, st);
   if (e != hipSuccess)
     return fail(ctx, ADLOCO_EHIP, "norm_test_noalloc: reduction launch failed: %s", hipGetErrorString(e));

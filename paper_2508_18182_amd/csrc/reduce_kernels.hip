@@ -132,10 +132,10 @@ size_t sqnorm_partials(const std::vector<LayerDev>& host_layers) {
 
 int sqnorm_chunk() { return kSqChunk; }
 
-bool kernel_can_read(const void* p) {
+bool kernel_can_read(const adloco_ctx* ctx, const void* p) {
   hipPointerAttribute_t a;
   if (reinterpret_cast<uintptr_t>(p) % 8 == 0 && hipPointerGetAttributes(&a, p) == hipSuccess)
-    return a.type == hipMemoryTypeDevice;
+    return is_memory_of(a, ctx->device);
   (void)hipGetLastError();
   return false;
 }
