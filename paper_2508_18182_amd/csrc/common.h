@@ -238,16 +238,47 @@ struct Scratch {
   size_t bytes = 0;
 };
 
-// Work list of the plain tile kernel (tile_plain_kernels.hip) for one layer table and batch shape.
-struct PlainTiles {
-  Scratch tab;              // int4 [8][slots] entries
-  Scratch part_idx, split, ptiles;   // statistics form: partial tile per entry, split tiles, their storage
-  Scratch out;              // double (16-bit kernel: float) [8 * slots][group][4 waves][2]
-  Scratch csr;              // int: listed layers | offsets | entries of each
-  int W = 2;                // tiles of 64 * W
-  int slots = 0, group = 1, n_split = 0, n_listed = 0;
-  int B = -1, T = -1;       // batch and (inner-product form) sequence length the list was built for (-1: none)
+// Tiles of the per-sample gradients of one layer table, for any batch size and sequence length: the same list serves
+// every call on these shapes, in whatever order batches come, and a captured call replays with it.
+struct TileList {
+  Scratch tab;              // int4 [8][slots] entries (layer, first row, first column, piece | pieces << 16), layer < 0: none;
+                            // int2 [8][slots]: (tile, first partial tile); int4 split tiles; int listed layers | tile ranges
+  Scratch ptiles;           // partial tiles of the entries that can be split along the samples
+  size_t off_part = 0, off_split = 0, off_csr = 0;
+  int edge = 0;             // tile rows
+  int slots = 0, n_tiles = 0, n_split = 0, n_listed = 0;
+  int n[kNumXcd] = {}, left[kNumXcd] = {}, pieces[kNumXcd] = {};   // per XCD: tiles; of them in the incomplete last round
+  std::vector<char> use;    // per block of the table: 1 = in the list
+  bool built = false;
+  // slots in use when a tile is split into at most `cap` pieces (first pieces come first on every XCD)
+  int used(int cap) const {
+    int u = 0;
+    for (int x = 0; x < kNumXcd; ++x) {
+      const int s = pieces[x] < cap ? pieces[x] : cap;
+      u = u > n[x] + left[x] * (s - 1) ? u : n[x] + left[x] * (s - 1);
+    }
+    return u;
+  }
+  template <typename T> const T* at(size_t off) const {
+    return reinterpret_cast<const T*>(static_cast<const char*>(tab.ptr) + off);
+  }
+  const int4* tiles() const { return at<int4>(0); }
+  const int2* part() const { return at<int2>(off_part); }
+  const int4* split() const { return at<int4>(off_split); }
+  const int* layers() const { return at<int>(off_csr); }
+  const int* ranges() const { return at<int>(off_csr) + n_listed; }   // tiles [q], .. of the q-th listed layer
 };
+// Samples that an entry covers: its piece of the batch (no more pieces than samples), or run `run` of `group` samples.
+struct SampleRun { int first, count; };
+__device__ __forceinline__ SampleRun list_piece(int w, int B, bool whole) {
+  const int S = whole ? 1 : min(w >> 16, B), p = w & 0xffff;
+  if (p >= S) return SampleRun{0, 0};
+  const int s0 = B * p / S;
+  return SampleRun{s0, B * (p + 1) / S - s0};
+}
+__device__ __forceinline__ SampleRun list_run(int w, int B, int group, int run) {
+  return (w & 0xffff) ? SampleRun{0, 0} : SampleRun{run * group, min(group, B - run * group)};
+}
 
 }  // namespace adloco
 
@@ -295,15 +326,15 @@ struct adloco_ctx {
   adloco::Scratch ip_dot, ip_sq;   // float [n_layers][B] of the blocks outside the tile table
   adloco::Scratch ip_flags;    // unsigned char [n_layers]: 1 = block is in the tile table
   int ip_slots = 0, ip_group = 1, ip_B = -1, ip_T = -1;
-  adloco::PlainTiles ip_plain; // linear blocks outside that table
+  adloco::TileList ip_rest;    // linear blocks outside that table
+  bool ip_any_rest = false;
+  int ip_rest_group = 1;
   int ip_group_tuning = 0;     // 0: cost model; else samples per tile entry
-  // statistics by per-sample gradient tiles (explicit form fused with the gradient sum)
-  adloco::Scratch ts_tab, ts_part_idx, ts_split, ts_ptiles, ts_out, ts_csr;
-  int ts_slots = 0, ts_n_split = 0, ts_n_listed = 0, ts_B = -1;
-  bool ts_ok = false;          // every linear block is aligned bf16 with its gradient sum formed here
-  adloco::PlainTiles st_plain; // the same for fp32 blocks
-  adloco::PlainTiles sum_plain; // gradient sums alone of fp32 blocks (B = 1: all token rows as one sample)
-  adloco::PlainTiles sq_tiles; // norms alone of blocks whose gradient sum is supplied (16-bit or plain kernel)
+  // statistics by per-sample gradient tiles: of the blocks whose gradient sum is formed here, or of all if none is.
+  // Built with the layer table; a list for which there is no memory is missing, and its routes with it.
+  adloco::TileList tiles16;    // aligned 16-bit blocks
+  adloco::TileList tiles32[2]; // fp32 blocks: 64- and 128-wide tiles
+  adloco::Scratch tile_out;    // results per (tile, sample)
   bool lin_fast = false;       // every linear block: 16-byte aligned rows, widths % 8 == 0, strides below 2^25
   int n_formed = 0;            // linear blocks whose gradient sum is formed here
   int stats_variant = 1;       // 1: tile form when eligible; 0: Gram + gradient-sum kernels
@@ -316,6 +347,7 @@ struct adloco_ctx {
   int wgrad_blocks = 0;        // workgroups of the wgrad launch for the uploaded table
   int table_dtype = -1;        // dtype the uploaded table was built for
   int table_inputs = -1;       // 1: the table was built by a call that reads a and delta
+  size_t scratch_limit = 0;    // largest scratch allocation, bytes (0: no limit); for tests of the calls' behaviour without memory
   int table_builds = 0;        // how often a shape-dependent table has been (re)built
   long long max_lin_stride = 0;  // widest row stride (elements) among the linear blocks of the table
   double* pinned = nullptr;    // 8 doubles of pinned host memory (read-back of the tests' sums)
@@ -359,6 +391,9 @@ void prof_end(adloco_ctx* ctx, int kernel, hipEvent_t start, hipStream_t st);
 
 // Grow-only scratch buffer.  Growing frees the old block, which waits for the device.
 int ensure_scratch(adloco_ctx* ctx, Scratch& s, size_t bytes);
+// The same for a route that a call can do without: false if the memory cannot be had, or not without an allocation while
+// the stream is being captured.
+bool obtain_scratch(adloco_ctx* ctx, Scratch& s, size_t bytes, hipStream_t st);
 
 // Kernel launchers (defined next to their kernels).  All return a hipError_t from the launch.
 struct GramLaunch {
@@ -417,32 +452,32 @@ struct TileGeom { int e, c, k, room; };
 int make_ip_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, int T, TileGeom geom,
                   int forced_group, std::vector<int4>& out, int& group);
 TileGeom ip_tile_geom();
-// For every layer of `use`: the indices into `tiles` of its entries, idx[ptr[q] .. ptr[q+1]) for lay[q]; appended to
-// one another in this order.
-std::vector<int> tiles_by_layer(const std::vector<int4>& tiles, const std::vector<char>& use, int& n_listed);
 hipError_t launch_ip_tiles(const LayerDev* layers, const void* tiles, int slots, int T, int group,
                            int dtype, bool want_sq, bool short_form, float* ip_out, hipStream_t st);
 // Which of the two 16-bit tile kernels: the one for short sequences (short_form), and the wave sums per tile and sample.
 bool short_sequences(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, int T, bool inner_products);
 int tile_waves(bool short_form);
-// ||g_i||^2 of aligned 16-bit blocks -> one partial sum per (layer, sample).
-hipError_t launch_square_tiles(const LayerDev* layers, const PlainTiles& p, int B, int T, int dtype, float* partials,
-                               hipStream_t st);
-// max_split: pieces of a tile at most
-int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, TileGeom geom, int max_split,
-                     std::vector<int4>& out, std::vector<int>& part, std::vector<int4>& split, int& n_pieces);
-hipError_t launch_stats_tiles(const LayerDev* layers, const void* tiles, const int* part, int slots,
-                              const void* split, int n_split, float* partial_tiles, int B, int T,
-                              int dtype, int accumulate, bool short_form, float* tile_out, const int* lay,
-                              const int* ptr, const int* idx, int n_listed, float* partials, int n_pairs,
-                              hipStream_t st);
+// Tile list of the blocks of `use`; split: the tiles of an XCD's incomplete last round can be cut along the samples.
+void make_tile_list(const std::vector<LayerDev>& layers, const std::vector<char>& use, TileGeom geom, bool split, TileList& list,
+                    std::vector<int4>& tiles, std::vector<int2>& part, std::vector<int4>& split_tiles, std::vector<int>& csr,
+                    int& n_pieces);
+// Samples per run that take the least time for `tiles` tiles.
+int run_length(long long tiles, int B, int T, TileGeom geom);
+// ||g_i||^2 of aligned 16-bit blocks, and (launch_stats_tiles) their gradient sums -> one partial sum per (layer, sample).
+// out: tile_waves() floats per (tile, sample).
+hipError_t launch_square_tiles(const LayerDev* layers, const TileList& list, int B, int T, int dtype, float* out,
+                               float* partials, hipStream_t st);
+hipError_t launch_stats_tiles(const LayerDev* layers, const TileList& list, int B, int T, int dtype, int accumulate,
+                              bool short_form, float* out, float* partials, hipStream_t st);
 // Resident workgroups per XCD of the plain tile kernel: two (128-wide tiles) or four per compute unit.
 constexpr int plain_tile_room(int W) { return kNumCu / kNumXcd * (W == 2 ? 2 : 4); }
+inline TileGeom plain_tile_geom(int W) { return TileGeom{64 * W, 64 * W, 32 / W, plain_tile_room(W)}; }
 int plain_tile_width(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B);
-// mode 0: <g_i, G> -> dot and ||g_i||^2 -> sq; fp32 only: mode 1: G and ||g_i||^2 -> sq; mode 2: G (B = 1, T = all
-// token rows, sq = NULL); mode 3: ||g_i||^2 -> sq.
-hipError_t launch_plain_tiles(const LayerDev* layers, const PlainTiles& p, int mode, int B, int T, int dtype,
-                              int accumulate, float* dot, float* sq, int sq_stride, hipStream_t st);
+// mode 0: <g_i, G> -> dot and ||g_i||^2 -> sq; fp32 only: mode 1: G and ||g_i||^2 -> sq (whole: no tile is split); mode 2: G
+// (B = 1, T = all token rows, sq = NULL); mode 3: ||g_i||^2 -> sq.  group: samples per run (modes 0 and 3).  out: one
+// double per (tile, sample), two in mode 0.
+hipError_t launch_plain_tiles(const LayerDev* layers, const TileList& list, int mode, int B, int T, int dtype, int accumulate,
+                              bool whole, int group, double* out, float* dot, float* sq, int sq_stride, hipStream_t st);
 hipError_t launch_ip_vector_table(const LayerDev* layers, const AuxDesc* vec_tab, int n_vec,
                                   const AuxDesc* emb_tab, int n_emb, int B, int T, int dtype,
                                   const float* vec, float* dot, hipStream_t st);

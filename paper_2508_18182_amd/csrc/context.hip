@@ -14,14 +14,22 @@ int ensure_scratch(adloco_ctx* ctx, Scratch& s, size_t bytes) {
     s.ptr = nullptr;
     s.bytes = 0;
   }
-  hipError_t e = hipMalloc(&s.ptr, want);
+  hipError_t e = ctx->scratch_limit && bytes > ctx->scratch_limit ? hipErrorOutOfMemory : hipMalloc(&s.ptr, want);
   if (e != hipSuccess) {
+    (void)hipGetLastError();
     s.ptr = nullptr;
     return fail(ctx, ADLOCO_ENOMEM, "scratch allocation of %zu bytes failed: %s", want,
                 hipGetErrorString(e));
   }
   s.bytes = want;
   return ADLOCO_OK;
+}
+
+bool obtain_scratch(adloco_ctx* ctx, Scratch& s, size_t bytes, hipStream_t st) {
+  if (bytes <= s.bytes) return true;
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capturing) != hipSuccess) (void)hipGetLastError();
+  return capturing == hipStreamCaptureStatusNone && ensure_scratch(ctx, s, bytes) == ADLOCO_OK;
 }
 
 static hipEvent_t get_event(adloco_ctx* ctx) {
@@ -141,12 +149,11 @@ extern "C" int adloco_destroy(adloco_ctx* ctx) {
                     &ctx->order_tab, &ctx->group_tab, &ctx->job_tab, &ctx->wgx_tab,
                     &ctx->wgx_split, &ctx->wgx_part, &ctx->vec_tab, &ctx->emb_tab,
                     &ctx->aux_vec, &ctx->aux_perm, &ctx->aux_part, &ctx->ip_tab, &ctx->ip_tile_out,
-                    &ctx->ip_dot, &ctx->ip_sq, &ctx->ip_flags, &ctx->ts_tab,
-                    &ctx->ts_part_idx, &ctx->ts_split, &ctx->ts_ptiles, &ctx->ts_out, &ctx->ts_csr};
+                    &ctx->ip_dot, &ctx->ip_sq, &ctx->ip_flags, &ctx->tile_out};
   for (Scratch* s : all)
     if (s->ptr) (void)hipFree(s->ptr);
-  for (PlainTiles* p : {&ctx->st_plain, &ctx->sum_plain, &ctx->sq_tiles, &ctx->ip_plain})
-    for (Scratch* s : {&p->tab, &p->part_idx, &p->split, &p->ptiles, &p->out, &p->csr})
+  for (TileList* p : {&ctx->tiles16, &ctx->tiles32[0], &ctx->tiles32[1], &ctx->ip_rest})
+    for (Scratch* s : {&p->tab, &p->ptiles})
       if (s->ptr) (void)hipFree(s->ptr);
   for (auto& r : ctx->prof) {
     (void)hipEventDestroy(r.start);
@@ -186,6 +193,9 @@ extern "C" int adloco_set_tuning(adloco_ctx* ctx, const char* name, int value) {
     ctx->overlap_aux = value ? 1 : 0;
   } else if (n == "stats_variant") {
     ctx->stats_variant = value ? 1 : 0;
+  } else if (n == "scratch_limit_kb") {
+    if (value < 0) return fail(ctx, ADLOCO_EINVAL, "scratch_limit_kb out of range");
+    ctx->scratch_limit = size_t(value) << 10;
   } else if (n == "stream_variant") ctx->stream_variant = value;
   else if (n == "profile") ctx->profile = value ? 1 : 0;
   else return fail(ctx, ADLOCO_EINVAL, "unknown tuning knob '%s'", name);

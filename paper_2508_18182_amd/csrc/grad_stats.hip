@@ -68,6 +68,34 @@ bool same_shape(const LayerDev& x, const LayerDev& y) {
          (x.grad_sum == nullptr) == (y.grad_sum == nullptr);
 }
 
+// Uploads a tile list.  One for which there is no memory stays missing: its routes are not taken.
+void build_tile_list(adloco_ctx* ctx, TileList& p, const std::vector<LayerDev>& tab, const std::vector<char>& use, TileGeom geom,
+                     bool split, hipStream_t st) {
+  ++ctx->table_builds;
+  p.built = false;
+  std::vector<int4> tiles, split_tiles;
+  std::vector<int2> part;
+  std::vector<int> csr;
+  int n_pieces = 0;
+  make_tile_list(tab, use, geom, split, p, tiles, part, split_tiles, csr, n_pieces);
+  p.use = use;
+  if ((long long)p.slots * kNumXcd > 0x7fffffffLL) return;
+  std::vector<char> blob;
+  auto append = [&](const void* src, size_t n) {
+    const size_t at = blob.size();
+    blob.insert(blob.end(), static_cast<const char*>(src), static_cast<const char*>(src) + n);
+    return at;
+  };
+  append(tiles.data(), tiles.size() * sizeof(int4));
+  p.off_split = append(split_tiles.data(), split_tiles.size() * sizeof(int4));
+  p.off_part = append(part.data(), part.size() * sizeof(int2));
+  p.off_csr = append(csr.data(), csr.size() * sizeof(int));
+  if (!obtain_scratch(ctx, p.tab, blob.size(), st)) return;
+  if (!obtain_scratch(ctx, p.ptiles, size_t(n_pieces) * geom.e * geom.c * sizeof(float), st)) return;
+  p.built = hipMemcpyAsync(p.tab.ptr, blob.data(), blob.size(), hipMemcpyHostToDevice, st) == hipSuccess &&
+            hipStreamSynchronize(st) == hipSuccess;
+}
+
 // Build the device view of the layer list.  A list whose shapes (widths, strides, kinds, flags,
 // alignment classes) equal those of the previous call only has its pointers refreshed, by a kernel on
 // the caller's stream; any other list rebuilds every table that depends on it, which allocates,
@@ -253,19 +281,22 @@ int prepare_tables(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_laye
   }
   ctx->aux_B = ctx->aux_T = -1;         // the vector / table descriptor lists follow the table
   ctx->ip_B = ctx->ip_T = -1;           // and so does the inner-product tile table
-  ctx->ts_B = -1;                       // and the statistics tile tables
-  ctx->st_plain.B = ctx->sum_plain.B = ctx->sq_tiles.B = -1;
   ctx->lin_fast = need_inputs && widest < (1 << 25);
   for (const LayerDev& L : tab)
     if (L.kind == ADLOCO_KIND_LINEAR) ctx->lin_fast = ctx->lin_fast && L.fast;
   ctx->n_formed = 0;
   for (const LayerDev& L : tab) ctx->n_formed += L.kind == ADLOCO_KIND_LINEAR && !L.provided;
   {
-    // (the tile kernels address the rows of a chunk with 32-bit byte offsets)
-    bool ok = need_inputs && is_16bit(dtype) && !order.empty() && widest < (1 << 25);
-    for (const LayerDev& L : tab)
-      if (L.kind == ADLOCO_KIND_LINEAR) ok = ok && !L.provided && L.fast;
-    ctx->ts_ok = ok;
+    // tile lists of every route that a call on this table can take, whatever its batch: of the blocks whose gradient sum is
+    // formed here, or of all linear blocks if none is (the 16-bit kernels take either all blocks or none)
+    for (TileList* p : {&ctx->tiles16, &ctx->tiles32[0], &ctx->tiles32[1], &ctx->ip_rest}) p->built = false;
+    std::vector<char> use(n_layers, 0);
+    for (int l = 0; l < n_layers; ++l) use[l] = tab[l].kind == ADLOCO_KIND_LINEAR && !(ctx->n_formed && tab[l].provided);
+    const bool all = ctx->n_formed == 0 || ctx->n_formed == ctx->n_linear;
+    if (need_inputs && ctx->n_linear > 0 && is_16bit(dtype) && ctx->lin_fast && all)
+      build_tile_list(ctx, ctx->tiles16, tab, use, ip_tile_geom(), ctx->n_formed > 0, st);
+    if (need_inputs && ctx->n_linear > 0 && dtype == ADLOCO_F32)
+      for (int W = 1; W <= 2; ++W) build_tile_list(ctx, ctx->tiles32[W - 1], tab, use, plain_tile_geom(W), ctx->n_formed > 0, st);
   }
   ctx->wgx_slots = 0;
   if (fast && is_16bit(dtype) && wg > 0 && widest < (1 << 25)) {
@@ -299,6 +330,14 @@ int prepare_tables(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_laye
 // the scratch they need.  Rebuilt when the layer table or the batch shape changed.
 int prepare_vector_table(adloco_ctx* ctx, int B, int T, hipStream_t st) {
   if (ctx->aux_B == B && ctx->aux_T == T) return ADLOCO_OK;
+  if (ctx->n_linear == int(ctx->layer_tab_host.size())) {      // no such blocks
+    ctx->vec_host.clear();
+    ctx->emb_host.clear();
+    ctx->vec_blocks = ctx->vec_blocks2 = ctx->emb_blocks = 0;
+    ctx->aux_B = B;
+    ctx->aux_T = T;
+    return ADLOCO_OK;
+  }
   ++ctx->table_builds;
   const int slab = vector_table_slab();
   std::vector<AuxDesc> vec, emb;
@@ -384,47 +423,6 @@ int prepare_vector_table(adloco_ctx* ctx, int B, int T, hipStream_t st) {
   ctx->emb_blocks = int(eb);
   ctx->aux_B = B;
   ctx->aux_T = T;
-  return ADLOCO_OK;
-}
-
-// Work list of the plain tile kernel (mfma16: of the 16-bit one) for the layers of `use`: statistics form (T = 0:
-// entries split along the samples, T = -1: whole entries only) or inner-product form.
-int build_plain_tiles(adloco_ctx* ctx, PlainTiles& p, const std::vector<char>& use, int B, int T, int forced_group,
-                      bool mfma16, hipStream_t st) {
-  ++ctx->table_builds;
-  p.B = -1;
-  const std::vector<LayerDev>& tab = ctx->layer_tab_host;
-  p.W = plain_tile_width(tab, use, B);
-  const TileGeom geom = mfma16 ? ip_tile_geom() : TileGeom{64 * p.W, 64 * p.W, 32 / p.W, plain_tile_room(p.W)};
-  std::vector<int4> tiles, split;
-  std::vector<int> part;
-  int n_pieces = 0;
-  if (T <= 0) {
-    p.slots = make_stats_tiles(tab, use, B, geom, T == 0 ? 0x7fff : 1, tiles, part, split, n_pieces);
-    p.group = B;
-  } else {
-    p.slots = make_ip_tiles(tab, use, B, T, geom, forced_group, tiles, p.group);
-    part.assign(1, -1);
-  }
-  if ((long long)p.slots * kNumXcd > 0x7fffffffLL)
-    return fail(ctx, ADLOCO_EUNSUPPORTED, "too many tiles for one launch");
-  const std::vector<int> csr = tiles_by_layer(tiles, use, p.n_listed);
-  p.n_split = int(split.size());
-  const size_t edge = size_t(64 * p.W);
-  const struct { Scratch* s; const void* src; size_t bytes; } up[] = {
-      {&p.tab, tiles.data(), tiles.size() * sizeof(int4)}, {&p.part_idx, part.data(), part.size() * sizeof(int)},
-      {&p.split, split.data(), split.size() * sizeof(int4)}, {&p.csr, csr.data(), csr.size() * sizeof(int)},
-      {&p.ptiles, nullptr, n_pieces * edge * edge * sizeof(float)},
-      {&p.out, nullptr, tiles.size() * p.group * 8 * (mfma16 ? sizeof(float) : sizeof(double))}};
-  for (const auto& u : up) {
-    int rc = ensure_scratch(ctx, *u.s, std::max<size_t>(u.bytes, 16));
-    if (rc) return rc;
-    if (u.src && u.bytes)
-      ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(u.s->ptr, u.src, u.bytes, hipMemcpyHostToDevice, st));
-  }
-  ADLOCO_HIP_CHECK(ctx, hipStreamSynchronize(st));
-  p.B = B;
-  p.T = T;
   return ADLOCO_OK;
 }
 
@@ -529,88 +527,54 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   // that add up to them are squared on the way, no Gram contraction is needed.  16-bit blocks if they are aligned;
   // fp32 ones too: 4 x {768 -> 2304, 768 -> 768, 768 -> 3072, 3072 -> 768}, B 8, T 256 takes 1.28 ms
   // against 5.02 ms with the vector-unit kernels of the two steps.
-  const bool tile_form = !sum_only && ctx->stats_variant != 0 && ctx->ts_ok &&
-                         (T % 32 == 0 || (!pinned_order && formed_tiles_pay(ctx->layer_tab_host, T, dtype, dual))) &&
-                         T <= (1 << 20) && B <= 0x7fff;
-  const bool plain_form = dtype == ADLOCO_F32 && !pinned_order && ctx->n_formed > 0 && B <= 0x7fff && ctx->stats_variant != 0 &&
-                          !sum_only && ctx->n_formed == ctx->n_linear &&
-                          formed_tiles_pay(ctx->layer_tab_host, T, dtype, dual);
+  const bool tiles_allowed = ctx->stats_variant != 0 && ctx->n_linear > 0 && B <= 0x7fff;
+  const bool all_formed = ctx->n_formed == ctx->n_linear;
+  const std::vector<LayerDev>& tab = ctx->layer_tab_host;
+  bool tile_form = !sum_only && tiles_allowed && all_formed && ctx->tiles16.built && is_16bit(dtype) &&
+                   (T % 32 == 0 || (!pinned_order && formed_tiles_pay(tab, T, dtype, dual))) && T <= (1 << 20);
+  bool plain_form = !sum_only && tiles_allowed && all_formed && dtype == ADLOCO_F32 && !pinned_order &&
+                    formed_tiles_pay(tab, T, dtype, dual);
+  bool square_form = !sum_only && tiles_allowed && ctx->n_formed == 0 && T <= (1 << 20) &&
+                     (dtype == ADLOCO_F32 || ctx->tiles16.built) && tiles_beat_gram(tab, B, T, dtype, dual);
+  const bool short_form = tile_form && short_sequences(tab, ctx->tiles16.use, B, T, false);
   const long long rows = (long long)B * T;
-  const bool plain_sum = dtype == ADLOCO_F32 && !plain_form && ctx->n_formed > 0 && rows < (1 << 30) &&
-                         ctx->stats_variant != 0;
-  const bool square_form = !sum_only && ctx->stats_variant != 0 && ctx->n_linear > 0 && ctx->n_formed == 0 &&
-                           B <= 0x7fff && T <= (1 << 20) && (dtype == ADLOCO_F32 || ctx->lin_fast) &&
-                           tiles_beat_gram(ctx->layer_tab_host, B, T, dtype, dual);
-  if (tile_form || plain_form || square_form) n_pairs = 1;      // one finished sum per (layer, sample)
-  const long long n_part = (long long)n_layers * B * n_pairs;
-  rc = ensure_scratch(ctx, ctx->partials, size_t(n_part) * sizeof(float));
+  // the list of the fp32 forms, and what a form leaves per (tile, sample)
+  const TileList* list = &ctx->tiles16;
+  size_t out_bytes = (tile_form ? tile_waves(short_form) : tile_waves(false)) * sizeof(float);
+  if (plain_form || (square_form && dtype == ADLOCO_F32)) {
+    list = &ctx->tiles32[plain_tile_width(tab, ctx->tiles32[0].use, B) - 1];
+    out_bytes = sizeof(double);
+  }
+  int group = 0;
+  if (square_form) {
+    group = run_length(list->n_tiles, B, T, dtype == ADLOCO_F32 ? plain_tile_geom(list->edge / 64) : ip_tile_geom());
+    square_form = (long long)list->used(1) * kNumXcd * ((B + group - 1) / group) <= 0x7fffffffLL;
+  }
+  // without the list or the memory for its results, a call takes the Gram contraction (and the sum over all rows)
+  if (!list->built || ((tile_form || plain_form || square_form) &&
+                       !obtain_scratch(ctx, ctx->tile_out, out_bytes * size_t(list->n_tiles) * B, st)))
+    tile_form = plain_form = square_form = false;
+  // (adding up partial tiles is one more launch of about 5 us, as long as 512 token rows of a tile take)
+  const bool whole = rows <= 512;
+  const bool formed = tile_form || plain_form || square_form;     // norms (and gradient sums) come from the tiles
+  const TileList* sum_list = nullptr;
+  if (dtype == ADLOCO_F32 && !formed && ctx->n_formed > 0 && rows < (1 << 30) && ctx->stats_variant != 0)
+    sum_list = &ctx->tiles32[plain_tile_width(tab, ctx->tiles32[0].use, 1) - 1];
+  const bool plain_sum = sum_list && sum_list->built;
+  const size_t part_bytes = size_t(n_layers) * B * sizeof(float);
+  // one finished sum per (layer, sample) comes from the tiles; up to 64 MiB, there is room for those of a Gram contraction
+  // too, so that a captured call on another batch finds it
+  if (formed) {
+    const size_t gram_bytes = part_bytes * size_t(n_pairs);
+    if (gram_bytes > (size_t(64) << 20) || !obtain_scratch(ctx, ctx->partials, gram_bytes, st))
+      rc = ensure_scratch(ctx, ctx->partials, part_bytes);
+    n_pairs = 1;
+  } else {
+    rc = ensure_scratch(ctx, ctx->partials, part_bytes * size_t(n_pairs));
+  }
   if (rc) return rc;
   rc = ensure_scratch(ctx, ctx->sample_f64, size_t(B) * sizeof(double));
   if (rc) return rc;
-  PlainTiles* const plain = plain_form ? &ctx->st_plain : plain_sum ? &ctx->sum_plain : nullptr;
-  const int plain_B = plain_form ? B : 1;
-  // (adding up partial tiles is one more launch of about 5 us, as long as 512 token rows of a tile take)
-  const int plain_T = plain_form && rows <= 512 ? -1 : 0;
-  if (plain && (plain->B != plain_B || plain->T != plain_T)) {
-    std::vector<char> use(n_layers, 0);
-    for (int l = 0; l < n_layers; ++l)
-      use[l] = ctx->layer_tab_host[l].kind == ADLOCO_KIND_LINEAR && !ctx->layer_tab_host[l].provided;
-    rc = build_plain_tiles(ctx, *plain, use, plain_B, plain_T, 0, false, st);
-    if (rc) return rc;
-  }
-  if (square_form && (ctx->sq_tiles.B != B || ctx->sq_tiles.T != T)) {
-    std::vector<char> use(n_layers, 0);
-    for (int l = 0; l < n_layers; ++l) use[l] = ctx->layer_tab_host[l].kind == ADLOCO_KIND_LINEAR;
-    rc = build_plain_tiles(ctx, ctx->sq_tiles, use, B, T, 0, is_16bit(dtype), st);
-    if (rc) return rc;
-  }
-  bool short_form = false;
-  if (tile_form) {
-    const std::vector<LayerDev>& tab = ctx->layer_tab_host;
-    std::vector<char> use(n_layers, 0);
-    for (int l = 0; l < n_layers; ++l) use[l] = tab[l].kind == ADLOCO_KIND_LINEAR;
-    short_form = short_sequences(tab, use, B, T, false);
-  }
-  if (tile_form && ctx->ts_B != B) {
-    ++ctx->table_builds;
-    const std::vector<LayerDev>& tab = ctx->layer_tab_host;
-    std::vector<char> use(n_layers, 0);
-    for (int l = 0; l < n_layers; ++l) use[l] = tab[l].kind == ADLOCO_KIND_LINEAR;
-    std::vector<int4> tiles, split;
-    std::vector<int> part;
-    int n_pieces = 0, n_listed = 0;
-    const int slots = make_stats_tiles(tab, use, B, ip_tile_geom(), 0x7fff, tiles, part, split, n_pieces);
-    if ((long long)slots * kNumXcd > 0x7fffffffLL)
-      return fail(ctx, ADLOCO_EUNSUPPORTED, "grad_stats: too many tiles for one launch");
-    const std::vector<int> csr = tiles_by_layer(tiles, use, n_listed);
-    rc = ensure_scratch(ctx, ctx->ts_tab, tiles.size() * sizeof(int4));
-    if (rc) return rc;
-    rc = ensure_scratch(ctx, ctx->ts_part_idx, part.size() * sizeof(int));
-    if (rc) return rc;
-    rc = ensure_scratch(ctx, ctx->ts_split, std::max<size_t>(split.size(), 1) * sizeof(int4));
-    if (rc) return rc;
-    rc = ensure_scratch(ctx, ctx->ts_ptiles, std::max<size_t>(n_pieces, 1) * 256 * 128 * sizeof(float));
-    if (rc) return rc;
-    rc = ensure_scratch(ctx, ctx->ts_out, tiles.size() * size_t(B) * 2 * tile_waves(true) * sizeof(float));
-    if (rc) return rc;
-    rc = ensure_scratch(ctx, ctx->ts_csr, csr.size() * sizeof(int));
-    if (rc) return rc;
-    ctx->ts_B = -1;
-    ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(ctx->ts_tab.ptr, tiles.data(), tiles.size() * sizeof(int4),
-                                         hipMemcpyHostToDevice, st));
-    ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(ctx->ts_part_idx.ptr, part.data(), part.size() * sizeof(int),
-                                         hipMemcpyHostToDevice, st));
-    if (!split.empty())
-      ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(ctx->ts_split.ptr, split.data(), split.size() * sizeof(int4),
-                                           hipMemcpyHostToDevice, st));
-    ADLOCO_HIP_CHECK(ctx, hipMemcpyAsync(ctx->ts_csr.ptr, csr.data(), csr.size() * sizeof(int),
-                                         hipMemcpyHostToDevice, st));
-    ADLOCO_HIP_CHECK(ctx, hipStreamSynchronize(st));
-    ctx->ts_slots = slots;
-    ctx->ts_n_split = int(split.size());
-    ctx->ts_n_listed = n_listed;
-    ctx->ts_B = B;
-  }
 
   GramLaunch g;
   g.layers = static_cast<const LayerDev*>(ctx->layer_tab.ptr);
@@ -659,35 +623,20 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   }
   hipEvent_t ev = nullptr;
   hipError_t e = hipSuccess;
-  if (tile_form) {
+  if (formed) {
     ev = prof_begin(ctx, st);
-    const int* csr = static_cast<const int*>(ctx->ts_csr.ptr);
-    const int nl = ctx->ts_n_listed;
-    e = launch_stats_tiles(g.layers, ctx->ts_tab.ptr, static_cast<const int*>(ctx->ts_part_idx.ptr),
-                           ctx->ts_slots, ctx->ts_split.ptr, ctx->ts_n_split,
-                           static_cast<float*>(ctx->ts_ptiles.ptr), B, T, dtype, accumulate, short_form,
-                           static_cast<float*>(ctx->ts_out.ptr), csr, csr + nl, csr + nl + nl + 1, nl,
-                           g.partials, int(n_pairs), st);
+    float* const out16 = static_cast<float*>(ctx->tile_out.ptr);
+    if (tile_form)
+      e = launch_stats_tiles(g.layers, *list, B, T, dtype, accumulate, short_form, out16, g.partials, st);
+    else if (square_form && is_16bit(dtype))
+      e = launch_square_tiles(g.layers, *list, B, T, dtype, out16, g.partials, st);
+    else
+      e = launch_plain_tiles(g.layers, *list, plain_form ? 1 : 3, B, T, dtype, accumulate, whole, group,
+                             static_cast<double*>(ctx->tile_out.ptr), nullptr, g.partials, 1, st);
     prof_end(ctx, kProfTileStats, ev, st);
     if (e != hipSuccess)
       return fail(ctx, ADLOCO_EHIP, "grad_stats: tile statistics launch failed: %s", hipGetErrorString(e));
   }
-  if (plain_form) {
-    ev = prof_begin(ctx, st);
-    e = launch_plain_tiles(g.layers, ctx->st_plain, 1, B, T, dtype, accumulate, nullptr, g.partials, int(n_pairs), st);
-    prof_end(ctx, kProfTileStats, ev, st);
-    if (e != hipSuccess)
-      return fail(ctx, ADLOCO_EHIP, "grad_stats: plain tile launch failed: %s", hipGetErrorString(e));
-  }
-  if (square_form) {
-    ev = prof_begin(ctx, st);
-    e = is_16bit(dtype) ? launch_square_tiles(g.layers, ctx->sq_tiles, B, T, dtype, g.partials, st)
-                        : launch_plain_tiles(g.layers, ctx->sq_tiles, 3, B, T, dtype, 0, nullptr, g.partials, 1, st);
-    prof_end(ctx, kProfTileStats, ev, st);
-    if (e != hipSuccess)
-      return fail(ctx, ADLOCO_EHIP, "grad_stats: square tile launch failed: %s", hipGetErrorString(e));
-  }
-  const bool formed = tile_form || plain_form || square_form;     // norms (and gradient sums) are done
   ev = (!formed && !sum_only && ctx->n_linear > 0) ? prof_begin(ctx, st) : nullptr;
   if (formed || sum_only || ctx->n_linear == 0)
     ;
@@ -714,7 +663,7 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   if (formed)
     ;
   else if (plain_sum)
-    e = launch_plain_tiles(g.layers, ctx->sum_plain, 2, 1, int(rows), dtype, accumulate, nullptr, nullptr, 0, st);
+    e = launch_plain_tiles(g.layers, *sum_list, 2, 1, int(rows), dtype, accumulate, true, 1, nullptr, nullptr, nullptr, 0, st);
   else if (is_16bit(dtype) && ctx->wgrad_variant >= 2 && ctx->wgx_slots > 0 && (rows % 32 == 0 || !pinned_order) &&
            rows / 32 < 0x7fffffffLL)
     e = launch_wgrad_x(g.layers, ctx->wgx_tab.ptr, ctx->wgx_slots, ctx->wgx_split.ptr,
@@ -886,16 +835,25 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
       rest[l] = tab[l].kind == ADLOCO_KIND_LINEAR && !use[l];
       any_rest = any_rest || rest[l];
     }
-    ctx->ip_plain.slots = 0;
     if (any_rest) {
-      rc = build_plain_tiles(ctx, ctx->ip_plain, rest, B, T, ctx->ip_group_tuning, false, st);
-      if (rc) return rc;
+      const TileGeom geom = plain_tile_geom(plain_tile_width(tab, rest, B));
+      TileList& p = ctx->ip_rest;
+      if (!p.built || p.use != rest || p.edge != geom.e) build_tile_list(ctx, p, tab, rest, geom, false, st);
+      if (!p.built) return fail(ctx, ADLOCO_ENOMEM, "inner_products: no memory for the tile list");
+      ctx->ip_rest_group = ctx->ip_group_tuning > 0 ? std::min(ctx->ip_group_tuning, B) : run_length(p.n_tiles, B, T, geom);
+      if ((long long)p.used(1) * kNumXcd * ((B + ctx->ip_rest_group - 1) / ctx->ip_rest_group) > 0x7fffffffLL)
+        return fail(ctx, ADLOCO_EUNSUPPORTED, "inner_products: too many tiles for one launch");
     }
+    ctx->ip_any_rest = any_rest;
     ctx->ip_slots = slots;
     ctx->ip_group = group;
     ctx->ip_short = short_form;
     ctx->ip_B = B;
     ctx->ip_T = T;
+  }
+  if (ctx->ip_any_rest) {
+    rc = ensure_scratch(ctx, ctx->tile_out, size_t(ctx->ip_rest.n_tiles) * B * 2 * sizeof(double));
+    if (rc) return rc;
   }
   rc = ensure_scratch(ctx, ctx->ip_dot, size_t(n_layers) * B * sizeof(float));
   if (rc) return rc;
@@ -910,8 +868,9 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
   hipError_t e = launch_ip_tiles(dl, ctx->ip_tab.ptr, ctx->ip_slots, T, ctx->ip_group, dtype,
                                  per_sample_sqnorm != nullptr, ctx->ip_short,
                                  static_cast<float*>(ctx->ip_tile_out.ptr), st);
-  if (e == hipSuccess)
-    e = launch_plain_tiles(dl, ctx->ip_plain, 0, B, T, dtype, 0, dot, sq, 1, st);
+  if (e == hipSuccess && ctx->ip_any_rest)
+    e = launch_plain_tiles(dl, ctx->ip_rest, 0, B, T, dtype, 0, true, ctx->ip_rest_group,
+                           static_cast<double*>(ctx->tile_out.ptr), dot, sq, 1, st);
   if (e == hipSuccess && !ctx->vec_host.empty())
     e = launch_vector_stats(dl, static_cast<const AuxDesc*>(ctx->vec_tab.ptr), int(ctx->vec_host.size()),
                             ctx->vec_blocks, ctx->vec_blocks2, B, T, dtype,

@@ -81,15 +81,14 @@ constexpr int kIpLds = kIpStages * kIpStage;      // 148.5 KiB
 
 struct IpTileArgs {
   const LayerDev* layers;
-  const int4* tiles;      // [8][slots]: (layer, e0, c0, first sample | samples << 16); layer < 0: none
-  float* out;             // [8 * slots][group][waves][2]: <tile_i, G tile>, sum of squares of tile_i
-                          // (statistics form: sum of squares, unused)
-  int slots, T, group;
-  // statistics form only
-  const int* part;        // [8][slots]: -1: the entry covers all samples and owns its tile of G;
-                          // else index of the partial tile that receives its share of the sum
-  float* partials;        // [pieces][256][128] fp32
-  int accumulate;         // G += sum instead of G = sum
+  const int4* tiles;      // MODE 0, [8][slots]: (layer, e0, c0, first sample | samples << 16); layer < 0: none; else the
+                          // entries of a tile list, of which `used` slots per XCD are launched
+  float* out;             // MODE 0, [8 * slots][group][waves][2]: <tile_i, G tile>, sum of squares of tile_i;
+                          // else [tile][B][waves]: sum of squares
+  int slots, used, T, B, group;
+  const int2* part;       // MODE 1 and 2: the list's (tile, first partial tile)
+  float* partials;        // MODE 1: [pieces][256][128] fp32
+  int accumulate;         // MODE 1: G += sum instead of G = sum
 };
 
 __device__ __attribute__((aligned(16))) const unsigned ip_zero_line[4] = {0, 0, 0, 0};
@@ -122,9 +121,15 @@ template <int N> __device__ __forceinline__ void ip_wait_vmcnt() {
 template <int MODE, bool SQ, bool F16, bool RAGGED, bool ODD>
 __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  const int xcd = blockIdx.x % kNumXcd, slot = blockIdx.x / kNumXcd;
-  const int4 tile = g.tiles[xcd * g.slots + slot];
+  const int xcd = blockIdx.x % kNumXcd, seq = blockIdx.x / kNumXcd, slot = MODE == 2 ? seq % g.used : seq;
+  const int entry = xcd * g.slots + slot;
+  const int4 tile = g.tiles[entry];
   if (tile.x < 0) return;
+  const SampleRun S = MODE == 0   ? SampleRun{tile.w & 0xffff, tile.w >> 16}
+                      : MODE == 1 ? list_piece(tile.w, g.B, false)
+                                  : list_run(tile.w, g.B, g.group, seq / g.used);
+  if (S.count == 0) return;
+  const int2 part = MODE == 0 ? int2{0, 0} : g.part[entry];
   const LayerDev L = g.layers[tile.x];
   const int e0 = tile.y, c0 = tile.z;
   const int lane = threadIdx.x & 63;
@@ -132,7 +137,7 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
   const int wm = wave >> 1, wn = wave & 1;        // 2 x 2 waves
   const int i16 = lane & 15, grp = lane >> 4;
   const int nk_sample = (g.T + kIpK - 1) / kIpK;  // chunks per sample
-  const int nk = (tile.w >> 16) * nk_sample;      // chunks of this entry: the host keeps it below 2^31
+  const int nk = S.count * nk_sample;             // chunks of this entry: the host keeps it below 2^31
   const unsigned lds_base = lds_address(lds);     // LDS byte addresses are handled as integers
 
   // ---- second register set.  Accumulator element j of a 16x16 block: row grp * 4 + j, column i16.  MODE 0: this
@@ -174,7 +179,7 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
   for (int i = 0; i < 2; ++i) off_c[i] = unsigned((row_c + 8 * i) * L.a_stride + col_c) * 2u;
   const unsigned long long all = __builtin_amdgcn_ballot_w64(lane < 64);   // (kept in scalar registers)
   const unsigned long long ok_e = __builtin_amdgcn_ballot_w64(col_e < L.d_out);
-  const long long first = (long long)(tile.w & 0xffff) * g.T;
+  const long long first = (long long)S.first * g.T;
   const unsigned short* pe = uniform_ptr(reinterpret_cast<const unsigned short*>(L.delta) + first * L.delta_stride);
   const unsigned short* pc = uniform_ptr(reinterpret_cast<const unsigned short*>(L.a) + first * L.a_stride);
   const unsigned ld_base = lds_base + wave * kIpBlk;
@@ -251,8 +256,9 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
   };
   // (Before the first sample ends there is no finished tile: the cleared accumulators, which give NaN on an infinite
   // entry of G, are taken and not stored.)
-  float* const dst0 = g.out + ((size_t(xcd) * g.slots + slot) * g.group * kIpWaves + wave) * 2;
-  float* dst = dst0 - 2 * kIpWaves;
+  constexpr int kDst = MODE == 0 ? 2 : 1;         // floats per sample and wave
+  float* const dst0 = g.out + ((MODE == 0 ? (size_t)entry * g.group : (size_t)part.x * g.B + S.first) * kIpWaves + wave) * kDst;
+  float* dst = dst0 - kDst * kIpWaves;
   // Rows past the edge are sums of zeros times a: zero, or NaN where a column of a has an infinite entry or a NaN.  The
   // last eight rows of the wave's part, past the edge if any are, tell which.  In the second case the finished tile is
   // summed here row by row, before the fresh MFMAs overwrite it, and put_sample takes these sums.
@@ -303,7 +309,7 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
         dst[0] = s;
       }
     }
-    dst += 2 * kIpWaves;
+    dst += kDst * kIpWaves;
 #pragma unroll
     for (int n = 0; n < kIpFN; ++n) dot[n] = sq[n] = 0.f;
   };
@@ -421,9 +427,8 @@ __global__ __launch_bounds__(64 * kIpWaves, 1) void ip_tile_kernel(IpTileArgs g)
   put_sample();
 
   if constexpr (MODE == 1) {
-    const int part = g.part[xcd * g.slots + slot];
-    if (part >= 0) {
-      float* pt = g.partials + (size_t)part * (kIpE * kIpC);
+    if (S.count < g.B) {
+      float* pt = g.partials + (size_t)(part.y + (tile.w & 0xffff)) * (kIpE * kIpC);
 #pragma unroll
       for (int m = 0; m < kIpFM; ++m)
 #pragma unroll
@@ -466,17 +471,20 @@ __device__ __forceinline__ int st_row_off_c(int row) { return (row & 7) * kStBlk
 template <int MODE, bool SQ, bool F16>
 __global__ __launch_bounds__(64 * kStWaves, 1) void short_tile_kernel(IpTileArgs g) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  const int xcd = blockIdx.x % kNumXcd, slot = blockIdx.x / kNumXcd;
-  const int4 tile = g.tiles[xcd * g.slots + slot];
+  const int entry = blockIdx.x % kNumXcd * g.slots + blockIdx.x / kNumXcd;
+  const int4 tile = g.tiles[entry];
   if (tile.x < 0) return;
+  const SampleRun S = MODE == 0 ? SampleRun{tile.w & 0xffff, tile.w >> 16} : list_piece(tile.w, g.B, false);
+  if (S.count == 0) return;
+  const int2 part = MODE == 0 ? int2{0, 0} : g.part[entry];
   const LayerDev L = g.layers[tile.x];
   const int e0 = tile.y, c0 = tile.z;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / kStWN, wn = wave % kStWN;  // kStWM x kStWN waves
   const int nk_sample = g.T / kIpK;               // chunks per sample
-  const long long ck0 = (long long)(tile.w & 0xffff) * nk_sample;
-  const int nk = (tile.w >> 16) * nk_sample;       // chunks of this entry: the host keeps it below 2^31
+  const long long ck0 = (long long)S.first * nk_sample;
+  const int nk = S.count * nk_sample;              // chunks of this entry: the host keeps it below 2^31
 
   // ---- second register set.  Accumulator element j of a 32x32 block: row
   // (j/4)*8 + (lane/32)*4 + j%4, column lane%32.  MODE 0: this lane's entries of the G tile
@@ -617,7 +625,8 @@ __global__ __launch_bounds__(64 * kStWaves, 1) void short_tile_kernel(IpTileArgs
   asm volatile("" ::: "memory");
 
   int left = nk_sample, sample_out = 0;
-  float* dst = g.out + ((size_t(xcd) * g.slots + slot) * g.group * kStWaves + wave) * 2;
+  constexpr int kDst = MODE == 0 ? 2 : 1;         // floats per sample and wave
+  float* dst = g.out + ((MODE == 0 ? (size_t)entry * g.group : (size_t)part.x * g.B + S.first) * kStWaves + wave) * kDst;
   mfma_bf16x8 fa[2][kStFM], fb[2][kStFN];
   read_frags(0, 0, fa[0], fb[0]);
   int st_cur = 0, st_load = kStStages - 1;        // stage of chunk c; stage that chunk c-1 frees
@@ -661,10 +670,10 @@ __global__ __launch_bounds__(64 * kStWaves, 1) void short_tile_kernel(IpTileArgs
       if (SQ) sq = ip_wave_sum_f32(sq);
       if (lane == 0) {
         if (MODE == 0) {
-          dst[size_t(sample_out) * (2 * kStWaves)] = dot;
-          dst[size_t(sample_out) * (2 * kStWaves) + 1] = sq;
+          dst[size_t(sample_out) * (kDst * kStWaves)] = dot;
+          dst[size_t(sample_out) * (kDst * kStWaves) + 1] = sq;
         } else {
-          dst[size_t(sample_out) * (2 * kStWaves)] = sq;
+          dst[size_t(sample_out) * (kDst * kStWaves)] = sq;
         }
       }
       ++sample_out;
@@ -672,8 +681,7 @@ __global__ __launch_bounds__(64 * kStWaves, 1) void short_tile_kernel(IpTileArgs
     }
   }
   if constexpr (MODE == 1) {
-    const int part = g.part[xcd * g.slots + slot];
-    float* const pt = part >= 0 ? g.partials + (size_t)part * (kIpE * kIpC) : nullptr;
+    float* const pt = S.count < g.B ? g.partials + (size_t)(part.y + (tile.w & 0xffff)) * (kIpE * kIpC) : nullptr;
 #pragma unroll
     for (int m = 0; m < kStFM; ++m)
 #pragma unroll
@@ -714,12 +722,12 @@ __global__ __launch_bounds__(64 * kStWaves, 1) void short_tile_kernel(IpTileArgs
 // one thread per column, rows unrolled so that their loads are in flight together;
 // split[t] = (layer, e0, c0, pieces << 16 | first partial tile).
 constexpr int kIpRedRows = 4;
-__global__ __launch_bounds__(kIpC) void stats_tile_reduce_kernel(const LayerDev* layers, const int4* split,
+__global__ __launch_bounds__(kIpC) void stats_tile_reduce_kernel(const LayerDev* layers, const int4* split, int B,
                                                                 const float* partials, int accumulate) {
   const int t = blockIdx.x / (kIpE / kIpRedRows), r0 = (blockIdx.x % (kIpE / kIpRedRows)) * kIpRedRows;
   const int4 S = split[t];
   const LayerDev L = layers[S.x];
-  const int pieces = S.w >> 16;
+  const int pieces = min(S.w >> 16, B);
   const float* base = partials + (size_t)(S.w & 0xffff) * (kIpE * kIpC) + threadIdx.x;
   const int col = S.z + threadIdx.x;
   float v[kIpRedRows];
@@ -737,31 +745,21 @@ __global__ __launch_bounds__(kIpC) void stats_tile_reduce_kernel(const LayerDev*
   }
 }
 
-// Statistics form: ||g_i^l||^2 = sum over the layer's tile entries and waves of the tile's sum of
-// squares -> slot 0 of the layer's partial sums (the other slots are cleared), from where the
-// common reduction picks it up.  One workgroup per (listed layer, sample); the entries of layer
-// `lay[q]` are idx[ptr[q] .. ptr[q+1]).
-__global__ __launch_bounds__(64) void stats_tile_finalize_kernel(const int4* tiles, const float* out, int group, int waves,
-                                                                const int* lay, const int* ptr, const int* idx,
-                                                                int B, float* partials, int n_pairs) {
+// Statistics form: ||g_i^l||^2 = sum over the layer's tiles and waves of the tile's sum of squares, to where the common
+// reduction picks it up.  One workgroup per (listed layer, sample); the tiles of the q-th listed layer lay[q] are
+// ranges[q], .., ranges[q + 1] - 1.
+__global__ __launch_bounds__(64) void stats_tile_finalize_kernel(const float* out, int waves, const int* lay,
+                                                                const int* ranges, int B, float* partials) {
   const int q = blockIdx.x / B, i = blockIdx.x % B;
-  const int l = lay[q];
   double s = 0.0;
-  for (int k = ptr[q] + threadIdx.x; k < ptr[q + 1]; k += 64) {
-    const int e = idx[k];
-    const int4 t = tiles[e];
-    const int s0 = t.w & 0xffff, cnt = t.w >> 16;
-    if (i >= s0 && i < s0 + cnt) {
-      const float* o = out + ((size_t)e * group + (i - s0)) * (2 * waves);
-      for (int w = 0; w < waves; w += 4)
+  for (int t = ranges[q] + threadIdx.x; t < ranges[q + 1]; t += 64) {
+    const float* o = out + ((size_t)t * B + i) * waves;
+    for (int w = 0; w < waves; w += 4)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) s += double(o[2 * (w + v)]);
-    }
+      for (int v = 0; v < 4; ++v) s += double(o[w + v]);
   }
   s = ip_wave_sum(s);
-  float* p = partials + (size_t(l) * B + i) * n_pairs;
-  if (threadIdx.x == 0) p[0] = float(s);
-  for (int k = 1 + threadIdx.x; k < n_pairs; k += 64) p[k] = 0.f;
+  if (threadIdx.x == 0) partials[size_t(lay[q]) * B + i] = float(s);
 }
 
 // Tile table.  All tiles of one (layer, run of samples) stream the same rows, so such a set
@@ -769,6 +767,23 @@ __global__ __launch_bounds__(64) void stats_tile_finalize_kernel(const int4* til
 // length trades the once-per-entry costs (G tile, pipeline fill) against the balance of the last
 // round of workgroups.
 TileGeom ip_tile_geom() { return TileGeom{kIpE, kIpC, kIpK, kNumCu / kNumXcd}; }
+
+// Cost in chunks: a run of s samples costs s * T/k + 8; `room` workgroups run at a time on each of the 8 XCDs.
+int run_length(long long tiles, int B, int T, TileGeom geom) {
+  const double per_sample = double((T + geom.k - 1) / geom.k), fixed = 8.0;
+  double best = 0.0;
+  int group = 1;
+  for (int gsz = 1; gsz <= std::min(B, 0x7fff); ++gsz) {
+    const long long runs = (B + gsz - 1) / gsz;
+    const double rounds = std::ceil(double(tiles * runs) / (double(geom.room) * kNumXcd));
+    const double cost = rounds * (gsz * per_sample + fixed);
+    if (gsz == 1 || cost < best * 0.999) {
+      best = cost;
+      group = gsz;
+    }
+  }
+  return group;
+}
 
 int make_ip_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, int T, TileGeom geom,
                   int forced_group, std::vector<int4>& out, int& group) {
@@ -778,19 +793,7 @@ int make_ip_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& 
   long long tiles_all = 0;
   for (size_t l = 0; l < layers.size(); ++l)
     if (use[l]) tiles_all += tiles_of(layers[l]);
-  // cost in chunks: an entry of s samples costs s * T/k + 8; `room` workgroups run at a time on each of the 8 XCDs
-  const double per_sample = double((T + geom.k - 1) / geom.k), fixed = 8.0;
-  double best = 0.0;
-  group = 1;
-  for (int gsz = 1; gsz <= std::min(B, 0x7fff); ++gsz) {
-    const long long runs = (B + gsz - 1) / gsz;
-    const double rounds = std::ceil(double(tiles_all * runs) / (double(geom.room) * kNumXcd));
-    const double cost = rounds * (gsz * per_sample + fixed);
-    if (gsz == 1 || cost < best * 0.999) {
-      best = cost;
-      group = gsz;
-    }
-  }
+  group = run_length(tiles_all, B, T, geom);
   if (forced_group > 0) group = std::min(std::min(forced_group, B), 0x7fff);
   struct Set { int layer, s0, cnt; long long n; };
   std::vector<Set> sets;
@@ -835,7 +838,8 @@ template <int MODE, bool SQ> static auto ip_tile_variant(int dtype, int T) {
 template <typename K> static hipError_t launch_tiles(K kern, int waves, int lds, const IpTileArgs& a, hipStream_t st) {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(unsigned(a.slots) * kNumXcd), dim3(64 * waves), lds, st, a);
+  const unsigned runs = a.group > 0 && a.part ? unsigned((a.B + a.group - 1) / a.group) : 1u;
+  hipLaunchKernelGGL(kern, dim3(unsigned(a.used) * runs * kNumXcd), dim3(64 * waves), lds, st, a);
   return hipGetLastError();
 }
 
@@ -860,7 +864,7 @@ int tile_waves(bool short_form) { return short_form ? kStWaves : kIpWaves; }
 hipError_t launch_ip_tiles(const LayerDev* layers, const void* tiles, int slots, int T, int group,
                            int dtype, bool want_sq, bool short_form, float* ip_out, hipStream_t st) {
   if (slots <= 0) return hipSuccess;
-  const IpTileArgs a{layers, static_cast<const int4*>(tiles), ip_out, slots, T, group, nullptr, nullptr, 0};
+  const IpTileArgs a{layers, static_cast<const int4*>(tiles), ip_out, slots, slots, T, 0, group, nullptr, nullptr, 0};
   if (short_form) {
     const bool h = dtype == ADLOCO_F16;
     auto kern = want_sq ? (h ? short_tile_kernel<0, true, true> : short_tile_kernel<0, true, false>)
@@ -871,100 +875,79 @@ hipError_t launch_ip_tiles(const LayerDev* layers, const void* tiles, int slots,
                       st);
 }
 
-hipError_t launch_square_tiles(const LayerDev* layers, const PlainTiles& p, int B, int T, int dtype, float* partials,
-                               hipStream_t st) {
-  if (p.slots <= 0) return hipSuccess;
-  const int4* tiles = static_cast<const int4*>(p.tab.ptr);
-  float* out = static_cast<float*>(p.out.ptr);
-  const IpTileArgs a{layers, tiles, out, p.slots, T, p.group, nullptr, nullptr, 0};
+hipError_t launch_square_tiles(const LayerDev* layers, const TileList& list, int B, int T, int dtype, float* out,
+                               float* partials, hipStream_t st) {
+  const IpTileArgs a{layers, list.tiles(), out, list.slots, list.used(1), T, B, run_length(list.n_tiles, B, T, ip_tile_geom()),
+                     list.part(), nullptr, 0};
   hipError_t e = launch_tiles(ip_tile_variant<2, true>(dtype, T), kIpWaves, kIpLds, a, st);
   if (e != hipSuccess) return e;
-  const int* csr = static_cast<const int*>(p.csr.ptr);
-  const int nl = p.n_listed;
-  hipLaunchKernelGGL(stats_tile_finalize_kernel, dim3(unsigned(nl) * B), dim3(64), 0, st, tiles, out, p.group,
-                     kIpWaves, csr, csr + nl, csr + nl + nl + 1, B, partials, 1);
+  hipLaunchKernelGGL(stats_tile_finalize_kernel, dim3(unsigned(list.n_listed) * B), dim3(64), 0, st, out, kIpWaves, list.layers(),
+                     list.ranges(), B, partials);
   return hipGetLastError();
 }
 
-// Tile table of the statistics form: one entry per tile covering all B samples; the tiles of a layer go to one XCD
-// where possible (they stream the same rows).  The entries of an XCD's incomplete last round of workgroups are split
-// along the samples into pieces whose partial sums a small kernel adds up in piece order.
-int make_stats_tiles(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, TileGeom geom, int max_split,
-                     std::vector<int4>& out, std::vector<int>& part, std::vector<int4>& split, int& n_pieces) {
-  // all tiles in layer order (within a layer: blocks of tiles that share rows), cut into eight
-  // equal runs: a layer stays on one XCD unless it straddles a cut, and the XCDs get the same
-  // number of tiles
+// The tiles of a layer go to one XCD where possible (they stream the same rows): all tiles in layer order (within a
+// layer: blocks of tiles that share rows) are cut into eight equal runs, so that a layer stays on one XCD unless it
+// straddles a cut, and the XCDs get the same number of tiles.  The tiles of an XCD's incomplete last round of workgroups
+// can be split along the samples into as many pieces as fill the round, whose partial sums a small kernel adds up in
+// piece order; all first pieces come first, then all second ones.
+void make_tile_list(const std::vector<LayerDev>& layers, const std::vector<char>& use, TileGeom geom, bool split, TileList& list,
+                    std::vector<int4>& tiles, std::vector<int2>& part, std::vector<int4>& split_tiles, std::vector<int>& csr,
+                    int& n_pieces) {
   std::vector<int4> all;
+  std::vector<int> lay, ranges(1, 0);
   for (size_t l = 0; l < layers.size(); ++l) {
     if (!use[l]) continue;
     for_tiles_blocked((layers[l].d_out + geom.e - 1) / geom.e, (layers[l].d_in + geom.c - 1) / geom.c, geom.e / geom.c,
-                      [&](int e, int c) { all.push_back(int4{int(l), e * geom.e, c * geom.c, B << 16}); });
+                      [&](int e, int c) { all.push_back(int4{int(l), e * geom.e, c * geom.c, 1 << 16}); });
+    lay.push_back(int(l));
+    ranges.push_back(int(all.size()));
   }
-  std::vector<std::vector<int4>> per(kNumXcd);
-  for (int x = 0; x < kNumXcd; ++x)
-    for (size_t i = all.size() * x / kNumXcd; i < all.size() * (x + 1) / kNumXcd; ++i)
-      per[x].push_back(all[i]);
-  split.clear();
+  split_tiles.clear();
   n_pieces = 0;
   std::vector<std::vector<int4>> fin(kNumXcd);
-  std::vector<std::vector<int>> finp(kNumXcd);
+  std::vector<std::vector<int2>> finp(kNumXcd);
   for (int x = 0; x < kNumXcd; ++x) {
-    const int n = int(per[x].size());
-    const int full = n / geom.room * geom.room, left = n - full;
-    const int S = left > 0 ? std::min(std::min(geom.room / left, B), max_split) : 1;
-    for (int i = 0; i < n; ++i) {
-      if (i < full || S < 2 || n_pieces + S > 0xffff) {
-        fin[x].push_back(per[x][i]);
-        finp[x].push_back(-1);
-        continue;
-      }
-      split.push_back(int4{per[x][i].x, per[x][i].y, per[x][i].z, (S << 16) | n_pieces});
-      for (int p = 0; p < S; ++p) {
-        const int s0 = int((long long)B * p / S), s1 = int((long long)B * (p + 1) / S);
-        int4 e = per[x][i];
-        e.w = s0 | ((s1 - s0) << 16);
+    const size_t first = all.size() * x / kNumXcd;
+    const int n = int(all.size() * (x + 1) / kNumXcd - first), full = n / geom.room * geom.room;
+    int left = n - full, S = split && left > 0 ? geom.room / left : 1;
+    if (S < 2 || n_pieces + left * S > 0xffff) left = 0, S = 1;
+    list.n[x] = n;
+    list.left[x] = left;
+    list.pieces[x] = S;
+    for (int p = 0; p < S; ++p)
+      for (int i = p == 0 ? 0 : n - left; i < n; ++i) {
+        int4 e = all[first + i];
+        const int at = i < n - left ? 0 : n_pieces + (i - (n - left)) * S;
+        e.w = i < n - left ? 1 << 16 : p | (S << 16);
         fin[x].push_back(e);
-        finp[x].push_back(n_pieces + p);
+        finp[x].push_back(int2{int(first) + i, at});
+        if (p == 0 && S > 1 && i >= n - left) split_tiles.push_back(int4{e.x, e.y, e.z, (S << 16) | at});
       }
-      n_pieces += S;
-    }
+    if (S > 1) n_pieces += left * S;
   }
   size_t slots = 0;
   for (auto& v : fin) slots = std::max(slots, v.size());
-  out.assign(size_t(kNumXcd) * slots, int4{-1, 0, 0, 0});
-  part.assign(size_t(kNumXcd) * slots, -1);
+  tiles.assign(size_t(kNumXcd) * slots, int4{-1, 0, 0, 0});
+  part.assign(size_t(kNumXcd) * slots, int2{0, 0});
   for (int x = 0; x < kNumXcd; ++x)
     for (size_t i = 0; i < fin[x].size(); ++i) {
-      out[x * slots + i] = fin[x][i];
+      tiles[x * slots + i] = fin[x][i];
       part[x * slots + i] = finp[x][i];
     }
-  return int(slots);
+  list.edge = geom.e;
+  list.slots = int(slots);
+  list.n_tiles = int(all.size());
+  list.n_split = int(split_tiles.size());
+  list.n_listed = int(lay.size());
+  csr = lay;
+  csr.insert(csr.end(), ranges.begin(), ranges.end());
 }
 
-std::vector<int> tiles_by_layer(const std::vector<int4>& tiles, const std::vector<char>& use, int& n_listed) {
-  std::vector<std::vector<int>> by_layer(use.size());
-  for (size_t k = 0; k < tiles.size(); ++k)
-    if (tiles[k].x >= 0) by_layer[tiles[k].x].push_back(int(k));
-  std::vector<int> lay, ptr(1, 0), idx;
-  for (size_t l = 0; l < use.size(); ++l) {
-    if (!use[l]) continue;
-    lay.push_back(int(l));
-    idx.insert(idx.end(), by_layer[l].begin(), by_layer[l].end());
-    ptr.push_back(int(idx.size()));
-  }
-  n_listed = int(lay.size());
-  lay.insert(lay.end(), ptr.begin(), ptr.end());
-  lay.insert(lay.end(), idx.begin(), idx.end());
-  return lay;
-}
-
-hipError_t launch_stats_tiles(const LayerDev* layers, const void* tiles, const int* part, int slots,
-                              const void* split, int n_split, float* partial_tiles, int B, int T,
-                              int dtype, int accumulate, bool short_form, float* tile_out, const int* lay,
-                              const int* ptr, const int* idx, int n_listed, float* partials, int n_pairs,
-                              hipStream_t st) {
-  if (slots <= 0) return hipSuccess;
-  const IpTileArgs a{layers, static_cast<const int4*>(tiles), tile_out, slots, T, B, part, partial_tiles, accumulate};
+hipError_t launch_stats_tiles(const LayerDev* layers, const TileList& list, int B, int T, int dtype, int accumulate,
+                              bool short_form, float* out, float* partials, hipStream_t st) {
+  const IpTileArgs a{layers, list.tiles(), out, list.slots, list.used(B), T, B, B, list.part(),
+                     static_cast<float*>(list.ptiles.ptr), accumulate};
   hipError_t e;
   if (short_form)
     e = launch_tiles(dtype == ADLOCO_F16 ? short_tile_kernel<1, true, true> : short_tile_kernel<1, true, false>, kStWaves,
@@ -972,12 +955,11 @@ hipError_t launch_stats_tiles(const LayerDev* layers, const void* tiles, const i
   else
     e = launch_tiles(ip_tile_variant<1, true>(dtype, T), kIpWaves, kIpLds, a, st);
   if (e != hipSuccess) return e;
-  if (n_split > 0)
-    hipLaunchKernelGGL(stats_tile_reduce_kernel, dim3(unsigned(n_split) * (kIpE / kIpRedRows)), dim3(kIpC), 0, st,
-                       layers, static_cast<const int4*>(split), partial_tiles, accumulate);
-  hipLaunchKernelGGL(stats_tile_finalize_kernel, dim3(unsigned(n_listed) * B), dim3(64), 0, st,
-                     static_cast<const int4*>(tiles), tile_out, B, tile_waves(short_form), lay, ptr, idx, B, partials,
-                     n_pairs);
+  if (list.n_split > 0 && B > 1)
+    hipLaunchKernelGGL(stats_tile_reduce_kernel, dim3(unsigned(list.n_split) * (kIpE / kIpRedRows)), dim3(kIpC), 0, st,
+                       layers, list.split(), B, a.partials, accumulate);
+  hipLaunchKernelGGL(stats_tile_finalize_kernel, dim3(unsigned(list.n_listed) * B), dim3(64), 0, st, out,
+                     tile_waves(short_form), list.layers(), list.ranges(), B, partials);
   return hipGetLastError();
 }
 

@@ -48,12 +48,12 @@ constexpr int kPtThreads = 256;
 
 struct PtArgs {
   const LayerDev* layers;
-  const int4* tiles;      // [8][slots]: (layer, e0, c0, first sample | samples << 16); layer < 0: none
-  double* out;            // [8 * slots][group][4 waves][2]: <tile_i, G tile> (MODE 0), sum of squares of tile_i
-  int slots, T, group;
-  const int* part;        // MODE 1, [8][slots]: -1: the entry covers all samples; else its partial tile
+  const int4* tiles;      // entries of a tile list, of which `used` slots per XCD are launched
+  const int2* part;       // the list's (tile, first partial tile)
+  double* out;            // MODE 0: [tile][B][2]: <tile_i, G tile>, sum of squares of tile_i; MODE 1 and 3, [tile][B]: the latter
+  int slots, used, T, B, group, whole;
   float* partials;        // MODE 1: [pieces][64W][64W]
-  int accumulate;         // MODE 1: G += sum instead of G = sum
+  int accumulate;         // MODE 1 and 2: G += sum instead of G = sum
 };
 
 template <typename E, int MODE, int W>
@@ -62,15 +62,18 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
   constexpr int kPieces = kEdge / 4;                         // pieces of four columns in a staged row
   constexpr int kLd = kK * kPieces / kPtThreads;             // pieces a thread stages per operand and chunk: 2
   __shared__ __attribute__((aligned(16))) float lds[2][2][kK][kEdge];
+  __shared__ double red[2][4][2];                            // sums of the four waves, samples in turn
   typedef typename PtVec<E>::type EV;
   typedef __attribute__((ext_vector_type(W))) float FV;
-  const int xcd = blockIdx.x % kNumXcd, slot = blockIdx.x / kNumXcd;
-  const int entry = xcd * g.slots + slot;
+  const int seq = blockIdx.x / kNumXcd, entry = blockIdx.x % kNumXcd * g.slots + seq % g.used;
   const int4 tile = g.tiles[entry];
   if (tile.x < 0) return;
+  const SampleRun S = MODE == 1 || MODE == 2 ? list_piece(tile.w, g.B, g.whole != 0) : list_run(tile.w, g.B, g.group, seq / g.used);
+  const int s0 = S.first, cnt = S.count;
+  if (cnt == 0) return;
+  const int2 part = g.part[entry];
   const LayerDev L = g.layers[tile.x];
   const int e0 = tile.y, c0 = tile.z, T = g.T;
-  const int s0 = tile.w & 0xffff, cnt = tile.w >> 16;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
@@ -189,9 +192,8 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
       if (MODE == 0) dot = pt_wave_sum(dot);
       sq = pt_wave_sum(sq);
       if (lane == 0) {
-        double* d = g.out + (((size_t)entry * g.group + sample) * 4 + wave) * 2;
-        d[0] = dot;
-        d[1] = sq;
+        red[sample & 1][wave][0] = dot;
+        red[sample & 1][wave][1] = sq;
       }
       ++sample;
       k = 0;
@@ -200,10 +202,15 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
     }
     if (more) store(st ^ 1);                      // (read last in the chunk before: everybody is past its barrier)
     __syncthreads();
+    if (MODE != 2 && last && threadIdx.x == 0) {  // (written again two samples, and so two barriers, later)
+      const double (*r)[2] = red[(sample - 1) & 1];
+      double* const d = g.out + ((size_t)part.x * g.B + s0 + sample - 1) * (MODE == 0 ? 2 : 1);
+      if (MODE == 0) d[0] = (r[0][0] + r[1][0]) + (r[2][0] + r[3][0]);
+      d[MODE == 0 ? 1 : 0] = (r[0][1] + r[1][1]) + (r[2][1] + r[3][1]);
+    }
   }
   if (MODE == 1 || MODE == 2) {
-    const int part = MODE == 1 ? g.part[entry] : -1;
-    float* pt = part >= 0 ? g.partials + (size_t)part * (kEdge * kEdge) : nullptr;
+    float* pt = MODE == 1 && cnt < g.B ? g.partials + (size_t)(part.y + (tile.w & 0xffff)) * (kEdge * kEdge) : nullptr;
 #pragma unroll
     for (int m = 0; m < W; ++m)
 #pragma unroll
@@ -226,12 +233,12 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
 // workgroup per 4 rows of a split tile, one thread per column;  split[t] = (layer, e0, c0, pieces << 16 | first piece).
 constexpr int kPtRedRows = 4;
 template <int EDGE>
-__global__ __launch_bounds__(EDGE) void plain_tile_reduce_kernel(const LayerDev* layers, const int4* split,
+__global__ __launch_bounds__(EDGE) void plain_tile_reduce_kernel(const LayerDev* layers, const int4* split, int B,
                                                                 const float* partials, int accumulate) {
   const int t = blockIdx.x / (EDGE / kPtRedRows), r0 = (blockIdx.x % (EDGE / kPtRedRows)) * kPtRedRows;
   const int4 S = split[t];
   const LayerDev L = layers[S.x];
-  const int pieces = S.w >> 16;
+  const int pieces = min(S.w >> 16, B);
   const float* base = partials + (size_t)(S.w & 0xffff) * (EDGE * EDGE) + threadIdx.x;
   const int col = S.z + threadIdx.x;
   float v[kPtRedRows];
@@ -249,25 +256,17 @@ __global__ __launch_bounds__(EDGE) void plain_tile_reduce_kernel(const LayerDev*
   }
 }
 
-// One workgroup per (listed layer, sample): the (tile, wave) sums of the layer's entries idx[ptr[q] .. ptr[q+1]).
-// dot (may be NULL) and sq receive one float per (layer, sample), `sq_stride` floats apart.
-__global__ __launch_bounds__(64) void plain_tile_finalize_kernel(const int4* tiles, const double* out, int group,
-                                                                const int* lay, const int* ptr, const int* idx,
-                                                                int B, float* dot, float* sq, int sq_stride) {
-  const int q = blockIdx.x / B, i = blockIdx.x % B;
+// One workgroup per (listed layer, sample): the sums of the layer's tiles ranges[q], .., ranges[q + 1] - 1.
+// dot (may be NULL; then `out` holds the sums of squares alone) and sq receive one float per (layer, sample), those of sq
+// `sq_stride` floats apart.
+__global__ __launch_bounds__(64) void plain_tile_finalize_kernel(const double* out, const int* lay, const int* ranges, int B,
+                                                                float* dot, float* sq, int sq_stride) {
+  const int q = blockIdx.x / B, i = blockIdx.x % B, width = dot ? 2 : 1;
   double d = 0.0, s = 0.0;
-  for (int k = ptr[q] + threadIdx.x; k < ptr[q + 1]; k += 64) {
-    const int e = idx[k];
-    const int w = tiles[e].w;
-    const int s0 = w & 0xffff, cnt = w >> 16;
-    if (i >= s0 && i < s0 + cnt) {
-      const double* o = out + ((size_t)e * group + (i - s0)) * 8;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        d += o[2 * v];
-        s += o[2 * v + 1];
-      }
-    }
+  for (int t = ranges[q] + threadIdx.x; t < ranges[q + 1]; t += 64) {
+    const double* o = out + ((size_t)t * B + i) * width;
+    if (dot) d += o[0];
+    s += o[width - 1];
   }
   d = pt_wave_sum(d);
   s = pt_wave_sum(s);
@@ -307,15 +306,16 @@ int plain_tile_width(const std::vector<LayerDev>& layers, const std::vector<char
   return pick;
 }
 
-hipError_t launch_plain_tiles(const LayerDev* layers, const PlainTiles& p, int mode, int B, int T, int dtype,
-                              int accumulate, float* dot, float* sq, int sq_stride, hipStream_t st) {
-  if (p.slots <= 0) return hipSuccess;
-  PtArgs a{layers, static_cast<const int4*>(p.tab.ptr), static_cast<double*>(p.out.ptr), p.slots, T, p.group,
-           static_cast<const int*>(p.part_idx.ptr), static_cast<float*>(p.ptiles.ptr), accumulate};
-  const dim3 grid(unsigned(p.slots) * kNumXcd), block(kPtThreads);
+hipError_t launch_plain_tiles(const LayerDev* layers, const TileList& list, int mode, int B, int T, int dtype, int accumulate,
+                              bool whole, int group, double* out, float* dot, float* sq, int sq_stride, hipStream_t st) {
+  const int used = mode == 1 && !whole ? list.used(B) : list.used(1);
+  const PtArgs a{layers, list.tiles(), list.part(), out, list.slots, used, T, B, group, whole ? 1 : 0,
+                 static_cast<float*>(list.ptiles.ptr), accumulate};
+  const int runs = mode == 0 || mode == 3 ? (B + group - 1) / group : 1;
+  const dim3 grid(unsigned(used) * unsigned(runs) * kNumXcd), block(kPtThreads);
 #define PT_LAUNCH(E, MODE)                                                                              \
   do {                                                                                                  \
-    if (p.W == 2) hipLaunchKernelGGL((plain_tile_kernel<E, MODE, 2>), grid, block, 0, st, a);           \
+    if (list.edge == 128) hipLaunchKernelGGL((plain_tile_kernel<E, MODE, 2>), grid, block, 0, st, a);   \
     else hipLaunchKernelGGL((plain_tile_kernel<E, MODE, 1>), grid, block, 0, st, a);                    \
   } while (0)
   if (mode == 2) PT_LAUNCH(float, 2);
@@ -325,20 +325,17 @@ hipError_t launch_plain_tiles(const LayerDev* layers, const PlainTiles& p, int m
   else if (dtype == ADLOCO_F16) PT_LAUNCH(_Float16, 0);
   else PT_LAUNCH(float, 0);
 #undef PT_LAUNCH
-  if (mode == 1 && p.n_split > 0) {
-    if (p.W == 2)
-      hipLaunchKernelGGL(plain_tile_reduce_kernel<128>, dim3(unsigned(p.n_split) * (128 / kPtRedRows)), dim3(128), 0,
-                         st, layers, static_cast<const int4*>(p.split.ptr), a.partials, accumulate);
+  if (mode == 1 && !whole && B > 1 && list.n_split > 0) {
+    if (list.edge == 128)
+      hipLaunchKernelGGL(plain_tile_reduce_kernel<128>, dim3(unsigned(list.n_split) * (128 / kPtRedRows)), dim3(128), 0,
+                         st, layers, list.split(), B, a.partials, accumulate);
     else
-      hipLaunchKernelGGL(plain_tile_reduce_kernel<64>, dim3(unsigned(p.n_split) * (64 / kPtRedRows)), dim3(64), 0,
-                         st, layers, static_cast<const int4*>(p.split.ptr), a.partials, accumulate);
+      hipLaunchKernelGGL(plain_tile_reduce_kernel<64>, dim3(unsigned(list.n_split) * (64 / kPtRedRows)), dim3(64), 0,
+                         st, layers, list.split(), B, a.partials, accumulate);
   }
-  if (sq) {
-    const int* csr = static_cast<const int*>(p.csr.ptr);
-    const int nl = p.n_listed;
-    hipLaunchKernelGGL(plain_tile_finalize_kernel, dim3(unsigned(nl) * B), dim3(64), 0, st, a.tiles, a.out, p.group,
-                       csr, csr + nl, csr + nl + nl + 1, B, dot, sq, sq_stride);
-  }
+  if (sq)
+    hipLaunchKernelGGL(plain_tile_finalize_kernel, dim3(unsigned(list.n_listed) * B), dim3(64), 0, st, out, list.layers(),
+                       list.ranges(), B, dot, sq, sq_stride);
   return hipGetLastError();
 }
 
