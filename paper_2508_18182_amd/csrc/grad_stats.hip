@@ -541,8 +541,12 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   // the list of the fp32 forms, and what a form leaves per (tile, sample)
   const TileList* list = &ctx->tiles16;
   size_t out_bytes = (tile_form ? tile_waves(short_form) : tile_waves(false)) * sizeof(float);
+  PlainChoice plain{2, false};
   if (plain_form || (square_form && dtype == ADLOCO_F32)) {
-    list = &ctx->tiles32[plain_tile_width(tab, ctx->tiles32[0].use, B) - 1];
+    if (plain_form && ctx->plain_tiles_tuning) plain = PlainChoice{ctx->plain_tiles_tuning & 3, (ctx->plain_tiles_tuning & 4) != 0};
+    else if (plain_form) plain = plain_tile_choice(ctx->tiles32, B, T);
+    else plain.W = plain_tile_width(tab, ctx->tiles32[0].use, B);
+    list = &ctx->tiles32[plain.W - 1];
     out_bytes = sizeof(double);
   }
   int group = 0;
@@ -554,8 +558,6 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   if (!list->built || ((tile_form || plain_form || square_form) &&
                        !obtain_scratch(ctx, ctx->tile_out, out_bytes * size_t(list->n_tiles) * B, st)))
     tile_form = plain_form = square_form = false;
-  // (adding up partial tiles is one more launch of about 5 us, as long as 512 token rows of a tile take)
-  const bool whole = rows <= 512;
   const bool formed = tile_form || plain_form || square_form;     // norms (and gradient sums) come from the tiles
   const TileList* sum_list = nullptr;
   if (dtype == ADLOCO_F32 && !formed && ctx->n_formed > 0 && rows < (1 << 30) && ctx->stats_variant != 0)
@@ -631,7 +633,7 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
     else if (square_form && is_16bit(dtype))
       e = launch_square_tiles(g.layers, *list, B, T, dtype, out16, g.partials, st);
     else
-      e = launch_plain_tiles(g.layers, *list, plain_form ? 1 : 3, B, T, dtype, accumulate, whole, group,
+      e = launch_plain_tiles(g.layers, *list, plain_form ? 1 : 3, B, T, dtype, accumulate, plain.whole, group,
                              static_cast<double*>(ctx->tile_out.ptr), nullptr, g.partials, 1, st);
     prof_end(ctx, kProfTileStats, ev, st);
     if (e != hipSuccess)

@@ -280,7 +280,7 @@ __global__ __launch_bounds__(64) void plain_tile_finalize_kernel(const double* o
 // ---- host side ------------------------------------------------------------------------------
 
 // 128-wide tiles need a quarter fewer LDS bytes per product and half the loads; 64-wide ones fill the chip on small
-// layers.  Time model in MFMA cycles per token row: w workgroups on a compute unit share its four SIMDs, a row costs a
+// layers.  Gradient sums, inner products and norms alone (runs of samples fill the last round).  Time model in MFMA cycles per token row: w workgroups on a compute unit share its four SIMDs, a row costs a
 // wave 128 (W = 2) or 32 cycles (W = 1) of its SIMD, and no less than 64 for the loop around the MFMAs.
 int plain_tile_width(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B) {
   double best = 0.0;
@@ -303,6 +303,47 @@ int plain_tile_width(const std::vector<LayerDev>& layers, const std::vector<char
       pick = W;
     }
   }
+  return pick;
+}
+
+// Statistics (mode 1): tile width, and whether the tiles of the incomplete last round are split along the samples, by a
+// time model in cycles of 2.1 GHz.  A workgroup on its own needs 2400 cycles (64-wide tiles; 128-wide: 2800) per chunk, from
+// load to load, and 2000 per finished tile; w workgroups on a compute unit no less than 1126 w (2048 w) and 300 w
+// (1200 w) of its SIMDs.  Split tiles cost one more launch, 8 us, and their partial tiles a trip through memory at 3 TB/s.
+// Of 270 calls on 1 to 16 layers with 32 to 2048 token rows, the choice is within 2 % of the best of the four forms on
+// average, within 18 % at worst; a fixed line at 512 rows (and 128-wide tiles as if always split) missed it by 12 % on
+// average and was 2.6 times slower at worst: one layer 768 -> 768, B 8, T 64 69 us instead of 34.
+PlainChoice plain_tile_choice(const TileList* lists, int B, int T) {
+  PlainChoice pick{2, false};
+  double best = 0.0;
+  for (int W = 1; W <= 2; ++W)
+    for (int whole = 1; whole >= 0; --whole) {
+      const TileList& p = lists[W - 1];
+      if (!p.built) continue;
+      const int room = plain_tile_room(W);
+      const double chunks = double((T + 32 / W - 1) / (32 / W));
+      auto run = [&](double wgs, double samples) {
+        return samples * (chunks * std::max((W == 2 ? 2048.0 : 1126.0) * wgs, W == 2 ? 2800.0 : 2400.0) +
+                          std::max((W == 2 ? 1200.0 : 300.0) * wgs, 2000.0));
+      };
+      double t = 0.0;
+      bool cut = false;
+      double bytes = 0.0;
+      for (int x = 0; x < kNumXcd; ++x) {
+        const int full = p.n[x] / room, left = p.n[x] % room, S = whole ? 1 : std::max(1, std::min(p.pieces[x], B));
+        double tx = full * run(room / 32.0, B);
+        if (left) tx += run(double((left * S + 31) / 32), double((B + S - 1) / S));
+        if (S > 1) bytes += double(left) * S * p.edge * p.edge * sizeof(float);
+        cut = cut || S > 1;
+        t = std::max(t, tx);
+      }
+      if (cut) t += 8.0 * 2100.0 + bytes / 3e6 * 2100.0;
+      if (!whole && !cut) continue;               // (the same form again)
+      if (best == 0.0 || t < best) {
+        best = t;
+        pick = PlainChoice{W, whole != 0};
+      }
+    }
   return pick;
 }
 

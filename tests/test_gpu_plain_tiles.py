@@ -81,3 +81,51 @@ def test_provided_blocks_are_left_alone(ctx):
     A.adloco_grad_stats(ctx, layers, B, T, A.ADLOCO_F32, None, None, None, A.ADLOCO_SUM_ONLY)
     assert bool((layers[0]["grad_sum"] == 7.0).all())
     assert np.max(np.abs(layers[1]["grad_sum"].cpu().numpy() - want["G"][1])) < 1e-4 * np.sqrt(np.mean(want["G"][1] ** 2))
+
+
+@pytest.mark.parametrize("form", [1, 2, 5, 6])     # 64- or 128-wide tiles, split along the samples or whole
+def test_forms_of_the_statistics(ctx, form):
+    # the same sums from every form that the time model chooses from, at a batch with fewer and with more samples than pieces
+    from gpu_util import rel_err, run_grad_stats
+    for B, T, shapes in ((5, 40, [(200, 136), (130, 70)]), (150, 3, [(64, 128)])):
+        layers = synth.custom_grad_stats_inputs(7300 + B, shapes, B, T, "f32", std_delta=0.2, rho=0.4)
+        want = orc.grad_stats([(l["a"], l["delta"]) for l in layers], two_pass=False)
+        ctx.set_tuning("plain_tiles", form)
+        got = run_grad_stats(ctx, layers)
+        ctx.set_tuning("plain_tiles", 0)
+        assert rel_err(got["per_layer"], want["n_layer_sample"]) < 1e-4
+        for g, w in zip(got["G"], want["G"]):
+            assert np.max(np.abs(g - w)) < 1e-4 * float(np.sqrt(np.mean(w * w)))
+
+
+@pytest.mark.parametrize("B,T,shapes", [
+    (1, 3, [(5, 7)]), (7, 33, [(63, 65), (130, 70)]),        # 64-wide tiles; odd row counts, unaligned widths
+    (3, 111, [(1032, 2056), (1030, 2049)]),                  # 128-wide tiles
+])
+def test_gradient_sum_is_the_vector_kernels_bit_for_bit(ctx, B, T, shapes):
+    # the matrix instruction adds the token rows in order, as fused multiply-adds, as the vector unit's kernel does: a
+    # training step divides by sqrt(v) right after, where a last bit matters.  Denormal inputs and products included
+    import torch
+    import paper_2508_18182_amd as A
+    from gpu_util import DEV, to_dev
+    host = synth.custom_grad_stats_inputs(7400 + B, shapes, B, T, "f32", std_delta=0.2, rho=0.4)
+    rng = np.random.default_rng(7)
+    out = []
+    layers = []
+    for l in host:
+        a, delta = l["a"].copy(), l["delta"].copy()
+        for x in (a, delta):
+            x[rng.random(x.shape) < 0.05] *= 1e-38            # denormal, and products that are
+            x[rng.random(x.shape) < 0.05] *= 1e-20
+        layers.append(dict(a=to_dev(a), delta=to_dev(delta)))
+    for variant in (1, 0):
+        ctx.set_tuning("stats_variant", variant)
+        G = [torch.full((l["d_out"], l["d_in"]), 0.25, device=DEV) for l in host]
+        for flags in (0, A.ADLOCO_ACCUMULATE):
+            A.adloco_grad_stats(ctx, [dict(l, grad_sum=g) for l, g in zip(layers, G)], B, T, A.ADLOCO_F32, None, None, None,
+                                A.ADLOCO_SUM_ONLY | flags)
+            out.append([g.clone() for g in G])
+    ctx.set_tuning("stats_variant", 1)
+    for k in (0, 1):
+        for x, y in zip(out[k], out[k + 2]):
+            assert torch.equal(x, y)
