@@ -361,6 +361,13 @@ int adloco_check_merge(const int64_t* b_req, int k, int w, int* sel_out, int* n_
  * adloco_round: one outer step t of Algorithm 3 for k trainers co-resident on the device,
  * as a host loop over the entry points above.  The model's forward / backward is the
  * caller's: the driver asks for it through `batch_fn`.
+ * One thing differs from calling them by hand: gradient sums of fp32 blocks, and of aligned 16-bit blocks
+ * whose B * T (with statistics: T) is no multiple of 32, are added up by the kernels that take all rows in
+ * order, and their norms come from the Gram contraction, which is slower than the sample-by-sample tiles
+ * that adloco_grad_stats takes there.  A round returns parameters after several AdamW steps; an entry whose
+ * gradient and second moment are both near zero turns a last bit of its gradient sum into up to 4e-4 of the
+ * outer momentum's norm, so the sums' order is kept fixed.  Neither order is the more accurate one: the
+ * figures of hand-sequenced calls agree up to fp32 summation order, not bit for bit.
  *
  *   1. k > 1: M_t = CheckMerge({b_req_i}, merge_w); if non-empty DoMerge (Algorithm 2) on the
  *      trainers' outer models with weights b_req; the merged-away trainers are moved to the end

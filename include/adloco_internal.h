@@ -14,8 +14,10 @@ extern "C" {
 #endif
 
 /* Tuning knob for benchmarking kernel variants ("gram_variant", "wgrad_variant",
- * "stream_blocks_per_cu", "ip_group", "stats_variant", "overlap_aux", ...).  Unknown names give
- * ADLOCO_EINVAL.  Results never depend on a knob beyond floating-point summation order. */
+ * "stream_blocks_per_cu", "ip_group", "stats_variant", "plain_tiles", "overlap_aux", ...), and
+ * "scratch_limit_kb", the largest scratch allocation that succeeds (0: no limit), for tests of what a call
+ * does without memory.  Unknown names give ADLOCO_EINVAL.  Results never depend on a knob beyond
+ * floating-point summation order. */
 int adloco_set_tuning(adloco_ctx* ctx, const char* name, int value);
 
 /* Measurement aid.  After adloco_set_tuning(ctx, "profile", 1) every launch of the named

@@ -5,8 +5,8 @@
 //   * the statistics of the norm test (eq. 4, Section 3.3.1): ||g_i||^2 from the squares of the
 //     tiles while they are being added up to G -- the route of adloco_grad_stats where G is
 //     formed by the library.
-// Aligned 16-bit layers take the MFMA tile kernel (ip_tile_kernel); every other layer the plain tile
-// kernel (tile_plain_kernels.hip).  The dot kernels of the vector / table blocks and the reductions
+// Aligned 16-bit layers take the MFMA tile kernels (ip_tile_kernel, and short_tile_kernel for short sequences); every
+// other layer the plain tile kernel (tile_plain_kernels.hip).  The dot kernels of the vector / table blocks and the reductions
 // follow.  The inner-product paths also return the explicit ||g_i||^2, a second
 // route to the Gram kernel's result.
 #include <type_traits>
@@ -51,16 +51,17 @@ __device__ __forceinline__ double ip_block_sum(double v, double* lds4) {
 //   Staging: global -> LDS directly, six stages of 32 token rows x (256 + 128) columns, loads five chunks ahead.  A
 //   load instruction moves 1 KiB: two token rows of delta (2 x 512 B) or four of a (4 x 256 B); the 1 KiB blocks are
 //   1056 bytes apart and the rows are dealt to them so that the eight rows that 32 lanes of a transpose read touch
-//   start in eight different groups of banks.  LDS reads and loads go out one by one behind the MFMAs, one barrier
+//   start in eight different groups of banks.  LDS reads go out one by one behind the MFMAs, loads in pairs from one
+//   scalar base (the rows are in the lane offsets: a scalar instruction counts here, with one wave per SIMD), one barrier
 //   per chunk.  Columns of a past the edge of the layer re-read the last valid 16-byte piece and are left out of every
 //   sum.  Columns of delta past the edge are never loaded: their lanes are switched off and the LDS is cleared
 //   beforehand; check_rows() takes care of what an infinite a makes of those zeros.  RAGGED (T not a multiple of 32):
 //   token rows past T come from a line of zeros.
 // What bounds it: the LDS (96 transpose reads of 512 B and 24 KiB of direct loads per chunk of 512 MFMA cycles) and the
-// chip's power.  48 GPT-2-small linears, B 32, T 512 (2.78 TFLOP): 2.82 ms for statistics, 2.95 ms for the inner
-// products with norms (eight waves of 64 x 64 with 32x32x16 MFMAs: 2.85 and 3.00 ms); without loads 2.4 ms, with loads
-// that all hit the L2 2.35 ms, without the work on finished tiles 2.6 ms.  The same linears in fp16 with B 5, T 1001,
-// added to a gradient sum: 1.10 ms (Gram kernel and 128 x 128 gradient-sum kernel: 2.37 ms).
+// chip's power.  48 GPT-2-small linears, B 32, T 512 (2.78 TFLOP): 2.73 ms for statistics, 2.85 ms for the inner
+// products with norms (eight waves of 64 x 64 with 32x32x16 MFMAs: 2.90 and 3.05 ms on the same card); without loads, with
+// loads that all hit the L2, or without the work on finished tiles each is 0.2 to 0.5 ms less.  The same linears in fp16
+// with B 5, T 1001, added to a gradient sum: 1.07 ms (Gram kernel and 128 x 128 gradient-sum kernel: 2.37 ms).
 // ---------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(4))) short ip_s16x4;
 typedef __attribute__((ext_vector_type(8))) short ip_s16x8;

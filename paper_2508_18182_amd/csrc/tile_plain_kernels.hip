@@ -38,9 +38,9 @@ __device__ __forceinline__ double pt_wave_sum(double v) {
 // two LDS stages and two (W = 2) to four (W = 1) workgroups per compute unit keep them fed; rows past T and columns
 // past the layer are staged as zeros, so any width, stride, alignment and sequence length runs here.  A chunk is
 // 32 / W token rows: 16 KiB of LDS and the same 1024 * W MFMA cycles in either form.
-// Statistics of 4 x {768 -> 2304, 768 -> 768, 768 -> 3072, 3072 -> 768}, B 8, T 256: 1.28 ms, 91 TFLOP/s (Gram and
-// gradient-sum kernels on the vector unit: 5.02 ms); inner products of one such block, B 4, T 250: 0.48 ms with the
-// statistics' read-back (one thread per gradient row: 145 ms).
+// Statistics of 4 x {768 -> 2304, 768 -> 768, 768 -> 3072, 3072 -> 768}, B 8, T 256: 1.25 ms, 93 TFLOP/s (Gram and
+// gradient-sum kernels on the vector unit: 5.02 ms); inner products of one such block, B 4, T 250: 0.18 ms (runs of
+// samples dealt to the XCDs layer by layer: 0.41 ms; one thread per gradient row: 145 ms).
 // W columns next to each other go to the W MFMA blocks of a wave (block m holds rows W * r + m): one LDS read of
 // W floats feeds W blocks, and a lane owns W consecutive columns of G.
 // ---------------------------------------------------------------------------------------

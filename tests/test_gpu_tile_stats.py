@@ -1,8 +1,9 @@
 """GPU parity of the route of adloco_grad_stats that takes the per-sample norms from the 256 x 128
-tiles of the per-sample gradients on their way into the gradient sum (aligned bf16 blocks,
-T % 32 == 0, gradient sum formed by the library), against the CPU oracle and against the Gram
-route: tiles on the edge of a layer, entries split along the samples (few tiles) and whole entries
-(more than 32 tiles on an XCD), accumulation over micro-batches, bitwise repeatability."""
+tiles of the per-sample gradients on their way into the gradient sum (aligned bf16 and fp16 blocks,
+gradient sum formed by the library), against the CPU oracle and against the Gram route: short and
+long sequences (a kernel each), ragged ones, tiles on the edge of a layer, entries split along the
+samples (few tiles) and whole entries (more than 32 tiles on an XCD), accumulation over
+micro-batches, bitwise repeatability."""
 import numpy as np
 import pytest
 
@@ -156,7 +157,8 @@ def test_tile_route_ragged_sequences(ctx, dtype, B, T, shapes):
 
 @pytest.mark.parametrize("B,T", [(3, 32), (2, 96), (5, 256),        # the tile kernel for short sequences: one chunk, odd, even
                                  (2, 288), (3, 320),                # statistics by the other one, odd and even
-                                 (2, 544), (2, 576)])               # inner products too
+                                 (2, 544), (2, 576),                # inner products too
+                                 (1, 64), (1, 288)])                # one piece: tiles stored where they belong
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
 def test_short_and_long_sequences(ctx, dtype, B, T):
     import torch
