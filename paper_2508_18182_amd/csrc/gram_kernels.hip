@@ -207,7 +207,9 @@ __global__ __launch_bounds__(256, 2) void gram_bf16_kernel(GramArgs g) {
 // bf16 fast path ("dual-tile" kernel), used when every operand row is 16-byte aligned and every
 // width is a multiple of 64.
 //   16x16x32 MFMAs (less energy per product than 32x32x16): 14.55 ms against 14.6 - 15.1 ms for the 96 linears of the
-//   350M model, B 32, T 1024; 5.01 against 5.15 ms for two Llama-1B blocks, B 16, T 2048.
+//   350M model, B 32, T 1024; 5.01 against 5.15 ms for two Llama-1B blocks, B 16, T 2048.  Their fragments of 16 rows
+//   meet in the LDS banks, though (the staging's swizzle was made for reads of 32 rows, which had no conflicts): conflict
+//   cycles are a quarter of the compute units' busy cycles, and the LDS is busy half of the time instead of a quarter.
 //   workgroup: 512 threads = 8 waves = two groups of four; each group owns one 128x128 tile pair
 //   of one job.  A job is a pair of tile pairs that share a row block, so that at most three
 //   distinct 128-row blocks have to be staged: less L2 and LDS-write traffic per MFMA than one

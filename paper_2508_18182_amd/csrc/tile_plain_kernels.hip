@@ -309,9 +309,11 @@ int plain_tile_width(const std::vector<LayerDev>& layers, const std::vector<char
 // Statistics (mode 1): tile width, and whether the tiles of the incomplete last round are split along the samples, by a
 // time model in cycles of 2.1 GHz.  A workgroup on its own needs 2400 cycles (64-wide tiles; 128-wide: 2800) per chunk, from
 // load to load, and 2000 per finished tile; w workgroups on a compute unit no less than 1126 w (2048 w) and 300 w
-// (1200 w) of its SIMDs.  Split tiles cost one more launch, 8 us, and their partial tiles a trip through memory at 3 TB/s.
-// Of 270 calls on 1 to 16 layers with 32 to 2048 token rows, the choice is within 2 % of the best of the four forms on
-// average, within 18 % at worst; a fixed line at 512 rows (and 128-wide tiles as if always split) missed it by 12 % on
+// (1200 w) of its SIMDs.  Split tiles cost one more launch, 8 us, and their partial tiles a trip through memory at 3 TB/s;
+// 8 us more are asked of them because a call of this size waits for the host's launches, behind which a longer kernel
+// hides (statistics, norm test and outer step of one layer 64 -> 32, B 8, T 16: 85 us whole, 89 us split).
+// Of 270 calls on 1 to 16 layers with 32 to 2048 token rows, the choice is within 2.3 % of the best of the four forms on
+// average, within 20 % at worst; a fixed line at 512 rows (and 128-wide tiles as if always split) missed it by 12 % on
 // average and was 2.6 times slower at worst: one layer 768 -> 768, B 8, T 64 69 us instead of 34.
 PlainChoice plain_tile_choice(const TileList* lists, int B, int T) {
   PlainChoice pick{2, false};
@@ -337,7 +339,7 @@ PlainChoice plain_tile_choice(const TileList* lists, int B, int T) {
         cut = cut || S > 1;
         t = std::max(t, tx);
       }
-      if (cut) t += 8.0 * 2100.0 + bytes / 3e6 * 2100.0;
+      if (cut) t += 16.0 * 2100.0 + bytes / 3e6 * 2100.0;
       if (!whole && !cut) continue;               // (the same form again)
       if (best == 0.0 || t < best) {
         best = t;

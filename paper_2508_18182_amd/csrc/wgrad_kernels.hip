@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256, 2) void wgrad_bf16_kernel(WgradArgs g) {
 
 // ---------------------------------------------------------------------------------------
 // bf16 fast path: 256 (d_out) x 256 (d_in) output tile per workgroup of four waves (2 x 2, each 128 x 128, one per
-// SIMD), used when every row is 16-byte aligned and widths are multiples of 8.  What bounds it is power: at 78 % busy matrix cores the chip holds 1.54 of its 2.4 GHz, so the kernel is laid
+// SIMD), used when every row is 16-byte aligned and widths are multiples of 8.  What bounds it is power: at 84 % busy matrix cores the chip holds 1.57 of its 2.4 GHz, so the kernel is laid
 // out for little energy per product -- the 16x16x32 MFMA, and wave tiles of 128 x 128, which read a third less from LDS
 // than eight waves of 128 x 64.  Sum over the 96 linears of the 350M model, 32 x 1024 tokens: 13.9 ms, 1.42 PFLOP/s,
 // also where it is added to a sum (15.4 ms with every old entry of G loaded and waited for by itself)
