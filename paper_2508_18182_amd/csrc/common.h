@@ -55,6 +55,14 @@ __device__ __forceinline__ mfma_f32x4 mfma_16x16x32_v(mfma_bf16x8 a, mfma_bf16x8
   else
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
+// The same with the accumulator in vector registers.
+template <bool F16>
+__device__ __forceinline__ void mfma_16x16x32_vgpr(mfma_f32x4& c, mfma_bf16x8 a, mfma_bf16x8 b) {
+  if constexpr (F16)
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+  else
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
 // The same from zero: the old accumulators are only overwritten.  A reader of the old values in between needs no fence
 // if many MFMAs lie between the one that wrote them and itself.
 template <bool F16>
@@ -76,6 +84,13 @@ template <int M, int N> __device__ __forceinline__ void mfma_fence(mfma_f32x4 (&
   for (int m = 0; m < M; ++m)
 #pragma unroll
     for (int n = 0; n < N; ++n) asm volatile("" : "+a"(acc[m][n]));   // ordered behind the wait states
+}
+template <int M, int N> __device__ __forceinline__ void mfma_fence_v(mfma_f32x4 (&acc)[M][N]) {     // ... in vector registers
+  asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+  for (int m = 0; m < M; ++m)
+#pragma unroll
+    for (int n = 0; n < N; ++n) asm volatile("" : "+v"(acc[m][n]));
 }
 
 // MI355X: 256 compute units in 8 XCDs; consecutive workgroup ids are dealt round-robin to
@@ -304,6 +319,7 @@ struct adloco_ctx {
                                // 1 last, 2 spread; -1: first for long sequences (T >= 768), last for short
                                // ones (measured: +9 % at T = 1024, -1.5 % at T = 512 for `first`)
   bool all_fast64 = false;     // every layer: aligned rows and widths that are multiples of 64
+  int min_width = 0;           // smallest width of a linear block
   adloco::Scratch wgx_tab;     // tile table of the fast gradient-sum kernel
   int wgx_slots = 0;           // tiles per XCD in that table (0: not built for this layer table)
   adloco::Scratch wgx_split;   // split tiles (layer, e0, c0, pieces) for the reduction
@@ -358,7 +374,7 @@ struct adloco_ctx {
   std::vector<hipEvent_t> prof_free;
   int profile = 0;
   // tuning
-  int gram_variant = 1;        // 1: dual-tile kernel when eligible, 0: always the generic one
+  int gram_variant = 1;        // 1: region or dual-tile kernel when eligible; 2, 3: the latter, the former; 0: always the generic one
   int wgrad_variant = 2;       // 2: 256x256 fast kernel when eligible; 1/0: 128x128 kernel (LDS transpose reads / gathers)
   int stream_blocks_per_cu = 0;   // resident workgroups per CU of the streaming kernels; 0: automatic
   int stream_variant = 0;
@@ -429,6 +445,10 @@ int gram_tile_edge(int dtype, int variant);
 hipError_t launch_gram_bf16_dual(const GramLaunch& g, const GramGroup* groups, const GramJob* jobs,
                                  int n_jobs, int variant, hipStream_t st);
 int gram_dual_parts(int n_jobs);
+// The same on 256 x 256 regions of the Gram matrices, for sequences that fill them: widths of at least 128 and
+// (T + 256) * row stride below 2^31 elements; g.n_pairs = 4 * gram_region_jobs(T) partial sums per (layer, sample).
+int gram_region_jobs(int T);
+hipError_t launch_gram_region(const GramLaunch& g, const GramGroup* groups, hipStream_t st);
 hipError_t launch_gram_bf16(const GramLaunch& g, int variant, hipStream_t st);
 hipError_t launch_gram_f32(const GramLaunch& g, hipStream_t st);
 int wgrad_tile_edge(int dtype);

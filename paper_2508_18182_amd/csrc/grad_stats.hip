@@ -216,6 +216,9 @@ int prepare_tables(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_laye
   for (const LayerDev& L : tab)
     if (L.kind == ADLOCO_KIND_LINEAR) f64 = f64 && L.fast && L.d_in % 64 == 0 && L.d_out % 64 == 0;
   ctx->all_fast64 = f64;
+  ctx->min_width = 0x7fffffff;
+  for (const LayerDev& L : tab)
+    if (L.kind == ADLOCO_KIND_LINEAR) ctx->min_width = std::min(ctx->min_width, std::min(L.d_in, L.d_out));
   long long widest = 0;
   for (const LayerDev& L : tab)
     if (L.kind == ADLOCO_KIND_LINEAR) widest = std::max(widest, std::max(L.a_stride, L.delta_stride));
@@ -426,29 +429,64 @@ int prepare_vector_table(adloco_ctx* ctx, int B, int T, hipStream_t st) {
   return ADLOCO_OK;
 }
 
+// Time of the Gram contraction of 16-bit blocks by the dual-tile and the region kernel, in microseconds: cycles of the jobs
+// (of a chunk of 64 elements: 1024 off the diagonal and 768 on it; region 2048 and 1152) and of their starts over 256
+// workgroups and a rate, plus most of a job at the end, and no less than the longest job.  Jobs of the region kernel are
+// twice as large and start more slowly, so it needs more of them to fill the chip, and its jobs on and off the diagonal
+// share no rows through the L2, so it streams every row twice from memory.  Fitted to 389 lists (T 64 .. 4096, widths
+// 128 .. 8192, 1 to 2000 units): the choice is within 1.2 % of the better kernel on average and 35 % at worst.  Measured,
+// dual -> region: 350M model, B 32, T 1024 13.7 -> 11.4 ms; two Llama-1B blocks, B 16, T 2048 4.88 -> 3.82; GPT-2-small,
+// B 32, T 512 1.50 -> 1.35, T 256 0.58 -> 0.41; two blocks of it, B 4, T 512 0.055 -> 0.083, not taken.
+struct GramTime { double dual, region; };
+GramTime gram_time(const std::vector<LayerDev>& tab, int B, int T) {
+  std::vector<double> k(tab.size(), 0.0);          // elements that a job contracts; layers that share activations are one
+  double bytes = 0.0;
+  for (size_t l = 0; l < tab.size(); ++l) {
+    const LayerDev& L = tab[l];
+    if (L.kind != ADLOCO_KIND_LINEAR) continue;
+    const double more = L.d_out + (L.a_twin < 0 ? L.d_in : 0);
+    bytes += more * B * T * 2.0;
+    k[L.a_twin < 0 ? l : size_t(L.a_twin)] += more;
+  }
+  auto model = [&](int edge, double off, double on, int per_job, double start, double rate) {
+    const double n = (T + edge - 1) / edge;
+    const double n_off = std::ceil(n * (n - 1) / 2 / per_job) * B, n_on = std::ceil(n / per_job) * B;
+    double work = 0.0, jobs = 0.0, longest = 0.0;
+    for (double x : k) {
+      if (x == 0.0) continue;
+      work += n_off * (x / 64 * off + start) + n_on * (x / 64 * on + start);
+      jobs += n_off + n_on;
+      longest = std::max(longest, x / 64 * (n_off > 0 ? off : on) + start);
+    }
+    return (jobs > kNumCu ? std::max(longest, work / kNumCu + 0.76 * work / jobs) : longest) / rate;
+  };
+  return GramTime{model(128, 1024, 768, 2, 5900, 1225),
+                  std::max(model(256, 2048, 1152, 1, 10400, 1485), bytes * (T > 256 ? 2 : 1) / 6.6e6)};
+}
+
 // Norms of linear blocks whose gradient sums are supplied: true where the tiles of the per-sample gradients
 // (2 d_in d_out T products) take less time than the Gram contraction ((d_in + d_out) T (T + 1)), as on sequences that
 // are long for the widths.  Microseconds from measured rates: 16-bit tiles 0.95 PFLOP/s on 256 workgroups of 256 x 128
-// (0.55 where widths are no multiple of 64: the pieces of a row straddle cache lines), the Gram kernel 0.92 (its general
-// form, for such widths, 0.35); fp32 tiles 80 TFLOP/s on 512 workgroups of 128 x 128, the fp32 Gram kernel 23; 20 us for
+// (0.55 where widths are no multiple of 64: the pieces of a row straddle cache lines), the general Gram kernel for such
+// widths 0.35; fp32 tiles 80 TFLOP/s on 512 workgroups of 128 x 128, the fp32 Gram kernel 23; 20 us for
 // starts and ends.  Measured, Gram -> tiles: bf16 7 x {600 -> 1800, ..}, B 3, T 2688 2.77 -> 0.77 ms; 6 x {320 -> 960,
 // ..}, B 6, T 1792 0.90 -> 0.37; fp32 {512 -> 1408, ..}, B 11, T 1395 8.3 -> 1.1; {1336 -> 4008, ..}, B 3, T 1024 stays
 // with the Gram kernel: 0.28 against 0.40.
-bool tiles_beat_gram(const std::vector<LayerDev>& tab, int B, int T, int dtype, bool dual) {
-  const bool b16 = is_16bit(dtype);
+// gram_us: the time of the kernels for widths that are multiples of 64 (0: they do not take this call).
+bool tiles_beat_gram(const std::vector<LayerDev>& tab, int B, int T, int dtype, double gram_us) {
+  const bool b16 = is_16bit(dtype), fast = gram_us > 0.0;
   const long long te = b16 ? 256 : 128, tc = 128, gt = b16 ? 128 : 32, wgs = b16 ? 256 : 512;
-  const double tile_rate = b16 ? (dual ? 9.5e8 : 5.5e8) : 8e7, gram_rate = b16 ? (dual ? 9.2e8 : 3.5e8) : 2.3e7;   // flop per us
+  const double tile_rate = b16 ? (fast ? 9.5e8 : 5.5e8) : 8e7, gram_rate = b16 ? 3.5e8 : 2.3e7;   // flop per us
   const double nt = double((T + gt - 1) / gt);
   double tiles = 0.0, gram = 0.0;
   for (const LayerDev& L : tab) {
     if (L.kind != ADLOCO_KIND_LINEAR) continue;
     tiles += double((L.d_out + te - 1) / te) * double((L.d_in + tc - 1) / tc);
-    // (layers that share their activations share that half of the contraction)
-    gram += nt * (nt + 1) * gt * gt * ((dual && T % 128 == 0 && L.a_twin >= 0 ? 0 : L.d_in) + L.d_out);
+    gram += nt * (nt + 1) * gt * gt * (double(L.d_in) + L.d_out);
   }
   const double per_round = 2.0 * te * tc * double((T + 31) / 32 * 32) * wgs / tile_rate;
   const double t_tiles = std::max(1.0, tiles * B / wgs) * per_round + 20.0;
-  return t_tiles < 0.95 * gram * B / gram_rate;
+  return t_tiles < 0.95 * (fast ? gram_us : gram * B / gram_rate);
 }
 
 // Gradient sums formed here: true where the tiles of the per-sample gradients, whose samples are padded to whole chunks
@@ -456,17 +494,19 @@ bool tiles_beat_gram(const std::vector<LayerDev>& tab, int B, int T, int dtype, 
 // no padding: short sequences on wide layers go the second way.  Rates as above, gradient sums at 1.2 PFLOP/s / 80
 // TFLOP/s; the work on a finished 16-bit tile is worth 48 token rows.  Measured, fp16: {1024 -> 3072, ..} x 4, B 8, T 17
 // 0.30 ms by tiles, 0.23 the second way; {512 -> 1536, ..}, B 8, T 333 0.11 against 0.14.
-bool formed_tiles_pay(const std::vector<LayerDev>& tab, int T, int dtype, bool dual) {
+// gram_us: as above, for one sample.
+bool formed_tiles_pay(const std::vector<LayerDev>& tab, int T, int dtype, double gram_us) {
   const bool b16 = is_16bit(dtype);
   const long long gt = b16 ? 128 : 32, chunk = b16 ? 32 : 16;
-  const double tile_rate = b16 ? 9.5e8 : 8e7, gram_rate = b16 ? (dual ? 9.2e8 : 3.5e8) : 2.3e7, sum_rate = b16 ? 1.2e9 : 8e7;
+  const double tile_rate = b16 ? 9.5e8 : 8e7, gram_rate = b16 ? 3.5e8 : 2.3e7, sum_rate = b16 ? 1.2e9 : 8e7;
   const double nt = double((T + gt - 1) / gt), rows = double((T + chunk - 1) / chunk * chunk + (b16 ? 48 : 0));
-  double tiles = 0.0, gram = 0.0;
+  double tiles = 0.0, gram = gram_us;
   for (const LayerDev& L : tab) {
     if (L.kind != ADLOCO_KIND_LINEAR) continue;
     const double io = 2.0 * L.d_in * L.d_out;
     tiles += io * rows / tile_rate;
-    gram += nt * (nt + 1) * gt * gt * (double(L.d_in) + L.d_out) / gram_rate + io * T / sum_rate;
+    if (gram_us == 0.0) gram += nt * (nt + 1) * gt * gt * (double(L.d_in) + L.d_out) / gram_rate;
+    gram += io * T / sum_rate;
   }
   return tiles <= gram;
 }
@@ -504,8 +544,14 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   // (the dual-tile kernel addresses a sample's rows with 32-bit byte offsets)
   const bool dual = is_16bit(dtype) && ctx->gram_variant != 0 && ctx->all_fast64 &&
                     (long long)T * ctx->max_lin_stride < (1LL << 31) - 64;
+  const GramTime gram_us = dual ? gram_time(ctx->layer_tab_host, B, T) : GramTime{0.0, 0.0};
+  const bool region = dual && ctx->min_width >= 128 && ((long long)T + 256) * ctx->max_lin_stride < (1LL << 31) &&
+                      (ctx->gram_variant == 3 || (ctx->gram_variant == 1 && gram_us.region < gram_us.dual));
+  const double t_gram = region ? gram_us.region : gram_us.dual;
   long long n_pairs = nt * (nt + 1) / 2;      // partial sums per (layer, sample)
-  if (dual) {
+  if (region) {
+    n_pairs = 4 * gram_region_jobs(T);
+  } else if (dual) {
     if (ctx->job_tab_nt != int(nt)) {
       ++ctx->table_builds;
       std::vector<GramJob> jobs = make_gram_jobs(int(nt), ctx->gram_job_order >= 0 ? ctx->gram_job_order : (nt >= 6 ? 0 : 1));
@@ -531,11 +577,11 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   const bool all_formed = ctx->n_formed == ctx->n_linear;
   const std::vector<LayerDev>& tab = ctx->layer_tab_host;
   bool tile_form = !sum_only && tiles_allowed && all_formed && ctx->tiles16.built && is_16bit(dtype) &&
-                   (T % 32 == 0 || (!pinned_order && formed_tiles_pay(tab, T, dtype, dual))) && T <= (1 << 20);
+                   (T % 32 == 0 || (!pinned_order && formed_tiles_pay(tab, T, dtype, t_gram / B))) && T <= (1 << 20);
   bool plain_form = !sum_only && tiles_allowed && all_formed && dtype == ADLOCO_F32 && !pinned_order &&
-                    formed_tiles_pay(tab, T, dtype, dual);
+                    formed_tiles_pay(tab, T, dtype, t_gram / B);
   bool square_form = !sum_only && tiles_allowed && ctx->n_formed == 0 && T <= (1 << 20) &&
-                     (dtype == ADLOCO_F32 || ctx->tiles16.built) && tiles_beat_gram(tab, B, T, dtype, dual);
+                     (dtype == ADLOCO_F32 || ctx->tiles16.built) && tiles_beat_gram(tab, B, T, dtype, t_gram);
   const bool short_form = tile_form && short_sequences(tab, ctx->tiles16.use, B, T, false);
   const long long rows = (long long)B * T;
   // the list of the fp32 forms, and what a form leaves per (tile, sample)
@@ -646,11 +692,14 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
     // the dual-tile kernel walks groups of layers that share their activations (A A^T once per group)
     // when some do and no tile is ragged, else every layer by itself
     GramLaunch gd = g;
-    const bool grouped = ctx->n_groups < ctx->n_linear && T % tile == 0;
+    const bool grouped = ctx->n_groups < ctx->n_linear && (region || T % tile == 0);
     const char* base = static_cast<const char*>(ctx->group_tab.ptr) + (grouped ? 0 : ctx->single_off);
     gd.n_layers = grouped ? ctx->n_groups : ctx->n_linear;
     gd.order = reinterpret_cast<const int*>(base + size_t(gd.n_layers) * sizeof(GramGroup));
-    e = launch_gram_bf16_dual(gd, reinterpret_cast<const GramGroup*>(base),
+    if (region)
+      e = launch_gram_region(gd, reinterpret_cast<const GramGroup*>(base), st);
+    else
+      e = launch_gram_bf16_dual(gd, reinterpret_cast<const GramGroup*>(base),
                               static_cast<const GramJob*>(ctx->job_tab.ptr), ctx->job_tab_n,
                               grouped ? kGramGroupMax : 1, st);
   }

@@ -68,6 +68,9 @@ constexpr int kGramLds = 2 * kStageBytes;             // two stages: 64 KiB
 
 __device__ __forceinline__ int swz(int row, int chunk) { return chunk ^ ((row ^ (row >> 3)) & 7); }
 
+// The same for fragments of 16 rows: with `swz` half of a read's lane groups meet in the banks (10.9 against 7.1 cycles).
+__device__ __forceinline__ int swz16(int row, int chunk) { return chunk ^ (row & 7); }
+
 struct ChunkRegs { u32x4 v[8]; };
 
 // Load the 16-byte pieces this thread stages for k-chunk `c` of the concatenated operand
@@ -207,9 +210,9 @@ __global__ __launch_bounds__(256, 2) void gram_bf16_kernel(GramArgs g) {
 // bf16 fast path ("dual-tile" kernel), used when every operand row is 16-byte aligned and every
 // width is a multiple of 64.
 //   16x16x32 MFMAs (less energy per product than 32x32x16): 14.55 ms against 14.6 - 15.1 ms for the 96 linears of the
-//   350M model, B 32, T 1024; 5.01 against 5.15 ms for two Llama-1B blocks, B 16, T 2048.  Their fragments of 16 rows
-//   meet in the LDS banks, though (the staging's swizzle was made for reads of 32 rows, which had no conflicts): conflict
-//   cycles are a quarter of the compute units' busy cycles, and the LDS is busy half of the time instead of a quarter.
+//   350M model, B 32, T 1024; 5.01 against 5.15 ms for two Llama-1B blocks, B 16, T 2048.  Their fragments of 16 rows are
+//   free of bank conflicts with swz16 (with the swizzle for 32 rows conflict cycles were a quarter of the busy cycles;
+//   without them the times are 0 - 2 % lower: the loads bound the kernel, not the LDS).
 //   workgroup: 512 threads = 8 waves = two groups of four; each group owns one 128x128 tile pair
 //   of one job.  A job is a pair of tile pairs that share a row block, so that at most three
 //   distinct 128-row blocks have to be staged: less L2 and LDS-write traffic per MFMA than one
@@ -308,7 +311,7 @@ __global__ __launch_bounds__(512, 1) void gram_bf16_dual_kernel(GramDualArgs g) 
   // row groups w and w+8 of each staged block.  Rows beyond T re-read row T-1 (their products
   // are masked in the epilogue).
   const int ld_row = wave * 8 + (lane >> 3);         // row within the block for i = 0; +64 for i = 1
-  const int ld_col = swz(ld_row, lane & 7) * 8;      // element offset within the 64-wide chunk
+  const int ld_col = swz16(ld_row, lane & 7) * 8;    // element offset within the 64-wide chunk
   // Address = (sample's first row + chunk's first column: wave-uniform, scalar registers) + (row
   // within the sample, position within the chunk: a 32-bit byte offset per lane, computed once for
   // each operand; the host keeps T * row stride below 2^31 elements).
@@ -417,7 +420,7 @@ __global__ __launch_bounds__(512, 1) void gram_bf16_dual_kernel(GramDualArgs g) 
     for (int f = 0; f < 2 * NF; ++f) {
       const int row = (S::from_b(f >> 1) ? slot_b : slot_a) * kTile + S::frag_block(f >> 1, wq) * 32 + (f & 1) * 16 + r16;
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) pre[ks][f] = unsigned(row * ROWB + ((ks * 4 + kg) ^ swz(row, 0)) * 16);
+      for (int ks = 0; ks < 2; ++ks) pre[ks][f] = unsigned(row * ROWB + swz16(row, ks * 4 + kg) * 16);
     }
     auto read_frags = [&](int st, int ks, bf16x8 (&f)[2 * NF]) {
       const unsigned stage = lds_base + unsigned(st) * st_bytes;
@@ -514,6 +517,441 @@ __global__ __launch_bounds__(512, 1) void gram_bf16_dual_kernel(GramDualArgs g) 
       default: run(GramShapeDiag<3>{}); break;
     }
   }
+}
+
+// ---------------------------------------------------------------------------------------
+// 16-bit fast path for long sequences ("region" kernel): 256 x 256 regions of the Gram matrices.
+//   The dual-tile kernel moves 12 rows of a chunk from L2 to LDS per 32 x 32 block of a tile pair, and is held by
+//   those loads (350M model, B 32, T 1024: 161 GB in 13.7 ms, matrix cores 50 % busy at 1.84 GHz; this kernel: 116 GB in
+//   11.4 ms, 68 % at 1.60 GHz, where the chip's power holds it).  Here a workgroup of four waves, one per SIMD, owns 256 rows x 256 columns:
+//   8 rows per block while the first operand X is contracted.  Both products of a region do not fit the register
+//   file, so X X^T (the wider of a and delta; a where layers share it) stays complete in the 256 accumulation
+//   registers and Y Y^T is formed in two halves of 256 x 128 in 128 vector registers (12 rows per block), each
+//   multiplied with its half of X X^T.  A region on the diagonal has its 36 upper 32 x 32 blocks dealt nine to a
+//   wave, both products complete, from 256 rows (7.1 per block).
+//   Staging as in the dual-tile kernel (direct loads, chunks of 64 elements, one barrier a chunk): when the second
+//   k-step of a chunk begins, all its fragments have been read and its stage takes the loads of a later chunk.
+// ---------------------------------------------------------------------------------------
+constexpr int kRegion = 256;
+constexpr int kRegionLds = 160 << 10;
+constexpr unsigned kRegStX = 64 << 10;      // X off the diagonal: two stages of 256 + 256 rows; chunk c of n in stage (n - 1 - c) & 1
+constexpr unsigned kRegStD = 32 << 10;      // on the diagonal: four stages of 256 rows
+// Y off the diagonal: three stages of 256 + 128 rows.  The last chunk of X lies in bytes 0 .. 64 K, so the first two are
+// free when the chunk before it has been read.
+__device__ __forceinline__ unsigned region_st_y(int i) { return (i == 0 ? 64u : i == 1 ? 112u : 0u) << 10; }
+
+struct GramRegionArgs {
+  const LayerDev* layers;
+  const GramGroup* groups;
+  const int* order;         // launch order of group indices
+  float* partials;          // [layer][sample][n_jobs * 4]: one partial sum per job and wave
+  int n_groups, B, T, n_jobs, n_blocks;
+};
+
+// Region `job` of a unit of n row blocks: the ones off the diagonal row by row, then the (shorter) ones on it; the other
+// way round the 350M model takes 11.65 instead of 11.45 ms, two Llama-1B blocks with T 2048 3.93 instead of 3.81.
+__device__ __forceinline__ int2 region_of(int job, int n) {
+  const int off = n * (n - 1) / 2;
+  if (job >= off) return make_int2(job - off, job - off);
+  int r = 0, left = job;
+  while (left >= n - 1 - r) left -= n - 1 - r++;
+  return make_int2(r, r + 1 + left);
+}
+
+// The accumulation registers of this kernel belong to its assembly: all 256 hold products, and the compiler, asked to keep
+// 64 blocks of four there, loses itself in copies.  Register numbers are constants after unrolling; nothing else in the
+// kernel uses the accumulation half of the register file (a test looks for it in the assembly).  The hazards are as for
+// mfma_16x16x32: areg_fence() around ordinary accesses.
+template <bool F16> __device__ __forceinline__ void mfma_areg(int r, bf16x8 a, bf16x8 b) {
+  if constexpr (F16)
+    asm volatile("v_mfma_f32_16x16x32_f16 a[%2:%3], %0, %1, a[%2:%3]" :: "v"(a), "v"(b), "i"(r), "i"(r + 3));
+  else
+    asm volatile("v_mfma_f32_16x16x32_bf16 a[%2:%3], %0, %1, a[%2:%3]" :: "v"(a), "v"(b), "i"(r), "i"(r + 3));
+}
+__device__ __forceinline__ void areg_zero(int r) { asm volatile("v_accvgpr_write_b32 a[%0:%0], 0" :: "i"(r)); }
+__device__ __forceinline__ float areg(int r) {
+  float v;
+  asm volatile("v_accvgpr_read_b32 %0, a[%1:%1]" : "=v"(v) : "i"(r));
+  return v;
+}
+// Zero in a vector register, written here and not earlier, where the register may still be needed.
+__device__ __forceinline__ float vreg_zero() {
+  float v;
+  asm volatile("v_mov_b32 %0, 0" : "=v"(v));
+  return v;
+}
+__device__ __forceinline__ void areg_fence() { asm volatile("s_nop 15\n\ts_nop 15"); }
+
+// Wave w of a diagonal region: fragments of 32 rows it reads, and its nine blocks (row fragment, column fragment).
+template <int W> struct RegionDiag {
+  static constexpr int NF = W < 2 ? 4 : 6;
+  __device__ static constexpr int frag(int f) { return W == 0 ? f : W == 1 ? f + 4 : W == 2 ? (f < 2 ? f : f + 2) : f + 2; }
+  // triangles of four without the block (0, 1), which wave W + 2 takes along with its 2 x 4 rectangle
+  __device__ static constexpr int fa(int b) {
+    return W < 2 ? (b == 0 ? 0 : b < 3 ? 0 : b < 6 ? 1 : b < 8 ? 2 : 3) : b < 4 ? 0 : b < 8 ? 1 : (W == 2 ? 0 : 2);
+  }
+  __device__ static constexpr int fb(int b) {
+    return W < 2 ? (b == 0 ? 0 : b == 1 ? 2 : b == 2 ? 3 : b < 6 ? b - 2 : b < 8 ? b - 4 : 3) : b < 8 ? 2 + (b & 3) : (W == 2 ? 1 : 3);
+  }
+  __device__ static constexpr float weight(int b) { return fa(b) == fb(b) ? 1.f : 2.f; }
+};
+
+template <bool F16>
+__global__ __launch_bounds__(256, 1) void gram_region_kernel(GramRegionArgs g) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  const int xcd = blockIdx.x % kNumXcd, slot = blockIdx.x / kNumXcd;
+  const int job = slot % g.n_jobs;
+  const int u = (slot / g.n_jobs) * kNumXcd + xcd;
+  if (u >= g.n_groups * g.B) return;
+  const int gi = __builtin_amdgcn_readfirstlane(g.order[u / g.B]);
+  const int sample = u % g.B;
+  const int n_mem = __builtin_amdgcn_readfirstlane(g.groups[gi].n);
+  const LayerDev L = g.layers[__builtin_amdgcn_readfirstlane(g.groups[gi].layer[0])];   // a, widths and strides are the group's
+  const int2 J = region_of(job, g.n_blocks);
+  const int r0 = __builtin_amdgcn_readfirstlane(J.x) * kRegion, c0 = __builtin_amdgcn_readfirstlane(J.y) * kRegion;
+  const int T = g.T;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool a_first = n_mem > 1 || L.d_in >= L.d_out;
+  typedef const unsigned short* elem_ptr;
+  const long long x_stride = a_first ? L.a_stride : L.delta_stride, y_stride = a_first ? L.delta_stride : L.a_stride;
+  const int nkx = __builtin_amdgcn_readfirstlane((a_first ? L.d_in : L.d_out) / kKc);
+  const int nky = __builtin_amdgcn_readfirstlane((a_first ? L.d_out : L.d_in) / kKc);
+  const elem_ptr x0 = uniform_ptr(static_cast<elem_ptr>(a_first ? L.a : L.delta) + (long long)sample * T * x_stride);
+  // Y of every member, and the chunk of it (all members and, off the diagonal, halves in turn) to be requested next.  Past
+  // the last chunk that one is requested again, so that every chunk waits for the same number of loads.
+  elem_ptr y0[kGramGroupMax];
+#pragma unroll
+  for (int m = 0; m < kGramGroupMax; ++m) {
+    const LayerDev& M = g.layers[__builtin_amdgcn_readfirstlane(g.groups[gi].layer[m < n_mem ? m : 0])];
+    y0[m] = uniform_ptr(static_cast<elem_ptr>(a_first ? M.delta : L.a) + (long long)sample * T * y_stride);
+  }
+  auto y_of = [&](int m) { return m == 0 ? y0[0] : m == 1 ? y0[1] : m == 2 ? y0[2] : y0[3]; };
+
+  // ---- direct loads: one instruction fills 8 rows of 128 bytes; lane -> row lane / 8, 16-byte position lane % 8, which
+  // receives piece position ^ (row & 7).  Rows past the last one repeat it (masked at the end).
+  const int ld_row = lane >> 3, ld_col = swz16(ld_row, lane & 7) * 8;
+  auto row_off = [&](int t, long long stride) {
+    t += ld_row;
+    t = t < T ? t : T - 1;
+    return unsigned((long long)t * stride + ld_col) * 2u;
+  };
+  const unsigned lds_base = lds_address(lds);
+  // ---- fragments: lane -> row lane % 16, elements 8 * (lane / 16) .. of the k-step's 32; k-step 1 is 64 bytes on
+  const int r16 = lane & 15, kg = lane >> 4;
+  const unsigned rd0 = lds_base + unsigned(r16 * (kKc * 2) + swz16(r16, kg) * 16);
+  const unsigned rd1 = rd0 ^ 64u;
+  typedef __attribute__((address_space(3))) const u32x4* lds_v4;
+  auto read_frag16 = [&](unsigned base, int f16) -> bf16x8 {
+    return __builtin_bit_cast(bf16x8, *((lds_v4)(size_t)base + f16 * (16 * kKc * 2 / 16)));
+  };
+  auto lds_done_and_barrier = [&]() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  asm volatile("" ::: "a0", "a255");               // (the kernel has all accumulation registers)
+  float* const out = g.partials + ((size_t)sample * g.n_jobs + job) * 4 + wave;
+  const size_t out_layer = (size_t)g.B * g.n_jobs * 4;
+  auto put = [&](int m, float s) {
+    s = wave_sum_f32(s);
+    const int layer = __builtin_amdgcn_readfirstlane(g.groups[gi].layer[m]);
+    if (lane == 0) out[layer * out_layer] = s;
+  };
+
+  if (r0 != c0) {
+    // ================ off the diagonal: 2 x 2 waves of 128 x 128
+    const int wm = wave >> 1, wn = wave & 1;
+    // Rows of the region's row block are never past the end: one lane offset, the loads 32 rows apart by the scalar base.
+    // Columns: lane offset of the first load + a scalar, clamped to the last row (the host keeps (T + 256) * row stride
+    // below 2^31 elements).
+    const int wrow = wave * 8;
+    const unsigned last_x = row_off(T, x_stride), last_y = row_off(T, y_stride);
+    const unsigned xr = row_off(r0 + wrow, x_stride), yr = row_off(r0 + wrow, y_stride);
+    const unsigned xc = unsigned((long long)(c0 + wrow + ld_row) * x_stride + ld_col) * 2u;
+    const unsigned yc = unsigned((long long)(c0 + wrow + ld_row) * y_stride + ld_col) * 2u;
+    const unsigned x32 = unsigned(x_stride) * 64u, y32 = unsigned(y_stride) * 64u;      // bytes of 32 rows
+    elem_ptr px = x0;                              // the chunk to be requested next
+    auto load_x = [&](int i, unsigned st) {
+      const unsigned to = lds_base + st + (i >> 3) * (32 << 10) + (wave + 4 * (i & 7)) * 1024;
+      if (i < 8) direct_load_lds16_s(xr, reinterpret_cast<const char*>(px) + i * (unsigned long long)x32, to);
+      else direct_load_lds16_s(min(xc + (i - 8) * x32, last_x), px, to);
+    };
+    elem_ptr py = y0[0];
+    int ld_k = 0, ld_seg = 0;                      // chunk of the half, and half (of all members): 2 * member + half
+    // i = 0 .. 7: rows; 8 .. 11: the half's 64 columns of either wave column
+    auto load_y = [&](int i, unsigned st) {
+      const unsigned to = lds_base + st + (i < 8 ? (wave + 4 * i) * 1024 : (32 << 10) + (wave + 4 * (i - 8)) * 1024);
+      if (i < 8) direct_load_lds16_s(yr, reinterpret_cast<const char*>(py) + i * (unsigned long long)y32, to);
+      else direct_load_lds16_s(min(yc + ((i & 1) + ((i - 8) >> 1) * 4 + (ld_seg & 1) * 2) * y32, last_y), py, to);
+    };
+    auto next_y = [&]() {
+      const bool wrap = ld_k + 1 == nky, end = wrap && ld_seg + 1 == 2 * n_mem;
+      ld_k = end ? ld_k : wrap ? 0 : ld_k + 1;
+      ld_seg += wrap && !end;
+      py = uniform_ptr(y_of(ld_seg >> 1) + ld_k * kKc);
+    };
+
+    // block (m, n) of X X^T: accumulation registers (m * 8 + n) * 4 ..
+#pragma unroll
+    for (int i = 0; i < 256; ++i) areg_zero(i);
+    areg_fence();
+
+    // ---- X X^T
+    unsigned st = (nkx - 1) & 1 ? kRegStX : 0u;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) load_x(i, st);
+    px += kKc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) load_x(i, kRegStX - st);
+    px += kKc;
+    wait_vmcnt<16>();
+    wg_barrier();
+    bf16x8 f0[16], f1[16];                         // fragments of a k-step: [0..7] columns, [8..15] rows
+    auto row_base = [&](unsigned rd, unsigned stage) { return rd + stage + wm * (16 << 10); };
+    auto col_base_x = [&](unsigned rd, unsigned stage) { return rd + stage + (32 << 10) + wn * (16 << 10); };
+    auto col_base_y = [&](unsigned rd, unsigned stage) { return rd + stage + (32 << 10) + wn * (8 << 10); };
+#pragma unroll
+    for (int i = 0; i < 16; ++i) f0[i] = read_frag16(i < 8 ? col_base_x(rd0, st) : row_base(rd0, st), i & 7);
+    // kind 0: chunk c + 2 of X takes this chunk's stage; 1: the last but one, the first two chunks of Y are requested;
+    // 2: the last, fragments of Y's first chunk are read and its third is requested
+    auto chunk_x = [&](auto kind_tag) {
+      constexpr int kind = decltype(kind_tag)::value;
+      const unsigned b1r = row_base(rd1, st), b1c = col_base_x(rd1, st);
+#pragma unroll
+      for (int i = 0; i < 64; ++i) {
+        const int m = i >> 3, n = m & 1 ? 7 - (i & 7) : i & 7;
+        mfma_areg<F16>((m * 8 + n) * 4, f0[8 + m], f0[n]);
+        if (i < 32 && !(i & 1)) f1[i >> 1] = read_frag16(i < 16 ? b1c : b1r, (i >> 1) & 7);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const unsigned nx = kind == 2 ? region_st_y(0) : kRegStX - st;
+      const unsigned b0r = row_base(rd0, nx), b0c = kind == 2 ? col_base_y(rd0, nx) : col_base_x(rd0, nx);
+#pragma unroll
+      for (int i = 0; i < 64; ++i) {
+        const int m = i >> 3, n = m & 1 ? 7 - (i & 7) : i & 7;
+        mfma_areg<F16>((m * 8 + n) * 4, f1[8 + m], f1[n]);
+        if (i == 1) {
+          // my share of the next chunk has landed, and everybody's; everybody has read all of this chunk
+          if (kind == 2) wait_vmcnt<12>(); else wait_vmcnt<0>();
+          lds_done_and_barrier();
+        }
+        if (i >= 2 && i < 34 && !(i & 1)) {
+          const int r = (i - 2) >> 1;
+          if (kind != 2) f0[r] = read_frag16(r < 8 ? b0c : b0r, r & 7);
+          else if (r < 4) f0[r] = read_frag16(b0c, r);
+          else if (r >= 8) f0[r] = read_frag16(b0r, r - 8);
+        }
+        if (kind == 0 && i >= 3 && i < 35 && (i & 1)) load_x((i - 3) >> 1, st);
+        if (kind == 1 && i >= 3 && i < 27) load_y((i - 3) % 12, region_st_y((i - 3) / 12));
+        if (kind == 1 && (i == 14 || i == 26)) next_y();
+        if (kind == 2 && i >= 3 && i < 27 && (i & 1)) load_y((i - 3) >> 1, region_st_y(2));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (kind == 0) px += kKc;
+      if (kind == 2) next_y();
+      st = kRegStX - st;
+    };
+    int c = 0;
+    for (; c + 2 < nkx; ++c) chunk_x(std::integral_constant<int, 0>{});
+    chunk_x(std::integral_constant<int, 1>{});
+    chunk_x(std::integral_constant<int, 2>{});
+
+    // ---- Y Y^T, half by half and member by member, in one pipeline of n2 chunks
+    mfma_f32x4 acy[8][4];
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+#pragma unroll
+      for (int n = 0; n < 4; ++n)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acy[m][n][j] = vreg_zero();
+    mfma_fence_v(acy);
+    int sy = 0;                                    // stage of the chunk
+    auto chunk_y = [&]() {
+      const unsigned cur = region_st_y(sy);
+      const int sn = sy == 2 ? 0 : sy + 1;
+      const unsigned nx = region_st_y(sn);
+      const unsigned b1r = row_base(rd1, cur), b1c = col_base_y(rd1, cur);
+      const unsigned b0r = row_base(rd0, nx), b0c = col_base_y(rd0, nx);
+#pragma unroll
+      for (int i = 0; i < 32; ++i) {
+        const int m = i >> 2, n = m & 1 ? 3 - (i & 3) : i & 3;
+        mfma_16x16x32_vgpr<F16>(acy[m][n], f0[8 + m], f0[n]);
+        if (i < 24 && !(i & 1)) { const int r = i >> 1; f1[r < 4 ? r : r + 4] = read_frag16(r < 4 ? b1c : b1r, r < 4 ? r : r - 4); }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int i = 0; i < 32; ++i) {
+        const int m = i >> 2, n = m & 1 ? 3 - (i & 3) : i & 3;
+        mfma_16x16x32_vgpr<F16>(acy[m][n], f1[8 + m], f1[n]);
+        if (i == 1) {
+          wait_vmcnt<12>();
+          lds_done_and_barrier();
+        }
+        if (i >= 2 && i < 26 && !(i & 1)) { const int r = (i - 2) >> 1; f0[r < 4 ? r : r + 4] = read_frag16(r < 4 ? b0c : b0r, r < 4 ? r : r - 4); }
+        if (i >= 3 && i < 27 && (i & 1)) load_y((i - 3) >> 1, cur);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      next_y();
+      sy = sn;
+    };
+    const bool whole = c0 + kRegion <= T;
+    auto product = [&](auto half_tag) {
+      constexpr int h = decltype(half_tag)::value;
+      mfma_fence_v(acy);
+      float s = 0.f;
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        const bool in = c0 + wn * 128 + (h * 4 + n) * 16 + r16 < T;      // (rows of these regions are never past the end)
+        float sn = 0.f;
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) sn += areg((m * 8 + h * 4 + n) * 4 + j) * acy[m][n][j];
+          asm volatile("" : "+v"(sn));             // (the products are summed here, not where the sum is used)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acy[m][n][j] = vreg_zero();
+        }
+        s += whole || in ? sn : 0.f;
+      }
+      mfma_fence_v(acy);
+      return s;
+    };
+    for (int m = 0; m < n_mem; ++m) {
+      for (int k = 0; k < nky; ++k) chunk_y();
+      float s = product(std::integral_constant<int, 0>{});
+      for (int k = 0; k < nky; ++k) chunk_y();
+      s += product(std::integral_constant<int, 1>{});
+      put(m, 2.f * s);
+    }
+    wait_vmcnt<0>();
+    return;
+  }
+
+  // ================ on the diagonal
+  unsigned off_x[8], off_y[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    off_x[i] = row_off(r0 + (wave + 4 * i) * 8, x_stride);
+    off_y[i] = row_off(r0 + (wave + 4 * i) * 8, y_stride);
+  }
+  elem_ptr p = x0;
+  int ld_k = 0, ld_m = -1;                         // the chunk to be requested next: of X (-1) or a member's Y
+  auto load = [&](int i, unsigned st) {
+    direct_load_lds16_s(ld_m < 0 ? off_x[i] : off_y[i], p, lds_base + st + (wave + 4 * i) * 1024);
+  };
+  auto next = [&]() {
+    const bool wrap = ld_k + 1 == (ld_m < 0 ? nkx : nky), end = wrap && ld_m + 1 == n_mem;
+    ld_k = end ? ld_k : wrap ? 0 : ld_k + 1;
+    ld_m += wrap && !end;
+    p = uniform_ptr((ld_m < 0 ? x0 : y_of(ld_m)) + ld_k * kKc);
+  };
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) load(i, s * kRegStD);
+    next();
+  }
+  wait_vmcnt<24>();
+  wg_barrier();
+  auto run = [&](auto shape) {
+    typedef decltype(shape) S;
+    constexpr int NF = 2 * S::NF;
+    bf16x8 f0[NF], f1[NF];
+    auto read = [&](unsigned base, int f) { return read_frag16(base, S::frag(f >> 1) * 2 + (f & 1)); };
+#pragma unroll
+    for (int f = 0; f < NF; ++f) f0[f] = read(rd0, f);
+    unsigned st = 0;
+    // MFMA i of a k-step: block i / 4, quarter i % 4
+    auto chunk = [&](auto mfma) {
+      const unsigned b1 = rd1 + st;
+      const unsigned stn = st + kRegStD == 4 * kRegStD ? 0u : st + kRegStD;
+      const unsigned b0 = rd0 + stn;
+#pragma unroll
+      for (int i = 0; i < 36; ++i) {
+        mfma(i, f0[2 * S::fa(i >> 2) + ((i >> 1) & 1)], f0[2 * S::fb(i >> 2) + (i & 1)]);
+        if (!(i & 1) && (i >> 1) < NF) f1[i >> 1] = read(b1, i >> 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int i = 0; i < 36; ++i) {
+        mfma(i, f1[2 * S::fa(i >> 2) + ((i >> 1) & 1)], f1[2 * S::fb(i >> 2) + (i & 1)]);
+        if (i == 1) {
+          wait_vmcnt<16>();
+          lds_done_and_barrier();
+        }
+        if (i >= 2 && !(i & 1) && ((i - 2) >> 1) < NF) f0[(i - 2) >> 1] = read(b0, (i - 2) >> 1);
+        if (i >= 3 && i < 19 && (i & 1)) load((i - 3) >> 1, st);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      next();
+      st = stn;
+    };
+    // block i of X X^T: accumulation registers 4 i ..; of Y Y^T: the remaining 112 and (the last eight) vector registers
+    mfma_f32x4 av[1][8];
+#pragma unroll
+    for (int i = 0; i < 256; ++i) areg_zero(i);
+    areg_fence();
+    for (int k = 0; k < nkx; ++k)
+      chunk([&](int i, bf16x8 x, bf16x8 y) { mfma_areg<F16>(4 * i, x, y); });
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) av[0][i][j] = vreg_zero();
+    mfma_fence_v(av);
+    const bool whole = r0 + kRegion <= T;
+    for (int m = 0; m < n_mem; ++m) {
+      for (int k = 0; k < nky; ++k)
+        chunk([&](int i, bf16x8 x, bf16x8 y) {
+          if (i < 28) mfma_areg<F16>(144 + 4 * i, x, y); else mfma_16x16x32_vgpr<F16>(av[0][i - 28], x, y);
+        });
+      mfma_fence_v(av);
+      auto entry = [&](int i, int j) { return areg(4 * i + j) * (i < 28 ? areg(i < 28 ? 144 + 4 * i + j : 0) : av[0][i < 28 ? 0 : i - 28][j]); };
+      float s = 0.f;
+      if (whole) {
+#pragma unroll
+        for (int b = 0; b < 9; ++b) {
+          float sb = 0.f;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) sb += entry(b * 4 + (e >> 2), e & 3);
+          asm volatile("" : "+v"(sb));
+          s += sb * S::weight(b);
+        }
+      } else {
+#pragma unroll
+        for (int b = 0; b < 9; ++b) {
+          float sb = 0.f;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            int left = T - (r0 + S::frag(S::fa(b)) * 32 + (q >> 1) * 16 + kg * 4);      // rows
+            asm volatile("" : "+v"(left));         // (else all the masks are formed beforehand and fill the scalar registers)
+            left = r0 + S::frag(S::fb(b)) * 32 + (q & 1) * 16 + r16 < T ? left : 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const float v = entry(b * 4 + q, j);
+              sb += j < left ? v : 0.f;
+            }
+          }
+          s += sb * S::weight(b);
+        }
+      }
+#pragma unroll
+      for (int i = 144; i < 256; ++i) areg_zero(i);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) av[0][i][j] = vreg_zero();
+      mfma_fence_v(av);
+      put(m, s);
+    }
+  };
+  switch (wave) {
+    case 0: run(RegionDiag<0>{}); break;
+    case 1: run(RegionDiag<1>{}); break;
+    case 2: run(RegionDiag<2>{}); break;
+    default: run(RegionDiag<3>{}); break;
+  }
+  wait_vmcnt<0>();
 }
 
 // ---------------------------------------------------------------------------------------
@@ -703,6 +1141,35 @@ hipError_t launch_gram_bf16_dual(const GramLaunch& l, const GramGroup* groups, c
   const long long grid = (long long)a.units_padded * n_jobs;
   if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
   hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(512), kDualLds, st, a);
+  return hipGetLastError();
+}
+
+int gram_region_jobs(int T) {
+  const int n = (T + kRegion - 1) / kRegion;
+  return n * (n + 1) / 2;
+}
+
+hipError_t launch_gram_region(const GramLaunch& l, const GramGroup* groups, hipStream_t st) {
+  auto kern = l.dtype == ADLOCO_F16 ? gram_region_kernel<true> : gram_region_kernel<false>;
+  {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kRegionLds);
+    if (e != hipSuccess) return e;
+  }
+  GramRegionArgs a;
+  a.layers = l.layers;
+  a.groups = groups;
+  a.order = l.order;
+  a.partials = l.partials;
+  a.n_groups = l.n_layers;
+  a.B = l.B;
+  a.T = l.T;
+  a.n_blocks = (l.T + kRegion - 1) / kRegion;
+  a.n_jobs = gram_region_jobs(l.T);
+  const long long units = (long long)l.n_layers * l.B;
+  const long long grid = (units + kNumXcd - 1) / kNumXcd * kNumXcd * a.n_jobs;
+  if (units > 0x7ffffff0LL || grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(kern, dim3(unsigned(grid)), dim3(256), kRegionLds, st, a);
   return hipGetLastError();
 }
 

@@ -1,0 +1,80 @@
+"""GPU parity of the region kernel of the Gram contraction (256 x 256 regions of A A^T and delta delta^T) against the CPU
+oracle: sequence ends around the 256-row blocks, their halves and the 32-row blocks of the diagonal, either operand the
+wider one, the fewest chunks of both, layers that share their activations (up to four to a group), strided rows.
+Tolerance: exact products, fp32 sums, the bar of the 16-bit norms (2e-3; the same sums in another order differ by 1e-6)."""
+import numpy as np
+import pytest
+
+import adloco_synth as synth
+from oracle import adloco_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import paper_2508_18182_amd as A
+    c = A.Context(0)
+    c.set_tuning("stats_variant", 0)
+    c.set_tuning("gram_variant", 3)
+    yield c
+    c.close()
+
+
+def _check(ctx, host, share, B, T, dtype, pad=0):
+    import torch
+    import paper_2508_18182_amd as A
+    from gpu_util import DEV, code_of, new_acc, rel_err, to_dev
+    for l, first in share.items():
+        host[l]["a"] = host[first]["a"]
+    want = orc.grad_stats([(l["a"], l["delta"]) for l in host], two_pass=False)
+
+    def rows(x):
+        x = to_dev(x)
+        if not pad:
+            return x
+        wide = torch.full((B, T, x.shape[2] + pad), float("nan"), dtype=x.dtype, device=DEV)
+        wide[:, :, :x.shape[2]] = x
+        return wide[:, :, :x.shape[2]]
+
+    a = {id(l["a"]): rows(l["a"]) for l in host}
+    layers = [dict(a=a[id(l["a"])], delta=rows(l["delta"]), provided=True,
+                   grad_sum=torch.zeros(l["d_out"], l["d_in"], device=DEV)) for l in host]
+    for _ in range(2):
+        ps, pl, acc = torch.zeros(B, device=DEV), torch.zeros(len(layers), B, device=DEV), new_acc()
+        A.adloco_grad_stats(ctx, layers, B, T, code_of(dtype), ps, pl, acc)
+        assert rel_err(pl.cpu().numpy(), want["n_layer_sample"]) < 1e-5
+        assert rel_err(ps.cpu().numpy(), want["n_sample"]) < 1e-5
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("T", [1, 32, 129, 255, 256, 257, 384, 511, 520, 769])
+def test_sequence_ends(ctx, dtype, T):
+    host = synth.custom_grad_stats_inputs(8100 + T, [(128, 192), (320, 128), (128, 128)], 2, T, dtype, std_delta=0.05, rho=0.5)
+    _check(ctx, host, {}, 2, T, dtype)
+
+
+@pytest.mark.parametrize("T", [200, 512, 600])
+def test_shared_activations_and_strides(ctx, T):
+    shapes = [(128, 256)] * 5 + [(256, 128), (192, 128)]
+    host = synth.custom_grad_stats_inputs(8200 + T, shapes, 3, T, "bf16", std_delta=0.05, rho=0.5)
+    _check(ctx, host, {1: 0, 2: 0, 3: 0, 4: 0}, 3, T, "bf16", pad=40)      # five readers: a group of four and one
+
+
+def test_an_infinite_row_stays_with_its_sample(ctx):
+    # the last token, which rows past the end of the sequence repeat
+    import torch
+    import paper_2508_18182_amd as A
+    from gpu_util import DEV, new_acc, to_dev
+    B, T = 3, 300
+    host = synth.custom_grad_stats_inputs(8300, [(128, 256)], B, T, "bf16", std_delta=0.05, rho=0.5)
+    a, d = to_dev(host[0]["a"]), to_dev(host[0]["delta"])
+    G = torch.zeros(256, 128, device=DEV)
+    got = []
+    for x in (0.0, float("inf")):
+        a[1, T - 1, 5] = x
+        ps, acc = torch.zeros(B, device=DEV), new_acc()
+        A.adloco_grad_stats(ctx, [dict(a=a, delta=d, provided=True, grad_sum=G)], B, T, A.ADLOCO_BF16, ps, None, acc)
+        got.append(ps.cpu().numpy())
+    assert np.all(np.isfinite(got[0])) and not np.isfinite(got[1][1])
+    assert got[0][0] == got[1][0] and got[0][2] == got[1][2]
