@@ -363,7 +363,7 @@ struct adloco_ctx {
   int wgrad_blocks = 0;        // workgroups of the wgrad launch for the uploaded table
   int table_dtype = -1;        // dtype the uploaded table was built for
   int table_inputs = -1;       // 1: the table was built by a call that reads a and delta
-  int plain_tiles_tuning = 0;  // fp32 statistics: 0: time model; 1, 2: 64- or 128-wide tiles; + 4: none split
+  int plain_tiles_tuning = 0;  // plain tiles: 0: time model; 1, 2: 64- or 128-wide; + 4 (fp32 statistics): none split
   size_t scratch_limit = 0;    // largest scratch allocation, bytes (0: no limit); for tests of the calls' behaviour without memory
   int table_builds = 0;        // how often a shape-dependent table has been (re)built
   long long max_lin_stride = 0;  // widest row stride (elements) among the linear blocks of the table
@@ -492,8 +492,9 @@ hipError_t launch_stats_tiles(const LayerDev* layers, const TileList& list, int 
                               bool short_form, float* out, float* partials, hipStream_t st);
 // Resident workgroups per XCD of the plain tile kernel: two (128-wide tiles) or four per compute unit.
 constexpr int plain_tile_room(int W) { return kNumCu / kNumXcd * (W == 2 ? 2 : 4); }
-inline TileGeom plain_tile_geom(int W) { return TileGeom{64 * W, 64 * W, 32 / W, plain_tile_room(W)}; }
-int plain_tile_width(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B);
+inline TileGeom plain_tile_geom(int W) { return TileGeom{64 * W, 64 * W, 32, plain_tile_room(W)}; }
+int plain_tile_width(const std::vector<LayerDev>& layers, const std::vector<char>& use, int B, int T);
+int sum_tile_width(const std::vector<LayerDev>& layers, const std::vector<char>& use);
 struct PlainChoice { int W; bool whole; };       // tile width 64 * W; whole: no tile is split
 PlainChoice plain_tile_choice(const TileList* lists, int B, int T);
 // mode 0: <g_i, G> -> dot and ||g_i||^2 -> sq; fp32 only: mode 1: G and ||g_i||^2 -> sq (whole: no tile is split); mode 2: G

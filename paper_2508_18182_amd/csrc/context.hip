@@ -196,6 +196,7 @@ extern "C" int adloco_set_tuning(adloco_ctx* ctx, const char* name, int value) {
   } else if (n == "plain_tiles") {
     if (value < 0 || value > 6 || value == 3 || value == 4) return fail(ctx, ADLOCO_EINVAL, "plain_tiles: 0, 1, 2, 5 or 6");
     ctx->plain_tiles_tuning = value;
+    ctx->ip_B = ctx->ip_T = -1;
   } else if (n == "scratch_limit_kb") {
     if (value < 0) return fail(ctx, ADLOCO_EINVAL, "scratch_limit_kb out of range");
     ctx->scratch_limit = size_t(value) << 10;

@@ -468,7 +468,7 @@ GramTime gram_time(const std::vector<LayerDev>& tab, int B, int T) {
 // (2 d_in d_out T products) take less time than the Gram contraction ((d_in + d_out) T (T + 1)), as on sequences that
 // are long for the widths.  Microseconds from measured rates: 16-bit tiles 0.95 PFLOP/s on 256 workgroups of 256 x 128
 // (0.55 where widths are no multiple of 64: the pieces of a row straddle cache lines), the general Gram kernel for such
-// widths 0.35; fp32 tiles 80 TFLOP/s on 512 workgroups of 128 x 128, the fp32 Gram kernel 23; 20 us for
+// widths 0.35; fp32 tiles 150 TFLOP/s on 512 workgroups of 128 x 128, the fp32 Gram kernel 15; 20 us for
 // starts and ends.  Measured, Gram -> tiles: bf16 7 x {600 -> 1800, ..}, B 3, T 2688 2.77 -> 0.77 ms; 6 x {320 -> 960,
 // ..}, B 6, T 1792 0.90 -> 0.37; fp32 {512 -> 1408, ..}, B 11, T 1395 8.3 -> 1.1; {1336 -> 4008, ..}, B 3, T 1024 stays
 // with the Gram kernel: 0.28 against 0.40.
@@ -476,7 +476,7 @@ GramTime gram_time(const std::vector<LayerDev>& tab, int B, int T) {
 bool tiles_beat_gram(const std::vector<LayerDev>& tab, int B, int T, int dtype, double gram_us) {
   const bool b16 = is_16bit(dtype), fast = gram_us > 0.0;
   const long long te = b16 ? 256 : 128, tc = 128, gt = b16 ? 128 : 32, wgs = b16 ? 256 : 512;
-  const double tile_rate = b16 ? (fast ? 9.5e8 : 5.5e8) : 8e7, gram_rate = b16 ? 3.5e8 : 2.3e7;   // flop per us
+  const double tile_rate = b16 ? (fast ? 9.5e8 : 5.5e8) : 1.5e8, gram_rate = b16 ? 3.5e8 : 1.5e7;   // flop per us
   const double nt = double((T + gt - 1) / gt);
   double tiles = 0.0, gram = 0.0;
   for (const LayerDev& L : tab) {
@@ -490,15 +490,15 @@ bool tiles_beat_gram(const std::vector<LayerDev>& tab, int B, int T, int dtype, 
 }
 
 // Gradient sums formed here: true where the tiles of the per-sample gradients, whose samples are padded to whole chunks
-// (32 token rows; fp32: 16), take less time than the Gram contraction followed by the sum over all rows, which pays for
+// (32 token rows), take less time than the Gram contraction followed by the sum over all rows, which pays for
 // no padding: short sequences on wide layers go the second way.  Rates as above, gradient sums at 1.2 PFLOP/s / 80
 // TFLOP/s; the work on a finished 16-bit tile is worth 48 token rows.  Measured, fp16: {1024 -> 3072, ..} x 4, B 8, T 17
 // 0.30 ms by tiles, 0.23 the second way; {512 -> 1536, ..}, B 8, T 333 0.11 against 0.14.
 // gram_us: as above, for one sample.
 bool formed_tiles_pay(const std::vector<LayerDev>& tab, int T, int dtype, double gram_us) {
   const bool b16 = is_16bit(dtype);
-  const long long gt = b16 ? 128 : 32, chunk = b16 ? 32 : 16;
-  const double tile_rate = b16 ? 9.5e8 : 8e7, gram_rate = b16 ? 3.5e8 : 2.3e7, sum_rate = b16 ? 1.2e9 : 8e7;
+  const long long gt = b16 ? 128 : 32, chunk = 32;
+  const double tile_rate = b16 ? 9.5e8 : 1.5e8, gram_rate = b16 ? 3.5e8 : 1.5e7, sum_rate = b16 ? 1.2e9 : 8e7;
   const double nt = double((T + gt - 1) / gt), rows = double((T + chunk - 1) / chunk * chunk + (b16 ? 48 : 0));
   double tiles = 0.0, gram = gram_us;
   for (const LayerDev& L : tab) {
@@ -591,7 +591,7 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   if (plain_form || (square_form && dtype == ADLOCO_F32)) {
     if (plain_form && ctx->plain_tiles_tuning) plain = PlainChoice{ctx->plain_tiles_tuning & 3, (ctx->plain_tiles_tuning & 4) != 0};
     else if (plain_form) plain = plain_tile_choice(ctx->tiles32, B, T);
-    else plain.W = plain_tile_width(tab, ctx->tiles32[0].use, B);
+    else plain.W = ctx->plain_tiles_tuning ? ctx->plain_tiles_tuning & 3 : plain_tile_width(tab, ctx->tiles32[0].use, B, T);
     list = &ctx->tiles32[plain.W - 1];
     out_bytes = sizeof(double);
   }
@@ -607,7 +607,7 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   const bool formed = tile_form || plain_form || square_form;     // norms (and gradient sums) come from the tiles
   const TileList* sum_list = nullptr;
   if (dtype == ADLOCO_F32 && !formed && ctx->n_formed > 0 && rows < (1 << 30) && ctx->stats_variant != 0)
-    sum_list = &ctx->tiles32[plain_tile_width(tab, ctx->tiles32[0].use, 1) - 1];
+    sum_list = &ctx->tiles32[sum_tile_width(tab, ctx->tiles32[0].use) - 1];
   const bool plain_sum = sum_list && sum_list->built;
   const size_t part_bytes = size_t(n_layers) * B * sizeof(float);
   // one finished sum per (layer, sample) comes from the tiles; up to 64 MiB, there is room for those of a Gram contraction
@@ -887,7 +887,7 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
       any_rest = any_rest || rest[l];
     }
     if (any_rest) {
-      const TileGeom geom = plain_tile_geom(plain_tile_width(tab, rest, B));
+      const TileGeom geom = plain_tile_geom(ctx->plain_tiles_tuning ? ctx->plain_tiles_tuning & 3 : plain_tile_width(tab, rest, B, T));
       TileList& p = ctx->ip_rest;
       if (!p.built || p.use != rest || p.edge != geom.e) build_tile_list(ctx, p, tab, rest, geom, false, st);
       if (!p.built) return fail(ctx, ADLOCO_ENOMEM, "inner_products: no memory for the tile list");
