@@ -73,14 +73,14 @@ def parse():
 
 def gram_flops(shapes, B, T, shared=()):
     """(algorithmic = symmetric half, full, executed) flops of the Gram contractions of B samples, per
-    linear layer as the method states them.  Executed: 128 x 128 tile pairs (p <= q), a pair on the
-    diagonal computes 10 of its 16 blocks of 32 x 32; `shared` names the linears (by the last part of
+    linear layer as the method states them.  Executed: regions of 256 x 256 (p <= q), one on the
+    diagonal computes 36 of its 64 blocks of 32 x 32; `shared` names the linears (by the last part of
     their name) that read the activation tensor of the linear before them in the block: the kernel
     forms A A^T once for such a group, so their d_in is not contracted again."""
     dsum = sum(di + do for _, di, do in shapes)
     dexec = sum((0 if nm.split(".")[-1] in shared else di) + do for nm, di, do in shapes)
-    nt = -(-T // 128)
-    blocks = 16 * nt * (nt - 1) / 2 + 10 * nt
+    nt = -(-T // 256)
+    blocks = 64 * nt * (nt - 1) / 2 + 36 * nt
     return B * T * (T + 1) * dsum, 2 * B * T * T * dsum, B * blocks * 2 * 32 * 32 * dexec
 
 
@@ -265,7 +265,7 @@ def llama_leg(torch, synth, A, ctx, args, dev, DT):
                                        norm_test=out["gradient_supplied"]["norm_test"]),
                 self_contained=dict(ms=out["self_contained"]["ms"], tokens_per_s=B * T / (out["self_contained"]["ms"] * 1e-3),
                                     norm_test=out["self_contained"]["norm_test"]),
-                gram=roof("mfma", sym, g_ms, PEAK_BF16_MFMA, "TFLOP/s", 1e12, kernel="gram_bf16_dual_kernel",
+                gram=roof("mfma", sym, g_ms, PEAK_BF16_MFMA, "TFLOP/s", 1e12, kernel="gram_region_kernel",
                           flops_algorithmic_symmetric=sym, flops_full=full, flops_executed=executed,
                           frac_executed=(executed / (g_ms * 1e-3) / PEAK_BF16_MFMA) if g_ms else None,
                           note="`frac` counts the symmetric-half flops of every linear; the kernel forms A A^T once "
@@ -346,7 +346,7 @@ def gpt2_leg(torch, synth, A, ctx, args, dev, DT, TDT):
                rotation_overhead=dict(self_contained=own_rot_ms / own_fixed_ms - 1.0,
                                       gradient_supplied=prov_rot_ms / prov_fixed_ms - 1.0,
                                       tables_rebuilt_while_timing=rebuilt[0]),
-               gram=roof("mfma", sym, g_ms, PEAK_BF16_MFMA, "TFLOP/s", 1e12, kernel="gram_bf16_dual_kernel",
+               gram=roof("mfma", sym, g_ms, PEAK_BF16_MFMA, "TFLOP/s", 1e12, kernel="gram_region_kernel",
                          flops_algorithmic_symmetric=sym, flops_full=full, flops_executed=executed,
                          frac_executed=(executed / (g_ms * 1e-3) / PEAK_BF16_MFMA) if g_ms else None),
                tile_stats=roof("mfma", wflops, t_ms, PEAK_BF16_MFMA, "TFLOP/s", 1e12,
@@ -601,7 +601,7 @@ def main():
     sym, full, executed = gram_flops(shapes, st["b_max"], T)       # per launch = per micro-batch
     g_ms = kern["gram"]["avg_ms"]
     traffic, traffic_note = measured_traffic("gram")
-    r_gram = roof("mfma", sym, g_ms, PEAK_BF16_MFMA, "TFLOP/s", 1e12, kernel="gram_bf16_dual_kernel",
+    r_gram = roof("mfma", sym, g_ms, PEAK_BF16_MFMA, "TFLOP/s", 1e12, kernel="gram_region_kernel",
                   launches=kern["gram"]["launches"], units_per_launch=f"{st['b_max']} samples x {T} tokens x {len(shapes)} linears",
                   flops_algorithmic_symmetric=sym, flops_full=full, flops_executed=executed,
                   frac_executed=(executed / (g_ms * 1e-3) / PEAK_BF16_MFMA) if g_ms else None,
