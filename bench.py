@@ -71,16 +71,16 @@ def parse():
 # work accounting
 # ------------------------------------------------------------------------------------------------
 
-def gram_flops(shapes, B, T, shared=()):
+def gram_flops(shapes, B, T, shared=(), edge=256):
     """(algorithmic = symmetric half, full, executed) flops of the Gram contractions of B samples, per
-    linear layer as the method states them.  Executed: regions of 256 x 256 (p <= q), one on the
-    diagonal computes 36 of its 64 blocks of 32 x 32; `shared` names the linears (by the last part of
+    linear layer as the method states them.  Executed: regions of 256 x 256 (p <= q; `edge` 128: the
+    tile pairs of the dual-tile kernel), one on the diagonal computes its upper blocks of 32 x 32; `shared` names the linears (by the last part of
     their name) that read the activation tensor of the linear before them in the block: the kernel
     forms A A^T once for such a group, so their d_in is not contracted again."""
     dsum = sum(di + do for _, di, do in shapes)
     dexec = sum((0 if nm.split(".")[-1] in shared else di) + do for nm, di, do in shapes)
-    nt = -(-T // 256)
-    blocks = 64 * nt * (nt - 1) / 2 + 36 * nt
+    nt, side = -(-T // edge), edge // 32
+    blocks = side * side * nt * (nt - 1) / 2 + side * (side + 1) / 2 * nt
     return B * T * (T + 1) * dsum, 2 * B * T * T * dsum, B * blocks * 2 * 32 * 32 * dexec
 
 
@@ -319,7 +319,7 @@ def gpt2_leg(torch, synth, A, ctx, args, dev, DT, TDT):
     own_rot_ms, _ = timed(d_own)
     prov_fixed_ms, prov_k = timed(d_prov[:1])
     prov_rot_ms, _ = timed(d_prov)
-    sym, full, executed = gram_flops(shapes, B, T)
+    sym, full, executed = gram_flops(shapes, B, T, edge=128)       # (the model takes the dual-tile kernel here)
     wflops = sum(2.0 * B * T * di * do for _, di, do in shapes)
     # outer step + merge, M = 4 x 124M
     ocfg = synth.CONFIGS[3]["outer"]
@@ -346,7 +346,7 @@ def gpt2_leg(torch, synth, A, ctx, args, dev, DT, TDT):
                rotation_overhead=dict(self_contained=own_rot_ms / own_fixed_ms - 1.0,
                                       gradient_supplied=prov_rot_ms / prov_fixed_ms - 1.0,
                                       tables_rebuilt_while_timing=rebuilt[0]),
-               gram=roof("mfma", sym, g_ms, PEAK_BF16_MFMA, "TFLOP/s", 1e12, kernel="gram_region_kernel",
+               gram=roof("mfma", sym, g_ms, PEAK_BF16_MFMA, "TFLOP/s", 1e12, kernel="gram_bf16_dual_kernel",
                          flops_algorithmic_symmetric=sym, flops_full=full, flops_executed=executed,
                          frac_executed=(executed / (g_ms * 1e-3) / PEAK_BF16_MFMA) if g_ms else None),
                tile_stats=roof("mfma", wflops, t_ms, PEAK_BF16_MFMA, "TFLOP/s", 1e12,

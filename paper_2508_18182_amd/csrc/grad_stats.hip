@@ -433,10 +433,11 @@ int prepare_vector_table(adloco_ctx* ctx, int B, int T, hipStream_t st) {
 // (of a chunk of 64 elements: 1024 off the diagonal and 768 on it; region 2048 and 1152) and of their starts over 256
 // workgroups and a rate, plus most of a job at the end, and no less than the longest job.  Jobs of the region kernel are
 // twice as large and start more slowly, so it needs more of them to fill the chip, and its jobs on and off the diagonal
-// share no rows through the L2, so it streams every row twice from memory.  Fitted to 389 lists (T 64 .. 4096, widths
+// share no rows through the L2, so it streams every row about twice from memory (measured 1.5 to 2.5 times).  Fitted to 389 lists (T 64 .. 4096, widths
 // 128 .. 8192, 1 to 2000 units): the choice is within 1.2 % of the better kernel on average and 35 % at worst.  Measured,
 // dual -> region: 350M model, B 32, T 1024 13.7 -> 11.4 ms; two Llama-1B blocks, B 16, T 2048 4.88 -> 3.82; GPT-2-small,
-// B 32, T 512 1.50 -> 1.35, T 256 0.58 -> 0.41; two blocks of it, B 4, T 512 0.055 -> 0.083, not taken.
+// B 32, T 256 0.58 -> 0.41; T 512 1.48 -> 1.35, where the model errs (a bound of the dual kernel by memory, which would
+// mend it, loses more on other lists); two blocks of it, B 4, T 512 0.055 -> 0.083, not taken.
 struct GramTime { double dual, region; };
 GramTime gram_time(const std::vector<LayerDev>& tab, int B, int T) {
   std::vector<double> k(tab.size(), 0.0);          // elements that a job contracts; layers that share activations are one
