@@ -17,10 +17,6 @@ namespace adloco {
 typedef __attribute__((ext_vector_type(4))) float pt_f32x4;
 typedef __attribute__((ext_vector_type(16))) float pt_f32x16;
 
-__device__ __forceinline__ float pt_elem(float v) { return v; }
-__device__ __forceinline__ float pt_elem(unsigned short h) { return __uint_as_float(unsigned(h) << 16); }
-__device__ __forceinline__ float pt_elem(_Float16 h) { return float(h); }
-
 __device__ __forceinline__ double pt_wave_sum(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -40,7 +36,7 @@ __device__ __forceinline__ double pt_wave_sum(double v) {
 // by fp32 multiply-adds (sum_plain, NaN at once: all NaN, the statistics of
 // {768 -> 3072}, B 8, T 256 take 0.27 ms instead of 0.13).
 // Bound by issue: beside a 16x16x32 MFMA two other instructions find room in its 16 cycles, here there are three (matrix
-// cores 49 % busy, one workgroup cutting and storing while the other's MFMAs run).  Not faster, measured on the statistics
+// cores 52 % busy, one workgroup cutting and storing while the other's MFMAs run).  Not faster, measured on the statistics
 // below: 32x32x16 MFMAs (0.71 ms); residuals by v_dot2c (fewer instructions, more wait states: 0.75); 256 x 128 tiles with
 // the cutting between the MFMAs of eight waves (0.75 ms), of four (0.89).
 // Statistics of 4 x {768 -> 2304, 768 -> 768, 768 -> 3072, 3072 -> 768}, B 8, T 256: 0.72 ms, 161 TFLOP/s (fp32 MFMA: 1.20
