@@ -32,9 +32,9 @@ __device__ __forceinline__ double pt_wave_sum(double v) {
 // is nearer to the exact sum than that of the fp32 MFMA, which rounds every product's addition (over fp32 cases of this
 // library 0.45 - 0.9 of its error).  Six bf16 MFMAs take 96 cycles where the fp32 MFMA takes 256.
 // Before it is cut a value is multiplied by 2^24, so that all its parts are normal numbers whatever it is.  Where a part or
-// a sum overflows (values from 2^103, sums from 2^79, infinities, NaN) the finished tile is not finite and is formed again
-// by fp32 multiply-adds (sum_plain, NaN at once: all NaN, the statistics of
-// {768 -> 3072}, B 8, T 256 take 0.27 ms instead of 0.13).
+// a sum overflows (values from 2^103, sums from 2^79, infinities, NaN) the finished tile is not finite, and each wave whose
+// part of it is not forms that part again by fp32 MFMA straight from memory (form_f32): statistics of {768 -> 3072}, B 8,
+// T 256 of values around 1e32, or of NaN alone, 0.28 ms; of ordinary values 0.104 (fp32 MFMA throughout: 0.157).
 // Bound by issue: beside a 16x16x32 MFMA two other instructions find room in its 16 cycles, here there are three (matrix
 // cores 52 % busy, one workgroup cutting and storing while the other's MFMAs run).  Not faster, measured on the statistics
 // below: 32x32x16 MFMAs (0.71 ms); residuals by v_dot2c (fewer instructions, more wait states: 0.75); 256 x 128 tiles with
@@ -67,24 +67,6 @@ __device__ __forceinline__ int pt_piece(int row, int piece) { return piece ^ (-(
 __device__ __forceinline__ unsigned pt_pack(float x, float y) {
   const pt_f32x2 v = {x, y};
   return __builtin_bit_cast(unsigned, __builtin_convertvector(v, pt_bf16x2));
-}
-
-// One entry of a sample's tile by fp32 multiply-adds in row order; NaN stays NaN.
-__device__ __noinline__ float sum_plain(const float* delta, const float* a, long long ds, long long as, int T) {
-  float v = 0.f;
-  int t = 0;
-  for (; t + 8 <= T && v == v; t += 8) {
-    float x[8], y[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      x[i] = delta[(t + i) * ds];
-      y[i] = a[(t + i) * as];
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v = fmaf(x[i], y[i], v);
-  }
-  for (; t < T && v == v; ++t) v = fmaf(delta[t * ds], a[t * as], v);
-  return v;
 }
 
 template <typename E, int MODE, int W>
@@ -215,7 +197,7 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
     }
   };
   // on a tile that reaches past the layer, an infinite input times a column of zeros is NaN: those entries are left out
-  auto clear_edge = [&]() {
+  auto clear_edge = [&]() __attribute__((always_inline)) {
     int rows = L.d_out - e0 - out_r0, cols = L.d_in - c0 - out_c;
     asm volatile("" : "+v"(rows), "+v"(cols));    // (or the comparisons would be kept in registers across the loop)
 #pragma unroll
@@ -226,7 +208,35 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
         for (int j = 0; j < 4; ++j)
           if (kC * j + m >= rows || n >= cols) acc[m][n][j] = 0.f;
   };
-  auto squares = [&]() {
+  // This wave's part of a sample's tile by fp32 MFMA (16x16x4, the accumulator layout of the 16-bit ones), from memory.
+  auto form_f32 = [&](long long row) __attribute__((always_inline)) {
+    int r = e0 + kC * (wm * 16 + r16), c = c0 + kC * (wn * 16 + r16), tk = kg;
+    asm volatile("" : "+v"(r), "+v"(c), "+v"(tk));              // (as in clear_edge)
+    const float* pd = reinterpret_cast<const float*>(L.delta) + (row + tk) * L.delta_stride + r;
+    const float* pa = reinterpret_cast<const float*>(L.a) + (row + tk) * L.a_stride + c;
+    r = L.d_out - r;
+    c = L.d_in - c;
+#pragma unroll
+    for (int m = 0; m < kC; ++m)
+#pragma unroll
+      for (int n = 0; n < kC; ++n)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[m][n][j] = 0.f;
+    for (int t = 0; t < T; t += 4, pd += 4 * L.delta_stride, pa += 4 * L.a_stride) {
+      const int rows = t + tk < T ? r : 0, cols = t + tk < T ? c : 0;       // valid columns from pd and pa on
+      float x[kC], y[kC];
+#pragma unroll
+      for (int j = 0; j < kC; ++j) {
+        x[j] = j < rows ? pd[j] : 0.f;
+        y[j] = j < cols ? pa[j] : 0.f;
+      }
+#pragma unroll
+      for (int m = 0; m < kC; ++m)
+#pragma unroll
+        for (int n = 0; n < kC; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[m], y[n], acc[m][n], 0, 0, 0);
+    }
+  };
+  auto squares = [&]() __attribute__((always_inline)) {
     double sq = 0.0;
 #pragma unroll
     for (int m = 0; m < kC; ++m)
@@ -271,22 +281,9 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
     }
     if (edge) clear_edge();
     double dot = 0.0, sq = squares();
-    if constexpr (kF32) if (__any(!(sq < __builtin_inf()))) {
-      const long long row = (long long)(s0 + sample) * T;
-      const float* pd = reinterpret_cast<const float*>(L.delta) + row * L.delta_stride + e0 + out_r0;
-      const float* pa = reinterpret_cast<const float*>(L.a) + row * L.a_stride + c0 + out_c;
-      const int rows = L.d_out - e0 - out_r0, cols = L.d_in - c0 - out_c;
-#pragma unroll
-      for (int m = 0; m < kC; ++m)
-#pragma unroll
-        for (int n = 0; n < kC; ++n)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            int left = rows - (kC * j + m);
-            asm volatile("" : "+v"(left));        // (one entry after the other)
-            if (left > 0 && n < cols && !(fabsf(acc[m][n][j]) < __builtin_inff()))
-              acc[m][n][j] = sum_plain(pd + kC * j + m, pa + n, L.delta_stride, L.a_stride, T);
-          }
+    if constexpr (kF32) if (__builtin_expect(__any(!(sq < __builtin_inf())), 0)) {
+      form_f32((long long)(s0 + sample) * T);
+      if (edge) clear_edge();
       sq = squares();
     }
 #pragma unroll
