@@ -28,9 +28,14 @@ __device__ __forceinline__ double pt_wave_sum(double v) {
 // four waves as 2 x 2, wave tile 32W x 32W, 16x16x32 MFMA of 16-bit values, two (W = 2) or four (W = 1) workgroups to a
 // compute unit.  16-bit elements are staged as they are.  An fp32 value is cut into three bf16 values that add up to it
 // exactly (8 significand bits each), and six of the nine products of two such values are summed; the three left out are
-// below 2^-26 of the product, a quarter of an fp32 rounding.  Every MFMA rounds its sum of 32 products once, so the result
-// is nearer to the exact sum than that of the fp32 MFMA, which rounds every product's addition (over fp32 cases of this
-// library 0.45 - 0.9 of its error).  Six bf16 MFMAs take 96 cycles where the fp32 MFMA takes 256.
+// below 2^-24 of the product together (2^-28 in the mean square).  Six bf16 MFMAs take 96 cycles where the fp32 MFMA takes 256.
+// Error against fp64: the MFMA rounds its sum of 32 products about once, not to nearest; a product that stands alone comes
+// out within 2.4 x 2^-24 (0.56 in the mean square) where a rounding to nearest gives 1 (0.42), but the fp32 MFMA rounds
+// every product's addition.  Normal values, T rows, of the fp32 MFMA's mean square error: T 1 1.36, 2 1.12, 3 0.91, 8 0.58,
+// 32 0.37, 256 0.80, 1024 0.84; positive ones T 256 0.78, 2048 0.64 (and 5e-8 too small on average).  So up to four rows the
+// tile is formed by fp32 MFMA (form_f32); with the two larger of the products left out (eight MFMAs) a single product is off
+// by 0.55 in the mean square, and the kernel takes 14 % longer.  Still less exact than the fp32 MFMA: an entry that one
+// token of a longer sequence makes up alone.
 // Before it is cut a value is multiplied by 2^24, so that all its parts are normal numbers whatever it is.  Where a part or
 // a sum overflows (values from 2^103, sums from 2^79, infinities, NaN) the finished tile is not finite, and each wave whose
 // part of it is not forms that part again by fp32 MFMA straight from memory (form_f32): statistics of {768 -> 3072}, B 8,
@@ -49,6 +54,7 @@ __device__ __forceinline__ double pt_wave_sum(double v) {
 // ---------------------------------------------------------------------------------------
 constexpr int kPtThreads = 256;
 constexpr int kPtK = 32;                                     // token rows of a chunk
+constexpr int kPtFew = 4;                                    // up to so many token rows, fp32 tiles are those of form_f32
 
 struct PtArgs {
   const LayerDev* layers;
@@ -281,7 +287,9 @@ __global__ __launch_bounds__(kPtThreads, W == 2 ? 2 : 4) void plain_tile_kernel(
     }
     if (edge) clear_edge();
     double dot = 0.0, sq = squares();
-    if constexpr (kF32) if (__builtin_expect(__any(!(sq < __builtin_inf())), 0)) {
+    double limit = T <= kPtFew ? 0.0 : __builtin_inf();
+    asm volatile("" : "+s"(limit));               // (or a second loop is made for few rows, and both are slower)
+    if constexpr (kF32) if (__builtin_expect(__any(!(sq < limit)), 0)) {
       form_f32((long long)(s0 + sample) * T);
       if (edge) clear_edge();
       sq = squares();

@@ -68,6 +68,16 @@ def test_large_values_throughout(ctx, T, d_in, d_out):
     _check(ctx, a, d, 3, T)
 
 
+@pytest.mark.parametrize("T", [1, 2, 3, 4])
+@pytest.mark.parametrize("d_in,d_out", SHAPES)
+def test_few_rows(ctx, T, d_in, d_out):
+    # a single product is rounded to nearest; at full size and where the products left out are the largest
+    a, d = _rows(2, T, d_in, d_out, 1.0, 1.0)
+    _check(ctx, a, d, 2, T)
+    a[:, :, ::3] = d[:, :, ::2] = 1 + 2.0 ** -8 - 2.0 ** -17
+    _check(ctx, a, d, 2, T)
+
+
 def test_large_values_take_no_more_than_a_few_times_as_long(ctx):
     # (2.7 times here; 58 when each entry was summed by one thread)
     import torch
