@@ -1,7 +1,6 @@
 /*
  * adloco_internal.h -- measurement aids of libadloco.  NOT part of the library's interface: these
- * two calls exist for the repository's own benchmark and tests (kernel variants, per-kernel
- * timing); nothing a caller of the library needs depends on them, and they may change or go
+ * calls exist for the repository's own benchmark and tests (kernel variants, per-kernel timing); nothing a caller of the library needs depends on them, and they may change or go
  * without notice.
  */
 #ifndef ADLOCO_INTERNAL_H
@@ -38,6 +37,10 @@ int adloco_probe_mfma_lds(adloco_ctx* ctx, int variant, int ksteps, double* ms, 
  * tables): it moves on the first call with a new list of shapes and stays put while only the
  * addresses in a, delta and grad_sum change from call to call. */
 int adloco_table_builds(const adloco_ctx* ctx);
+
+/* The Gram kernel of the context's last adloco_grad_stats: 0 none, 1 the general one of its element type, 2 the
+ * dual-tile kernel, 3 the region kernel. */
+int adloco_gram_kernel(const adloco_ctx* ctx);
 
 #ifdef __cplusplus
 }

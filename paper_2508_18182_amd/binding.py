@@ -136,6 +136,8 @@ def load_library():
     lib.adloco_probe_mfma_lds.argtypes = [vp, C.c_int, C.c_int, C.POINTER(dbl), C.POINTER(dbl)]
     lib.adloco_probe_mfma_lds.restype = C.c_int
     lib.adloco_table_builds.restype = C.c_int
+    lib.adloco_gram_kernel.argtypes = [vp]
+    lib.adloco_gram_kernel.restype = C.c_int
     lib.adloco_grad_stats.argtypes = [vp, C.POINTER(LinearDesc), C.c_int, C.c_int, C.c_int, C.c_int,
                                       vp, vp, vp, u32, vp]
     lib.adloco_norm_test.argtypes = [vp, C.POINTER(LinearDesc), C.c_int, vp, dbl, i64, i64, i32,
@@ -212,6 +214,10 @@ class Context:
     def table_builds(self) -> int:
         """Number of times this context has (re)built its shape-dependent tables (measurement aid)."""
         return int(load_library().adloco_table_builds(self._h))
+
+    def gram_kernel(self) -> int:
+        """Gram kernel of the last adloco_grad_stats: 0 none, 1 general, 2 dual-tile, 3 region (measurement aid)."""
+        return int(load_library().adloco_gram_kernel(self._h))
 
     def probe_mfma_lds(self, variant: int, ksteps: int = 4096):
         """(ms, flops) of the LDS-fed MFMA loop (measurement aid, see adloco_internal.h)."""

@@ -375,6 +375,7 @@ struct adloco_ctx {
   int profile = 0;
   // tuning
   int gram_variant = 1;        // 1: region or dual-tile kernel when eligible; 2, 3: the latter, the former; 0: always the generic one
+  int gram_kernel = 0;         // of the last statistics call: 0 none, 1 general, 2 dual-tile, 3 region
   int wgrad_variant = 2;       // 2: 256x256 fast kernel when eligible; 1/0: 128x128 kernel (LDS transpose reads / gathers)
   int stream_blocks_per_cu = 0;   // resident workgroups per CU of the streaming kernels; 0: automatic
   int stream_variant = 0;

@@ -102,6 +102,8 @@ extern "C" int adloco_version(void) { return 101; }
 
 extern "C" int adloco_table_builds(const adloco_ctx* ctx) { return ctx ? ctx->table_builds : -1; }
 
+extern "C" int adloco_gram_kernel(const adloco_ctx* ctx) { return ctx ? ctx->gram_kernel : -1; }
+
 extern "C" int adloco_create(adloco_ctx** out, int device) {
   if (!out) {
     g_create_err = "adloco_create: out is NULL";

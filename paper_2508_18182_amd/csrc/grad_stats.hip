@@ -686,8 +686,10 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
     if (e != hipSuccess)
       return fail(ctx, ADLOCO_EHIP, "grad_stats: tile statistics launch failed: %s", hipGetErrorString(e));
   }
-  ev = (!formed && !sum_only && ctx->n_linear > 0) ? prof_begin(ctx, st) : nullptr;
-  if (formed || sum_only || ctx->n_linear == 0)
+  const bool gram = !formed && !sum_only && ctx->n_linear > 0;
+  ctx->gram_kernel = !gram ? 0 : region ? 3 : dual ? 2 : 1;
+  ev = gram ? prof_begin(ctx, st) : nullptr;
+  if (!gram)
     ;
   else if (dual) {
     // the dual-tile kernel walks groups of layers that share their activations (A A^T once per group)

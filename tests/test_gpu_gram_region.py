@@ -43,6 +43,7 @@ def _check(ctx, host, share, B, T, dtype, pad=0):
     for _ in range(2):
         ps, pl, acc = torch.zeros(B, device=DEV), torch.zeros(len(layers), B, device=DEV), new_acc()
         A.adloco_grad_stats(ctx, layers, B, T, code_of(dtype), ps, pl, acc)
+        assert ctx.gram_kernel() == 3
         assert rel_err(pl.cpu().numpy(), want["n_layer_sample"]) < 1e-5
         assert rel_err(ps.cpu().numpy(), want["n_sample"]) < 1e-5
 
@@ -75,6 +76,7 @@ def test_an_infinite_row_stays_with_its_sample(ctx):
         a[1, T - 1, 5] = x
         ps, acc = torch.zeros(B, device=DEV), new_acc()
         A.adloco_grad_stats(ctx, [dict(a=a, delta=d, provided=True, grad_sum=G)], B, T, A.ADLOCO_BF16, ps, None, acc)
+        assert ctx.gram_kernel() == 3
         got.append(ps.cpu().numpy())
     assert np.all(np.isfinite(got[0])) and not np.isfinite(got[1][1])
     assert got[0][0] == got[1][0] and got[0][2] == got[1][2]
