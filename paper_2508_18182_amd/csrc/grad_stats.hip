@@ -549,10 +549,10 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   const bool region = dual && ctx->min_width >= 128 && ((long long)T + 256) * ctx->max_lin_stride < (1LL << 31) &&
                       (ctx->gram_variant == 3 || (ctx->gram_variant == 1 && gram_us.region < gram_us.dual));
   const double t_gram = region ? gram_us.region : gram_us.dual;
-  long long n_pairs = nt * (nt + 1) / 2;      // partial sums per (layer, sample)
-  if (region) {
-    n_pairs = 4 * gram_region_jobs(T);
-  } else if (dual) {
+  long long n_pairs = nt * (nt + 1) / 2, spare_pairs = n_pairs;      // partial sums per (layer, sample)
+  if (dual) {
+    // built whichever of the two kernels this batch takes, and room kept for the sums of the one that leaves more: another
+    // batch of the same sequence length may take the other, in a call that is being captured
     if (ctx->job_tab_nt != int(nt)) {
       ++ctx->table_builds;
       std::vector<GramJob> jobs = make_gram_jobs(int(nt), ctx->gram_job_order >= 0 ? ctx->gram_job_order : (nt >= 6 ? 0 : 1));
@@ -565,7 +565,11 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
       ctx->job_tab_nt = int(nt);
       ctx->job_tab_n = int(jobs.size());
     }
-    n_pairs = gram_dual_parts(ctx->job_tab_n);
+    n_pairs = spare_pairs = gram_dual_parts(ctx->job_tab_n);
+    if (region) {
+      n_pairs = 4 * gram_region_jobs(T);
+      spare_pairs = std::max(spare_pairs, n_pairs);
+    }
   }
   if (n_pairs > 0x7fffffffLL || (long long)n_layers * B * n_pairs > (1LL << 40))
     return fail(ctx, ADLOCO_EUNSUPPORTED, "grad_stats: T = %d gives too many tile pairs", T);
@@ -613,14 +617,10 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   const size_t part_bytes = size_t(n_layers) * B * sizeof(float);
   // one finished sum per (layer, sample) comes from the tiles; up to 64 MiB, there is room for those of a Gram contraction
   // too, so that a captured call on another batch finds it
-  if (formed) {
-    const size_t gram_bytes = part_bytes * size_t(n_pairs);
-    if (gram_bytes > (size_t(64) << 20) || !obtain_scratch(ctx, ctx->partials, gram_bytes, st))
-      rc = ensure_scratch(ctx, ctx->partials, part_bytes);
-    n_pairs = 1;
-  } else {
+  if (formed) n_pairs = 1;
+  const size_t spare_bytes = part_bytes * size_t(spare_pairs);
+  if (spare_bytes > (size_t(64) << 20) || !obtain_scratch(ctx, ctx->partials, spare_bytes, st))
     rc = ensure_scratch(ctx, ctx->partials, part_bytes * size_t(n_pairs));
-  }
   if (rc) return rc;
   rc = ensure_scratch(ctx, ctx->sample_f64, size_t(B) * sizeof(double));
   if (rc) return rc;

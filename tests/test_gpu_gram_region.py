@@ -80,3 +80,58 @@ def test_an_infinite_row_stays_with_its_sample(ctx):
         got.append(ps.cpu().numpy())
     assert np.all(np.isfinite(got[0])) and not np.isfinite(got[1][1])
     assert got[0][0] == got[1][0] and got[0][2] == got[1][2]
+
+
+@pytest.mark.parametrize("T", [700, 1024])
+def test_another_batch_may_take_the_other_kernel_and_be_captured(T):
+    # one sequence length: large batches take the region kernel, a single sample the dual-tile kernel and its job table
+    import torch
+    import paper_2508_18182_amd as A
+    from gpu_util import DEV, new_acc, to_dev
+    shapes = [(512, 1536), (512, 512), (512, 2048), (2048, 512)]
+
+    def call(B):
+        host = synth.custom_grad_stats_inputs(8400 + B, shapes, B, T, "bf16", std_delta=0.05, rho=0.5)
+        layers = [dict(a=to_dev(l["a"]), delta=to_dev(l["delta"]), provided=True,
+                       grad_sum=torch.zeros(l["d_out"], l["d_in"], device=DEV)) for l in host]
+        ps, pl, acc = torch.zeros(B, device=DEV), torch.zeros(len(layers), B, device=DEV), new_acc()
+        return lambda c: A.adloco_grad_stats(c, layers, B, T, A.ADLOCO_BF16, ps, pl, acc), [ps, pl, acc]
+
+    def context():
+        c = A.Context(0)
+        c.set_tuning("stats_variant", 0)
+        return c
+
+    (many, many_out), (one, one_out) = call(8), call(1)
+    want = []
+    for run, out, kernel in ((many, many_out, 3), (one, one_out, 2)):      # each on a context of its own
+        with context() as own:
+            run(own)
+            torch.cuda.synchronize()
+            assert own.gram_kernel() == kernel
+            want.append([t.clone() for t in out])
+    with context() as ctx:
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            many(ctx)
+        torch.cuda.synchronize()
+        builds = ctx.table_builds()
+        with torch.cuda.stream(s):
+            one(ctx)
+        torch.cuda.synchronize()
+        assert ctx.table_builds() == builds
+    with context() as ctx:
+        with torch.cuda.stream(s):
+            many(ctx)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            one(ctx)
+        for _ in range(3):
+            for t in one_out + many_out:
+                t.fill_(-1)
+            g.replay()
+            many(ctx)
+            torch.cuda.synchronize()
+            for got, w in zip(one_out + many_out, want[1] + want[0]):
+                assert torch.equal(got, w)
