@@ -319,7 +319,8 @@ def gpt2_leg(torch, synth, A, ctx, args, dev, DT, TDT):
     own_rot_ms, _ = timed(d_own)
     prov_fixed_ms, prov_k = timed(d_prov[:1])
     prov_rot_ms, _ = timed(d_prov)
-    sym, full, executed = gram_flops(shapes, B, T, edge=128)       # (the model takes the dual-tile kernel here)
+    region = ctx.gram_kernel() == 3
+    sym, full, executed = gram_flops(shapes, B, T, edge=256 if region else 128)
     wflops = sum(2.0 * B * T * di * do for _, di, do in shapes)
     # outer step + merge, M = 4 x 124M
     ocfg = synth.CONFIGS[3]["outer"]
@@ -346,7 +347,8 @@ def gpt2_leg(torch, synth, A, ctx, args, dev, DT, TDT):
                rotation_overhead=dict(self_contained=own_rot_ms / own_fixed_ms - 1.0,
                                       gradient_supplied=prov_rot_ms / prov_fixed_ms - 1.0,
                                       tables_rebuilt_while_timing=rebuilt[0]),
-               gram=roof("mfma", sym, g_ms, PEAK_BF16_MFMA, "TFLOP/s", 1e12, kernel="gram_bf16_dual_kernel",
+               gram=roof("mfma", sym, g_ms, PEAK_BF16_MFMA, "TFLOP/s", 1e12,
+                         kernel="gram_region_kernel" if region else "gram_bf16_dual_kernel",
                          flops_algorithmic_symmetric=sym, flops_full=full, flops_executed=executed,
                          frac_executed=(executed / (g_ms * 1e-3) / PEAK_BF16_MFMA) if g_ms else None),
                tile_stats=roof("mfma", wflops, t_ms, PEAK_BF16_MFMA, "TFLOP/s", 1e12,

@@ -248,6 +248,12 @@ __device__ __forceinline__ void put_grad_tile(float* G, int d_out, int d_in, int
   }
 }
 
+// What the Gram contraction of a layer table contracts, for the choice between its kernels.
+struct GramLoad {
+  int count = 0;                 // groups of linear layers that are contracted together
+  double chunks = 0, longest = 0;  // elements of all of them and of the longest, in chunks of 64
+};
+
 struct Scratch {
   void* ptr = nullptr;
   size_t bytes = 0;
@@ -310,6 +316,7 @@ struct adloco_ctx {
                                // single_off, the same with every linear layer in a group of its own
   int n_groups = 0;
   size_t single_off = 0;
+  adloco::GramLoad gram_load[2];   // with every linear layer by itself; in groups
   std::vector<adloco::LayerDev> layer_tab_host;  // last uploaded copy
   std::vector<int> order_host;
   adloco::Scratch job_tab;     // GramJob[] of the dual-tile Gram kernel

@@ -281,6 +281,17 @@ int prepare_tables(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_laye
       ADLOCO_HIP_CHECK(ctx, hipStreamSynchronize(st));
     }
     ctx->n_groups = int(groups.size());
+    for (int g = 0; g < 2; ++g) {
+      GramLoad& load = ctx->gram_load[g];
+      load = GramLoad{};
+      for (const GramGroup& G : g ? groups : single) {
+        const LayerDev& L = tab[G.layer[0]];
+        const double chunks = (L.d_in + double(G.n) * L.d_out) / 64;
+        ++load.count;
+        load.chunks += chunks;
+        load.longest = std::max(load.longest, chunks);
+      }
+    }
   }
   ctx->aux_B = ctx->aux_T = -1;         // the vector / table descriptor lists follow the table
   ctx->ip_B = ctx->ip_T = -1;           // and so does the inner-product tile table
@@ -429,85 +440,93 @@ int prepare_vector_table(adloco_ctx* ctx, int B, int T, hipStream_t st) {
   return ADLOCO_OK;
 }
 
-// Time of the Gram contraction of 16-bit blocks by the dual-tile and the region kernel, in microseconds: cycles of the jobs
-// (of a chunk of 64 elements: 1024 off the diagonal and 768 on it; region 2048 and 1152) and of their starts over 256
-// workgroups and a rate, plus most of a job at the end, and no less than the longest job.  Jobs of the region kernel are
-// twice as large and start more slowly, so it needs more of them to fill the chip, and its jobs on and off the diagonal
-// share no rows through the L2, so it streams every row about twice from memory (measured 1.5 to 2.5 times).  Fitted to 389 lists (T 64 .. 4096, widths
-// 128 .. 8192, 1 to 2000 units): the choice is within 1.2 % of the better kernel on average and 35 % at worst.  Measured,
-// dual -> region: 350M model, B 32, T 1024 13.7 -> 11.4 ms; two Llama-1B blocks, B 16, T 2048 4.88 -> 3.82; GPT-2-small,
-// B 32, T 256 0.58 -> 0.41; T 512 1.48 -> 1.35, where the model errs (a bound of the dual kernel by memory, which would
-// mend it, loses more on other lists); two blocks of it, B 4, T 512 0.055 -> 0.083, not taken.
+// Time of the Gram contraction of 16-bit blocks by the dual-tile and the region kernel, in microseconds: the jobs of the XCD
+// with the most units (cycles a chunk of 64 elements: 1024 off the diagonal and 768 on it; region 2048 and 1152) and their
+// starts over its 32 workgroups and a rate, plus most of a job at the end, and no less than the longest job.  The region
+// kernel always contracts the activations that layers share once, the dual-tile kernel only where no tile is ragged.  Jobs
+// of the region kernel are twice as large and start more slowly, so it needs more of them to fill the chip, and a last block
+// that is mostly padding costs it more (T 257 to 384: 1.13 to 1.3 times the time of the dual-tile kernel).  Fitted to 760
+// lists on data that no cache held (T 17 .. 4096, widths 128 .. 2048, 1 to 24 blocks of GPT or Llama shapes, B 1 to 64):
+// the choice is within 0.2 % of the better kernel on average and 16 % at worst; up to T 128 it is the dual-tile kernel in all
+// of them.  Measured, dual -> region: 350M model, B 32, T 1024 13.7 -> 11.4 ms; two Llama-1B blocks, B 16, T 2048 4.88 ->
+// 3.82; GPT-2-small, B 32, T 256 0.58 -> 0.41, T 512 1.50 -> 1.35; two blocks of it, B 4, T 512 0.055 -> 0.083, not taken.
 struct GramTime { double dual, region; };
-GramTime gram_time(const std::vector<LayerDev>& tab, int B, int T) {
-  std::vector<double> k(tab.size(), 0.0);          // elements that a job contracts; layers that share activations are one
-  double bytes = 0.0;
-  for (size_t l = 0; l < tab.size(); ++l) {
-    const LayerDev& L = tab[l];
-    if (L.kind != ADLOCO_KIND_LINEAR) continue;
-    const double more = L.d_out + (L.a_twin < 0 ? L.d_in : 0);
-    bytes += more * B * T * 2.0;
-    k[L.a_twin < 0 ? l : size_t(L.a_twin)] += more;
-  }
-  auto model = [&](int edge, double off, double on, int per_job, double start, double rate) {
-    const double n = (T + edge - 1) / edge;
-    const double n_off = std::ceil(n * (n - 1) / 2 / per_job) * B, n_on = std::ceil(n / per_job) * B;
-    double work = 0.0, jobs = 0.0, longest = 0.0;
-    for (double x : k) {
-      if (x == 0.0) continue;
-      work += n_off * (x / 64 * off + start) + n_on * (x / 64 * on + start);
-      jobs += n_off + n_on;
-      longest = std::max(longest, x / 64 * (n_off > 0 ? off : on) + start);
-    }
-    return (jobs > kNumCu ? std::max(longest, work / kNumCu + 0.76 * work / jobs) : longest) / rate;
+GramTime gram_time(const adloco_ctx* ctx, int B, int T) {
+  auto model = [&](const GramLoad& g, int edge, double off, double on, int per_job, double start, double rate, double fixed) {
+    const int n = (T + edge - 1) / edge;
+    const double n_off = std::ceil(double(n) * (n - 1) / 2 / per_job);
+    // (of an odd number of tile pairs on and off the diagonal, the last two make one job)
+    const double n_on = (n + per_job - 1) / per_job - (per_job == 2 && n % 4 == 3);
+    const double units = std::max(1.0, double(g.count) * B), most = std::ceil(units / kNumXcd), jobs = (n_off + n_on) * most;
+    const double work = (n_off * (g.chunks * off + start * g.count) + n_on * (g.chunks * on + start * g.count)) * B * most / units;
+    const double longest = g.longest * (n_off > 0 ? off : on) + start, wgs = kNumCu / kNumXcd;
+    return (jobs > wgs ? std::max(longest, work / wgs + 0.66 * work / jobs) : longest) / rate + fixed;
   };
-  return GramTime{model(128, 1024, 768, 2, 5900, 1225),
-                  std::max(model(256, 2048, 1152, 1, 10400, 1485), bytes * (T > 256 ? 2 : 1) / 6.6e6)};
+  return GramTime{model(ctx->gram_load[T % 128 == 0], 128, 1024, 768, 2, 5270, 1203, 2.7),
+                  model(ctx->gram_load[1], 256, 2048, 1152, 1, 9950, 1474, 2.2)};
 }
 
 // Norms of linear blocks whose gradient sums are supplied: true where the tiles of the per-sample gradients
 // (2 d_in d_out T products) take less time than the Gram contraction ((d_in + d_out) T (T + 1)), as on sequences that
-// are long for the widths.  Microseconds from measured rates: 16-bit tiles 0.95 PFLOP/s on 256 workgroups of 256 x 128
-// (0.55 where widths are no multiple of 64: the pieces of a row straddle cache lines), the general Gram kernel for such
-// widths 0.35; fp32 tiles 150 TFLOP/s on 512 workgroups of 128 x 128, the fp32 Gram kernel 15; 20 us for
-// starts and ends.  Measured, Gram -> tiles: bf16 7 x {600 -> 1800, ..}, B 3, T 2688 2.77 -> 0.77 ms; 6 x {320 -> 960,
-// ..}, B 6, T 1792 0.90 -> 0.37; fp32 {512 -> 1408, ..}, B 11, T 1395 8.3 -> 1.1; {1336 -> 4008, ..}, B 3, T 1024 stays
-// with the Gram kernel: 0.28 against 0.40.
-// gram_us: the time of the kernels for widths that are multiples of 64 (0: they do not take this call).
-bool tiles_beat_gram(const std::vector<LayerDev>& tab, int B, int T, int dtype, double gram_us) {
-  const bool b16 = is_16bit(dtype), fast = gram_us > 0.0;
+// are long for the widths.  gram_us: the time of the Gram kernels for widths that are multiples of 64 (0: they do not take
+// this call); the tiles then take 0.46 us a chunk, 0.72 a finished tile, 2.8 a run of samples and 8 in all, and the choice
+// is within 0.7 % of the better way on average and 24 % at worst (260 lists as above; 17 % and 3.3 times with rates alone).
+// Else microseconds from measured rates: 16-bit tiles 0.55 PFLOP/s on 256 workgroups of 256 x 128 (the pieces of a row
+// straddle cache lines), the general Gram kernel 0.35; fp32 tiles 150 TFLOP/s on 512 workgroups of 128 x 128, the fp32 Gram
+// kernel 15; 20 us for starts and ends.  Measured, Gram -> tiles: bf16 7 x {600 -> 1800, ..}, B 3, T 2688 2.77 -> 0.77 ms; 6 x
+// {320 -> 960, ..}, B 6, T 1792 0.90 -> 0.37; fp32 {512 -> 1408, ..}, B 11, T 1395 8.3 -> 1.1; {1336 -> 4008, ..}, B 3,
+// T 1024 stays with the Gram kernel: 0.28 against 0.40, and so does {960 -> 960, .., 960 -> 2240} x 3, B 15, T 27: 46 us
+// against 119.
+bool tiles_beat_gram(const adloco_ctx* ctx, int B, int T, int dtype, double gram_us) {
+  if (gram_us > 0.0) {
+    const TileGeom geom = ip_tile_geom();
+    const long long n = ctx->tiles16.n_tiles, room = (long long)geom.room * kNumXcd;
+    const int group = run_length(n, B, T, geom);
+    const double rounds = double((n * ((B + group - 1) / group) + room - 1) / room), chunks = (T + geom.k - 1) / geom.k;
+    return 8.0 + rounds * (group * (chunks * 0.46 + 0.72) + 2.8) < 0.95 * gram_us;
+  }
+  const bool b16 = is_16bit(dtype);
   const long long te = b16 ? 256 : 128, tc = 128, gt = b16 ? 128 : 32, wgs = b16 ? 256 : 512;
-  const double tile_rate = b16 ? (fast ? 9.5e8 : 5.5e8) : 1.5e8, gram_rate = b16 ? 3.5e8 : 1.5e7;   // flop per us
+  const double tile_rate = b16 ? 5.5e8 : 1.5e8, gram_rate = b16 ? 3.5e8 : 1.5e7;   // flop per us
   const double nt = double((T + gt - 1) / gt);
   double tiles = 0.0, gram = 0.0;
-  for (const LayerDev& L : tab) {
+  for (const LayerDev& L : ctx->layer_tab_host) {
     if (L.kind != ADLOCO_KIND_LINEAR) continue;
     tiles += double((L.d_out + te - 1) / te) * double((L.d_in + tc - 1) / tc);
     gram += nt * (nt + 1) * gt * gt * (double(L.d_in) + L.d_out);
   }
   const double per_round = 2.0 * te * tc * double((T + 31) / 32 * 32) * wgs / tile_rate;
   const double t_tiles = std::max(1.0, tiles * B / wgs) * per_round + 20.0;
-  return t_tiles < 0.95 * (fast ? gram_us : gram * B / gram_rate);
+  return t_tiles < 0.95 * gram * B / gram_rate;
 }
 
 // Gradient sums formed here: true where the tiles of the per-sample gradients, whose samples are padded to whole chunks
 // (32 token rows), take less time than the Gram contraction followed by the sum over all rows, which pays for
-// no padding: short sequences on wide layers go the second way.  Rates as above, gradient sums at 1.2 PFLOP/s / 80
-// TFLOP/s; the work on a finished 16-bit tile is worth 48 token rows.  Measured, fp16: {1024 -> 3072, ..} x 4, B 8, T 17
-// 0.30 ms by tiles, 0.23 the second way; {512 -> 1536, ..}, B 8, T 333 0.11 against 0.14.
-// gram_us: as above, for one sample.
-bool formed_tiles_pay(const std::vector<LayerDev>& tab, int T, int dtype, double gram_us) {
+// no padding: short sequences on wide layers go the second way.  With the time of the Gram kernels (gram_us, as above) the
+// tiles take 0.53 us a chunk, 1.1 a finished tile, 7 a tile of G and 16 in all, the sum over all rows 0.74 a chunk of its
+// 256 x 256 tiles, 13 a tile and 16 in all: within 0.4 % of the better way on average and 19 % at worst (142 ragged lists
+// as above).  Else rates as above, gradient sums at 1.2 PFLOP/s / 80 TFLOP/s; the work on a finished 16-bit tile is worth
+// 48 token rows.  Measured, fp16: {1024 -> 3072, ..} x 4, B 8, T 17 0.30 ms by tiles, 0.23 the second way; {512 -> 1536,
+// ..}, B 8, T 333 0.11 against 0.14; {960 -> 960, .., 960 -> 2240} x 3, B 15, T 27 0.158 against 0.114.
+bool formed_tiles_pay(const adloco_ctx* ctx, int B, int T, int dtype, double gram_us) {
+  if (gram_us > 0.0) {
+    const double chunks = (T + 31) / 32, n = double(ctx->tiles16.n_tiles) / kNumCu, sample = chunks * 0.53 + 1.1;
+    const double tiles = 16.0 + std::max(n * (B * sample + 7.0), std::min(double(B), std::max(1.0, n * B)) * sample + 7.0);
+    const double w = n / 2, rows = double(B) * T / 32;           // (half as many tiles, each of twice the size)
+    const double pieces = std::max(1.0, std::floor(1.0 / std::max(w, 1.0 / kNumCu)));
+    const double sum = 16.0 + std::max(w * (rows * 0.74 + 13.0), std::ceil(rows / pieces) * 0.74 + 13.0);
+    return tiles <= gram_us + sum;
+  }
   const bool b16 = is_16bit(dtype);
   const long long gt = b16 ? 128 : 32, chunk = 32;
   const double tile_rate = b16 ? 9.5e8 : 1.5e8, gram_rate = b16 ? 3.5e8 : 1.5e7, sum_rate = b16 ? 1.2e9 : 8e7;
   const double nt = double((T + gt - 1) / gt), rows = double((T + chunk - 1) / chunk * chunk + (b16 ? 48 : 0));
-  double tiles = 0.0, gram = gram_us;
-  for (const LayerDev& L : tab) {
+  double tiles = 0.0, gram = 0.0;
+  for (const LayerDev& L : ctx->layer_tab_host) {
     if (L.kind != ADLOCO_KIND_LINEAR) continue;
     const double io = 2.0 * L.d_in * L.d_out;
     tiles += io * rows / tile_rate;
-    if (gram_us == 0.0) gram += nt * (nt + 1) * gt * gt * (double(L.d_in) + L.d_out) / gram_rate;
-    gram += io * T / sum_rate;
+    gram += nt * (nt + 1) * gt * gt * (double(L.d_in) + L.d_out) / gram_rate + io * T / sum_rate;
   }
   return tiles <= gram;
 }
@@ -545,9 +564,9 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   // (the dual-tile kernel addresses a sample's rows with 32-bit byte offsets)
   const bool dual = is_16bit(dtype) && ctx->gram_variant != 0 && ctx->all_fast64 &&
                     (long long)T * ctx->max_lin_stride < (1LL << 31) - 64;
-  const GramTime gram_us = dual ? gram_time(ctx->layer_tab_host, B, T) : GramTime{0.0, 0.0};
+  const GramTime gram_us = dual ? gram_time(ctx, B, T) : GramTime{0.0, 0.0};
   const bool region = dual && ctx->min_width >= 128 && ((long long)T + 256) * ctx->max_lin_stride < (1LL << 31) &&
-                      (ctx->gram_variant == 3 || (ctx->gram_variant == 1 && gram_us.region < gram_us.dual));
+                      (ctx->gram_variant == 3 || (ctx->gram_variant == 1 && T > 128 && gram_us.region < gram_us.dual));
   const double t_gram = region ? gram_us.region : gram_us.dual;
   long long n_pairs = nt * (nt + 1) / 2, spare_pairs = n_pairs;      // partial sums per (layer, sample)
   if (dual) {
@@ -582,11 +601,11 @@ int grad_stats(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_layers, 
   const bool all_formed = ctx->n_formed == ctx->n_linear;
   const std::vector<LayerDev>& tab = ctx->layer_tab_host;
   bool tile_form = !sum_only && tiles_allowed && all_formed && ctx->tiles16.built && is_16bit(dtype) &&
-                   (T % 32 == 0 || (!pinned_order && formed_tiles_pay(tab, T, dtype, t_gram / B))) && T <= (1 << 20);
+                   (T % 32 == 0 || (!pinned_order && formed_tiles_pay(ctx, B, T, dtype, t_gram))) && T <= (1 << 20);
   bool plain_form = !sum_only && tiles_allowed && all_formed && dtype == ADLOCO_F32 && !pinned_order &&
-                    formed_tiles_pay(tab, T, dtype, t_gram / B);
+                    formed_tiles_pay(ctx, B, T, dtype, t_gram);
   bool square_form = !sum_only && tiles_allowed && ctx->n_formed == 0 && T <= (1 << 20) &&
-                     (dtype == ADLOCO_F32 || ctx->tiles16.built) && tiles_beat_gram(tab, B, T, dtype, t_gram);
+                     (dtype == ADLOCO_F32 || ctx->tiles16.built) && tiles_beat_gram(ctx, B, T, dtype, t_gram);
   const bool short_form = tile_form && short_sequences(tab, ctx->tiles16.use, B, T, false);
   const long long rows = (long long)B * T;
   // the list of the fp32 forms, and what a form leaves per (tile, sample)

@@ -102,7 +102,7 @@ def test_another_batch_may_take_the_other_kernel_and_be_captured(T):
         c.set_tuning("stats_variant", 0)
         return c
 
-    (many, many_out), (one, one_out) = call(8), call(1)
+    (many, many_out), (one, one_out) = call(16), call(1)
     want = []
     for run, out, kernel in ((many, many_out, 3), (one, one_out, 2)):      # each on a context of its own
         with context() as own:
@@ -135,3 +135,77 @@ def test_another_batch_may_take_the_other_kernel_and_be_captured(T):
             torch.cuda.synchronize()
             for got, w in zip(one_out + many_out, want[1] + want[0]):
                 assert torch.equal(got, w)
+
+
+def _gpt(d, blocks):
+    return [(d, 3 * d, 0), (d, d, 1), (d, 4 * d, 2), (4 * d, d, 3)] * blocks
+
+
+def _llama(d, ff, blocks):
+    return [(d, d, 0), (d, d, 0), (d, d, 0), (d, d, 1), (d, ff, 2), (d, ff, 2), (ff, d, 3)] * blocks
+
+
+@pytest.mark.parametrize("name,shapes,B,T,kernel", [
+    # the dual-tile kernel contracts shared activations once only where no tile is ragged
+    ("llama ragged", _llama(832, 2048, 2), 37, 500, 3),
+    ("llama, whole tiles", _llama(1664, 3328, 1), 8, 512, 2),
+    # two row blocks of 256: full, and nearly empty
+    ("gpt2", _gpt(768, 2), 32, 512, 3),
+    ("gpt2 ragged", _gpt(768, 2), 32, 300, 2),
+    # few units: the XCD with the most of them counts
+    ("two blocks of gpt2, few samples", _gpt(768, 2), 4, 512, 2),
+    # tiles of the per-sample gradients, and where their starts and ends outweigh them
+    ("llama, narrow and ragged", _llama(320, 768, 3), 43, 595, 0),
+    ("llama, long and ragged", _llama(512, 1408, 4), 8, 1100, 0),
+    ("llama, short", _llama(960, 2240, 3), 15, 27, 2),
+    ("gpt, short", _gpt(1344, 8), 3, 32, 2),
+])
+def test_the_faster_way_is_taken(name, shapes, B, T, kernel):
+    # (each measured: the other ways take 1.06 to 2.6 times as long)
+    import torch
+    import paper_2508_18182_amd as A
+    from gpu_util import DEV, new_acc
+    g = torch.Generator(device=DEV).manual_seed(T)
+
+    def rows(w):
+        return torch.empty(B, T, w, dtype=torch.bfloat16, device=DEV).normal_(0, 1, generator=g)
+
+    layers, acts = [], {}
+    for i, (d_in, d_out, group) in enumerate(shapes):
+        if i and shapes[i - 1][2] > group:
+            acts = {}
+        acts.setdefault(group, rows(d_in))
+        layers.append(dict(a=acts[group], delta=rows(d_out), provided=True, grad_sum=None))
+    got = {}
+    for variant in (1, 2, 3):
+        with A.Context(0) as ctx:
+            ctx.set_tuning("gram_variant", variant)
+            ctx.set_tuning("stats_variant", int(variant == 1))
+            ps = torch.zeros(B, device=DEV)
+            A.adloco_grad_stats(ctx, layers, B, T, A.ADLOCO_BF16, ps, None, new_acc())
+            assert ctx.gram_kernel() == (kernel if variant == 1 else variant)
+            got[variant] = ps.double()
+    for v in (2, 3):
+        assert float((got[1] / got[v] - 1).abs().max()) < 1e-4      # fp32 sums in another order
+
+
+@pytest.mark.parametrize("shapes,B,T,kernel", [(_llama(960, 2240, 3), 15, 27, 2), (_gpt(512, 1), 8, 333, 0)])
+def test_the_faster_way_to_form_gradient_sums_is_taken(shapes, B, T, kernel):
+    # tiles of the per-sample gradients, or Gram contraction and sum over all rows where most of a chunk would be padding
+    import torch
+    import paper_2508_18182_amd as A
+    from gpu_util import DEV, new_acc
+    g = torch.Generator(device=DEV).manual_seed(T)
+    layers = [dict(a=torch.empty(B, T, i, dtype=torch.bfloat16, device=DEV).normal_(0, 1, generator=g),
+                   delta=torch.empty(B, T, o, dtype=torch.bfloat16, device=DEV).normal_(0, 1, generator=g)) for i, o, _ in shapes]
+    got = []
+    for stats_variant in (1, 0):
+        with A.Context(0) as ctx:
+            ctx.set_tuning("stats_variant", stats_variant)
+            sums = [torch.zeros(o, i, device=DEV) for i, o, _ in shapes]
+            ps = torch.zeros(B, device=DEV)
+            A.adloco_grad_stats(ctx, [dict(l, grad_sum=s) for l, s in zip(layers, sums)], B, T, A.ADLOCO_BF16, ps, None, new_acc())
+            assert stats_variant == 0 or ctx.gram_kernel() == kernel
+            got.append([ps.double()] + [s.double() for s in sums])
+    for x, y in zip(*got):
+        assert float((x - y).norm() / y.norm()) < 1e-5              # fp32 sums in another order
