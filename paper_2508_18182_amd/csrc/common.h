@@ -349,7 +349,8 @@ struct adloco_ctx {
   adloco::Scratch ip_dot, ip_sq;   // float [n_layers][B] of the blocks outside the tile table
   adloco::Scratch ip_flags;    // unsigned char [n_layers]: 1 = block is in the tile table
   int ip_slots = 0, ip_group = 1, ip_B = -1, ip_T = -1;
-  adloco::TileList ip_rest;    // linear blocks outside that table
+  adloco::TileList ip_rest[2]; // linear blocks outside that table: 64- and 128-wide tiles
+  int ip_rest_W = 1;           // which of them the batch takes
   bool ip_any_rest = false;
   int ip_rest_group = 1;
   int ip_group_tuning = 0;     // 0: cost model; else samples per tile entry

@@ -154,7 +154,7 @@ extern "C" int adloco_destroy(adloco_ctx* ctx) {
                     &ctx->ip_dot, &ctx->ip_sq, &ctx->ip_flags, &ctx->tile_out};
   for (Scratch* s : all)
     if (s->ptr) (void)hipFree(s->ptr);
-  for (TileList* p : {&ctx->tiles16, &ctx->tiles32[0], &ctx->tiles32[1], &ctx->ip_rest})
+  for (TileList* p : {&ctx->tiles16, &ctx->tiles32[0], &ctx->tiles32[1], &ctx->ip_rest[0], &ctx->ip_rest[1]})
     for (Scratch* s : {&p->tab, &p->ptiles})
       if (s->ptr) (void)hipFree(s->ptr);
   for (auto& r : ctx->prof) {

@@ -303,7 +303,7 @@ int prepare_tables(adloco_ctx* ctx, const adloco_linear_desc* layers, int n_laye
   {
     // tile lists of every route that a call on this table can take, whatever its batch: of the blocks whose gradient sum is
     // formed here, or of all linear blocks if none is (the 16-bit kernels take either all blocks or none)
-    for (TileList* p : {&ctx->tiles16, &ctx->tiles32[0], &ctx->tiles32[1], &ctx->ip_rest}) p->built = false;
+    for (TileList* p : {&ctx->tiles16, &ctx->tiles32[0], &ctx->tiles32[1], &ctx->ip_rest[0], &ctx->ip_rest[1]}) p->built = false;
     std::vector<char> use(n_layers, 0);
     for (int l = 0; l < n_layers; ++l) use[l] = tab[l].kind == ADLOCO_KIND_LINEAR && !(ctx->n_formed && tab[l].provided);
     const bool all = ctx->n_formed == 0 || ctx->n_formed == ctx->n_linear;
@@ -909,9 +909,10 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
       any_rest = any_rest || rest[l];
     }
     if (any_rest) {
-      const TileGeom geom = plain_tile_geom(ctx->plain_tiles_tuning ? ctx->plain_tiles_tuning & 3 : plain_tile_width(tab, rest, B, T));
-      TileList& p = ctx->ip_rest;
-      if (!p.built || p.use != rest || p.edge != geom.e) build_tile_list(ctx, p, tab, rest, geom, false, st);
+      ctx->ip_rest_W = ctx->plain_tiles_tuning ? ctx->plain_tiles_tuning & 3 : plain_tile_width(tab, rest, B, T);
+      const TileGeom geom = plain_tile_geom(ctx->ip_rest_W);
+      TileList& p = ctx->ip_rest[ctx->ip_rest_W - 1];          // (one per width, which changes from batch to batch)
+      if (!p.built || p.use != rest) build_tile_list(ctx, p, tab, rest, geom, false, st);
       if (!p.built) return fail(ctx, ADLOCO_ENOMEM, "inner_products: no memory for the tile list");
       ctx->ip_rest_group = ctx->ip_group_tuning > 0 ? std::min(ctx->ip_group_tuning, B) : run_length(p.n_tiles, B, T, geom);
       if ((long long)p.used(1) * kNumXcd * ((B + ctx->ip_rest_group - 1) / ctx->ip_rest_group) > 0x7fffffffLL)
@@ -924,8 +925,9 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
     ctx->ip_B = B;
     ctx->ip_T = T;
   }
+  const TileList& ip_rest = ctx->ip_rest[ctx->ip_rest_W - 1];
   if (ctx->ip_any_rest) {
-    rc = ensure_scratch(ctx, ctx->tile_out, size_t(ctx->ip_rest.n_tiles) * B * 2 * sizeof(double));
+    rc = ensure_scratch(ctx, ctx->tile_out, size_t(ip_rest.n_tiles) * B * 2 * sizeof(double));
     if (rc) return rc;
   }
   rc = ensure_scratch(ctx, ctx->ip_dot, size_t(n_layers) * B * sizeof(float));
@@ -942,7 +944,7 @@ extern "C" int adloco_inner_products(adloco_ctx* ctx, const adloco_linear_desc* 
                                  per_sample_sqnorm != nullptr, ctx->ip_short,
                                  static_cast<float*>(ctx->ip_tile_out.ptr), st);
   if (e == hipSuccess && ctx->ip_any_rest)
-    e = launch_plain_tiles(dl, ctx->ip_rest, 0, B, T, dtype, 0, true, ctx->ip_rest_group,
+    e = launch_plain_tiles(dl, ip_rest, 0, B, T, dtype, 0, true, ctx->ip_rest_group,
                            static_cast<double*>(ctx->tile_out.ptr), dot, sq, 1, st);
   if (e == hipSuccess && !ctx->vec_host.empty())
     e = launch_vector_stats(dl, static_cast<const AuxDesc*>(ctx->vec_tab.ptr), int(ctx->vec_host.size()),

@@ -92,3 +92,28 @@ def test_without_memory_for_the_tiles():
         assert np.max(np.abs(a - b) / np.abs(b)) < 1e-4
     for a, b in zip(got[0][3:], got[1][3:]):
         assert np.max(np.abs(a - b)) < 1e-4 * np.sqrt(np.mean(b * b))
+
+
+def test_inner_products_keep_the_list_of_either_tile_width():
+    # {768 -> 2304}, B 8: 64-wide tiles up to T 64, 128-wide ones from T 100 on; what belongs to B and T is one table
+    import torch
+    import paper_2508_18182_amd as A
+    from gpu_util import DEV
+    B, g = 8, torch.Generator().manual_seed(77)
+    calls = []
+    for T in (64, 128):
+        layers = [dict(a=torch.randn(B, T, 768, generator=g).cuda(), delta=torch.randn(B, T, 2304, generator=g).cuda(),
+                       grad_sum=torch.randn(2304, 768, generator=g).cuda())]
+        calls.append((T, layers))
+    ctx, seen = A.Context(0), []
+    for _ in range(3):
+        for T, layers in calls:
+            dots, acc = torch.zeros(B, device=DEV), torch.zeros(4, dtype=torch.float64, device=DEV)
+            builds = ctx.table_builds()
+            A.adloco_inner_products(ctx, layers, B, T, A.ADLOCO_F32, dots, None, acc)
+            seen.append(ctx.table_builds() - builds)
+            want = torch.stack([(layers[0]["delta"][i].double().t() @ layers[0]["a"][i].double() *
+                                 layers[0]["grad_sum"].double()).sum() for i in range(B)])
+            assert float((dots.double() - want).norm() / want.norm()) < 1e-5
+    assert seen[2:] == [1, 1, 1, 1]
+    ctx.close()
