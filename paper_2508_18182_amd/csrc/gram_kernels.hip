@@ -523,7 +523,7 @@ __global__ __launch_bounds__(512, 1) void gram_bf16_dual_kernel(GramDualArgs g) 
 // 16-bit fast path for long sequences ("region" kernel): 256 x 256 regions of the Gram matrices.
 //   The dual-tile kernel moves 12 rows of a chunk from L2 to LDS per 32 x 32 block of a tile pair, and is held by
 //   those loads (350M model, B 32, T 1024: 161 GB in 13.7 ms, matrix cores 50 % busy at 1.84 GHz; this kernel: 116 GB in
-//   11.4 ms, 68 % at 1.60 GHz, where the chip's power holds it).  Here a workgroup of four waves, one per SIMD, owns 256 rows x 256 columns:
+//   11.4 ms, 66 % at 1.7 GHz, where the chip's power holds it).  Here a workgroup of four waves, one per SIMD, owns 256 rows x 256 columns:
 //   8 rows per block while the first operand X is contracted.  Both products of a region do not fit the register
 //   file, so X X^T (the wider of a and delta; a where layers share it) stays complete in the 256 accumulation
 //   registers and Y Y^T is formed in two halves of 256 x 128 in 128 vector registers (12 rows per block), each
