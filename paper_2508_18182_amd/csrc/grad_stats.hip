@@ -481,9 +481,11 @@ bool tiles_beat_gram(const adloco_ctx* ctx, int B, int T, int dtype, double gram
   if (gram_us > 0.0) {
     const TileGeom geom = ip_tile_geom();
     const long long n = ctx->tiles16.n_tiles, room = (long long)geom.room * kNumXcd;
+    const double sample = (T + geom.k - 1) / geom.k * 0.46 + 0.72;
+    if (8.0 + double(n) * B / room * sample >= 0.95 * gram_us) return false;       // (whatever the runs, which are searched for)
     const int group = run_length(n, B, T, geom);
-    const double rounds = double((n * ((B + group - 1) / group) + room - 1) / room), chunks = (T + geom.k - 1) / geom.k;
-    return 8.0 + rounds * (group * (chunks * 0.46 + 0.72) + 2.8) < 0.95 * gram_us;
+    const double rounds = double((n * ((B + group - 1) / group) + room - 1) / room);
+    return 8.0 + rounds * (group * sample + 2.8) < 0.95 * gram_us;
   }
   const bool b16 = is_16bit(dtype);
   const long long te = b16 ? 256 : 128, tc = 128, gt = b16 ? 128 : 32, wgs = b16 ? 256 : 512;
